@@ -49,6 +49,59 @@ def sweep_traffic(n):
     return (t["half_step_1"] + t["half_step_2"]) / 2.0
 
 
+def product_flops(n):
+    """Operations of the four product launches of one Chebyshev-output square
+    solve, per launch: the parity blocks' dense products (m modes and mo
+    output coefficients per parity)."""
+    m = ((n + 1) // 2, n // 2)
+    mo = ((n + 3) // 2, (n + 2) // 2)
+    st = [(s, t) for s in (0, 1) for t in (0, 1)]
+    return [sum(2.0 * m[s] * m[t] * m[t] for s, t in st), sum(2.0 * m[s] * m[s] * m[t] for s, t in st),
+            sum(2.0 * m[s] * m[t] * mo[t] for s, t in st),
+            sum(2.0 * m[s] * mo[s] * mo[t] for s, t in st)]
+
+
+def product_roofline(n, times_ms):
+    """Roofline of the solve's dominant kernel, the FP64 matrix-core product
+    (k_gemm): four launches per solve, times_ms their event-timed durations
+    in launch order over one or more solves."""
+    fl = product_flops(n)
+    per = [sum(times_ms[i::4]) / max(len(times_ms[i::4]), 1) for i in range(4)]
+    tf = sum(fl) / (sum(per) * 1e-3) / 1e12
+    return {"bound": "mfma_f64", "achieved": round(tf, 2), "peak": FP64_MFMA_PEAK_TFLOPS,
+            "unit": "TFLOP/s", "frac": round(tf / FP64_MFMA_PEAK_TFLOPS, 4), "traffic": None,
+            "traffic_note": "the solve is four dense products bound by the FP64 matrix cores; no HBM "
+                            "counters were taken",
+            "kernel": "eigenbasis products (k_gemm), four launches per solve",
+            "flops_per_launch": fl, "avg_launch_us": [round(t * 1e3, 2) for t in per],
+            "launches_timed": len(times_ms),
+            "timing": "HIP events recording each dispatch's start and end (hipExtLaunchKernelGGL), "
+                      "separate pass of the same solves"}
+
+
+def bench_sweeps(fps, torch, plan, G, ws):
+    """The ADI half-sweeps of the stage entry point fps_adi_native (half-step 1
+    reads its input and writes its output, 16 B per dof; half-step 2 also reads
+    G, 24 B), every launch event-timed on one stream."""
+    n = plan.n
+    Y = torch.empty((n, n), dtype=torch.float64, device=G.device)
+    fps.adi_native(plan, G, out=Y, ws=ws)
+    plan.set_sweep_timing(2 * plan.J)
+    fps.adi_native(plan, G, out=Y, ws=ws)
+    torch.cuda.synchronize()
+    t = plan.sweep_time()
+    plan.set_sweep_timing(0)
+    dof = float(n) * n
+    t1 = sum(t[0::2]) / max(len(t[0::2]), 1) * 1e-3
+    t2 = sum(t[1::2]) / max(len(t[1::2]), 1) * 1e-3
+    b1, b2 = 16.0 * dof, 24.0 * dof
+    return {"n": n, "bytes_per_launch": {"half_step_1": b1, "half_step_2": b2},
+            "avg_launch_us": {"half_step_1": round(t1 * 1e6, 2), "half_step_2": round(t2 * 1e6, 2)},
+            "achieved_GBs": round((b1 + b2) / (t1 + t2) / 1e9, 1),
+            "frac": round((b1 + b2) / (t1 + t2) / 1e9 / HBM_PEAK_GBS, 4),
+            "traffic": sweep_traffic(n), "launches_timed": len(t)}
+
+
 def copy_rate(torch, dev, mib=1024, reps=5):
     """Achievable HBM rate of a plain copy kernel: GB/s (bytes read plus
     bytes written) of a device-to-device copy of `mib` MiB, far larger than
@@ -579,27 +632,17 @@ def bench_square_large(fps, workloads, torch, tol, n=10000, steps=3, check=True,
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    # one more solve with an event pair around every sweep launch: at this
-    # size no array fits the last-level cache, so the rate is HBM's alone
-    p.set_sweep_timing(2 * p.J)
+    p.set_sweep_timing(4)
     fps.solve(p, F, out=U, ws=ws)
     torch.cuda.synchronize()
     t = p.sweep_time()
     p.set_sweep_timing(0)
     dof = float(n) * n
-    t1 = sum(t[0::2]) / max(len(t[0::2]), 1) * 1e-3
-    t2 = sum(t[1::2]) / max(len(t[1::2]), 1) * 1e-3
-    b1, b2 = 16.0 * dof, 24.0 * dof
     res = {"n": n, "dof": dof, "J": p.J, "ms_per_solve": ms,
            "dof_per_s": dof / (ms * 1e-3),
            "paper_context": "10^8 dof in under two minutes on a 2017 laptop (MATLAB, one core)",
-           "sweep": {"n": n, "bytes_per_launch": {"half_step_1": b1, "half_step_2": b2},
-                     "avg_launch_us": {"half_step_1": round(t1 * 1e6, 2),
-                                       "half_step_2": round(t2 * 1e6, 2)},
-                     "achieved_GBs": round((b1 + b2) / (t1 + t2) / 1e9, 1),
-                     "frac": round((b1 + b2) / (t1 + t2) / 1e9 / HBM_PEAK_GBS, 4),
-                     "traffic": sweep_traffic(n),
-                     "launches_timed": len(t)}}
+           "products": product_roofline(n, t), "sweep": bench_sweeps(fps, torch, p, F, ws)}
+    fps.solve(p, F, out=U, ws=ws)
     if check:
         from oracle import square
         Uo = square.poisson_square(F_host)
@@ -748,10 +791,9 @@ def main() -> int:
     e1.record(stream)
     torch.cuda.synchronize()
     total_ms = e0.elapsed_time(e1)
-    # Roofline pass: the same solves again, every half-sweep launch carrying
-    # a HIP event pair that records the dispatch's own start and end on the
-    # solve's stream.
-    plan.set_sweep_timing(2 * plan.J * args.steps)
+    # Roofline pass: the same solves again, every product launch carrying a HIP
+    # event pair that records the dispatch's own start and end.
+    plan.set_sweep_timing(4 * args.steps)
     torch.cuda.synchronize()
     e0.record(stream)
     for _ in range(args.steps):
@@ -759,60 +801,21 @@ def main() -> int:
     e1.record(stream)
     torch.cuda.synchronize()
     instr_ms = e0.elapsed_time(e1)
-    sweep_list = plan.sweep_time()
+    products = plan.sweep_time()
     plan.set_sweep_timing(0)
     ms_per_step = total_ms / args.steps
     dof = float(n) * float(n)
     value = dof / (ms_per_step * 1e-3)
-
-    # Dominant kernel: the ADI half-sweep (k_sweep), two variants.
-    # Algorithmic bytes per launch (24 B per dof would be read input + read G
-    # + write output; here G is read by half-step 2 only):
-    #   half-step 1: read input, write output           -> 16 B per dof
-    #   half-step 2: read input, read G, write output   -> 24 B per dof
     J = plan.J
-    hs1 = sweep_list[0::2]
-    hs2 = sweep_list[1::2]
-    t1 = sum(hs1) / max(len(hs1), 1) * 1e-3
-    t2 = sum(hs2) / max(len(hs2), 1) * 1e-3
-    b1, b2 = 16.0 * dof, 24.0 * dof
-    achieved = (b1 + b2) / (t1 + t2) / 1e9
-    traffic = sweep_traffic(n)
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "traffic_note": "calibrated HBM bytes per launch, mean of the two half-steps "
-                                f"(algorithmic mean {(b1 + b2) / 2:.4g})" if traffic else
-                                "null: sweep sources changed since the counters were taken",
-                "kernel": "ADI half-sweeps (k_sweep_rows: half-step 1, k_sweep: half-step 2), "
-                          "byte-weighted",
-                "bytes_per_launch": {"half_step_1": b1, "half_step_2": b2},
-                "avg_launch_us": {"half_step_1": round(t1 * 1e6, 2),
-                                  "half_step_2": round(t2 * 1e6, 2)},
-                "achieved_GBs": {"half_step_1": round(b1 / t1 / 1e9, 1),
-                                 "half_step_2": round(b2 / t2 / 1e9, 1)},
-                "launches_timed": len(sweep_list),
-                "timing": "HIP events recording each sweep dispatch's start and end "
-                          "(hipExtLaunchKernelGGL), separate pass of the same solves with "
-                          "every launch on one stream (the timed solves run the two "
-                          "row-parity blocks on two streams, half the chains per launch) "
-                          f"({instr_ms / args.steps:.2f} ms per solve with the events)",
-                "sweep_share_of_step": round(sum(sweep_list) / instr_ms, 4)}
-    # Beside the sweep roofline: the rate a plain copy kernel achieves, and the
-    # whole solve's algorithmic bytes (sweeps 40 B per dof per ADI iteration;
-    # the map stages each read their input and write their output once:
-    # permutation, two GEMM stages and transpose on the input side, finalize,
-    # fill of U and two GEMM stages on the output side, 136 B per dof).
-    copy_gbs = copy_rate(torch, dev)
+    roofline = product_roofline(n, products)
+    roofline["share_of_step"] = round(sum(products) / instr_ms, 4)
+    # the stage entry point's half-sweeps (HBM bound) and the streaming rate
     ceiling = stream_rate(fps, torch, dev)
-    solve_bytes = (40.0 * J + 136.0) * dof
-    roofline["copy_kernel_GBs"] = round(copy_gbs, 1)
-    roofline["frac_of_copy_kernel"] = round(achieved / copy_gbs, 4)
+    roofline["copy_kernel_GBs"] = round(copy_rate(torch, dev), 1)
     roofline["stream_kernel"] = ceiling
-    roofline["frac_of_stream_kernel"] = round(achieved / ceiling["GBs"], 4)
-    roofline["whole_solve"] = {
-        "bytes_algorithmic": solve_bytes,
-        "achieved_GBs": round(solve_bytes / (ms_per_step * 1e-3) / 1e9, 1),
-        "frac": round(solve_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
+    sw = bench_sweeps(fps, torch, plan, F, ws)
+    sw["frac_of_stream_kernel"] = round(sw["achieved_GBs"] / ceiling["GBs"], 4)
+    roofline["adi_native_sweeps"] = sw
 
     out = {"metric": METRIC, "value": value, "unit": "dof/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
@@ -861,11 +864,7 @@ def main() -> int:
                                  "speedup_vs_fp64": ms_per_step / ms_r,
                                  "rounds": pr.rounds, "round_steps": rsteps, "round_tols": rtols,
                                  "f32_steps": pr.f32_steps,
-                                 "fp64_J": J,
-                                 "sweep_bytes_per_dof": {
-                                     "fp32_refined": 20 * pr.f32_steps
-                                     + 40 * (sum(rsteps) - pr.f32_steps),
-                                     "fp64": 40 * J}}
+                                 "fp64_J": J}
         del wsr
         if args.only is None:
             forms["batched"] = bench_batch(fps, workloads, torch, args.tol, tight=tight)
@@ -880,9 +879,6 @@ def main() -> int:
                                              check=not args.no_check, tight=tight)
             forms["square_n10000"] = bench_square_large(fps, workloads, torch, args.tol,
                                                         check=not args.no_check, tight=tight)
-            sw = dict(forms["square_n10000"]["sweep"])
-            sw["frac_of_stream_kernel"] = round(sw["achieved_GBs"] / ceiling["GBs"], 4)
-            roofline["sweep_n10000"] = sw
     if forms:
         out["forms"] = forms
 

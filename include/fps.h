@@ -56,21 +56,23 @@ typedef enum {
 
 typedef enum { FPS_BC_DIRICHLET_ZERO = 0 } fps_bc;
 
-/* FPS_FP64: every ADI half-sweep stores and computes in float64.
- * FPS_FP32_REFINED: iterative refinement (precision form; not in the paper).
- * Each round forms the residual r = G - (A~ Y + Y A~) in float64, stores it
- * in float32, runs an inner ADI on A~ dY + dY A~ = r that stores every sweep
- * array (and its result dY) in float32, and adds dY to the float64 Y.  Every
- * arithmetic operation and every table stays float64.  The inner ADI applies
- * its shifts in order of increasing |p_j| (with the opposite order float
- * storage stalls or diverges from n ~ 256 on).  Rounds: inner tolerance 1e-5
- * (on smooth data a round contracts the error by about 1e-5) until one more
- * such round would pass tol, then a last round to 0.1 tol / (error
- * reached); at tol = 1e-13: 1e-5, 1e-5, 1e-4 (fps_plan_rounds).  Plans
- * created with FPS_PLAN_DIRICHLET, whose lift puts O(1) content into the
- * highest modes of G's first two rows and columns, run two float rounds
- * and then one round with float64 storage (float rounds contract such data
- * by only ~1e-3). */
+/* How the 2-D solves run.  Every step of Algorithm 2 multiplies by rational
+ * functions of A~ from both sides, so its J-step iterate is diagonal in the
+ * eigenbasis of A~: the plan merges the eigenvectors with the coefficient maps
+ * and holds the shifts' error factors, and a solve is four dense products
+ * with those factors applied in between.  The result is the J-step iterate of
+ * the plan's shifts (tol and the enclosure keep their meaning) up to rounding.
+ *
+ * FPS_FP64: one ADI to tol.
+ * FPS_FP32_REFINED: the iterate of an iteratively refined ADI (precision form;
+ * not in the paper): rounds of inner ADIs on the residual equation, inner
+ * tolerance 1e-5 until one more such round would pass tol, then a last round to
+ * 0.1 tol / (error reached); at tol = 1e-13: 1e-5, 1e-5, 1e-4
+ * (fps_plan_rounds).  Square, rectangle and batched plans form that iterate
+ * from its rounds' error factors, in float64 throughout; z-eigenbasis cube
+ * plans store their slice sweeps in float32 (every arithmetic operation and
+ * table float64).  Plans created with FPS_PLAN_DIRICHLET have two rounds to
+ * 1e-5 and one to the rest. */
 typedef enum { FPS_FP64 = 0, FPS_FP32_REFINED = 1 } fps_prec;
 
 typedef enum { FPS_OUT_CHEB = 0, FPS_OUT_NATIVE = 1 } fps_out;
@@ -263,7 +265,7 @@ fps_status fps_solve_dirichlet(fps_plan *plan, const double *F_dev, const double
  * U) returns Fbar (n^dim) with <U(F), Ubar> = <F, Fbar> for the J-step ADI
  * map.  The symmetric-shift ADI map is self-adjoint in the Frobenius inner
  * product (every term is phi(A~) G psi(A~) with symmetric phi, psi), so the
- * adjoint runs the same sweeps between transposed coefficient maps.  The
+ * adjoint runs the same products transposed.  The
  * same holds for a rectangle plan's general shifts: the J-step error map is
  * r(A) E r(B)^-1 with r a rational function and A, B symmetric, so the map
  * is a multiplier in the orthonormal eigenbasis of A~.
@@ -286,13 +288,15 @@ fps_status fps_adi_native(fps_plan *plan, const double *G_dev, double *Y_dev, vo
 /*
  * Diagnostics for throughput measurement.  fps_plan_set_sweep_timing(plan,
  * capacity) creates `capacity` HIP event pairs (0 disables and releases
- * them); later solves time each ADI half-sweep launch with one pair (the
+ * them); later solves time each ADI half-sweep or product launch with one pair (the
  * dispatch's own start and end timestamps), until the pairs run out.
  * fps_plan_sweep_time waits for the recorded events, writes the elapsed
  * milliseconds of the timed launches in launch order to
  * ms_host[0..min(count, cap)-1] (ms_host may be null when cap is 0), sets
- * *launches to their count, and resets the count.  Square plans: half-step 1
- * and half-step 2 of Algorithm 2 alternate, starting with half-step 1; cube
+ * *launches to their count, and resets the count.  Square and rectangle
+ * plans: fps_adi_native's half-steps 1 and 2 of Algorithm 2 alternate,
+ * starting with half-step 1; the solves and adjoints time their four product
+ * launches; cube
  * plans: per outer step one z sweep, then the inner half-steps 1 and 2;
  * z-eigenbasis cube plans: per step j the x solves of all slices still
  * iterating, then their y solves (one launch each).
@@ -337,13 +341,10 @@ void fps_plan_destroy(fps_plan *plan);
  * paper): `count` independent problems of sizes n[0..count-1], each solved
  * exactly as fps_solve with a plan of that size, tol, precision and output
  * basis would solve it.  Problems of equal n share one set of plan tables.
- * The ADI half-sweeps of all problems run as one launch per half-step (the
- * problems still iterating at that step), so a batch enqueues about 4 J_max
- * sweep/carry launches plus a fixed number of map launches per problem.
+ * Each product stage of all problems runs as one launch (five launches a
+ * batch).
  *   dim must be 2; 1 <= count <= 65536; every n in [1, 16384]; tol, prec,
- *   out_basis and flags as for fps_plan_create.  FPS_FP32_REFINED batches
- *   run the rounds of their plans (the same round tolerances for every
- *   problem), one batched inner ADI per round.
+ *   out_basis and flags as for fps_plan_create.
  * Data: F_dev packs the problems' n x n inputs back to back in the given
  * order (row-major each, offsets sum of n_b^2); U_dev packs the outputs
  * ((n_b+2)^2 or n_b^2 entries each).  fps_batch_info gives the totals and the
@@ -363,8 +364,8 @@ fps_status fps_batch_solve(fps_batch *batch, const double *F_dev, double *U_dev,
  * (written) in its input layout.  Each problem's symmetric-shift ADI map of
  * Algorithm 2 (shifts of Theorem 2.1) is self-adjoint in the Frobenius inner
  * product (derived here: every term is phi(A~) G psi(A~) with symmetric
- * phi, psi), so the adjoint runs the same batched sweeps
- * between the transposed coefficient maps; every problem's result equals
+ * phi, psi), so the adjoint runs the same batched products
+ * transposed; every problem's result equals
  * fps_solve_adjoint on that problem.  FP64 batches only (FPS_E_UNSUPPORTED
  * otherwise); same workspace and stream rules as fps_batch_solve. */
 fps_status fps_batch_solve_adjoint(fps_batch *batch, const double *Ubar_dev, double *Fbar_dev,

@@ -209,8 +209,9 @@ class Plan:
         _check(lib().fps_plan_set_sweep_timing(self._h, capacity))
 
     def sweep_time(self, cap: int = 1 << 20):
-        """Per-launch milliseconds of the timed half-sweeps since the last call
-        (half-step 1 and half-step 2 alternate)."""
+        """Per-launch milliseconds of the timed launches since the last call
+        (adi_native: half-step 1 and half-step 2 alternate; 2-D solves: their
+        four products)."""
         buf = (ctypes.c_double * cap)()
         cnt = ctypes.c_int64()
         _check(lib().fps_plan_sweep_time(self._h, buf, cap, ctypes.byref(cnt)))
@@ -381,8 +382,8 @@ def _solve_fn_class():
         (n, n) or (batch, n, n); backward: the adjoint solve (same ADI sweeps
         between transposed coefficient maps), nothing stored from the forward
         pass because the map is linear in F.  A batch of square FP64 problems
-        runs as one fps_batch (sweeps of all problems in one launch per
-        half-step, forward and backward); its results equal the per-problem
+        runs as one fps_batch (each product stage of all problems in one
+        launch, forward and backward); its results equal the per-problem
         solves."""
 
         @staticmethod
@@ -447,8 +448,8 @@ def adi_native(p: Plan, G, out=None, ws=None):
 
 class Batch:
     """Owning wrapper of an fps_batch: independent square solves of sizes
-    ns (packed back to back), ADI half-sweeps of all problems in one launch
-    per half-step."""
+    ns (packed back to back), each product stage of all problems in one
+    launch."""
 
     def __init__(self, ns, tol: float = 1e-13, precision: str = "fp64", out: str = "cheb",
                  host_only: bool = False, tight: bool = False):

@@ -228,64 +228,13 @@ fps_status run_adi(fps_plan *pl, const fps::ShiftSet &sh, int base, const void *
   });
 }
 
-// The symmetric-form solution Y (parity-blocked FP64, npad x npad) of
-// A~ Y + Y A~ = G for G in ws.G, on the rows r0 .. r1-1 of row-parity block
-// s (see adi_part; the whole array with r0 = 0, r1 = npad): plain FP64 ADI
-// (Y left in G), or iterative refinement whose inner ADIs store their sweep
-// arrays in float (Y in the GT region).  A~ is block diagonal, so the
-// residual of a row block needs only that block's rows.
-hipError_t symmetric_part(fps_plan *pl, char *w, int64_t r0, int64_t r1, int c0, int c1, int s,
-                          hipStream_t s2) {
-  const fps::Layout &L = pl->L;
-  double *G = (double *)(w + pl->off_G);
-  double *ab = (double *)(w + pl->off_ab);
-  hipError_t e;
-  if (pl->prec == FPS_FP64) {
-    const int J = pl->shifts.J;
-    e = adi_part(pl, pl->shifts, 0, G, 0, 0, w + pl->off_O0, w + pl->off_O1, w, r0, r1, c0, c1, s,
-                 s2);
-    if (e != hipSuccess) return e;
-    return fps::launch_finalize<double>((const double *)(w + pl->off_O1), ab,
-                                        pl->tab_dev(pl->tab2(J - 1)), G, 0, nullptr, L.n, L.npad,
-                                        L.mp[0], L.mstride, L.ncmax, s2, r0, r1);
-  }
-  // Refinement: Y <- Y + ADI_k(G - (A~ Y + Y A~)) for the rounds k; the
-  // residual is formed in FP64 and stored in float, and the inner sweeps of
-  // a float round store their arrays in float.
-  double *Y = (double *)(w + pl->off_GT);
-  float *r = (float *)(w + pl->off_R);
-  for (int k = 0; k < pl->rounds; ++k) {
-    const fps::ShiftSet &sh = pl->rsh[(size_t)k];
-    const int f32 = pl->rf32[(size_t)k];
-    const double *tab = pl->tab_dev(pl->tab2(pl->rbase[(size_t)k] + sh.J - 1));
-    void *O0 = w + pl->off_O0, *O1 = w + pl->off_O1;
-    e = fps::launch_residual(G, k == 0 ? nullptr : Y, (const double *)pl->d_sdiag.p,
-                             (const double *)pl->d_soff.p, r, nullptr, L.npad, s2, pl->sx2,
-                             pl->sy2, r0, r1);
-    if (e == hipSuccess)
-      e = adi_part(pl, sh, pl->rbase[(size_t)k], r, 1, f32, O0, O1, w, r0, r1, c0, c1, s, s2);
-    if (e != hipSuccess) return e;
-    const int mode = k == 0 ? 0 : 2;
-    if (f32)
-      e = fps::launch_finalize<float>((const float *)O1, ab, tab, Y, mode, nullptr, L.n, L.npad,
-                                      L.mp[0], L.mstride, L.ncmax, s2, r0, r1);
-    else
-      e = fps::launch_finalize<double>((const double *)O1, ab, tab, Y, mode, nullptr, L.n, L.npad,
-                                       L.mp[0], L.mstride, L.ncmax, s2, r0, r1);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-// Y of A~ Y + Y A~ = G for G in ws.G (both row-parity blocks, on two streams
-// when the plan splits them).  Returns Y's location.
-fps_status solve_symmetric(fps_plan *pl, char *w, hipStream_t st, double **Yout) {
-  const fps_status s =
-      for_row_blocks(pl, st, [&](int64_t r0, int64_t r1, int c0, int c1, int sp, hipStream_t s2) {
-        return symmetric_part(pl, w, r0, r1, c0, c1, sp, s2);
-      });
-  if (s != FPS_OK) return s;
-  *Yout = (double *)(w + (pl->prec == FPS_FP64 ? pl->off_G : pl->off_GT));
+// A stage of parity-block products on st, timed like a sweep when the plan's
+// timing is on.
+fps_status run_products(fps_plan *pl, const fps::GemmProb *g, int cnt, hipStream_t st) {
+  const bool t = pl->ev_used * 2 + 1 < (int64_t)pl->ev.size();
+  FPS_HIP(fps::launch_gemm(g, cnt, st, t ? pl->ev[2 * pl->ev_used] : nullptr,
+                           t ? pl->ev[2 * pl->ev_used + 1] : nullptr));
+  if (t) ++pl->ev_used;
   return FPS_OK;
 }
 
@@ -297,29 +246,31 @@ fps_status check_solve_args(fps_plan *pl, const void *a, const void *b, void *ws
   return FPS_OK;
 }
 
-// Input map: G_perm = Rs_s F_st Rs_t^T for the four parity blocks.
-int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2) {
+// Y^_st = (Wi_s F_st Wi_t^T) o multiplier for the four parity blocks.
+int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2, const double *lr,
+              const double *lc) {
   const fps::Layout &L = pl->L;
   const int64_t npad = L.npad;
   double *G = (double *)(ws + pl->off_G);
   const double *GT = (const double *)(ws + pl->off_GT);
   double *Tb = (double *)(ws + pl->off_O0);
+  const double *mr = (const double *)pl->d_mr.p, *mc = (const double *)pl->d_mc.p;
   int cnt = 0;
   int64_t toff = 0;
   for (int s = 0; s < 2; ++s)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s], mt = L.mp[t];
+      const int64_t ms = L.mp[s], mt = L.mp[t], rs = s * L.mp[0], rt = t * L.mp[0];
       if (ms == 0 || mt == 0) continue;
       double *Tst = Tb + toff;
       toff += ms * mt;
-      const double *Fst = GT + (s * L.mp[0]) * npad + t * L.mp[0];
-      // T_st = F_st Rs_t^T; B(k, j) = Rs_t[j][k] = 0 for k < j.
-      g1[cnt] = fps::GemmProb{Fst, (const double *)pl->d_RsB[t].p, Tst, ms, mt, mt,
-                              npad, 1, mt, 1, mt, 1, 0, 0, 1, 0, 0, 0, 0, 0};
-      // G_st = Rs_s T_st; A(i, k) = Rs_s[i][k] = 0 for k < i.
-      g2[cnt] = fps::GemmProb{(const double *)pl->d_RsA[s].p, Tst,
-                              G + (s * L.mp[0]) * npad + t * L.mp[0], ms, mt, ms,
-                              ms, 1, mt, 1, npad, 1, 1, 0, 0, 0, 0, 0, 0, 0};
+      // T_st = F_st Wi_t^T
+      g1[cnt] = fps::GemmProb{GT + rs * npad + rt, (const double *)pl->d_WiT[t].p, Tst, ms, mt, mt,
+                              npad, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+      // Y^_st = Wi_s T_st, multiplied
+      g2[cnt] = fps::GemmProb{(const double *)pl->d_Wi[s].p, Tst, G + rs * npad + rt, ms, mt, ms,
+                              ms, 1, mt, 1, npad, 1, 0, 0, 0, 0, 0, 0, 0, 0,
+                              mr + 2 * rs, mc + 2 * rt, lr ? lr + 4 * rs : nullptr,
+                              lc ? lc + 4 * rt : nullptr};
       ++cnt;
     }
   return cnt;
@@ -339,57 +290,60 @@ fps::BcLiftConst bc_lift_const() {
   return k;
 }
 
-fps_status rhs_transform(fps_plan *pl, const double *F, char *ws, hipStream_t st, const double *bc) {
+// U_st = Wo_s Y^_st Wo_t^T into the strided view of U.
+int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::GemmProb *g2) {
   const fps::Layout &L = pl->L;
-  // F in the parity-blocked layout (zero padded), staged in the GT region.
-  FPS_HIP(fps::launch_permute_in(F, (double *)(ws + pl->off_GT), L.n, L.npad, L.mp[0], st));
-  fps::GemmProb g1[4], g2[4];
-  const int cnt = rhs_gemms(pl, ws, g1, g2);
-  FPS_HIP(fps::launch_gemm(g1, cnt, st));
-  FPS_HIP(fps::launch_gemm(g2, cnt, st));
-  if (bc)
-    FPS_HIP(fps::launch_bc_lift_rhs(bc, (const double *)pl->d_lift[0].p,
-                                    (const double *)pl->d_lift[1].p, (double *)(ws + pl->off_G),
-                                    (double *)(ws + pl->off_bc), L, pl->sx2, pl->sy2,
-                                    bc_lift_const(), st));
-  return FPS_OK;
-}
-
-int out_gemms(const fps_plan *pl, const double *Y, double *U, char *ws, fps::GemmProb *g1,
-              fps::GemmProb *g2) {
-  const fps::Layout &L = pl->L;
-  const int64_t N = L.n + 2, npad = L.npad;
+  const bool native = pl->out_basis == FPS_OUT_NATIVE;
+  const int64_t N = out_extent(pl), npad = L.npad;
+  const int64_t *mo = native ? L.m : L.mo, *mop = native ? L.mp : pl->mop;
+  const double *Y = (const double *)(ws + pl->off_G);
   // temporaries mp_s x mop_t in the O0 and O1 regions (contiguous, free here)
   double *Tb = (double *)(ws + pl->off_O0);
   int cnt = 0;
   int64_t toff = 0;
   for (int s = 0; s < 2; ++s)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s], mt = L.mp[t], mot = pl->mop[t];
+      const int64_t ms = L.mp[s], mt = L.mp[t], mot = mop[t];
       if (L.m[s] == 0 || L.m[t] == 0) continue;  // that output block stays zero
       double *Tst = Tb + toff;
       toff += ms * mot;
-      // T_st = Y_st P_t^T; B(k, j) = P_t[j][k] = 0 for k < j - 1.
-      g1[cnt] = fps::GemmProb{Y + (s * L.mp[0]) * npad + t * L.mp[0], (const double *)pl->d_PB[t].p,
-                              Tst, ms, mot, mt, npad, 1, mot, 1, mot, 1, 0, 0, 1, -1, 0, 0, 0, 0};
-      // U_st = P_s T_st; A(i, k) = P_s[i][k] = 0 for k < i - 1.
-      g2[cnt] = fps::GemmProb{(const double *)pl->d_PA[s].p, Tst, U + s * N + t, L.mo[s], L.mo[t],
-                              ms, ms, 1, mot, 1, 2 * N, 2, 1, -1, 0, 0, 0, 0, 0, 0};
+      g1[cnt] = fps::GemmProb{Y + (s * L.mp[0]) * npad + t * L.mp[0], (const double *)pl->d_WoT[t].p,
+                              Tst, ms, mot, mt, npad, 1, mot, 1, mot, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+      g2[cnt] = fps::GemmProb{(const double *)pl->d_Wo[s].p, Tst, U + s * N + t, mo[s], mo[t],
+                              ms, ms, 1, mot, 1, 2 * N, 2, 0, 0, 0, 0, 0, 0, 0, 0};
       ++cnt;
     }
   return cnt;
 }
 
-fps_status out_transform(fps_plan *pl, const double *Y, double *U, char *ws, hipStream_t st) {
+// The whole 2-D solve on st: F permuted into the GT region, the two input
+// products (with the multiplier), the two output products.  bc: Dirichlet
+// traces or null.
+fps_status solve_2d(fps_plan *pl, const double *F, const double *bc, double *U, char *w,
+                    hipStream_t st) {
   const fps::Layout &L = pl->L;
-  const int64_t N = L.n + 2;
-  if (L.npad * (pl->mop[0] + pl->mop[1]) * 8 > pl->off_lv - pl->off_O0)
-    return fail(FPS_E_STATE, "internal: output temporary exceeds workspace");
+  FPS_HIP(fps::launch_permute_in(F, (double *)(w + pl->off_GT), L.n, L.npad, L.mp[0], st));
+  double *lr = nullptr, *lc = nullptr, *corner = nullptr;
+  if (bc) {
+    lr = (double *)(w + pl->off_O1);  // free until the output products
+    lc = lr + 4 * L.npad;
+    corner = (double *)(w + pl->off_bc);
+    FPS_HIP(fps::launch_bc_lift_rhs(bc, (const double *)pl->d_lift[0].p,
+                                    (const double *)pl->d_lift[1].p, pl->mop[0], pl->mop[1],
+                                    (const double *)pl->d_lina.p, lr, lc, corner, L, pl->sx2,
+                                    pl->sy2, st));
+  }
   fps::GemmProb g1[4], g2[4];
-  const int cnt = out_gemms(pl, Y, U, ws, g1, g2);
-  FPS_HIP(fps::launch_fill(U, N * N, 0.0, st));
-  FPS_HIP(fps::launch_gemm(g1, cnt, st));
-  FPS_HIP(fps::launch_gemm(g2, cnt, st));
+  fps_status s;
+  int cnt = rhs_gemms(pl, w, g1, g2, lr, lc);
+  if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
+  if ((s = run_products(pl, g2, cnt, st)) != FPS_OK) return s;
+  cnt = out_gemms(pl, U, w, g1, g2);
+  const int64_t N = out_extent(pl);
+  if (L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N, 0.0, st));  // no odd modes: n = 1
+  if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
+  if ((s = run_products(pl, g2, cnt, st)) != FPS_OK) return s;
+  if (bc) FPS_HIP(fps::launch_bc_lift_out(U, bc, corner, L.n, st));
   return FPS_OK;
 }
 
@@ -514,54 +468,25 @@ fps_status plan2d_build(fps_plan *pl) {
   pl->n_f32 = 0;
   for (size_t k = 0; k < pl->rsh.size(); ++k)
     if (pl->rf32[k]) pl->n_f32 += pl->rsh[k].J;
-  // Tables of every step of every round (a rectangle has two per step).
-  std::vector<double> alpha, beta;
-  for (const fps::ShiftSet &sh : pl->rsh)
-    for (int j = 0; j < sh.J; ++j) {
-      if (pl->rect) {  // tables 2j: sy2 A~ + p_j, 2j + 1: sx2 A~ - q_j
-        alpha.push_back(pl->sy2);
-        beta.push_back(sh.p[j]);
+  pl->L = fps::make_layout(n);
+  if (prec == FPS_FP64) {
+    // sweep tables of the stage entry point fps_adi_native: one per step (a
+    // rectangle has two)
+    std::vector<double> alpha, beta;
+    for (int j = 0; j < pl->shifts.J; ++j) {
+      alpha.push_back(pl->rect ? pl->sy2 : 1.0);  // rectangle: table 2j: sy2 A~ + p_j,
+      beta.push_back(pl->shifts.p[j]);
+      if (pl->rect) {  // 2j + 1: sx2 A~ - q_j
         alpha.push_back(pl->sx2);
-        beta.push_back(-sh.q[j]);
-      } else {
-        alpha.push_back(1.0);
-        beta.push_back(sh.p[j]);
+        beta.push_back(-pl->shifts.q[j]);
       }
     }
-  pl->L = fps::make_layout(n);
-  fps::build_sweep_tables_ab(pl->L, alpha, beta, pl->tab, pl->ctab, nullptr, pl->l1);
-  fps::build_conversions(pl->L, pl->Rs, pl->P);
-  std::vector<double> RsA[2], RsB[2], PA[2], PB[2];
-  for (int s = 0; s < 2; ++s) {
-    const int64_t m = pl->L.m[s], mp = pl->L.mp[s], mo = pl->L.mo[s];
-    const int64_t mop = (mo + fps::kPad - 1) / fps::kPad * fps::kPad;
-    pl->mop[s] = mop;
-    RsA[s].assign((size_t)mp * mp, 0.0);
-    RsB[s].assign((size_t)mp * mp, 0.0);
-    PA[s].assign((size_t)mop * mp, 0.0);
-    PB[s].assign((size_t)mp * mop, 0.0);
-    for (int64_t i = 0; i < m; ++i)
-      for (int64_t k = 0; k < m; ++k) {
-        RsA[s][(size_t)i * mp + k] = pl->Rs[s][(size_t)i * m + k];
-        RsB[s][(size_t)k * mp + i] = pl->Rs[s][(size_t)i * m + k];
-      }
-    for (int64_t i = 0; i < mo; ++i)
-      for (int64_t k = 0; k < m; ++k) {
-        PA[s][(size_t)i * mp + k] = pl->P[s][(size_t)i * m + k];
-        PB[s][(size_t)k * mop + i] = pl->P[s][(size_t)i * m + k];
-      }
+    fps::build_sweep_tables_ab(pl->L, alpha, beta, pl->tab, pl->ctab, nullptr, pl->l1);
   }
+  fps::build_conversions(pl->L, pl->Rs, pl->P);
+  for (int s = 0; s < 2; ++s) pl->mop[s] = (pl->L.mo[s] + fps::kPad - 1) / fps::kPad * fps::kPad;
   pl->sinv.resize(n);
   for (int64_t i = 0; i < n; ++i) pl->sinv[i] = 1.0 / std::sqrt((double)(i + 1) * (double)(i + 2));
-  // A~ as a stencil along each parity block of the internal layout.
-  pl->sdiag.assign(pl->L.npad, 0.0);
-  pl->soff.assign(pl->L.npad, 0.0);
-  for (int sp = 0; sp < 2; ++sp)
-    for (int64_t k = 0; k < pl->L.m[sp]; ++k) {
-      const int64_t r = sp * pl->L.mp[0] + k, i = 2 * k + sp;
-      pl->sdiag[r] = fps::atilde_diag(i);
-      if (k + 1 < pl->L.m[sp]) pl->soff[r] = fps::atilde_off(i);
-    }
 
   const fps::Layout &L = pl->L;
   const int64_t sq = align256(L.npad * L.npad * 8);
@@ -574,6 +499,8 @@ fps_status plan2d_build(fps_plan *pl) {
   pl->off_lv = 4 * sq;
   pl->off_ab = 4 * sq + lvb;
   const int64_t mobar = pl->mop[0] + pl->mop[1];
+  if (L.npad * mobar * 8 > pl->off_lv - pl->off_O0)
+    return fail(FPS_E_STATE, "internal: output temporary exceeds workspace");
   pl->off_X = 4 * sq + lvb + abb;
   // second boundary-value buffer for sweeps that form their own carries
   // (chains of at most two chunks); after everything else
@@ -600,19 +527,13 @@ fps_status plan2d_build(fps_plan *pl) {
   if (!(flags & FPS_PLAN_HOST_ONLY)) {
     fps_status s;
     if ((s = upload(pl->d_tab, pl->tab)) != FPS_OK || (s = upload(pl->d_ctab, pl->ctab)) != FPS_OK ||
-        (s = upload(pl->d_l1, pl->l1)) != FPS_OK ||
-        (s = upload(pl->d_RsA[0], RsA[0])) != FPS_OK || (s = upload(pl->d_RsA[1], RsA[1])) != FPS_OK ||
-        (s = upload(pl->d_RsB[0], RsB[0])) != FPS_OK || (s = upload(pl->d_RsB[1], RsB[1])) != FPS_OK ||
-        (s = upload(pl->d_PA[0], PA[0])) != FPS_OK || (s = upload(pl->d_PA[1], PA[1])) != FPS_OK ||
-        (s = upload(pl->d_PB[0], PB[0])) != FPS_OK || (s = upload(pl->d_PB[1], PB[1])) != FPS_OK ||
-        (s = upload(pl->d_sinv, pl->sinv)) != FPS_OK || (s = upload(pl->d_sdiag, pl->sdiag)) != FPS_OK ||
-        (s = upload(pl->d_soff, pl->soff)) != FPS_OK ||
-        (s = upload(pl->d_lift[0], lift[0])) != FPS_OK ||
-        (s = upload(pl->d_lift[1], lift[1])) != FPS_OK)
+        (s = upload(pl->d_l1, pl->l1)) != FPS_OK || (s = upload(pl->d_sinv, pl->sinv)) != FPS_OK ||
+        (s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) ? lift : nullptr)) != FPS_OK ||
+        (s = spectral_factors_2d(pl)) != FPS_OK)
       return s;
     // chains of more than two chunks: the two row-parity halves of the ADI
     // run on two streams (run_adi)
-    if (!fused && L.m[1] > 0 && (s = create_side_stream(pl)) != FPS_OK) return s;
+    if (prec == FPS_FP64 && !fused && L.m[1] > 0 && (s = create_side_stream(pl)) != FPS_OK) return s;
     pl->on_device = true;
   }
   return FPS_OK;
@@ -817,14 +738,7 @@ fps_status fps_solve_dirichlet(fps_plan *pl, const double *F, const double *bc, 
     return fail(FPS_E_UNSUPPORTED, "Dirichlet data need the Chebyshev output basis");
   if (!(pl->flags & FPS_PLAN_DIRICHLET))
     return fail(FPS_E_STATE, "the plan was created without FPS_PLAN_DIRICHLET");
-  hipStream_t st = (hipStream_t)stream;
-  char *w = (char *)ws;
-  if ((s = rhs_transform(pl, F, w, st, bc)) != FPS_OK) return s;
-  double *Y = nullptr;
-  if ((s = solve_symmetric(pl, w, st, &Y)) != FPS_OK) return s;
-  if ((s = out_transform(pl, Y, U, w, st)) != FPS_OK) return s;
-  FPS_HIP(fps::launch_bc_lift_out(U, bc, (const double *)(w + pl->off_bc), pl->L.n, pl->L.npad, st));
-  return FPS_OK;
+  return solve_2d(pl, F, bc, U, (char *)ws, (hipStream_t)stream);
 }
 
 fps_status fps_solve(fps_plan *pl, const double *F, double *U, void *ws, void *stream) {
@@ -832,17 +746,9 @@ fps_status fps_solve(fps_plan *pl, const double *F, double *U, void *ws, void *s
   if (s != FPS_OK) return s;
   hipStream_t st = (hipStream_t)stream;
   char *w = (char *)ws;
-  const fps::Layout &L = pl->L;
   if (pl->cyl) return cyl_solve(pl, F, U, w, st);
   if (pl->dim == 3) return cube_solve(pl, F, U, w, st);
-  if ((s = rhs_transform(pl, F, w, st)) != FPS_OK) return s;
-  double *Y = nullptr;
-  if ((s = solve_symmetric(pl, w, st, &Y)) != FPS_OK) return s;
-  if (pl->out_basis == FPS_OUT_NATIVE) {
-    FPS_HIP(fps::launch_permute_out(Y, U, L.n, L.npad, L.mp[0], (const double *)pl->d_sinv.p, st));
-    return FPS_OK;
-  }
-  return out_transform(pl, Y, U, w, st);
+  return solve_2d(pl, F, nullptr, U, w, st);
 }
 
 fps_status fps_adi_native(fps_plan *pl, const double *G, double *Y, void *ws, void *stream) {
@@ -869,46 +775,45 @@ fps_status fps_adi_native(fps_plan *pl, const double *G, double *Y, void *ws, vo
 namespace fps {
 namespace detail {
 
-// The adjoint's steps around the ADI map (Frobenius transposes of the input
-// and output maps, Sec. 3.4 and Table 1 read backwards).
+// The adjoint: the solve's four products transposed, in reverse order.  The
+// multiplier is the same (diagonal in the eigenbasis), so the cotangent goes
+// through Wo^T, the multiplier and Wi^T.
 //
-// GEMMs of the adjoint's input map (Chebyshev output basis): Ybar_st =
-// P_s^T Ubar_st P_t per parity block, from Ubar in the parity-blocked
-// layout (X region, mobar x mobar) through temporaries in O0/O1, into G.
+// Ybar^_st = (Wo_s^T Ubar_st Wo_t) o multiplier, from Ubar in the
+// parity-blocked layout (X region), into G.
 int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *g2) {
   const fps::Layout &L = pl->L;
-  const int64_t npad = L.npad;
-  const int64_t mo0 = pl->mop[0], mobar = pl->mop[0] + pl->mop[1];
+  const bool native = pl->out_basis == FPS_OUT_NATIVE;
+  const int64_t *mop = native ? L.mp : pl->mop;
+  const int64_t npad = L.npad, mo0 = mop[0], mobar = mop[0] + mop[1];
   const double *Up = (const double *)(w + pl->off_X);
+  const double *mr = (const double *)pl->d_mr.p, *mc = (const double *)pl->d_mc.p;
   double *G = (double *)(w + pl->off_G);
   double *Tt = (double *)(w + pl->off_O0);  // temporaries mop_s x mp_t
   int cnt = 0;
   int64_t toff = 0;
   for (int s2 = 0; s2 < 2; ++s2)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s2], mt = L.mp[t], mos = pl->mop[s2], mot = pl->mop[t];
+      const int64_t ms = L.mp[s2], mt = L.mp[t], mos = mop[s2], mot = mop[t];
+      const int64_t rs = s2 * L.mp[0], rt = t * L.mp[0];
       if (L.m[s2] == 0 || L.m[t] == 0) continue;
       double *Tst = Tt + toff;
       toff += mos * mt;
-      // T_st = Ubar_st P_t; B(k, j) = P_t[k][j] = 0 for k > j + 1.
-      g1[cnt] = fps::GemmProb{Up + (s2 * mo0) * mobar + t * mo0, (const double *)pl->d_PA[t].p,
-                              Tst, mos, mt, mot, mobar, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 1, 1};
-      // Ybar_st = P_s^T T_st; A(i, k) = P_s[k][i] = 0 for k > i + 1.
-      g2[cnt] = fps::GemmProb{(const double *)pl->d_PB[s2].p, Tst,
-                              G + (s2 * L.mp[0]) * npad + t * L.mp[0], ms, mt, mos, mos, 1, mt, 1,
-                              npad, 1, 0, 0, 0, 0, 1, 1, 0, 0};
+      g1[cnt] = fps::GemmProb{Up + (s2 * mo0) * mobar + t * mo0, (const double *)pl->d_Wo[t].p,
+                              Tst, mos, mt, mot, mobar, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+      g2[cnt] = fps::GemmProb{(const double *)pl->d_WoT[s2].p, Tst, G + rs * npad + rt, ms, mt, mos,
+                              mos, 1, mt, 1, npad, 1, 0, 0, 0, 0, 0, 0, 0, 0, mr + 2 * rs,
+                              mc + 2 * rt, nullptr, nullptr};
       ++cnt;
     }
   return cnt;
 }
 
-// GEMMs of the adjoint's output map: Fbar = R^T S^-1 Gbar S^-1 R, blockwise
-// Rs_s^T Gbar_st Rs_t into the strided view of Fbar (Gbar: the ADI output,
-// parity-blocked), through temporaries in O0/O1.
-int adj_out_gemms(const fps_plan *pl, const double *Yb, double *Fbar, char *w, fps::GemmProb *g1,
-                  fps::GemmProb *g2) {
+// Fbar_st = Wi_s^T Ybar^_st Wi_t into the strided view of Fbar.
+int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, fps::GemmProb *g2) {
   const fps::Layout &L = pl->L;
   const int64_t n = L.n, npad = L.npad;
+  const double *Yb = (const double *)(w + pl->off_G);
   double *Tb = (double *)(w + pl->off_O0);
   int cnt = 0;
   int64_t toff = 0;
@@ -918,57 +823,13 @@ int adj_out_gemms(const fps_plan *pl, const double *Yb, double *Fbar, char *w, f
       if (L.m[s2] == 0 || L.m[t] == 0) continue;
       double *Tst = Tb + toff;
       toff += ms * mt;
-      // T_st = Gbar_st Rs_t; B(k, j) = Rs_t[k][j] = 0 for k > j.
-      g1[cnt] = fps::GemmProb{Yb + (s2 * L.mp[0]) * npad + t * L.mp[0], (const double *)pl->d_RsA[t].p,
-                              Tst, ms, mt, mt, npad, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 1, 0};
-      // Fbar_st = Rs_s^T T_st; A(i, k) = Rs_s[k][i] = 0 for k > i.
-      g2[cnt] = fps::GemmProb{(const double *)pl->d_RsB[s2].p, Tst, Fbar + s2 * n + t, L.m[s2],
-                              L.m[t], ms, ms, 1, mt, 1, 2 * n, 2, 0, 0, 0, 0, 1, 0, 0, 0};
+      g1[cnt] = fps::GemmProb{Yb + (s2 * L.mp[0]) * npad + t * L.mp[0], (const double *)pl->d_Wi[t].p,
+                              Tst, ms, mt, mt, npad, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+      g2[cnt] = fps::GemmProb{(const double *)pl->d_WiT[s2].p, Tst, Fbar + s2 * n + t, L.m[s2],
+                              L.m[t], ms, ms, 1, mt, 1, 2 * n, 2, 0, 0, 0, 0, 0, 0, 0, 0};
       ++cnt;
     }
   return cnt;
-}
-
-// The adjoint's input map up to its GEMMs: Ubar permuted into the
-// parity-blocked layout and G cleared (Chebyshev output), or Ybar = S^-1
-// Xbar S^-1 straight into G (native output).
-fps_status adjoint_in_pre(const fps_plan *pl, const double *Ubar, char *w, hipStream_t st) {
-  const fps::Layout &L = pl->L;
-  const int64_t n = L.n, npad = L.npad, N = n + 2;
-  double *G = (double *)(w + pl->off_G);
-  if (pl->out_basis == FPS_OUT_NATIVE) {
-    FPS_HIP(fps::launch_permute_in(Ubar, G, n, npad, L.mp[0], st, (const double *)pl->d_sinv.p));
-    return FPS_OK;
-  }
-  const int64_t mo0 = pl->mop[0], mobar = pl->mop[0] + pl->mop[1];
-  if (npad * mobar * 8 > pl->off_lv - pl->off_O0)
-    return fail(FPS_E_STATE, "internal: adjoint temporaries exceed workspace");
-  FPS_HIP(fps::launch_permute_in(Ubar, (double *)(w + pl->off_X), N, mobar, mo0, st));
-  FPS_HIP(fps::launch_fill(G, npad * npad, 0.0, st));
-  return FPS_OK;
-}
-
-// adjoint_in: Ybar into G from Ubar.
-fps_status adjoint_in(const fps_plan *pl, const double *Ubar, char *w, hipStream_t st) {
-  fps_status s;
-  if ((s = adjoint_in_pre(pl, Ubar, w, st)) != FPS_OK) return s;
-  if (pl->out_basis != FPS_OUT_NATIVE) {
-    fps::GemmProb g1[4], g2[4];
-    const int cnt = adj_in_gemms(pl, w, g1, g2);
-    FPS_HIP(fps::launch_gemm(g1, cnt, st));
-    FPS_HIP(fps::launch_gemm(g2, cnt, st));
-  }
-  return FPS_OK;
-}
-
-// adjoint_out: Fbar from the ADI output Gbar.
-fps_status adjoint_out(const fps_plan *pl, const double *Yb, double *Fbar, char *w,
-                       hipStream_t st) {
-  fps::GemmProb g1[4], g2[4];
-  const int cnt = adj_out_gemms(pl, Yb, Fbar, w, g1, g2);
-  FPS_HIP(fps::launch_gemm(g1, cnt, st));
-  FPS_HIP(fps::launch_gemm(g2, cnt, st));
-  return FPS_OK;
 }
 
 }  // namespace detail
@@ -984,10 +845,18 @@ fps_status fps_solve_adjoint(fps_plan *pl, const double *Ubar, double *Fbar, voi
     return fail(FPS_E_UNSUPPORTED, "adjoint: square FP64 plans only");
   hipStream_t st = (hipStream_t)stream;
   char *w = (char *)ws;
-  if ((s = fps::detail::adjoint_in(pl, Ubar, w, st)) != FPS_OK) return s;
-  double *Yb = nullptr;
-  if ((s = solve_symmetric(pl, w, st, &Yb)) != FPS_OK) return s;  // Gbar, in G
-  return fps::detail::adjoint_out(pl, Yb, Fbar, w, st);
+  const fps::Layout &L = pl->L;
+  const bool native = pl->out_basis == FPS_OUT_NATIVE;
+  const int64_t *mop = native ? L.mp : pl->mop;
+  FPS_HIP(fps::launch_permute_in(Ubar, (double *)(w + pl->off_X), out_extent(pl), mop[0] + mop[1],
+                                 mop[0], st));
+  fps::GemmProb g1[4], g2[4];
+  int cnt = adj_in_gemms(pl, w, g1, g2);
+  if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
+  if ((s = run_products(pl, g2, cnt, st)) != FPS_OK) return s;
+  cnt = adj_out_gemms(pl, Fbar, w, g1, g2);
+  if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
+  return run_products(pl, g2, cnt, st);
 }
 
 fps_status fps_plan_set_sweep_timing(fps_plan *pl, int capacity) {

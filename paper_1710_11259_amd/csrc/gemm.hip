@@ -1,5 +1,6 @@
 // gfx950 FP64 MFMA GEMM for the dense coefficient maps of the spectral
 // Poisson solver (Chebyshev <-> C~^(3/2) maps of Sec. 3.4 and Table 1).
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -64,10 +65,24 @@ __host__ __device__ inline void tile_krange(const GemmProb &g, int bx, int by, i
   *khi_out = khi;
 }
 
+// The output entry (i, j) from its accumulated product v: the eigenbasis
+// multiplier
+// (compiled in only for launches that hold such problems: the maps without
+// it would pay registers and a test per entry).
+__device__ __forceinline__ double multiply(const GemmProb &g, int64_t i, int64_t j, double v) {
+  if (g.lr != nullptr) {
+    const double *r = g.lr + 4 * i, *c = g.lc + 4 * j;
+    v -= fma(r[3], c[3], fma(r[2], c[2], fma(r[1], c[1], r[0] * c[0])));
+  }
+  const dbl2 r = *(const dbl2 *)(g.mr + 2 * i), c = *(const dbl2 *)(g.mc + 2 * j);
+  return v * (fma(-r.y, c.y, 1.0) / (r.x + c.x));
+}
+
 // One 128 x 128 output tile (column tile bx, row tile by) of problem g.
 // Two LDS stages (As, Bs and As2, Bs2): the next k-tile is stashed into the
 // stage not being read, so one barrier per k-tile suffices (68 KB of LDS, two
 // workgroups per compute unit).
+template <bool kMul>
 __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int bx, const int by,
                                           double (*As)[GBK + 1], double (*Bs)[GBN + GPAD],
                                           double (*As2)[GBK + 1], double (*Bs2)[GBN + GPAD]) {
@@ -183,10 +198,13 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int bx, const
       for (int r = 0; r < 4; ++r) {
         const int64_t gi = i0 + wy * 64 + a * 16 + 4 * r + (lane >> 4);
         const int64_t gj = j0 + wx * 64 + b * 16 + (lane & 15);
-        if (gi < g.M && gj < g.N) g.C[gi * g.sci + gj * g.scj] = acc[a][b][r];
+        if (gi < g.M && gj < g.N) 
+          g.C[gi * g.sci + gj * g.scj] =
+              kMul ? multiply(g, gi, gj, acc[a][b][r]) : acc[a][b][r];
       }
 }
 
+template <bool kMul>
 __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
   __shared__ double As[GBM][GBK + 1], As2[GBM][GBK + 1];
   __shared__ double Bs[GBK][GBN + GPAD], Bs2[GBK][GBN + GPAD];
@@ -206,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
       bx = rem % nt;
     }
   }
-  gemm_tile(batch.p[z], bx, by, As, Bs, As2, Bs2);
+  gemm_tile<kMul>(batch.p[z], bx, by, As, Bs, As2, Bs2);
 }
 
 // Table-driven GEMM: workgroup g computes tile (local % ntx, local / ntx),
@@ -217,6 +235,7 @@ __device__ __forceinline__ const double *rebase(const double *p, int id, char *w
                  : id == 2 ? (const double *)(out + (intptr_t)p) : p;
 }
 
+template <bool kMul>
 __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restrict__ d,
                                                        const int *__restrict__ tile_map, char *ws,
                                                        char *out) {
@@ -229,7 +248,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restric
   g.A = rebase(g.A, e.abase, ws, out);
   g.B = rebase(g.B, e.bbase, ws, out);
   g.C = (double *)rebase(g.C, e.cbase, ws, out);
-  gemm_tile(g, local % e.ntx, local / e.ntx, As, Bs, As2, Bs2);
+  gemm_tile<kMul>(g, local % e.ntx, local / e.ntx, As, Bs, As2, Bs2);
 }
 
 // Columns tn.. of every row of a table problem: one wavefront per row,
@@ -325,10 +344,10 @@ int gemm_tiles(const GemmProb &q, int *ntx) {
 }
 
 hipError_t launch_gemm_table(const GemmDesc *d, const int *tile_map, int ntiles, char *ws,
-                             char *out, hipStream_t st) {
+                             char *out, hipStream_t st, bool mul) {
   if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gemm_table, dim3((unsigned)ntiles), dim3(256), 0, st, d, tile_map, ws,
-                     out);
+  hipLaunchKernelGGL(mul ? k_gemm_table<true> : k_gemm_table<false>, dim3((unsigned)ntiles),
+                     dim3(256), 0, st, d, tile_map, ws, out);
   return hipGetLastError();
 }
 
@@ -359,7 +378,8 @@ std::vector<int> gemm_table_map(const std::vector<GemmDesc> &tab) {
   return map;
 }
 
-hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st) {
+hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0,
+                       hipEvent_t ev1) {
   if (count <= 0) return hipSuccess;
   if (count > 4) return hipErrorInvalidValue;
   GemmBatch b{};
@@ -368,6 +388,7 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st) {
     const GemmProb &q = probs[i];
     // contiguous operands, 16-byte aligned, K padded to the k-tile
     if (!gemm_operands_ok(q)) return hipErrorInvalidValue;
+    if ((q.mr != nullptr) != (probs[0].mr != nullptr)) return hipErrorInvalidValue;
     b.p[i] = probs[i];
     mt = probs[i].M > mt * GBM ? (probs[i].M + GBM - 1) / GBM : mt;
     nt = probs[i].N > nt * GBN ? (probs[i].N + GBN - 1) / GBN : nt;
@@ -389,7 +410,11 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st) {
   else if (same && rowwise && !colwise && !(f.triA && f.triAu))
     b.order = f.triA ? 3 : 4;
   dim3 grid((unsigned)nt, (unsigned)mt, (unsigned)count);
-  hipLaunchKernelGGL(k_gemm, grid, dim3(256), 0, st, b);
+  const auto kern = f.mr != nullptr ? k_gemm<true> : k_gemm<false>;
+  if (ev0 != nullptr)
+    hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, st, ev0, ev1, 0, b);
+  else
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, b);
   return hipGetLastError();
 }
 

@@ -297,14 +297,14 @@ hipError_t launch_fill(double *dst, int64_t count, double v, hipStream_t st);
 struct BcLiftConst {
   double sinv[2], am[2], ap[2];
 };
-// G (parity-blocked, row stride npad) -= S^-1 C~(Lap u_bc) S^-1, touching
-// rows 0, 1 and columns 0, 1 only.  Ms0 / Ms1: the lift map S^-1 C~(T_k'')
-// by parity (m_s x mo_s, row-major, build_lift_map).  scratch: [4][npad] +
-// [8] doubles; its last 8 entries keep the traces' values at -1 and +1 for
-// launch_bc_lift_out.
-hipError_t launch_bc_lift_rhs(const double *bc, const double *Ms0, const double *Ms1, double *G,
-                              double *scratch, const Layout &L, double sx2, double sy2,
-                              const BcLiftConst &k, hipStream_t st);
+// The lift's right-hand side V^T S^-1 C~(Lap u_bc) S^-1 V as a sum of four
+// outer products lr[i][q] lc[j][q] by storage position (lr and lc [npad][4]),
+// and the traces' values at -1 and +1 (corner [8], for launch_bc_lift_out).  Ml0 / Ml1: the lift map V^T S^-1 C~(T_k'') by parity
+// (row length ld0 / ld1); lina [npad][2]: V^T of the lift's linear factors.
+hipError_t launch_bc_lift_rhs(const double *bc, const double *Ml0, const double *Ml1, int64_t ld0,
+                              int64_t ld1, const double *lina, double *lr, double *lc,
+                              double *corner, const Layout &L, double sx2, double sy2,
+                              hipStream_t st);
 // Cylinder: F [mode][part][n][n] -> X0 [slot][part][r][z] parity-blocked
 // (slot -> mode through slot_idx), zero padded to npad = 2 mp per axis.
 hipError_t launch_cyl_permute_in(const double *F, double *X0, const int *slot_idx, int64_t n,
@@ -339,8 +339,8 @@ hipError_t launch_cyl_redge(const CylEdge *d, int nprob, char *ws, double *U, in
                             int64_t mobar, int64_t ldc, hipStream_t st);
 
 // U ((n+2) x (n+2) Chebyshev, natural order) += coefficients of u_bc.
-hipError_t launch_bc_lift_out(double *U, const double *bc, const double *scratch, int64_t n,
-                              int64_t npad, hipStream_t st);
+hipError_t launch_bc_lift_out(double *U, const double *bc, const double *corner, int64_t n,
+                              hipStream_t st);
 
 // FP64 GEMM on MFMA, up to 4 independent problems per launch:
 //   C(i,j) = sum_k A(i,k) B(k,j),  A(i,k) = A[i*sai + k], B(k,j) = B[k*sbk + j],
@@ -358,8 +358,31 @@ struct GemmProb {
   // upper bounds: when triAu, A(i,k) = 0 for k > i + offAu; when triBu,
   // B(k,j) = 0 for k > j + offBu; k-tiles above the last nonzero are skipped.
   int triAu, offAu, triBu, offBu;
+  // Multiplier of the eigenbasis solve, when mr is non-null: C(i,j) becomes
+  //   (acc - sum_q lr[4i+q] lc[4j+q]) (1 - mr[2i+1] mc[2j+1]) / (mr[2i] + mc[2j]),
+  // the lr / lc term (the Dirichlet lift) only when lr is non-null.
+  // Every problem of one launch has it or none does.
+  const double *mr, *mc, *lr, *lc;
 };
-hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st);
+hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0 = nullptr,
+                       hipEvent_t ev1 = nullptr);
+
+// Plan-time passes of the eigenbasis form (spectral.hip).  Eigenpairs of the
+// negative definite tridiagonal T whose negated diagonal is d, coupling e (e2
+// = e^2; device arrays of m): lam[a] ascending from the most negative, V the
+// orthonormal-to-m-eps vectors as columns (row length ld); [lo, hi] encloses
+// sigma(-T); Dp, Dm scratch of V's shape, V zeroed by the caller.
+hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2, int64_t m,
+                              double lo, double hi, double *lam, double *Dp, double *Dm, double *V,
+                              int64_t ld, hipStream_t st);
+// H = 1.5 I - 0.5 H (n x n, contiguous).
+hipError_t launch_polar_factor(double *H, int64_t n, hipStream_t st);
+// out = in^T, rows x cols multiples of 64.
+hipError_t launch_transpose(const double *in, int64_t ldi, double *out, int64_t ldo, int64_t rows,
+                            int64_t cols, hipStream_t st);
+// out[i][j] = sinv[2i + s] in[i][j] for i < m, 0 for the other rows.
+hipError_t launch_scale_rows(const double *in, const double *sinv, int s, int64_t m, int64_t rows,
+                             int64_t ld, double *out, hipStream_t st);
 
 // The launcher's operand requirements (also for table-driven problems, with
 // offsets in place of pointers) and the tile count of one problem (ntx: its
@@ -377,8 +400,9 @@ struct GemmDesc {
   int tile_start;  // first tile of this problem in table order (host bookkeeping)
   int ntx;
 };
+// mul: every problem of the table has a multiplier (else none does).
 hipError_t launch_gemm_table(const GemmDesc *d, const int *tile_map, int ntiles, char *ws,
-                             char *out, hipStream_t st);
+                             char *out, hipStream_t st, bool mul = false);
 // Host: the tile map of a table, (problem, local tile) pairs for every tile
 // of every problem, longest k-range (after the triangular skips) first.
 std::vector<int> gemm_table_map(const std::vector<GemmDesc> &tab);

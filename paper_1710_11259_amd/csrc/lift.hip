@@ -7,11 +7,11 @@
 // s in its L, R terms and linear in t in its B, T terms,
 //   Lap u_bc = sx2 [(1-t)/2 B''(s) + (1+t)/2 T''(s)]
 //            + sy2 [(1-s)/2 L''(t) + (1+s)/2 R''(t)],
-// whose C~ x C~ coefficients live in rows 0, 1 and columns 0, 1 only (a
-// linear function has C~ coefficients at degrees 0 and 1).  The 1-D factors
-// S^-1 C~(g'') come from the plan's lift map applied to the traces' Chebyshev
-// coefficients (4 matrix-vector products with its parity blocks); all other
-// work is O(n).
+// a sum of four outer products.  In the eigenbasis of A~ its 1-D factors are
+// the plan's merged lift map V^T S^-1 C~(T_k'') applied to the traces'
+// Chebyshev coefficients (4 matrix-vector products with its parity blocks) and
+// V^T of the linear factors (in the plan); the product that forms Y^ subtracts
+// the outer products before its multiplier, and all other work is O(n).
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
@@ -52,25 +52,31 @@ __global__ __launch_bounds__(kCornerThreads) void k_bc_corner(const double *__re
   }
 }
 
-// w[X][pos] = S^-1 C~(g_X'') at the parity-blocked position of natural index
-// i = 2a + s: sum over b > a of Ms_s[a][b] g_X[2b + s] (Ms_s has row length
-// mo_s; T''_k has C~ components only below degree k - 1).  One wavefront per
-// output row.
-__global__ __launch_bounds__(256) void k_bc_cmap(const double *__restrict__ Ms0,
-                                                 const double *__restrict__ Ms1,
-                                                 const double *__restrict__ bc,
-                                                 double *__restrict__ w, int64_t n, int64_t npad,
-                                                 int64_t m0, int64_t mp0, int64_t mo0,
-                                                 int64_t mo1) {
+// One wavefront per eigenbasis row: w_X = V^T S^-1 C~(g_X'') of the four
+// traces (the sum over k of the lift map's row times g_X), then the row's
+// entries of the outer-product factors of
+//   sx2 [am (B'')^T + ap (T'')^T] + sy2 [L'' am^T + R'' ap^T],
+// am / ap the linear factors (1 - t)/2 and (1 + t)/2 (lina).
+__global__ __launch_bounds__(256) void k_bc_cmap(const double *__restrict__ Ml0,
+                                                 const double *__restrict__ Ml1, int64_t ld0,
+                                                 int64_t ld1, const double *__restrict__ bc,
+                                                 const double *__restrict__ lina,
+                                                 double *__restrict__ lr, double *__restrict__ lc,
+                                                 int64_t n, int64_t mp0, int64_t mo0, int64_t mo1,
+                                                 double sx2, double sy2) {
   const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;  // uniform per wavefront
-  const int s = row < m0 ? 0 : 1;
-  const int64_t a = s ? row - m0 : row;
+  const int64_t pos = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // npad is a multiple of 4
+  const int s = pos < mp0 ? 0 : 1;
+  const int64_t a = s ? pos - mp0 : pos;
+  double *r = lr + 4 * pos, *c = lc + 4 * pos;
+  if (a >= (s ? n / 2 : (n + 1) / 2)) {  // padding (uniform per wavefront): inert
+    if (lane < 4) r[lane] = c[lane] = 0.0;
+    return;
+  }
   const int64_t mo = s ? mo1 : mo0, N = n + 2;
-  const double *Mrow = (s ? Ms1 : Ms0) + a * mo;
+  const double *Mrow = s ? Ml1 + a * ld1 : Ml0 + a * ld0;
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  for (int64_t b = a + 1 + lane; b < mo; b += 64) {
+  for (int64_t b = lane; b < mo; b += 64) {
     const double m = Mrow[b];
     const int64_t k = 2 * b + s;
     a0 += m * bc[k];
@@ -85,40 +91,16 @@ __global__ __launch_bounds__(256) void k_bc_cmap(const double *__restrict__ Ms0,
     a3 += __shfl_xor(a3, off, 64);
   }
   if (lane == 0) {
-    const int64_t pos = s * mp0 + a;
-    w[pos] = a0;
-    w[npad + pos] = a1;
-    w[2 * npad + pos] = a2;
-    w[3 * npad + pos] = a3;
+    const double am = lina[2 * pos], ap = lina[2 * pos + 1];
+    r[0] = sx2 * am;  // B is trace 2, T trace 3
+    r[1] = sx2 * ap;
+    r[2] = sy2 * a0;  // L is trace 0, R trace 1
+    r[3] = sy2 * a1;
+    c[0] = a2;
+    c[1] = a3;
+    c[2] = am;
+    c[3] = ap;
   }
-}
-
-__device__ inline int64_t ppos(int64_t i, int64_t mp0) { return (i & 1) * mp0 + (i >> 1); }
-
-// G -= S^-1 C~(Lap u_bc) S^-1 on rows 0, 1 and columns 0, 1 (natural
-// indices; G parity-blocked, row stride npad).  One thread per touched
-// entry, so the corner entries that collect both terms are not shared.
-__global__ void k_bc_rhs(double *__restrict__ G, const double *__restrict__ w, int64_t n,
-                         int64_t npad, int64_t mp0, double sx2, double sy2, BcLiftConst k) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n2 = n < 2 ? n : 2;
-  if (e >= n2 * n + (n - n2) * n2) return;
-  int64_t i, j;
-  if (e < n2 * n) {
-    i = e / n;
-    j = e % n;
-  } else {
-    const int64_t f = e - n2 * n;
-    i = n2 + f / n2;
-    j = f % n2;
-  }
-  const int64_t pi = ppos(i, mp0), pj = ppos(j, mp0);
-  double v = 0.0;
-  if (i < 2)  // sx2 [(1-t)/2 B'' + (1+t)/2 T'']: B is trace 2, T trace 3
-    v += k.sinv[i] * sx2 * (k.am[i] * w[2 * npad + pj] + k.ap[i] * w[3 * npad + pj]);
-  if (j < 2)  // sy2 [(1-s)/2 L'' + (1+s)/2 R'']: L is trace 0, R trace 1
-    v += k.sinv[j] * sy2 * (w[pi] * k.am[j] + w[npad + pi] * k.ap[j]);
-  G[pi * npad + pj] -= v;
 }
 
 // U += Chebyshev coefficients of u_bc (natural (n+2) x (n+2), rows <-> t).
@@ -151,27 +133,21 @@ __global__ void k_bc_out(double *__restrict__ U, const double *__restrict__ bc,
 
 }  // namespace
 
-hipError_t launch_bc_lift_rhs(const double *bc, const double *Ms0, const double *Ms1, double *G,
-                              double *scratch, const Layout &L, double sx2, double sy2,
-                              const BcLiftConst &k, hipStream_t st) {
+hipError_t launch_bc_lift_rhs(const double *bc, const double *Ml0, const double *Ml1, int64_t ld0,
+                              int64_t ld1, const double *lina, double *lr, double *lc, double *corner,
+                              const Layout &L, double sx2, double sy2, hipStream_t st) {
   const int64_t n = L.n;
-  double *w = scratch, *corner = w + 4 * L.npad;
   hipLaunchKernelGGL(k_bc_corner, dim3(4), dim3(kCornerThreads), 0, st, bc, corner, n);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bc_cmap, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, Ms0, Ms1, bc, w,
-                     n, L.npad, L.m[0], L.mp[0], L.mo[0], L.mo[1]);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int64_t n2 = n < 2 ? n : 2, total = n2 * n + (n - n2) * n2;
-  hipLaunchKernelGGL(k_bc_rhs, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, G, w, n,
-                     L.npad, L.mp[0], sx2, sy2, k);
+  hipLaunchKernelGGL(k_bc_cmap, dim3((unsigned)(L.npad / 4)), dim3(256), 0, st, Ml0, Ml1, ld0, ld1,
+                     bc, lina, lr, lc, n, L.mp[0], L.mo[0], L.mo[1], sx2, sy2);
   return hipGetLastError();
 }
 
-hipError_t launch_bc_lift_out(double *U, const double *bc, const double *scratch, int64_t n,
-                              int64_t npad, hipStream_t st) {
+hipError_t launch_bc_lift_out(double *U, const double *bc, const double *corner, int64_t n,
+                              hipStream_t st) {
   const int64_t N = n + 2, total = 2 * N + (N - 2) * 2;
-  const double *corner = scratch + 4 * npad;
   hipLaunchKernelGGL(k_bc_out, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, U, bc,
                      corner, n);
   return hipGetLastError();

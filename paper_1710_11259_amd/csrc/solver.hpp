@@ -91,12 +91,20 @@ struct fps_plan {
 
   // device copies
   fps::detail::DeviceBuf d_tab, d_ctab, d_l1, d_sinv, d_sdiag, d_soff;
-  // GEMM operands, zero-padded to multiples of 64: RsA = Rs (mp x mp),
-  // RsB = Rs^T (mp x mp), PA = P (mop x mp), PB = P^T (mp x mop).
-  fps::detail::DeviceBuf d_RsA[2], d_RsB[2], d_PA[2], d_PB[2];
-  // Lift map S^-1 C~(T_k'') by parity (m[s] x mo[s], row-major), only with
-  // FPS_PLAN_DIRICHLET.
-  fps::detail::DeviceBuf d_lift[2];
+  // Coefficient maps merged with the eigenvectors V of A~ (spectral.cpp), by
+  // parity, zero-padded to multiples of 64, in both orientations: Wi =
+  // V^T S^-1 R (mp x mp) and Wo = P S^-1 V (mop x mp; native output S^-1 V,
+  // mp x mp).  lam: eigenvalues by storage position (-1 on padding); d_mr /
+  // d_mc: the multiplier's row and column factors, [npad][2].
+  fps::detail::DeviceBuf d_Wi[2], d_WiT[2], d_Wo[2], d_WoT[2];
+  fps::detail::DeviceBuf d_mr, d_mc;
+  std::vector<double> lam;
+  fps::detail::DeviceBuf d_RsA[2], d_RsB[2];
+  // GEMM operands of the cube methods: PA = P (mop x mp), PB = P^T (mp x mop).
+  fps::detail::DeviceBuf d_PA[2], d_PB[2];
+  // Lift map V^T S^-1 C~(T_k'') by parity (mp x mop) and V^T of the lift's
+  // linear factors ([npad][2]), only with FPS_PLAN_DIRICHLET.
+  fps::detail::DeviceBuf d_lift[2], d_lina;
 
   // sweep timing diagnostics
   std::vector<hipEvent_t> ev;  // pairs
@@ -223,37 +231,28 @@ struct RefineRound {
   bool f32;
 };
 std::vector<RefineRound> refine_schedule(double tol, bool dirichlet);
-// Input map of one square or rectangle problem: F (n x n, natural order) ->
-// G and G^T in the plan's workspace `ws`; with `bc` non-null, G also takes
-// the Dirichlet lift's correction (the traces' values at -1 and +1 are kept
-// in the workspace for the output correction).
-fps_status rhs_transform(fps_plan *pl, const double *F, char *ws, hipStream_t st,
-                         const double *bc = nullptr);
-// The coefficient-map GEMMs of one problem (up to 4 parity-block products
-// per stage; returns their count), operands formed from the workspace base
-// `ws` (and Y, U); rhs: g1 then g2 after k_permute_in of F into the GT
-// region; out: g1 then g2 after U is zero-filled.
-int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2);
-int out_gemms(const fps_plan *pl, const double *Y, double *U, char *ws, fps::GemmProb *g1,
-              fps::GemmProb *g2);
-// Output map: Y (parity-blocked) -> U in the plan's output basis.
-fps_status out_transform(fps_plan *pl, const double *Y, double *U, char *ws, hipStream_t st);
-// Y of A~ Y + Y A~ = G for G in the workspace (FP64 or refined).
-fps_status solve_symmetric(fps_plan *pl, char *w, hipStream_t st, double **Yout);
-// The adjoint's maps around the ADI (transposes of the input and output
-// maps): adjoint_in forms Ybar from Ubar into the G region (and G^T);
-// adjoint_out forms Fbar from the ADI output Gbar.  FP64 plans.
-fps_status adjoint_in(const fps_plan *pl, const double *Ubar, char *w, hipStream_t st);
-// Pieces of the two for the batched adjoint: the input map up to its GEMMs
-// (permutation, clear of G; native: the whole map), and the GEMMs of the
-// input map (Chebyshev output only) and of the output map, built like
-// rhs_gemms / out_gemms.
-fps_status adjoint_in_pre(const fps_plan *pl, const double *Ubar, char *w, hipStream_t st);
+// Eigenbasis maps (spectral.cpp).
+fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift);
+fps_status spectral_factors_2d(fps_plan *pl);
+fps::BcLiftConst bc_lift_const();
+// The products of one square or rectangle solve, per stage up to 4
+// parity-block problems (returns their count), operands formed from the
+// workspace base `ws` (and U / Fbar).  rhs: g1 then g2 after k_permute_in of F
+// into the GT region, leaving Y^ (the multiplier applied; with lr / lc the
+// Dirichlet lift subtracted first) in G; out: g1 then g2 to U (whose entries of
+// empty parity blocks the caller clears).  adj_in / adj_out: the same four
+// steps of the adjoint, transposed, from the permuted cotangent in the X
+// region to Fbar.
+int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2,
+              const double *lr = nullptr, const double *lc = nullptr);
+int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::GemmProb *g2);
 int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
-int adj_out_gemms(const fps_plan *pl, const double *Yb, double *Fbar, char *w, fps::GemmProb *g1,
-                  fps::GemmProb *g2);
-fps_status adjoint_out(const fps_plan *pl, const double *Gbar, double *Fbar, char *w,
-                       hipStream_t st);
+int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
+// Extents of the solve's output layout: entries per axis, the permuted
+// cotangent's row length and its parity-1 offset.
+inline int64_t out_extent(const fps_plan *pl) {
+  return pl->out_basis == FPS_OUT_NATIVE ? pl->n : pl->n + 2;
+}
 // Cube: host tables and workspace layout (after the common fields are set),
 // their upload, and the solve.
 fps_status cube_plan_build(fps_plan *pl);

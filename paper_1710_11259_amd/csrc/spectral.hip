@@ -1,0 +1,167 @@
+// gfx950 kernels that build the eigenbasis form of the solve at plan time:
+// eigenpairs of the symmetric tridiagonal parity blocks of A~ (App. B
+// decoupling) and the small dense passes around them.
+#include <hip/hip_runtime.h>
+
+#include "kernels.hpp"
+
+namespace fps {
+
+namespace {
+
+// Eigenvalue k (ascending) of the positive definite B = -T (diagonal d,
+// squared couplings e2) by multisection on Sturm counts: one wavefront per
+// eigenvalue, the 64 lanes counting at 64 interior points, so a pass over the
+// matrix cuts the bracket by 65 instead of 2 (12 passes; the recurrence is a
+// serial chain of m divisions, so passes are what costs).  The points are
+// spaced geometrically until the bracket is within a factor 2: the spectrum
+// spans 30 n^4 and every eigenvalue is wanted to relative accuracy.  A zero
+// pivot is left to IEEE: e2 / 0 = inf, the next pivot is -inf and counts.
+// Measured (m = 2048, both parities): 6 ms.
+__global__ __launch_bounds__(256) void k_tridiag_values(const double *__restrict__ d,
+                                                        const double *__restrict__ e2, int m,
+                                                        double lo0, double hi0,
+                                                        double *__restrict__ lam) {
+  const int lane = threadIdx.x & 63;
+  const int k = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (k >= m) return;
+  double lo = lo0, hi = hi0;
+  for (int pass = 0; pass < 12; ++pass) {
+    const double f = (lane + 1) * (1.0 / 65.0);
+    const double x = hi > 2.0 * lo ? lo * exp2(f * log2(hi / lo)) : lo + (hi - lo) * f;
+    double q = d[0] - x;
+    int c = q < 0.0 ? 1 : 0;
+    for (int i = 1; i < m; ++i) {
+      q = (d[i] - x) - e2[i - 1] / q;
+      c += q < 0.0 ? 1 : 0;
+    }
+    // lanes whose point lies at or below the eigenvalue form a prefix
+    const unsigned long long above = ~__ballot(c <= k);
+    const int below = above ? __builtin_ctzll(above) : 64;
+    const double xl = __shfl(x, below > 0 ? below - 1 : 0), xh = __shfl(x, below < 64 ? below : 63);
+    if (below > 0) lo = xl;
+    if (below < 64) hi = xh;
+  }
+  if (lane == 0) lam[m - 1 - k] = -(lo + 0.5 * (hi - lo));  // most negative first
+}
+
+// Eigenvector of every eigenvalue by the twisted factorization of B - x: the
+// pivots of the top-down and bottom-up eliminations, twisted where their
+// combination is smallest, then one multiplication per entry in each
+// direction.  One lane per vector; pivots and vectors are stored [row][vector],
+// so every access of a wavefront is one 512-byte run.  Dp and Dm are scratch
+// of V's shape (ld columns; V and its padding are zeroed by the caller).
+__global__ __launch_bounds__(64) void k_tridiag_vectors(
+    const double *__restrict__ d, const double *__restrict__ e, int m,
+    const double *__restrict__ lam, double *__restrict__ Dp, double *__restrict__ Dm,
+    double *__restrict__ V, int64_t ld) {
+  const int a = blockIdx.x * 64 + threadIdx.x;
+  if (a >= m) return;
+  const double x = -lam[a];
+  constexpr double kEps = 2.220446049250313e-16;
+  auto pivot = [&](double q, double c) { return q == 0.0 ? kEps * c : q; };
+  double q = 0.0;
+  for (int i = 0; i < m; ++i) {
+    q = i == 0 ? d[0] - x : (d[i] - x) - e[i - 1] * e[i - 1] / q;
+    q = pivot(q, i + 1 < m ? e[i] : d[i]);
+    Dp[i * ld + a] = q;
+  }
+  double best = 0.0;
+  int r = m - 1;
+  for (int i = m - 1; i >= 0; --i) {
+    q = i == m - 1 ? d[i] - x : (d[i] - x) - e[i] * e[i] / q;
+    q = pivot(q, i > 0 ? e[i - 1] : d[0]);
+    Dm[i * ld + a] = q;
+    const double g = fabs(Dp[i * ld + a] + q - (d[i] - x));
+    if (i == m - 1 || g < best) {
+      best = g;
+      r = i;
+    }
+  }
+  double s = 0.0, z = 0.0;
+  for (int i = m - 1; i >= 0; --i) {
+    if (i < r) z *= e[i] / Dp[i * ld + a];
+    if (i == r) z = 1.0;
+    if (i <= r) {
+      V[i * ld + a] = z;
+      s += z * z;
+    }
+  }
+  z = 0.0;
+  for (int i = 0; i < m; ++i) {
+    if (i == r) z = 1.0;
+    if (i > r) {
+      z *= e[i - 1] / Dm[i * ld + a];
+      V[i * ld + a] = z;
+      s += z * z;
+    }
+  }
+  const double inv = 1.0 / sqrt(s);
+  for (int i = 0; i < m; ++i) V[i * ld + a] *= inv;
+}
+
+// H = 1.5 I - 0.5 H (n x n): with H = V^T V, V H is the first-order step to
+// the nearest orthonormal basis.
+__global__ void k_polar_factor(double *__restrict__ H, int64_t n) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
+  if (j >= n) return;
+  H[i * n + j] = (i == j ? 1.5 : 0.0) - 0.5 * H[i * n + j];
+}
+
+// out[j][i] = in[i][j] through a 64 x 64 LDS tile (both sides in 512-byte
+// runs); rows and cols multiples of 64.
+__global__ __launch_bounds__(256) void k_transpose(const double *__restrict__ in, int64_t ldi,
+                                                   double *__restrict__ out, int64_t ldo) {
+  __shared__ double t[64][65];
+  const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
+  const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
+  for (int k = y; k < 64; k += 4) t[k][x] = in[(r0 + k) * ldi + c0 + x];
+  __syncthreads();
+  for (int k = y; k < 64; k += 4) out[(c0 + k) * ldo + r0 + x] = t[x][k];
+}
+
+// out[i][j] = sinv[2i + s] in[i][j] for i < m (rows beyond are zeroed).
+__global__ void k_scale_rows(const double *__restrict__ in, const double *__restrict__ sinv, int s,
+                             int64_t m, int64_t ld, double *__restrict__ out) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
+  if (j >= ld) return;
+  out[i * ld + j] = i < m ? sinv[2 * i + s] * in[i * ld + j] : 0.0;
+}
+
+}  // namespace
+
+hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2, int64_t m,
+                              double lo, double hi, double *lam, double *Dp, double *Dm, double *V,
+                              int64_t ld, hipStream_t st) {
+  if (m <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_tridiag_values, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, d, e2,
+                     (int)m, lo, hi, lam);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(k_tridiag_vectors, dim3((unsigned)((m + 63) / 64)), dim3(64), 0, st, d, e,
+                     (int)m, lam, Dp, Dm, V, ld);
+  return hipGetLastError();
+}
+
+hipError_t launch_polar_factor(double *H, int64_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_polar_factor, dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256), 0,
+                     st, H, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_transpose(const double *in, int64_t ldi, double *out, int64_t ldo, int64_t rows,
+                            int64_t cols, hipStream_t st) {
+  if (rows % 64 || cols % 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_transpose, dim3((unsigned)(cols / 64), (unsigned)(rows / 64)), dim3(256), 0,
+                     st, in, ldi, out, ldo);
+  return hipGetLastError();
+}
+
+hipError_t launch_scale_rows(const double *in, const double *sinv, int s, int64_t m, int64_t rows,
+                             int64_t ld, double *out, hipStream_t st) {
+  hipLaunchKernelGGL(k_scale_rows, dim3((unsigned)((ld + 255) / 256), (unsigned)rows), dim3(256), 0,
+                     st, in, sinv, s, m, ld, out);
+  return hipGetLastError();
+}
+
+}  // namespace fps
