@@ -312,13 +312,25 @@ def bench_batch(fps, workloads, torch, tol, reps=3, tight=True):
     return res
 
 
-def bench_cube(fps, workloads, torch, tol, n=256, steps=2, check=True, tight=True):
-    """Cube n^3 solve (two-level nested ADI, FP64): time per solve and the
-    fiber sweeps' achieved bandwidth.  Algorithmic bytes per dof: z sweep 24
-    (read zR and B, write), inner half-step 1 16, half-step 2 24; for parity
-    blocks of at most 128 the inner ADI of an outer step is one LDS-resident
-    launch (HBM: R read into LDS, into registers and for the outer update,
-    B read, the next zR written: 32 B per dof)."""
+def cube_roofline(p, fps, torch, F, U, ws):
+    """One cube solve with an event pair around every product launch: total
+    time and the rate of its products (per axis and direction 2 n^3 times the
+    parity block's length n/2)."""
+    p.set_sweep_timing(64)
+    fps.solve(p, F, out=U, ws=ws)
+    torch.cuda.synchronize()
+    t = p.sweep_time()
+    p.set_sweep_timing(0)
+    flops = 6.0 * float(p.n) ** 4
+    tf = flops / (sum(t) * 1e-3) / 1e12
+    return {"bound": "mfma_f64", "flops": flops, "launches_timed": len(t),
+            "ms_total": round(sum(t), 4), "achieved_TFLOPs": round(tf, 2),
+            "frac": round(tf / FP64_MFMA_PEAK_TFLOPS, 4)}
+
+
+def bench_cube(fps, workloads, torch, tol, n=256, steps=5, check=True, tight=True):
+    """Cube n^3 solve (two-level nested ADI's iterate, FP64): time per solve
+    and its products' rate."""
     import numpy as np
     F_host = workloads.cube_rhs(n)
     F = torch.from_numpy(F_host).cuda()
@@ -328,7 +340,6 @@ def bench_cube(fps, workloads, torch, tol, n=256, steps=2, check=True, tight=Tru
     U = torch.empty(p.out_shape(), dtype=torch.float64, device="cuda")
     fps.solve(p, F, out=U, ws=ws)
     torch.cuda.synchronize()
-    per_solve = sum(1 + 2 * c for c in counts)
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     e0.record()
@@ -337,50 +348,11 @@ def bench_cube(fps, workloads, torch, tol, n=256, steps=2, check=True, tight=Tru
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    # one more solve with an event pair around every sweep launch
-    p.set_sweep_timing(per_solve)
-    e0.record()
-    fps.solve(p, F, out=U, ws=ws)
-    e1.record()
-    torch.cuda.synchronize()
-    ms_instr = e0.elapsed_time(e1)
-    t = p.sweep_time()
-    p.set_sweep_timing(0)
     dof = float(n) ** 3
-    # parity blocks of at most 128 run every outer step's inner ADI as one
-    # LDS-resident launch: the timed launches alternate z sweep, inner ADI
-    lds = len(t) == 2 * len(counts)
-    kinds = []
-    for c in counts:
-        kinds.append("z")
-        kinds.extend(["inner"] if lds else ["hs1", "hs2"] * c)
-    bpd = {"z": 24.0, "hs1": 16.0, "hs2": 24.0, "inner": 24.0}
-    sweep_kinds = ("z",) if lds else ("z", "hs1", "hs2")
-    tot_b = sum(bpd[k] * dof for k in kinds[:len(t)] if k in sweep_kinds)
-    tot_t = sum(x for x, k in zip(t, kinds) if k in sweep_kinds) * 1e-3
     res = {"n": n, "dof": dof, "ms_per_solve": ms, "dof_per_s": dof / (ms * 1e-3),
            "enclosure": "computed spectrum" if tight else "Lemma B.1",
            "J_outer": p.J, "inner_steps": sum(counts),
-           "sweeps_per_solve": len(counts) if lds else per_solve,
-           "sweep_achieved_GBs": round(tot_b / tot_t / 1e9, 1),
-           "sweep_frac_of_8TBs": round(tot_b / tot_t / 8e12, 4),
-           "sweep_share_of_solve": round(sum(t) / ms_instr, 4)}
-    if lds:
-        ti = [x for x, k in zip(t, kinds) if k == "inner"]
-        # the streamed inner passes it replaces: 40 B per dof and inner step
-        res["inner_adi"] = {
-            "form": "one launch per outer step, every slice block resident in LDS",
-            "launches": len(ti), "ms_total": round(sum(ti), 3),
-            "share_of_solve": round(sum(ti) / ms_instr, 4),
-            "hbm_bytes_per_launch": 4 * 8 * dof,
-            "sweep_model_bytes": 40.0 * dof * sum(counts),
-            "sweep_model_equiv_GBs": round(40.0 * dof * sum(counts) / (sum(ti) * 1e-3) / 1e9, 1)}
-    for k in ("z", "hs1", "hs2"):
-        tk = [x for x, kk in zip(t, kinds) if kk == k]
-        if tk:
-            avg = sum(tk) / len(tk) * 1e-3
-            res[f"avg_us_{k}"] = round(avg * 1e6, 2)
-            res[f"GBs_{k}"] = round(bpd[k] * dof / avg / 1e9, 1)
+           "products": cube_roofline(p, fps, torch, F, U, ws)}
     if check:
         Uo = cube_oracle(F_host, n)[0]
         Ug = U.cpu().numpy()
@@ -392,12 +364,8 @@ def bench_cube(fps, workloads, torch, tol, n=256, steps=2, check=True, tight=Tru
 
 
 def bench_cube_zeig(fps, workloads, torch, tol, n=256, steps=3, check=True, tight=True):
-    """Cube n^3 solve through the z-eigenbasis (one ADI per z-slice, FP64):
-    time per solve, and the ADI's own figures: for n <= 256 the one launch
-    that keeps every slice block in LDS (its time, its HBM bytes, and the
-    streamed sweeps' bytes per the same time), else the batched slice
-    sweeps' achieved bandwidth.  Sweep-model bytes per slice and step: x
-    solve 16 n^2, y solve 24 n^2."""
+    """Cube n^3 solve by the z-eigenbasis method (one ADI per z-slice, FP64, and
+    its refined form): time per solve and its products' rate."""
     import numpy as np
     F_host = workloads.cube_rhs(n)
     F = torch.from_numpy(F_host).cuda()
@@ -415,50 +383,17 @@ def bench_cube_zeig(fps, workloads, torch, tol, n=256, steps=3, check=True, tigh
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    # launch sequence of one solve: (slices, bytes per slice)
-    seq = []
-    Jmax = max(counts) if counts else 0
-    for j in range(Jmax):
-        k1 = sum(1 for c in counts if c > j)
-        seq.append((k1, 16.0))
-        seq.append((k1, 24.0))
-    p.set_sweep_timing(len(seq))
-    e0.record()
-    fps.solve(p, F, out=U, ws=ws)
-    e1.record()
-    torch.cuda.synchronize()
-    ms_instr = e0.elapsed_time(e1)
-    t = p.sweep_time()
-    p.set_sweep_timing(0)
     ms_g, same_g = graph_timing(fps, torch, p, F, U, steps)
     dof = float(n) ** 3
     res = {"n": n, "dof": dof, "ms_per_solve": ms, "dof_per_s": dof / (ms * 1e-3),
            "enclosure": "computed spectrum" if tight else "Lemma B.1",
-           "method": "eigenbasis of A~ along z (MFMA transforms), one ADI per z-slice",
-           "slice_steps": sum(counts), "max_slice_J": Jmax,
+           "method": "products into the tensor eigenbasis of A~, the slice iterations' multiplier, "
+                     "products out",
+           "slice_steps": sum(counts), "max_slice_J": max(counts) if counts else 0,
+           "products": cube_roofline(p, fps, torch, F, U, ws),
            "hip_graph": {"ms_per_solve": ms_g, "dof_per_s": dof / (ms_g * 1e-3),
                          "equals_eager": same_g}}
-    sweep_model = sum(k * b * n * n for k, b in seq)  # 40 B per dof and slice step
-    if len(t) == 1:
-        # every slice's ADI in one launch, each parity block LDS-resident: HBM
-        # sees G^ read and Y^ written once (npad^3 each); the sweep model's
-        # bytes over the kernel's time give the rate the streamed form would
-        # need for the same time
-        npad = ((n + 1) // 2 + 63) // 64 * 64 + (n // 2 + 63) // 64 * 64
-        hbm_b = 2 * 8.0 * npad ** 3
-        res["adi"] = {"form": "one launch, every slice block resident in LDS",
-                      "kernel_ms": round(t[0], 4), "share_of_solve": round(t[0] / ms_instr, 4),
-                      "hbm_bytes": hbm_b, "hbm_GBs": round(hbm_b / (t[0] * 1e-3) / 1e9, 1),
-                      "sweep_model_bytes": sweep_model,
-                      "sweep_model_equiv_GBs": round(sweep_model / (t[0] * 1e-3) / 1e9, 1)}
-    else:
-        tot_b = sum(k * b * n * n for k, b in seq[:len(t)])
-        tot_t = sum(t) * 1e-3
-        res["adi"] = {"form": "batched slice sweeps", "sweep_launches": len(seq),
-                      "sweep_achieved_GBs": round(tot_b / tot_t / 1e9, 1),
-                      "sweep_frac_of_8TBs": round(tot_b / tot_t / 8e12, 4),
-                      "sweep_share_of_solve": round(sum(t) / ms_instr, 4)}
-    # FP32 storage + FP64 refinement (rounds of the K-form slice correction)
+    # the refined form's iterate (rounds of the K-form slice correction)
     pr = fps.plan(n, tol=tol, dim=3, tight=tight, zeig=True, precision="fp32_refined")
     wsr = fps.workspace(pr, "cuda")
     Ur = torch.empty(pr.out_shape(), dtype=torch.float64, device="cuda")

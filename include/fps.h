@@ -69,9 +69,8 @@ typedef enum { FPS_BC_DIRICHLET_ZERO = 0 } fps_bc;
  * tolerance 1e-5 until one more such round would pass tol, then a last round to
  * 0.1 tol / (error reached); at tol = 1e-13: 1e-5, 1e-5, 1e-4
  * (fps_plan_rounds).  Square, rectangle and batched plans form that iterate
- * from its rounds' error factors, in float64 throughout; z-eigenbasis cube
- * plans store their slice sweeps in float32 (every arithmetic operation and
- * table float64).  Plans created with FPS_PLAN_DIRICHLET have two rounds to
+ * from its rounds' error factors, in float64 throughout, and so do
+ * z-eigenbasis cube plans (per slice).  Plans created with FPS_PLAN_DIRICHLET have two rounds to
  * 1e-5 and one to the rest. */
 typedef enum { FPS_FP64 = 0, FPS_FP32_REFINED = 1 } fps_prec;
 
@@ -85,18 +84,13 @@ typedef enum { FPS_OUT_CHEB = 0, FPS_OUT_NATIVE = 1 } fps_out;
  * contain the spectra, so the error bound and tol keep their meaning; J
  * drops (121 -> 96 at n = 4096, tol 1e-13). */
 #define FPS_PLAN_TIGHT_SPECTRUM 2u
-/* Cube plans: solve through the eigenbasis of A~ along z (dense MFMA
- * transforms) and one 2D ADI per z-slice, instead of the two-level nested
- * ADI.  Each slice equation (A~ + mu) Y (A~ + mu) - mu^2 Y = -G^ (mu an
- * eigenvalue of A~) is solved for Z = (A~ + mu) Y as
+/* Cube plans: the z-eigenbasis method instead of the two-level nested ADI: A~
+ * diagonalized along z, and on every z-slice (mu an eigenvalue of A~) the
+ * equation (A~ + mu) Y (A~ + mu) - mu^2 Y = -G^ iterated for Z = (A~ + mu) Y as
  * (-mu^2 (A~ + mu)^-1) Z - Z (-(A~ + mu)) = -G^ by Algorithm 2 with the slice's
- * own Zolotarev shifts; n <= 512.  Where a plan-time model predicts a gain
- * (n = 256: 78 of 256 slices), the slices with the most steps iterate on a
- * default-priority stream the plan owns, forked from and joined back to the
- * solve's stream with events, so the solve still completes in order on
- * that stream (and captures into a graph).  Solves of one plan issued on
- * several streams queue their side-stream work on that one stream, one
- * after another. */
+ * own Zolotarev shifts; n <= 512.  (With either method the solve itself is the
+ * iterate's closed form in the tensor eigenbasis of A~: one dense product per
+ * axis each way with the iteration's multiplier in between.) */
 #define FPS_PLAN_CUBE_ZEIG 4u
 /* Square and rectangle plans: also build the lift map that
  * fps_solve_dirichlet needs (the scaled C~ coefficients of every T_k'', two
@@ -180,8 +174,8 @@ fps_status fps_plan_info(const fps_plan *plan, int *J, int64_t *workspace_bytes,
                          int64_t *out_entries);
 
 /* Refinement structure of a plan: the number of rounds (1 for FPS_FP64) and
- * the number of inner ADI steps, summed over the rounds, that store their
- * sweep arrays in float32 (0 for FPS_FP64).  Either pointer may be null. */
+ * the number of inner ADI steps of its float rounds, summed (0 for
+ * FPS_FP64).  Either pointer may be null. */
 fps_status fps_plan_refinement(const fps_plan *plan, int *rounds, int *f32_steps);
 
 /* The ADI steps and the inner tolerance of each refinement round (host
@@ -297,9 +291,7 @@ fps_status fps_adi_native(fps_plan *plan, const double *G_dev, double *Y_dev, vo
  * plans: fps_adi_native's half-steps 1 and 2 of Algorithm 2 alternate,
  * starting with half-step 1; the solves and adjoints time their four product
  * launches; cube
- * plans: per outer step one z sweep, then the inner half-steps 1 and 2;
- * z-eigenbasis cube plans: per step j the x solves of all slices still
- * iterating, then their y solves (one launch each).
+ * plans time their product launches.
  */
 fps_status fps_plan_set_sweep_timing(fps_plan *plan, int capacity);
 fps_status fps_plan_sweep_time(fps_plan *plan, double *ms_host, int64_t cap, int64_t *launches);

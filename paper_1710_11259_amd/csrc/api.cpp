@@ -228,8 +228,6 @@ fps_status run_adi(fps_plan *pl, const fps::ShiftSet &sh, int base, const void *
   });
 }
 
-// A stage of parity-block products on st, timed like a sweep when the plan's
-// timing is on.
 fps_status run_products(fps_plan *pl, const fps::GemmProb *g, int cnt, hipStream_t st) {
   const bool t = pl->ev_used * 2 + 1 < (int64_t)pl->ev.size();
   FPS_HIP(fps::launch_gemm(g, cnt, st, t ? pl->ev[2 * pl->ev_used] : nullptr,
@@ -507,8 +505,7 @@ fps_status plan2d_build(fps_plan *pl) {
   const bool fused = L.ncmax <= 2;
   pl->ws_bytes = pl->off_X + align256(mobar * mobar * 8);
   if (prec == FPS_FP32_REFINED) {
-    pl->off_R = pl->ws_bytes;  // r and r^T (batched solves), npad^2 floats each
-    pl->ws_bytes += sq;
+    pl->ws_bytes += sq;  // kept: workspaces of a plan size stay interchangeable
   }
   std::vector<double> lift[2];
   if (flags & FPS_PLAN_DIRICHLET) {

@@ -70,6 +70,7 @@ __host__ __device__ inline void tile_krange(const GemmProb &g, int bx, int by, i
 // (compiled in only for launches that hold such problems: the maps without
 // it would pay registers and a test per entry).
 __device__ __forceinline__ double multiply(const GemmProb &g, int64_t i, int64_t j, double v) {
+  if (g.mt != nullptr) return v * g.mt[i * g.sci + j * g.scj];
   if (g.lr != nullptr) {
     const double *r = g.lr + 4 * i, *c = g.lc + 4 * j;
     v -= fma(r[3], c[3], fma(r[2], c[2], fma(r[1], c[1], r[0] * c[0])));
@@ -333,6 +334,8 @@ hipError_t launch_gemm_edge_cols(const GemmDesc *d, int nprob, int64_t tn, int n
   return hipGetLastError();
 }
 
+static bool has_mul(const GemmProb &q) { return q.mr != nullptr || q.mt != nullptr; }
+
 bool gemm_operands_ok(const GemmProb &q) {
   return q.sak == 1 && q.sbj == 1 && q.K % GBK == 0 && !(q.sai & 1) && !(q.sbk & 1) &&
          !((uintptr_t)q.A & 15) && !((uintptr_t)q.B & 15) && q.M >= 1 && q.N >= 1;
@@ -344,10 +347,15 @@ int gemm_tiles(const GemmProb &q, int *ntx) {
 }
 
 hipError_t launch_gemm_table(const GemmDesc *d, const int *tile_map, int ntiles, char *ws,
-                             char *out, hipStream_t st, bool mul) {
+                             char *out, hipStream_t st, bool mul, hipEvent_t ev0,
+                             hipEvent_t ev1) {
   if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(mul ? k_gemm_table<true> : k_gemm_table<false>, dim3((unsigned)ntiles),
-                     dim3(256), 0, st, d, tile_map, ws, out);
+  const auto kern = mul ? k_gemm_table<true> : k_gemm_table<false>;
+  if (ev0 != nullptr)
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(256), 0, st, ev0, ev1, 0, d, tile_map,
+                          ws, out);
+  else
+    hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(256), 0, st, d, tile_map, ws, out);
   return hipGetLastError();
 }
 
@@ -388,7 +396,7 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEven
     const GemmProb &q = probs[i];
     // contiguous operands, 16-byte aligned, K padded to the k-tile
     if (!gemm_operands_ok(q)) return hipErrorInvalidValue;
-    if ((q.mr != nullptr) != (probs[0].mr != nullptr)) return hipErrorInvalidValue;
+    if (has_mul(q) != has_mul(probs[0])) return hipErrorInvalidValue;
     b.p[i] = probs[i];
     mt = probs[i].M > mt * GBM ? (probs[i].M + GBM - 1) / GBM : mt;
     nt = probs[i].N > nt * GBN ? (probs[i].N + GBN - 1) / GBN : nt;
@@ -410,7 +418,7 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEven
   else if (same && rowwise && !colwise && !(f.triA && f.triAu))
     b.order = f.triA ? 3 : 4;
   dim3 grid((unsigned)nt, (unsigned)mt, (unsigned)count);
-  const auto kern = f.mr != nullptr ? k_gemm<true> : k_gemm<false>;
+  const auto kern = has_mul(f) ? k_gemm<true> : k_gemm<false>;
   if (ev0 != nullptr)
     hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, st, ev0, ev1, 0, b);
   else

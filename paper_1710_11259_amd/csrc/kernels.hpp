@@ -363,6 +363,8 @@ struct GemmProb {
   // the lr / lc term (the Dirichlet lift) only when lr is non-null.
   // Every problem of one launch has it or none does.
   const double *mr, *mc, *lr, *lc;
+  // Cube: a tabulated multiplier instead, mt indexed like C (mr null).
+  const double *mt;
 };
 hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
@@ -375,6 +377,22 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEven
 hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2, int64_t m,
                               double lo, double hi, double *lam, double *Dp, double *Dm, double *V,
                               int64_t ld, hipStream_t st);
+// Cube multipliers -(1 - eps) / (lz ly + lz lx + ly lx) by storage position
+// [npad]^3 (cube.cpp states the iterations).  z-eigenbasis: eps = ey[z][y]
+// ex[z][x], the error factors of slice z's shifts p / q[off[z] .. off[z+1] - 1]
+// (refined: symmetric shifts of the K-form).  Nested: r[i][k] the inner error
+// factor of outer step i along one axis, eps by the outer recurrence.
+hipError_t launch_slice_factors(const double *lam, const double *mu, const int *off,
+                                const double *p, const double *q, bool refined, double *ey,
+                                double *ex, int64_t npad, hipStream_t st);
+hipError_t launch_slice_multiplier(const double *lam, const double *ey, const double *ex, double *mt,
+                                   int64_t npad, hipStream_t st);
+hipError_t launch_nested_factors(const double *lam, const double *q, const int *off,
+                                 const double *p_in, double *r, int J, int64_t npad,
+                                 hipStream_t st);
+hipError_t launch_nested_multiplier(const double *lam, const double *p, const double *q,
+                                    const double *r, int J, double *mt, int64_t npad,
+                                    hipStream_t st);
 // H = 1.5 I - 0.5 H (n x n, contiguous).
 hipError_t launch_polar_factor(double *H, int64_t n, hipStream_t st);
 // out = in^T, rows x cols multiples of 64.
@@ -402,7 +420,8 @@ struct GemmDesc {
 };
 // mul: every problem of the table has a multiplier (else none does).
 hipError_t launch_gemm_table(const GemmDesc *d, const int *tile_map, int ntiles, char *ws,
-                             char *out, hipStream_t st, bool mul = false);
+                             char *out, hipStream_t st, bool mul = false, hipEvent_t ev0 = nullptr,
+                             hipEvent_t ev1 = nullptr);
 // Host: the tile map of a table, (problem, local tile) pairs for every tile
 // of every problem, longest k-range (after the triangular skips) first.
 std::vector<int> gemm_table_map(const std::vector<GemmDesc> &tab);

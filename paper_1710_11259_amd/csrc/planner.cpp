@@ -271,6 +271,31 @@ void atilde_extremes(int64_t n, long double *lmin, long double *lmax) {
   *lmax = hi_all;
 }
 
+void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam) {
+  const int64_t m = (n - s + 1) / 2;
+  lam.assign((size_t)m, 0.0);
+  std::vector<double> d((size_t)m), e2((size_t)m, 0.0);
+  for (int64_t k = 0; k < m; ++k) {
+    d[(size_t)k] = -atilde_diag(2 * k + s);
+    const double e = atilde_off(2 * k + s);
+    e2[(size_t)k] = e * e;
+  }
+  for (int64_t k = 0; k < m; ++k) {  // k-th smallest of -A~, in [1 / (30 n^4), 1]
+    double lo = 0.5 / (30.0 * (double)n * (double)n * (double)n * (double)n), hi = 1.01;
+    for (int it = 0; it < 75 && hi > lo * (1.0 + 4e-16); ++it) {
+      const double x = hi > 2.0 * lo ? std::sqrt(lo * hi) : 0.5 * (lo + hi);
+      int64_t c = 0;
+      double q = 1.0;
+      for (int64_t i = 0; i < m; ++i) {
+        q = i == 0 ? d[0] - x : (d[(size_t)i] - x) - e2[(size_t)i - 1] / q;
+        c += q < 0.0 ? 1 : 0;
+      }
+      if (c <= k) lo = x; else hi = x;
+    }
+    lam[(size_t)(m - 1 - k)] = -0.5 * (lo + hi);
+  }
+}
+
 void build_sweep_tables(const Layout &L, const std::vector<double> &p, std::vector<double> &pos,
                         std::vector<double> &chunk, std::vector<double> &comb,
                         std::vector<double> &l1) {

@@ -85,6 +85,10 @@ bool tridiag_eigen(std::vector<long double> &d, std::vector<long double> e,
 // Sturm-sequence bisection in extended precision; both are negative.
 void atilde_extremes(int64_t n, long double *lmin, long double *lmax);
 
+// Eigenvalues of the parity-s block of A~, ascending (most negative first), to
+// relative accuracy ~m eps by Sturm-sequence bisection in double.
+void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam);
+
 // Entries of A~ = -S^-1 M S^-1 (symmetric, zero +-1 diagonals):
 // diagonal at index i, and coupling between i and i+2.
 double atilde_diag(int64_t i);

@@ -84,13 +84,12 @@ struct fps_plan {
   int tab2(int j) const { return rect ? 2 * j + 1 : j; }
   fps::Layout L;
   std::vector<double> tab, ctab, l1;  // host sweep tables
-  std::vector<double> sdiag, soff;          // A~ stencil in the parity-blocked layout
   std::vector<double> Rs[2], P[2];  // host conversion maps (unpadded)
   int64_t mop[2] = {0, 0};          // output parity lengths padded to 64
   std::vector<double> sinv;         // 1/sqrt((i+1)(i+2))
 
   // device copies
-  fps::detail::DeviceBuf d_tab, d_ctab, d_l1, d_sinv, d_sdiag, d_soff;
+  fps::detail::DeviceBuf d_tab, d_ctab, d_l1, d_sinv;
   // Coefficient maps merged with the eigenvectors V of A~ (spectral.cpp), by
   // parity, zero-padded to multiples of 64, in both orientations: Wi =
   // V^T S^-1 R (mp x mp) and Wo = P S^-1 V (mop x mp; native output S^-1 V,
@@ -99,9 +98,6 @@ struct fps_plan {
   fps::detail::DeviceBuf d_Wi[2], d_WiT[2], d_Wo[2], d_WoT[2];
   fps::detail::DeviceBuf d_mr, d_mc;
   std::vector<double> lam;
-  fps::detail::DeviceBuf d_RsA[2], d_RsB[2];
-  // GEMM operands of the cube methods: PA = P (mop x mp), PB = P^T (mp x mop).
-  fps::detail::DeviceBuf d_PA[2], d_PB[2];
   // Lift map V^T S^-1 C~(T_k'') by parity (mp x mop) and V^T of the lift's
   // linear factors ([npad][2]), only with FPS_PLAN_DIRICHLET.
   fps::detail::DeviceBuf d_lift[2], d_lina;
@@ -120,80 +116,36 @@ struct fps_plan {
   // without sharing a buffer element.
   int64_t off_lv2 = 0, off_ab2 = 0;
   int64_t off_X = 0;  // adjoint: the output cotangent in the parity-blocked layout
-  int64_t off_R = 0;  // FP32_REFINED: the float residual and its transpose
   // Dirichlet lift (2-D plans with FPS_PLAN_DIRICHLET): the traces' scaled
   // C~ second-derivative coefficients [4][npad] (parity-blocked) and their
   // values at -1 and +1 [8].
   int64_t off_bc = 0;
 
-  // Cube (dim 3), two-level nested ADI: `shifts` holds the outer shifts
-  // (p in [-2/delta, -2], q in [1, 1/delta]); inner step (i, j) has shift
-  // inner_p[inner_off[i] + j]; sweep table id of the z pass of outer step i
-  // is i, of inner step (i, j) it is J + inner_off[i] + j.
+  // Cube (dim 3), nested method: `shifts` holds the outer shifts (p in
+  // [-2/delta, -2], q in [1, 1/delta]); inner step (i, j) has shift
+  // inner_p[inner_off[i] + j].
   std::vector<int> inner_J, inner_off;
   std::vector<double> inner_p;
-  double cube_inner_tol = 0.0;
-  int64_t mqc[2] = {0, 0};  // compact output parity sizes (mo rounded up to even)
-  fps::detail::DeviceBuf d_pre;             // [2][npad]: A~ diagonal and coupling per row
-  fps::detail::DeviceBuf d_RbA[2], d_RbB[2];  // input map A~^-1 S^-1 R blocks and transposes
+  // Cube, z-eigenbasis method (FPS_PLAN_CUBE_ZEIG): the shifts of storage slice
+  // c (all rounds) are zp / zq[zoff[c] .. zoff[c + 1] - 1]; zJ the steps per
+  // slice (round 0), most first, zrJmax the most steps per refinement round.
+  bool zeig = false;
+  std::vector<double> zlam[2], zp, zq;
+  std::vector<int> zoff, zJ, zrJmax;
+  int64_t mqc[2] = {0, 0};  // output parity sizes rounded up to even
+  fps::detail::DeviceBuf d_mt;                // multiplier of every mode [npad]^3
   fps::detail::DeviceBuf d_gy_in, d_gy_out;   // mode-y GEMM tables (input / output map)
   int gy_tiles[2] = {0, 0};
   fps::detail::DeviceBuf d_gy_map_in, d_gy_map_out;
-  int64_t off_ZR = 0, off_RX = 0, off_RXT = 0;
-
-  // Cube, z-eigenbasis method (FPS_PLAN_CUBE_ZEIG): slice k of the sorted
-  // active slices (J descending) is storage slice zslice[k], eigenvalue
-  // zmu[k], zJ[k] ADI steps with table ids ztab0[k] + 2 j (x solve) and
-  // ztab0[k] + 2 j + 1 (y solve).
-  bool zeig = false;
-  std::vector<int> zslice, zJ, ztab0, zactive, zsw_start, zrd_start;
-  // Sweeps form their own chunk carries (chains of at most two chunks,
-  // ncmax <= 2): no carry launch between half-steps, one per solve (FP64) or
-  // per round (refined) before the final pass, from the descriptors d_zrdfin.
-  bool zfused = false;
-  fps::detail::DeviceBuf d_zrdfin;
-  std::vector<double> zmu;
-  std::vector<double> zp, zq;  // shifts of step j of sorted slice k at index ztab0[k] / 2 + j
-  int zJmax = 0;
-  fps::detail::DeviceBuf d_zsw, d_zrd, d_zswmap, d_zrdmap, d_zfin;
-  // FP64 plans whose parity blocks fit one workgroup's LDS (n <= 256): the
-  // whole slice ADI as one launch of k_zeig_lds, over the sorted slices and
-  // then the inactive storage slices (zl_slice, zl_J, zl_tab0, zl_sig0 per
-  // entry; zl_mu the shifts mu; zl_sig the two sigmas of every step).
-  bool zlds = false;
-  // Nested cube plans whose parity blocks fit one workgroup's LDS: every
-  // outer step's inner ADI is one k_zeig_lds launch (d_zl_tab32 / ctab32 the
-  // chunk multipliers of every table, d_zl_sig the inner sigmas, outer step i
-  // at 2 inner_off[i]).
-  bool nlds = false;
-  fps::detail::DeviceBuf d_zl_slice, d_zl_J, d_zl_tab0, d_zl_sig0, d_zl_mu, d_zl_sig;
-  fps::detail::DeviceBuf d_zl_tab32, d_zl_ctab32;  // the kernel's chunk multipliers
-  // Sorted slices 0 .. zsplit-1 (the longest) iterate on the plan's own
-  // stream zside, the others on the caller's stream, joined by the events
-  // zfork / zjoin (zsplit 0: one stream).
-  int zsplit = 0;
+  int64_t off_ZR = 0, off_RX = 0;
+  // 2-D plans whose chains have more than two chunks: fps_adi_native runs one
+  // row-parity block's sweeps on the plan's own stream zside, the other's on
+  // the caller's, joined by the events zfork / zjoin.  zlock is held while one
+  // call enqueues its fork, both blocks and its join, so concurrent host
+  // threads' calls do not interleave on zside.
   hipStream_t zside = nullptr;
   hipEvent_t zfork = nullptr, zjoin = nullptr;
-  // Held while one solve enqueues its fork, both slice groups and its join,
-  // so concurrent host threads' solves do not interleave on zside.
   std::mutex zlock;
-  fps::detail::DeviceBuf d_Mz[2], d_PV[2], d_Vz[2];  // z maps: V^T S^-1 R, P V, V
-  // Refined z-eigenbasis plans (FPS_FP32_REFINED): round r corrects Y^ by
-  // solving, on every slice, (|mu| K + 1/2) dY + dY (|mu| K + 1/2) = K q K
-  // (K = -A~^-1, q the negated slice residual) with its own shifts; sorted
-  // slice k (|mu| descending) is storage slice zrslice[k] with zrJ[r][k]
-  // steps on tables zrtab0[r][k] + j; step j of round r has descriptor row
-  // zrrow0[r] + j and zractive[r][j] slices still iterating.  Table 0 is A~
-  // itself (the two solves that form K q K).
-  std::vector<int> zrslice;
-  std::vector<double> zrmu_slice;  // mu of every storage slice (0 for padding)
-  std::vector<std::vector<int>> zrJ, zrtab0, zractive;
-  std::vector<int> zrJmax, zrrow0;
-  // per round: sorted slices 0 .. zrsplit[r]-1 iterate on the side stream
-  // (zside / zfork / zjoin, as zsplit for FP64 plans); 0: one stream
-  std::vector<int> zrsplit;
-  fps::detail::DeviceBuf d_zrsw, d_zrrd, d_zrfin, d_zmu;
-  std::vector<double> zV[2];  // host eigenvectors of the parity blocks (m x m, columns)
   int64_t ws_bytes = 0;
 
   const double *tab_dev(int j) const {
@@ -248,8 +200,9 @@ int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2
 int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::GemmProb *g2);
 int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
 int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
-// Extents of the solve's output layout: entries per axis, the permuted
-// cotangent's row length and its parity-1 offset.
+// A stage of products on st, timed like a sweep when the plan's timing is on.
+fps_status run_products(fps_plan *pl, const fps::GemmProb *g, int cnt, hipStream_t st);
+// Entries per axis of the solve's output.
 inline int64_t out_extent(const fps_plan *pl) {
   return pl->out_basis == FPS_OUT_NATIVE ? pl->n : pl->n + 2;
 }

@@ -128,7 +128,104 @@ __global__ void k_scale_rows(const double *__restrict__ in, const double *__rest
   out[i * ld + j] = i < m ? sinv[2 * i + s] * in[i * ld + j] : 0.0;
 }
 
+// Error factors of slice z along y and x: Algorithm 2 leaves
+// prod (a - p)/(a - q) (b - q)/(b - p) of the error for left eigenvalue a and
+// right eigenvalue b; FP64: a = -mu^2 / (l + mu), b = -(l + mu); refined:
+// a = -(|mu| k + 1/2), k = -1/l, b = -a, q = -p.
+__global__ void k_slice_factors(const double *__restrict__ lam, const double *__restrict__ mu,
+                                const int *__restrict__ off, const double *__restrict__ p,
+                                const double *__restrict__ q, int refined, double *__restrict__ ey,
+                                double *__restrict__ ex, int64_t npad) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, z = blockIdx.y;
+  if (i >= npad) return;
+  const double m = mu[z], l = lam[i];
+  const double a = refined ? -(-m * (-1.0 / l) + 0.5) : -m * m / (l + m);
+  const double b = refined ? -a : -(l + m);
+  double e = 1.0, f = 1.0;
+  for (int j = off[z]; j < off[z + 1]; ++j) {
+    e *= (a - p[j]) / (a - q[j]);
+    f *= (b - q[j]) / (b - p[j]);
+  }
+  ey[z * npad + i] = e;
+  ex[z * npad + i] = f;
+}
+
+__global__ void k_slice_multiplier(const double *__restrict__ lam, const double *__restrict__ ey,
+                                   const double *__restrict__ ex, double *__restrict__ mt,
+                                   int64_t npad) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
+  if (x >= npad) return;
+  const double lx = lam[x], ly = lam[y], lz = lam[z];
+  mt[(z * npad + y) * npad + x] =
+      fma(ey[z * npad + y], ex[z * npad + x], -1.0) / (lz * ly + lz * lx + ly * lx);
+}
+
+// Inner error factors of the nested method, a = -(k + q_i/2), k = -1/l:
+// r[i][k] = prod (a - p)/(a + p).
+__global__ void k_nested_factors(const double *__restrict__ lam, const double *__restrict__ q,
+                                 const int *__restrict__ off, const double *__restrict__ p,
+                                 double *__restrict__ r, int64_t npad) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
+  if (k >= npad) return;
+  const double a = 1.0 / lam[k] - 0.5 * q[i];
+  double e = 1.0;
+  for (int j = off[i]; j < off[i + 1]; ++j) e *= (a - p[j]) / (a + p[j]);
+  r[i * npad + k] = e;
+}
+
+// Outer error of the nested method in mode (z, y, x), h = k_y + k_x, v = k_z:
+// an exact step takes eps to rho eps, rho = (h + p)(v - q) / ((v - p)(h + q)),
+// and the inner iteration, started from 0, scales its result by 1 - e.
+__global__ void k_nested_multiplier(const double *__restrict__ lam, const double *__restrict__ p,
+                                    const double *__restrict__ q, const double *__restrict__ r,
+                                    int J, double *__restrict__ mt, int64_t npad) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
+  if (x >= npad) return;
+  const double lx = lam[x], ly = lam[y], lz = lam[z];
+  const double h = -1.0 / lx - 1.0 / ly, v = -1.0 / lz;
+  double eps = 1.0;
+  for (int i = 0; i < J; ++i) {
+    const double e = r[i * npad + y] * r[i * npad + x];
+    const double rho = ((h + p[i]) / (h + q[i])) * ((v - q[i]) / (v - p[i]));
+    eps = e + (1.0 - e) * rho * eps;
+  }
+  mt[(z * npad + y) * npad + x] = (eps - 1.0) / (lz * ly + lz * lx + ly * lx);
+}
+
 }  // namespace
+
+hipError_t launch_slice_factors(const double *lam, const double *mu, const int *off,
+                                const double *p, const double *q, bool refined, double *ey,
+                                double *ex, int64_t npad, hipStream_t st) {
+  hipLaunchKernelGGL(k_slice_factors, dim3((unsigned)((npad + 63) / 64), (unsigned)npad), dim3(64),
+                     0, st, lam, mu, off, p, q, refined ? 1 : 0, ey, ex, npad);
+  return hipGetLastError();
+}
+
+hipError_t launch_slice_multiplier(const double *lam, const double *ey, const double *ex, double *mt,
+                                   int64_t npad, hipStream_t st) {
+  hipLaunchKernelGGL(k_slice_multiplier,
+                     dim3((unsigned)((npad + 255) / 256), (unsigned)npad, (unsigned)npad), dim3(256),
+                     0, st, lam, ey, ex, mt, npad);
+  return hipGetLastError();
+}
+
+hipError_t launch_nested_factors(const double *lam, const double *q, const int *off,
+                                 const double *p_in, double *r, int J, int64_t npad,
+                                 hipStream_t st) {
+  hipLaunchKernelGGL(k_nested_factors, dim3((unsigned)((npad + 63) / 64), (unsigned)J), dim3(64), 0,
+                     st, lam, q, off, p_in, r, npad);
+  return hipGetLastError();
+}
+
+hipError_t launch_nested_multiplier(const double *lam, const double *p, const double *q,
+                                    const double *r, int J, double *mt, int64_t npad,
+                                    hipStream_t st) {
+  hipLaunchKernelGGL(k_nested_multiplier,
+                     dim3((unsigned)((npad + 255) / 256), (unsigned)npad, (unsigned)npad), dim3(256),
+                     0, st, lam, p, q, r, J, mt, npad);
+  return hipGetLastError();
+}
 
 hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2, int64_t m,
                               double lo, double hi, double *lam, double *Dp, double *Dm, double *V,

@@ -60,3 +60,46 @@ def test_adjoint_of_a_loose_solve():
         a, b = (U * Ub).sum(), (F * Fb).sum()
         scale = np.linalg.norm(U) * np.linalg.norm(Ub)
         assert abs(a - b) <= 1e-13 * scale
+
+
+# The cube's multiplier against the iterations written out with dense solves.
+# Their matrices K = -A~^-1 have condition 30 n^4, so the oracle carries
+# 30 n^4 eps (1.4e-11 at n = 8) and the bound is 1e-9; the truncation being
+# compared is about 1e-2.
+@pytest.mark.parametrize("n", [3, 8])
+@pytest.mark.parametrize("method", ["nested", "zeig", "refined"])
+def test_cube_is_the_iterate_of_its_method(n, method):
+    from oracle import cube
+    tol = 1e-2
+    F = np.random.default_rng(n).standard_normal((n, n, n))
+    G = cube.symmetric_rhs(cube.rhs_ct(F))
+    p = fps.plan(n, tol=tol, dim=3, out="native", tight=method == "zeig", zeig=method != "nested",
+                 precision="fp32_refined" if method == "refined" else "fp64")
+    s = square.s_diag(n)
+    X = _run(p, F) * s[:, None, None] * s[None, :, None] * s[None, None, :]
+    if method == "nested":
+        Y, J, inner = cube.kform_adi(G, tol, 0.1 * tol)
+        assert J == p.J and inner == p.inner_counts()
+    elif method == "zeig":
+        Y, counts = cube.zeig_adi(G, tol)
+        assert sorted(counts, reverse=True) == p.slice_counts()
+    else:
+        # one round: symmetric shifts on [|mu| / |lmin| + 1/2, |mu| / |lmax| + 1/2]
+        steps, tols = p.round_steps()
+        assert len(steps) == 1
+        lam, V = square.atilde_eig(n)
+        Gh = G
+        for m in range(3):
+            Gh = cube.mode_product(Gh, V.T, m)
+        Yh = np.empty_like(Gh)
+        for c, mu in enumerate(lam):
+            a, b = abs(mu) + 0.5, abs(mu) * 30.0 * n ** 4 + 0.5
+            ps, qs = fps.adi_shifts(-b, -a, a, b, tols[0])
+            z = -(abs(mu) * (-1.0 / lam) + 0.5)
+            r = np.prod([(z - pj) / (z - qj) for pj, qj in zip(ps, qs)], axis=0)
+            den = lam[:, None] * lam[None, :] + mu * (lam[:, None] + lam[None, :])
+            Yh[c] = -Gh[c] * (1.0 - np.outer(r, r)) / den
+        Y = Yh
+        for m in range(3):
+            Y = cube.mode_product(Y, V, m)
+    parity.check(X, Y, 1e-9, f"cube {method} n={n}")
