@@ -257,16 +257,16 @@ int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2
   int64_t toff = 0;
   for (int s = 0; s < 2; ++s)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s], mt = L.mp[t], rs = s * L.mp[0], rt = t * L.mp[0];
+      const int64_t ms = k_round(L.m[s]), mt = k_round(L.m[t]), rs = s * L.mp[0], rt = t * L.mp[0];
       if (ms == 0 || mt == 0) continue;
       double *Tst = Tb + toff;
       toff += ms * mt;
       // T_st = F_st Wi_t^T
       g1[cnt] = fps::GemmProb{GT + rs * npad + rt, (const double *)pl->d_WiT[t].p, Tst, ms, mt, mt,
-                              npad, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+                              npad, 1, L.mp[t], 1, mt, 1};
       // Y^_st = Wi_s T_st, multiplied
       g2[cnt] = fps::GemmProb{(const double *)pl->d_Wi[s].p, Tst, G + rs * npad + rt, ms, mt, ms,
-                              ms, 1, mt, 1, npad, 1, 0, 0, 0, 0, 0, 0, 0, 0,
+                              L.mp[s], 1, mt, 1, npad, 1, 0, 0, nullptr, nullptr,
                               mr + 2 * rs, mc + 2 * rt, lr ? lr + 4 * rs : nullptr,
                               lc ? lc + 4 * rt : nullptr};
       ++cnt;
@@ -301,14 +301,14 @@ int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::G
   int64_t toff = 0;
   for (int s = 0; s < 2; ++s)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s], mt = L.mp[t], mot = mop[t];
+      const int64_t ms = k_round(L.m[s]), mt = k_round(L.m[t]), mot = mop[t];
       if (L.m[s] == 0 || L.m[t] == 0) continue;  // that output block stays zero
       double *Tst = Tb + toff;
       toff += ms * mot;
       g1[cnt] = fps::GemmProb{Y + (s * L.mp[0]) * npad + t * L.mp[0], (const double *)pl->d_WoT[t].p,
-                              Tst, ms, mot, mt, npad, 1, mot, 1, mot, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+                              Tst, ms, mo[t], mt, npad, 1, mot, 1, mot, 1};
       g2[cnt] = fps::GemmProb{(const double *)pl->d_Wo[s].p, Tst, U + s * N + t, mo[s], mo[t],
-                              ms, ms, 1, mot, 1, 2 * N, 2, 0, 0, 0, 0, 0, 0, 0, 0};
+                              ms, L.mp[s], 1, mot, 1, 2 * N, 2};
       ++cnt;
     }
   return cnt;
@@ -781,7 +781,7 @@ namespace detail {
 int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *g2) {
   const fps::Layout &L = pl->L;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
-  const int64_t *mop = native ? L.mp : pl->mop;
+  const int64_t *mo = native ? L.m : L.mo, *mop = native ? L.mp : pl->mop;
   const int64_t npad = L.npad, mo0 = mop[0], mobar = mop[0] + mop[1];
   const double *Up = (const double *)(w + pl->off_X);
   const double *mr = (const double *)pl->d_mr.p, *mc = (const double *)pl->d_mc.p;
@@ -791,15 +791,20 @@ int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *
   int64_t toff = 0;
   for (int s2 = 0; s2 < 2; ++s2)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s2], mt = L.mp[t], mos = mop[s2], mot = mop[t];
+      const int64_t ms = k_round(L.m[s2]), mt = k_round(L.m[t]);
+      const int64_t mos = k_round(mo[s2]), mot = k_round(mo[t]);
       const int64_t rs = s2 * L.mp[0], rt = t * L.mp[0];
       if (L.m[s2] == 0 || L.m[t] == 0) continue;
       double *Tst = Tt + toff;
       toff += mos * mt;
       g1[cnt] = fps::GemmProb{Up + (s2 * mo0) * mobar + t * mo0, (const double *)pl->d_Wo[t].p,
-                              Tst, mos, mt, mot, mobar, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+                              Tst, mos, mt, mot, mobar, 1, L.mp[t], 1, mt, 1};
+      if (fps::gemm_has_edge(mo[s2])) {  // rows mo .. mos - 1 are zero: cleared
+        g1[cnt].M = mo[s2];
+        g1[cnt].Mz = mos;
+      }
       g2[cnt] = fps::GemmProb{(const double *)pl->d_WoT[s2].p, Tst, G + rs * npad + rt, ms, mt, mos,
-                              mos, 1, mt, 1, npad, 1, 0, 0, 0, 0, 0, 0, 0, 0, mr + 2 * rs,
+                              mop[s2], 1, mt, 1, npad, 1, 0, 0, nullptr, nullptr, mr + 2 * rs,
                               mc + 2 * rt, nullptr, nullptr};
       ++cnt;
     }
@@ -816,14 +821,14 @@ int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, 
   int64_t toff = 0;
   for (int s2 = 0; s2 < 2; ++s2)
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = L.mp[s2], mt = L.mp[t];
+      const int64_t ms = k_round(L.m[s2]), mt = k_round(L.m[t]);
       if (L.m[s2] == 0 || L.m[t] == 0) continue;
       double *Tst = Tb + toff;
       toff += ms * mt;
       g1[cnt] = fps::GemmProb{Yb + (s2 * L.mp[0]) * npad + t * L.mp[0], (const double *)pl->d_Wi[t].p,
-                              Tst, ms, mt, mt, npad, 1, mt, 1, mt, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+                              Tst, ms, mt, mt, npad, 1, L.mp[t], 1, mt, 1};
       g2[cnt] = fps::GemmProb{(const double *)pl->d_WiT[s2].p, Tst, Fbar + s2 * n + t, L.m[s2],
-                              L.m[t], ms, ms, 1, mt, 1, 2 * n, 2, 0, 0, 0, 0, 0, 0, 0, 0};
+                              L.m[t], ms, L.mp[s2], 1, mt, 1, 2 * n, 2};
       ++cnt;
     }
   return cnt;

@@ -36,7 +36,7 @@ struct fps_batch {
   // products of all problems: input map g1, g2; output map g1, g2; (FP64
   // batches) the adjoint's input map g1, g2 and output map g1, g2
   DeviceBuf d_gd[8], d_gmap[8];
-  int gtiles[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  fps::GemmTable gt[8];
   // the permutations of F (0) and of the adjoint's cotangent (1) as one
   // launch each (elem_ok; else, for very large batches, one per problem)
   bool elem_ok = false;
@@ -76,17 +76,15 @@ fps_status build_gemm_tables(fps_batch *bt) {
     for (int t = 0; t < 8; ++t) {
       const int cnt = counts[t];
       for (int i = 0; i < cnt; ++i) {
-        if (!fps::gemm_operands_ok(g[t][i]))
-          return fail(FPS_E_STATE, "internal: batched GEMM operand layout");
-        fps::GemmDesc d{g[t][i], ids[t][0], ids[t][1], ids[t][2], bt->gtiles[t], 0};
-        bt->gtiles[t] += fps::gemm_tiles(g[t][i], &d.ntx);
-        tab[t].push_back(d);
+        tab[t].push_back(fps::GemmDesc{g[t][i], ids[t][0], ids[t][1], ids[t][2]});
       }
     }
   }
   for (int t = 0; t < 8; ++t) {
     if (tab[t].empty()) continue;
-    const std::vector<int> map = fps::gemm_table_map(tab[t]);
+    std::vector<int> map;
+    if (!fps::gemm_table(tab[t], bt->gt[t], map))
+      return fail(FPS_E_STATE, "internal: batched GEMM operand layout");
     fps_status s;
     if ((s = upload(bt->d_gd[t], tab[t])) != FPS_OK || (s = upload(bt->d_gmap[t], map)) != FPS_OK)
       return s;
@@ -257,9 +255,8 @@ fps_status fps_batch_solve(fps_batch *bt, const double *F, double *U, void *ws, 
   if ((s = permute_all(bt, 0, F, w, st)) != FPS_OK) return s;
   if (bt->has_n1) FPS_HIP(fps::launch_fill(U, bt->out_entries, 0.0, st));
   for (int t = 0; t < 4; ++t)
-    FPS_HIP(fps::launch_gemm_table((const fps::GemmDesc *)bt->d_gd[t].p,
-                                   (const int *)bt->d_gmap[t].p, bt->gtiles[t], w, (char *)U, st,
-                                   t == 1));
+    FPS_HIP(fps::launch_gemm_table(bt->gt[t], (const fps::GemmDesc *)bt->d_gd[t].p,
+                                   (const int *)bt->d_gmap[t].p, w, (char *)U, st));
   return FPS_OK;
 }
 
@@ -275,9 +272,8 @@ fps_status fps_batch_solve_adjoint(fps_batch *bt, const double *Ubar, double *Fb
   fps_status s;
   if ((s = permute_all(bt, 1, Ubar, w, st)) != FPS_OK) return s;
   for (int t = 4; t < 8; ++t)
-    FPS_HIP(fps::launch_gemm_table((const fps::GemmDesc *)bt->d_gd[t].p,
-                                   (const int *)bt->d_gmap[t].p, bt->gtiles[t], w, (char *)Fbar,
-                                   st, t == 5));
+    FPS_HIP(fps::launch_gemm_table(bt->gt[t], (const fps::GemmDesc *)bt->d_gd[t].p,
+                                   (const int *)bt->d_gmap[t].p, w, (char *)Fbar, st));
   return FPS_OK;
 }
 

@@ -55,18 +55,17 @@ void mode_probs(const double *in, const Dims &di, double *out, const Dims &dout,
     if (mode == 2) {
       probs.push_back(fps::GemmProb{in + s * di.b0[2], MB[s], out + s * dout.b0[2],
                                     di.d[0] * di.d[1], N[s], K[s], di.d[2], 1, ldb[s], 1,
-                                    dout.d[2], 1, 0, 0, 0, 0, 0, 0, 0, 0});
+                                    dout.d[2], 1});
     } else if (mode == 0) {
       const int64_t pin = di.d[1] * di.d[2], pout = dout.d[1] * dout.d[2];
       probs.push_back(fps::GemmProb{MA[s], in + s * di.b0[0] * pin, out + s * dout.b0[0] * pout,
-                                    N[s], pin, K[s], lda[s], 1, pin, 1, pout, 1, 0, 0, 0, 0, 0,
-                                    0, 0, 0});
+                                    N[s], pin, K[s], lda[s], 1, pin, 1, pout, 1});
     } else {
       for (int64_t z = 0; z < di.d[0]; ++z)
         probs.push_back(fps::GemmProb{
             MA[s], in + z * di.d[1] * di.d[2] + s * di.b0[1] * di.d[2],
             out + z * dout.d[1] * dout.d[2] + s * dout.b0[1] * dout.d[2], N[s], di.d[2], K[s],
-            lda[s], 1, di.d[2], 1, dout.d[2], 1, 0, 0, 0, 0, 0, 0, 0, 0});
+            lda[s], 1, di.d[2], 1, dout.d[2], 1});
     }
   }
 }
@@ -81,11 +80,11 @@ fps_status launch_probs(fps_plan *pl, const std::vector<fps::GemmProb> &probs, h
 }
 
 // One table launch, timed like run_products.
-fps_status run_table(fps_plan *pl, const DeviceBuf &d, const DeviceBuf &map, int tiles, char *w,
-                     char *out, hipStream_t st) {
+fps_status run_table(fps_plan *pl, const fps::GemmTable &g, const DeviceBuf &d, const DeviceBuf &map,
+                     char *w, char *out, hipStream_t st) {
   const bool t = pl->ev_used * 2 + 1 < (int64_t)pl->ev.size();
-  FPS_HIP(fps::launch_gemm_table((const fps::GemmDesc *)d.p, (const int *)map.p, tiles, w, out, st,
-                                 false, t ? pl->ev[2 * pl->ev_used] : nullptr,
+  FPS_HIP(fps::launch_gemm_table(g, (const fps::GemmDesc *)d.p, (const int *)map.p, w, out, st,
+                                 t ? pl->ev[2 * pl->ev_used] : nullptr,
                                  t ? pl->ev[2 * pl->ev_used + 1] : nullptr));
   if (t) ++pl->ev_used;
   return FPS_OK;
@@ -94,18 +93,13 @@ fps_status run_table(fps_plan *pl, const DeviceBuf &d, const DeviceBuf &map, int
 // Device GEMM table of per-slice problems (A absolute, B workspace-relative, C
 // of base id `cbase`).
 fps_status upload_table(const std::vector<fps::GemmProb> &probs, int cbase, DeviceBuf &d,
-                        DeviceBuf &map, int &tiles) {
+                        DeviceBuf &map, fps::GemmTable &t) {
   std::vector<fps::GemmDesc> tab;
-  tiles = 0;
-  for (const fps::GemmProb &q : probs) {
-    if (!fps::gemm_operands_ok(q)) return fail(FPS_E_STATE, "internal: cube GEMM operand layout");
-    fps::GemmDesc e{q, 0, 1, cbase, tiles, 0};
-    tiles += fps::gemm_tiles(q, &e.ntx);
-    tab.push_back(e);
-  }
+  for (const fps::GemmProb &q : probs) tab.push_back(fps::GemmDesc{q, 0, 1, cbase});
+  std::vector<int> m;
+  if (!fps::gemm_table(tab, t, m)) return fail(FPS_E_STATE, "internal: cube GEMM operand layout");
   fps_status s;
-  if ((s = upload(d, tab)) != FPS_OK || (s = upload(map, fps::gemm_table_map(tab))) != FPS_OK)
-    return s;
+  if ((s = upload(d, tab)) != FPS_OK || (s = upload(map, m)) != FPS_OK) return s;
   return FPS_OK;
 }
 
@@ -166,13 +160,13 @@ fps_status zeig_shifts(fps_plan *pl, double ea, double eb) {
   };
   std::vector<Slice> sl;
   std::string err;
-  pl->zoff.assign((size_t)L.npad + 1, 0);
+  pl->zoff.assign((size_t)pl->cnp + 1, 0);
   pl->zp.clear();
   pl->zq.clear();
-  for (int64_t c = 0; c < L.npad; ++c) {
+  for (int64_t c = 0; c < pl->cnp; ++c) {
     pl->zoff[(size_t)c] = (int)pl->zp.size();
-    const int sp = c < L.mp[0] ? 0 : 1;
-    const int64_t k = c - sp * L.mp[0];
+    const int sp = c < pl->cmp[0] ? 0 : 1;
+    const int64_t k = c - sp * pl->cmp[0];
     if (k == 0) fps::atilde_eigenvalues(pl->n, sp, pl->zlam[sp]);
     if (k >= L.m[sp]) continue;
     Slice x;
@@ -199,7 +193,7 @@ fps_status zeig_shifts(fps_plan *pl, double ea, double eb) {
     }
     sl.push_back(x);
   }
-  pl->zoff[(size_t)L.npad] = (int)pl->zp.size();
+  pl->zoff[(size_t)pl->cnp] = (int)pl->zp.size();
   pl->n_f32 = 0;
   for (int J : pl->zrJmax) pl->n_f32 += J;
   // the queries report the slices by decreasing steps, and the longest
@@ -220,6 +214,8 @@ fps_status cube_plan_build(fps_plan *pl) {
   pl->zeig = (pl->flags & FPS_PLAN_CUBE_ZEIG) != 0;
   pl->L = fps::make_layout(n);
   const fps::Layout &L = pl->L;
+  for (int sp = 0; sp < 2; ++sp) pl->cmp[sp] = k_round(L.m[sp]);
+  pl->cnp = pl->cmp[0] + pl->cmp[1];
   double ea, eb;
   enclosure(pl, &ea, &eb);
   const fps_status s = pl->zeig ? zeig_shifts(pl, ea, eb) : nested_shifts(pl, ea, eb);
@@ -232,7 +228,7 @@ fps_status cube_plan_build(fps_plan *pl) {
   }
   pl->sinv.resize(n);
   for (int64_t i = 0; i < n; ++i) pl->sinv[i] = 1.0 / std::sqrt((double)(i + 1) * (double)(i + 2));
-  // Workspace: six arrays of npad^3 (input stages in G / O0 / O1, Y^ in ZR,
+  // Workspace: six arrays of (up to) npad^3 (input stages in G / O0 / O1, Y^ in ZR,
   // output stages in O0..O1 and RX..RX + 1), then what the chunk carries of
   // npad^2 chains would take (kept, so that workspaces allocated for a plan
   // size stay interchangeable).
@@ -255,7 +251,7 @@ fps_status cube_plan_build(fps_plan *pl) {
 
 fps_status cube_plan_upload(fps_plan *pl) {
   const fps::Layout &L = pl->L;
-  const int64_t npad = L.npad;
+  const int64_t npad = pl->cnp, *mp = pl->cmp;
   fps_status s;
   if ((s = upload(pl->d_sinv, pl->sinv)) != FPS_OK || (s = spectral_build(pl, nullptr)) != FPS_OK)
     return s;
@@ -264,12 +260,15 @@ fps_status cube_plan_upload(fps_plan *pl) {
   DeviceBuf lam, ey, ex, p, q, off, mu;
   if (hipMalloc(&pl->d_mt.p, (size_t)(npad * npad * npad) * 8) != hipSuccess)
     return fail(FPS_E_NOMEM, "hipMalloc of a plan table failed");
-  if ((s = upload(lam, pl->lam)) != FPS_OK) return s;
+  std::vector<double> lc((size_t)npad, -1.0);  // eigenvalues by cube position
+  for (int sp = 0; sp < 2; ++sp)
+    std::copy_n(pl->lam.begin() + sp * L.mp[0], L.m[sp], lc.begin() + sp * mp[0]);
+  if ((s = upload(lam, lc)) != FPS_OK) return s;
   const double *dl = (const double *)lam.p;
   if (pl->zeig) {
     std::vector<double> t((size_t)(npad * npad), 0.0), m((size_t)npad, -1.0);
     for (int sp = 0; sp < 2; ++sp)
-      for (int64_t k = 0; k < L.m[sp]; ++k) m[(size_t)(sp * L.mp[0] + k)] = pl->zlam[sp][(size_t)k];
+      for (int64_t k = 0; k < L.m[sp]; ++k) m[(size_t)(sp * mp[0] + k)] = pl->zlam[sp][(size_t)k];
     if ((s = upload(ey, t)) != FPS_OK || (s = upload(ex, t)) != FPS_OK ||
         (s = upload(p, pl->zp)) != FPS_OK || (s = upload(q, pl->zq)) != FPS_OK ||
         (s = upload(off, pl->zoff)) != FPS_OK || (s = upload(mu, m)) != FPS_OK)
@@ -296,13 +295,13 @@ fps_status cube_plan_upload(fps_plan *pl) {
   }
   FPS_HIP(hipStreamSynchronize(st));
   // per-slice products: y on the way in, y (the last, into U) on the way out
-  const Dims full{{npad, npad, npad}, {L.mp[0], L.mp[0], L.mp[0]}};
+  const Dims full{{npad, npad, npad}, {mp[0], mp[0], mp[0]}};
   const double *Wi[2] = {(const double *)pl->d_Wi[0].p, (const double *)pl->d_Wi[1].p};
-  const int64_t K[2] = {L.mp[0], L.mp[1]};
+  const int64_t ld[2] = {L.mp[0], L.mp[1]};
   std::vector<fps::GemmProb> probs;
   mode_probs((const double *)(intptr_t)pl->off_O1, full, (double *)(intptr_t)pl->off_O0, full, 1, Wi,
-             K, nullptr, K, K, K, probs);
-  if ((s = upload_table(probs, 1, pl->d_gy_in, pl->d_gy_map_in, pl->gy_tiles[0])) != FPS_OK)
+             ld, nullptr, ld, mp, mp, probs);
+  if ((s = upload_table(probs, 1, pl->d_gy_in, pl->d_gy_map_in, pl->t_gy[0])) != FPS_OK)
     return s;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
   const int64_t *mo = native ? L.m : L.mo;
@@ -314,19 +313,19 @@ fps_status cube_plan_upload(fps_plan *pl) {
         for (int sx = 0; sx < 2; ++sx) {
           if (L.m[sz] == 0 || L.m[sy] == 0 || L.m[sx] == 0) continue;
           const int64_t zs = sz * pl->mqc[0] + z, zn = 2 * z + sz;
-          const int64_t in = (zs * npad + sy * L.mp[0]) * mq + sx * pl->mqc[0];
+          const int64_t in = (zs * npad + sy * mp[0]) * mq + sx * pl->mqc[0];
           const int64_t out = (zn * N + sy) * N + sx;
           probs.push_back(fps::GemmProb{(const double *)pl->d_Wo[sy].p,
                                         (const double *)(intptr_t)(pl->off_RX + 8 * in),
-                                        (double *)(intptr_t)(8 * out), mo[sy], mo[sx], L.mp[sy],
-                                        L.mp[sy], 1, mq, 1, 2 * N, 2, 0, 0, 0, 0, 0, 0, 0, 0});
+                                        (double *)(intptr_t)(8 * out), mo[sy], mo[sx], mp[sy],
+                                        L.mp[sy], 1, mq, 1, 2 * N, 2});
         }
-  return upload_table(probs, 2, pl->d_gy_out, pl->d_gy_map_out, pl->gy_tiles[1]);
+  return upload_table(probs, 2, pl->d_gy_out, pl->d_gy_map_out, pl->t_gy[1]);
 }
 
 fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStream_t st) {
   const fps::Layout &L = pl->L;
-  const int64_t npad = L.npad, mp0 = L.mp[0];
+  const int64_t npad = pl->cnp, mp0 = pl->cmp[0], *K = pl->cmp;
   double *G = (double *)(w + pl->off_G), *Y = (double *)(w + pl->off_ZR);
   double *RX = (double *)(w + pl->off_RX);
   double *O0 = (double *)(w + pl->off_O0), *O1 = (double *)(w + pl->off_O1);
@@ -339,7 +338,7 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
     Wo[s] = (const double *)pl->d_Wo[s].p;
     WoT[s] = (const double *)pl->d_WoT[s].p;
   }
-  const int64_t K[2] = {L.mp[0], L.mp[1]};
+  const int64_t ldi[2] = {L.mp[0], L.mp[1]};
   const int64_t No[2] = {L.m[0] > 0 ? mo[0] : 0, L.m[1] > 0 ? mo[1] : 0};
   const int64_t ldo[2] = {mop[0], mop[1]};
   const Dims full{{npad, npad, npad}, {mp0, mp0, mp0}};
@@ -347,11 +346,11 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
   // in: x, y, z (the multiplier in the last product's epilogue)
   FPS_HIP(fps::launch_permute3_in(F, G, L.n, npad, mp0, st));
   std::vector<fps::GemmProb> px, pz, qz, qx;
-  mode_probs(G, full, O1, full, 2, Wi, K, WiT, K, K, K, px);
+  mode_probs(G, full, O1, full, 2, Wi, ldi, WiT, ldi, K, K, px);
   if ((s = launch_probs(pl, px, st)) != FPS_OK) return s;
-  if ((s = run_table(pl, pl->d_gy_in, pl->d_gy_map_in, pl->gy_tiles[0], w, nullptr, st)) != FPS_OK)
+  if ((s = run_table(pl, pl->t_gy[0], pl->d_gy_in, pl->d_gy_map_in, w, nullptr, st)) != FPS_OK)
     return s;
-  mode_probs(O0, full, Y, full, 0, Wi, K, WiT, K, K, K, pz);
+  mode_probs(O0, full, Y, full, 0, Wi, ldi, WiT, ldi, K, K, pz);
   for (fps::GemmProb &g : pz) g.mt = (const double *)pl->d_mt.p + (g.C - Y);
   if ((s = launch_probs(pl, pz, st)) != FPS_OK) return s;
   // out: z, x, y
@@ -360,11 +359,11 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
   const Dims d2{{mq, npad, mq}, {mb0, mp0, mb0}};
   const int64_t N = out_extent(pl);
   if (L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N * N, 0.0, st));  // no odd modes: n = 1
-  mode_probs(Y, full, O0, d1, 0, Wo, K, WoT, ldo, No, K, qz);
+  mode_probs(Y, full, O0, d1, 0, Wo, ldi, WoT, ldo, No, K, qz);
   if ((s = launch_probs(pl, qz, st)) != FPS_OK) return s;
-  mode_probs(O0, d1, RX, d2, 2, Wo, K, WoT, ldo, No, K, qx);
+  mode_probs(O0, d1, RX, d2, 2, Wo, ldi, WoT, ldo, No, K, qx);
   if ((s = launch_probs(pl, qx, st)) != FPS_OK) return s;
-  return run_table(pl, pl->d_gy_out, pl->d_gy_map_out, pl->gy_tiles[1], w, (char *)U, st);
+  return run_table(pl, pl->t_gy[1], pl->d_gy_out, pl->d_gy_map_out, w, (char *)U, st);
 }
 
 // The plan's default-priority side stream and its fork / join events

@@ -14,53 +14,76 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // FP64 GEMM on v_mfma_f64_16x16x4f64: C = A B with A row-major (k
-// contiguous, lda), B row-major (n contiguous, ldb), C(i, j) at
-// C[i*ldci + j*ldcj].  Tile 128 x 128 x 16, four wavefronts in a 2 x 2
-// grid, each computing a 64 x 64 quarter as 4 x 4 MFMA blocks; the next
-// k-tile is fetched into registers while the current one is multiplied, and
-// stashed into the second of two LDS stages.
+// contiguous, sai), B row-major (n contiguous, sbk), C(i, j) at
+// C[i*sci + j*scj].  Tile T x T x 16, four wavefronts in a 2 x 2 grid, each
+// computing a quarter as (T/32)^2 MFMA blocks; k-tiles are loaded into
+// registers two ahead and stashed into the second of two LDS stages (one
+// barrier per k-tile).
 // Operand layout of the 16x16x4 f64 instruction: lane l supplies
 // A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator register r of lane l
 // holds C[4r + l / 16][l % 16].
-// Requirements (checked by the launcher): K, lda, ldb multiples of 16 bytes'
-// worth of doubles (even) and A, B 16-byte aligned; rows/columns of A and B
-// beyond M, N, K must be readable up to the next multiple of the tile (the
-// plan pads every operand to multiples of 64 with zeros) -- loads are
-// clamped to M and N and zero-filled, so only K needs padding.
+// Every output entry is accumulated over k in the same order whatever the
+// tile, so launches with different tiles agree bit for bit.
+//
+// Requirements (checked by the launcher): K a multiple of 16, sai and sbk
+// even, A and B 16-byte aligned; loads are clamped to M and N, so only K needs
+// padding.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 
-// order: tile dispatch order of a triangular batch, longest k-range first
-// (0: natural; 1 / 2: column tile slowest, ascending / descending; 3 / 4:
-// row tile slowest, ascending / descending).  Workgroups start in id order,
-// so the short tiles fill the tail instead of the long ones.
+// order: tile dispatch order (0: natural; 1 / 2: column tile slowest,
+// ascending / descending; 3 / 4: row tile slowest, ascending / descending), so
+// that with a limited k-range the longest tiles start first and the short ones
+// fill the tail.  Workgroups 0 .. nedge-1 take edge units (equal counts per
+// problem), mt x nt tiles per problem follow.
 struct GemmBatch {
   GemmProb p[4];
-  int order;
+  int order, count, mt, nt, nedge;
 };
 
-constexpr int GBM = 128, GBN = 128, GBK = 16, GPAD = 2;
-static_assert(GBM == kGemmTile && GBN == kGemmTile, "tile size shared with the edge split");
+constexpr int kGroup = kGemmGroup, kBK = 16;
 
-// k-range [klo, khi) of tile (bx, by) after the triangular skips.
-__host__ __device__ inline void tile_krange(const GemmProb &g, int bx, int by, int64_t *klo_out,
-                                            int64_t *khi_out) {
-  const int64_t i0 = (int64_t)by * GBM, j0 = (int64_t)bx * GBN;
-  int64_t klo = 0;
-  if (g.triA) klo = i0 + g.offA > klo ? i0 + g.offA : klo;
-  if (g.triB) klo = j0 + g.offB > klo ? j0 + g.offB : klo;
-  klo = klo / GBK * GBK;
-  int64_t khi = g.K;
-  if (g.triAu) {
-    const int64_t e = i0 + GBM - 1 + g.offAu + 1;
-    khi = e < khi ? e : khi;
+// Extent covered by MFMA tiles: the 1 to 4 rows or columns past a multiple of 32
+// (the output maps have n/2 + 1) would cost a row of almost empty tiles, so
+// they are left to edge units, workgroups of the same launch.  (Carrying them
+// along in the last tiles, in FMAs from the staged operands, was slower from
+// K = 256 on, 1309 against 1050 us per launch at n = 4096: the border column's
+// strided loads arrive late in every k-tile.)
+__host__ __device__ inline int64_t main_extent(int64_t x) {
+  return gemm_has_edge(x) ? x - x % 32 : x;
+}
+
+// Edge units of a problem: first those of its edge columns, then those of its
+// edge rows.  A unit covers more rows or columns where k is short, so that its
+// loads still fill a memory round trip.
+__host__ __device__ inline int edge_rows_per_unit(const GemmProb &g) {
+  return g.K <= 128 ? 32 : g.K <= 256 ? 16 : 8;
+}
+__host__ __device__ inline int edge_column_units(const GemmProb &g) {
+  const int64_t mm = main_extent(g.M), r = edge_rows_per_unit(g);
+  return main_extent(g.N) < g.N ? (int)((mm + r - 1) / r) : 0;
+}
+__host__ __device__ inline int edge_units(const GemmProb &g) {
+  const int64_t c = g.K <= 256 ? 64 : 16;
+  return edge_column_units(g) + (main_extent(g.M) < g.M ? (int)((g.N + c - 1) / c) : 0);
+}
+
+// k-range [klo, khi) of the tile at (i0, j0): the limits of its first and last
+// 64-row (or column) group, rounded out to the k-tile.
+__host__ __device__ inline void tile_krange(const GemmProb &g, const int *lim, int64_t i0, int64_t j0,
+                                            int T, int64_t *klo_out, int64_t *khi_out) {
+  int64_t klo = 0, khi = g.K;
+  if (g.kside != 0) {
+    const int64_t x0 = g.kside == 1 ? i0 : j0, X = g.kside == 1 ? g.M : g.N;
+    const int64_t last = (x0 + T < X ? x0 + T : X) - 1;
+    if (g.khigh) {
+      const int64_t h = (lim[last / kGroup] + 31) / 32 * 32;
+      khi = h < khi ? h : khi;
+    } else {
+      klo = lim[x0 / kGroup] / 32 * 32;
+      if (klo > khi) klo = khi;
+    }
   }
-  if (g.triBu) {
-    const int64_t e = j0 + GBN - 1 + g.offBu + 1;
-    khi = e < khi ? e : khi;
-  }
-  khi = (khi + GBK - 1) / GBK * GBK;
-  if (khi > g.K) khi = g.K;
   *klo_out = klo;
   *khi_out = khi;
 }
@@ -79,169 +102,303 @@ __device__ __forceinline__ double multiply(const GemmProb &g, int64_t i, int64_t
   return v * (fma(-r.y, c.y, 1.0) / (r.x + c.x));
 }
 
-// One 128 x 128 output tile (column tile bx, row tile by) of problem g.
-// Two LDS stages (As, Bs and As2, Bs2): the next k-tile is stashed into the
-// stage not being read, so one barrier per k-tile suffices (68 KB of LDS, two
-// workgroups per compute unit).
-template <bool kMul>
-__device__ __forceinline__ void gemm_tile(const GemmProb &g, const int bx, const int by,
-                                          double (*As)[GBK + 1], double (*Bs)[GBN + GPAD],
-                                          double (*As2)[GBK + 1], double (*Bs2)[GBN + GPAD]) {
-  const int64_t i0 = (int64_t)by * GBM, j0 = (int64_t)bx * GBN;
-  if (i0 >= g.M || j0 >= g.N) return;
+// LDS of one workgroup: two stages of A [T][BK + 1] and B [BK][T + 2].  A is
+// kept row-major with one double of padding: the stash writes each thread's
+// k-run in place and the fragment reads (16 rows at one k per quarter-wave) hit
+// distinct banks.
+template <int T>
+struct Tile {
+  static constexpr int kA = T * (kBK + 1), kB = kBK * (T + 2), kStage = kA + kB;
+  static constexpr int kLds = 2 * kStage;
+};
+
+// One T x T output tile at (i0, j0) of problem g.
+template <int T, bool kMul>
+__device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, const int64_t j0,
+                                          double *lds) {
+  constexpr int BK = kBK;
+  constexpr int W = T / 2, NB = T / 32;            // quarter of a wavefront, its MFMA blocks
+  constexpr int RA = T * BK / 256, TA = BK / RA;   // A: doubles per thread, threads per row
+  constexpr int TB = 256 / BK, QB = T / (2 * TB);  // B: threads per k-row, column pairs per thread
+  using L = Tile<T>;
+  const int64_t Mm = main_extent(g.M), Nm = main_extent(g.N);
+  if (i0 >= Mm || j0 >= Nm) return;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wy = wid >> 1, wx = wid & 1;
   int64_t klo, khi;
-  tile_krange(g, bx, by, &klo, &khi);
+  tile_krange(g, g.klim, i0, j0, T, &klo, &khi);
 
-  // Loader mapping.  A tile 128 x 16: thread t reads row t/2, k-run (t%2)*8..+8.
-  // B tile 16 x 128: thread t reads k-row t/16, the column pairs bc + 32 q
-  // (bc = 2 (t%16), q = 0..3), so the 16 threads of a row read and stash
-  // 256 contiguous bytes per q (no LDS bank conflicts on the stash).
-  const int ar = tid >> 1, ak = (tid & 1) * 8;
-  const int bk = tid >> 4, bc = (tid & 15) * 2;
+  // Loaders.  A: thread t reads row t / TA, k-run (t % TA) RA ..; B: thread t
+  // reads k-row t / TB, the column pairs bc + 2 TB q, so the threads of a row
+  // read and stash one contiguous run per q (no LDS bank conflicts).  Rows and
+  // columns past M and N are clamped to the last one: what they add to lands
+  // in output entries that are not stored, so the loop has no branches (with
+  // one per k-step the compiler waited for every LDS read before its products:
+  // 34 against 21 us per 64 x 64 stage at n = 1024).
+  const int ar = tid / TA, ak = (tid % TA) * RA;
+  const int bk = tid / TB, bc = (tid % TB) * 2;
   const int64_t arow = i0 + ar < g.M ? i0 + ar : g.M - 1;
-  const double az = i0 + ar < g.M ? 1.0 : 0.0;
-  const double *__restrict__ Ap = g.A + arow * g.sai + ak;
-  const double *__restrict__ Bp = g.B + (int64_t)bk * g.sbk + j0 + bc;
-  const bool bfull = j0 + bc + 3 * 32 + 2 <= g.N;
+  const double *__restrict__ Ap = g.A + arow * g.sai + klo + ak;
+  const double *__restrict__ Bp = g.B + (klo + bk) * g.sbk;
+  const int64_t jlast = (g.N - 1) & ~(int64_t)1;  // row strides are even: the pair exists
+  int bcol[QB];
+#pragma unroll
+  for (int q = 0; q < QB; ++q) {
+    const int64_t j = j0 + bc + 2 * TB * q;
+    bcol[q] = (int)(j < jlast ? j : jlast);
+  }
 
-  dbl2 ra[4], rb[4];
-  auto fetch = [&](int64_t k0) {
+  dbl2 ra[2][RA / 2], rb[2][QB];
+  auto fetch = [&](int r) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) ra[q] = *(const dbl2 *)(Ap + k0 + 2 * q);
-    const double *bp = Bp + k0 * g.sbk;
-    if (bfull) {
+    for (int q = 0; q < RA / 2; ++q) ra[r][q] = *(const dbl2 *)(Ap + 2 * q);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) rb[q] = *(const dbl2 *)(bp + 32 * q);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t jj = j0 + bc + 32 * q;
-        rb[q].x = jj < g.N ? bp[32 * q] : 0.0;
-        rb[q].y = jj + 1 < g.N ? bp[32 * q + 1] : 0.0;
-      }
-    }
+    for (int q = 0; q < QB; ++q) rb[r][q] = *(const dbl2 *)(Bp + bcol[q]);
+    Ap += BK;
+    Bp += BK * g.sbk;
   };
-  // A is kept row-major in LDS ([row][k], one double of padding): the
-  // stash writes each thread's k-run in place and the fragment reads
-  // (16 rows at one k per quarter-wave) hit distinct banks.
-  auto stash_to = [&](double (*Ad)[GBK + 1], double (*Bd)[GBN + GPAD]) {
+  auto stash = [&](double *st, int r) {
+    double *Ad = st + ar * (BK + 1) + ak;
+    double *Bd = st + L::kA + bk * (T + 2) + bc;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      Ad[ar][ak + 2 * q] = az * ra[q].x;
-      Ad[ar][ak + 2 * q + 1] = az * ra[q].y;
-      *(dbl2 *)&Bd[bk][bc + 32 * q] = rb[q];
+    for (int q = 0; q < RA / 2; ++q) {
+      Ad[2 * q] = ra[r][q].x;
+      Ad[2 * q + 1] = ra[r][q].y;
     }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) *(dbl2 *)(Bd + 2 * TB * q) = rb[r][q];
   };
 
-
-  dbl4 acc[4][4];
+  dbl4 acc[NB][NB];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NB; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = dbl4{0.0, 0.0, 0.0, 0.0};
-
-  // 16 x 16 blocks of this wavefront's 64 x 64 quarter that hold output
-  // entries: a thin last tile (a few rows or columns past whole tiles) skips
-  // the products of its empty blocks (uniform per wavefront).
-  const int64_t mrem = g.M - (i0 + wy * 64), nrem = g.N - (j0 + wx * 64);
-  const int na = mrem >= 64 ? 4 : mrem <= 0 ? 0 : (int)((mrem + 15) / 16);
-  const int nb = nrem >= 64 ? 4 : nrem <= 0 ? 0 : (int)((nrem + 15) / 16);
-  const bool full = na == 4 && nb == 4;
-  // the products of one k-tile from the stage (Ar, Br)
-  auto mma = [&](double (*Ar)[GBK + 1], double (*Br)[GBN + GPAD]) {
+    for (int b = 0; b < NB; ++b) acc[a][b] = dbl4{0.0, 0.0, 0.0, 0.0};
+  const double *Ar = lds + (wy * W + (lane & 15)) * (BK + 1) + (lane >> 4);
+  const double *Br = lds + L::kA + (lane >> 4) * (T + 2) + wx * W + (lane & 15);
+  // The products of one k-tile from the stage at offset so; the fragments of
+  // the next k-step are read under the products of the current one.
+  auto mma = [&](int so) {
+    double av[2][NB], bv[2][NB];
+    auto frag = [&](int ks) {
+      const int f = (ks >> 2) & 1;
 #pragma unroll
-    for (int ks = 0; ks < GBK; ks += 4) {
-      double av[4], bv[4];
+      for (int a = 0; a < NB; ++a) av[f][a] = Ar[so + a * 16 * (BK + 1) + ks];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) av[a] = Ar[wy * 64 + a * 16 + (lane & 15)][ks + (lane >> 4)];
+      for (int b = 0; b < NB; ++b) bv[f][b] = Br[so + ks * (T + 2) + b * 16];
+    };
+    frag(0);
 #pragma unroll
-      for (int b = 0; b < 4; ++b) bv[b] = Br[ks + (lane >> 4)][wx * 64 + b * 16 + (lane & 15)];
-      if (full) {
+    for (int ks = 0; ks < BK; ks += 4) {
+      const int f = (ks >> 2) & 1;
+      if (ks + 4 < BK) frag(ks + 4);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < NB; ++a)
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b)
-            if (a < na && b < nb)
-              acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-      }
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[f][a], bv[f][b], acc[a][b], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  if (klo < khi) {
-    fetch(klo);
-    stash_to(As, Bs);
+  // Stage s is read in k-tile t while stage 1 - s receives tile t + 1; the
+  // barrier after the stash orders both the stash before the next tile's
+  // reads and this tile's reads before the stash that follows.  The loads of
+  // tile t + 2 are issued before the products of tile t, so a load has two
+  // k-tiles to arrive.
+  const int nk = (int)((khi - klo + BK - 1) / BK);
+  if (nk > 0) {
+    fetch(0);
+    stash(lds, 0);
+    if (nk > 1) fetch(1);
     __syncthreads();
-    // stage s is read in k-tile t while stage 1 - s receives tile t + 1; the
-    // barrier after the stash orders both the stash before the next tile's
-    // reads and this tile's reads before the stash that follows
     int t = 0;
-    for (int64_t k0 = klo; k0 < khi; k0 += GBK, ++t) {
-      const bool more = k0 + GBK < khi;
-      if (more) fetch(k0 + GBK);
-      const bool odd = (t & 1) != 0;
-      mma(odd ? As2 : As, odd ? Bs2 : Bs);
-      if (more) stash_to(odd ? As : As2, odd ? Bs : Bs2);
+#pragma unroll 1
+    for (; t + 2 < nk; t += 2) {
+      fetch(0);
+      mma(0);
+      stash(lds + L::kStage, 1);
+      __syncthreads();
+      if (t + 3 < nk) fetch(1);
+      mma(L::kStage);
+      stash(lds, 0);
       __syncthreads();
     }
+    mma(0);
+    if (t + 1 < nk) {
+      stash(lds + L::kStage, 1);
+      __syncthreads();
+      mma(L::kStage);
+    }
   }
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < NB; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t gi = i0 + wy * 64 + a * 16 + 4 * r + (lane >> 4);
-        const int64_t gj = j0 + wx * 64 + b * 16 + (lane & 15);
-        if (gi < g.M && gj < g.N) 
-          g.C[gi * g.sci + gj * g.scj] =
-              kMul ? multiply(g, gi, gj, acc[a][b][r]) : acc[a][b][r];
+        const int64_t gi = i0 + wy * W + a * 16 + 4 * r + (lane >> 4);
+        const int64_t gj = j0 + wx * W + b * 16 + (lane & 15);
+        if (gi < Mm && gj < Nm)
+          g.C[gi * g.sci + gj * g.scj] = kMul ? multiply(g, gi, gj, acc[a][b][r]) : acc[a][b][r];
       }
 }
 
-template <bool kMul>
-__global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
-  __shared__ double As[GBM][GBK + 1], As2[GBM][GBK + 1];
-  __shared__ double Bs[GBK][GBN + GPAD], Bs2[GBK][GBN + GPAD];
-  int bx = blockIdx.x, by = blockIdx.y, z = blockIdx.z;
-  if (batch.order != 0) {
-    const int nt = gridDim.x, mt = gridDim.y, nz = gridDim.z;
-    const int L = blockIdx.x + nt * (blockIdx.y + mt * blockIdx.z);
-    if (batch.order <= 2) {
-      const int c = L / (mt * nz), rem = L % (mt * nz);
-      bx = batch.order == 1 ? c : nt - 1 - c;
-      z = rem / mt;
-      by = rem % mt;
-    } else {
-      const int r = L / (nt * nz), rem = L % (nt * nz);
-      by = batch.order == 3 ? r : mt - 1 - r;
-      z = rem / nt;
-      bx = rem % nt;
+// One edge unit in plain FP64 FMAs: latency bound, so a unit is small and issues
+// its loads together; the units start first and run beside the MFMA tiles.
+// (8 loads of A in flight per lane: with 16 the kernel needs more registers
+// than its MFMA tiles, which costs those a wavefront per SIMD.)
+// Column units: a wavefront takes R rows, lanes along k (U chunks of 128 at a
+// time, R U = 8), and sums across lanes by a butterfly.  The last wavefront
+// overlaps its neighbour's rows (Mm >= 32) instead of passing the end.
+template <int U>
+__device__ __forceinline__ void edge_columns(const GemmProb &g, int64_t i, int64_t Mm, int64_t Nm,
+                                             int lane) {
+  constexpr int R = 8 / U;
+  const int K = (int)g.K;
+  const int64_t i0 = i + R <= Mm ? i : Mm - R;
+  const double *A = g.A + i0 * g.sai;
+  for (int64_t j = Nm; j < g.N; ++j) {
+    const double *B = g.B + j;
+    double acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.0;
+    for (int k0 = 2 * lane; k0 < K; k0 += 128 * U) {
+      dbl2 a[U][R], b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 128 * u < K ? k0 + 128 * u : k0;
+        b[u].x = B[k * g.sbk];
+        b[u].y = B[(k + 1) * g.sbk];
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[u][r] = *(const dbl2 *)(A + r * g.sai + k);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k0 + 128 * u < K) {
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            acc[r] = fma(a[u][r].y, b[u].y, fma(a[u][r].x, b[u].x, acc[r]));
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double v = acc[r];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+      if (lane == 0) g.C[(i0 + r) * g.sci + j * g.scj] = v;
     }
   }
-  gemm_tile<kMul>(batch.p[z], bx, by, As, Bs, As2, Bs2);
 }
 
-// Table-driven GEMM: workgroup g computes tile (local % ntx, local / ntx),
-// local = tile_map[2g + 1], of problem tile_map[2g]; operand pointers are
-// rebased per GemmDesc base ids.
+// Row units: kCols columns x (256 / kCols) parts of k, the parts' sums added in
+// order; the last lanes clear rows M .. Mz - 1.
+template <int kCols>
+__device__ __forceinline__ void edge_rows(const GemmProb &g, int64_t j0, int64_t Mm, double *lds) {
+  constexpr int kParts = 256 / kCols;
+  const int tid = threadIdx.x, part = tid / kCols;
+  const int64_t j = j0 + tid % kCols, kp = g.K / kParts;  // K is a multiple of 16
+  const int ne = (int)(g.M - Mm);
+  const double *bp = g.B + part * kp * g.sbk + (j < g.N ? j : g.N - 1);
+  const double *ap = g.A + Mm * g.sai + part * kp;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t k0 = 0; k0 < kp; k0 += 16) {
+    double b[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) b[u] = bp[(k0 + u < kp ? k0 + u : k0) * g.sbk];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < ne) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (k0 + u < kp) acc[e] = fma(ap[e * g.sai + k0 + u], b[u], acc[e]);
+      }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) lds[e * 256 + tid] = acc[e];
+  __syncthreads();
+  if (j >= g.N) return;
+  for (int e = part; e < ne; e += kParts) {
+    double v = 0.0;
+#pragma unroll
+    for (int u = 0; u < kParts; ++u) v += lds[e * 256 + u * kCols + tid % kCols];
+    g.C[(Mm + e) * g.sci + j * g.scj] = v;
+  }
+  for (int64_t i = g.M + part; i < g.Mz; i += kParts) g.C[i * g.sci + j * g.scj] = 0.0;
+}
+
+__device__ __forceinline__ void gemm_edge(const GemmProb &g, int unit, double *lds) {
+  const int64_t Mm = main_extent(g.M), Nm = main_extent(g.N);
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int rows = edge_rows_per_unit(g), ncu = edge_column_units(g);
+  if (unit < ncu) {
+    const int64_t i0 = (int64_t)unit * rows + wid * (rows / 4);
+    if (rows == 32)
+      edge_columns<1>(g, i0, Mm, Nm, lane);
+    else if (rows == 16)
+      edge_columns<2>(g, i0, Mm, Nm, lane);
+    else
+      edge_columns<4>(g, i0, Mm, Nm, lane);
+    return;
+  }
+  if (g.K > 256)
+    edge_rows<16>(g, (int64_t)(unit - ncu) * 16, Mm, lds);
+  else
+    edge_rows<64>(g, (int64_t)(unit - ncu) * 64, Mm, lds);
+}
+
+// Plain products allocate 52 KB, three workgroups per compute unit: four run in
+// step, their first and last k-tiles at the same time (n = 2048: 155 against
+// 141 us per launch).
+template <int T, bool kMul>
+constexpr int lds_doubles() {
+  return T == 64 && !kMul ? 52 * 128 : Tile<T>::kLds;
+}
+
+template <int T, bool kMul>
+__global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
+  __shared__ __align__(16) double lds[lds_doubles<T, kMul>()];
+  int L = blockIdx.x;
+  if (!kMul && L < batch.nedge) {
+    const int per = batch.nedge / batch.count;
+    const GemmProb &g = batch.p[L / per];
+    if (L % per < edge_units(g)) gemm_edge(g, L % per, lds);
+    return;
+  }
+  if (!kMul) L -= batch.nedge;
+  const int nt = batch.nt, mt = batch.mt, nz = batch.count;
+  int bx, by, z;
+  if (batch.order == 0) {
+    bx = L % nt;
+    by = L / nt % mt;
+    z = L / (nt * mt);
+  } else if (batch.order <= 2) {
+    const int c = L / (mt * nz), rem = L % (mt * nz);
+    bx = batch.order == 1 ? c : nt - 1 - c;
+    z = rem / mt;
+    by = rem % mt;
+  } else {
+    const int r = L / (nt * nz), rem = L % (nt * nz);
+    by = batch.order == 3 ? r : mt - 1 - r;
+    z = rem / nt;
+    bx = rem % nt;
+  }
+  gemm_tile<T, kMul>(batch.p[z], (int64_t)by * T, (int64_t)bx * T, lds);
+}
+
+// Table-driven GEMM: workgroup g computes unit tile_map[2g + 1] of problem
+// tile_map[2g]: its tiles row by row (ntx per row), then its edge units.
+// Operand pointers are rebased per GemmDesc base ids.
 __device__ __forceinline__ const double *rebase(const double *p, int id, char *ws, char *out) {
   return id == 1 ? (const double *)(ws + (intptr_t)p)
                  : id == 2 ? (const double *)(out + (intptr_t)p) : p;
 }
 
-template <bool kMul>
+template <int T, bool kMul>
 __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restrict__ d,
                                                        const int *__restrict__ tile_map, char *ws,
                                                        char *out) {
-  __shared__ double As[GBM][GBK + 1], As2[GBM][GBK + 1];
-  __shared__ double Bs[GBK][GBN + GPAD], Bs2[GBK][GBN + GPAD];
+  __shared__ __align__(16) double lds[lds_doubles<T, kMul>()];
   const int k = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x]);
   const int local = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x + 1]);
   const GemmDesc &e = d[k];
@@ -249,176 +406,129 @@ __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restric
   g.A = rebase(g.A, e.abase, ws, out);
   g.B = rebase(g.B, e.bbase, ws, out);
   g.C = (double *)rebase(g.C, e.cbase, ws, out);
-  gemm_tile<kMul>(g, local % e.ntx, local / e.ntx, As, Bs, As2, Bs2);
-}
-
-// Columns tn.. of every row of a table problem: one wavefront per row,
-// lanes striding over k with coalesced loads of the row, then a butterfly
-// sum across the wavefront (fixed order, so the result is reproducible).
-// kRows rows per wavefront iteration keep their loads in flight together;
-// rows with k contiguous, even K and a 16-byte aligned start are read two
-// k at a time (kVecRows rows in flight).  Workgroup b serves problem
-// b % nprob, so problems that read different parts of the same rows (the
-// parity blocks of one array) read them at the same time.
-__global__ __launch_bounds__(256) void k_gemm_edge_cols(const GemmDesc *__restrict__ d, int nprob,
-                                                        int64_t tn, char *ws, char *out) {
-  constexpr int kRows = 4, kVecRows = 8;
-  const GemmDesc &e = d[blockIdx.x % nprob];
-  const double *__restrict__ A = rebase(e.p.A, e.abase, ws, out);
-  const double *__restrict__ B = rebase(e.p.B, e.bbase, ws, out);
-  double *__restrict__ C = (double *)rebase(e.p.C, e.cbase, ws, out);
-  const int64_t M = e.p.M, N = e.p.N, K = e.p.K;
-  const int64_t nn = N < tn ? N : tn;
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t)(blockIdx.x / nprob) * 4 + (threadIdx.x >> 6);
-  const int64_t nwaves = (int64_t)(gridDim.x / nprob) * 4;
-  if (e.p.sak == 1 && !(e.p.sai & 1) && !(K & 1) && !((uintptr_t)A & 15)) {
-    for (int64_t i0 = wave * kVecRows; i0 < M; i0 += nwaves * kVecRows) {
-      for (int64_t j = nn; j < N; ++j) {
-        double acc[kVecRows];
-#pragma unroll
-        for (int r = 0; r < kVecRows; ++r) acc[r] = 0.0;
-        for (int64_t k = 2 * lane; k < K; k += 128) {
-          const double b0 = B[k * e.p.sbk + j * e.p.sbj], b1 = B[(k + 1) * e.p.sbk + j * e.p.sbj];
-          dbl2 a[kVecRows];
-#pragma unroll
-          for (int r = 0; r < kVecRows; ++r) {
-            const int64_t i = i0 + r < M ? i0 + r : M - 1;
-            a[r] = *(const dbl2 *)(A + i * e.p.sai + k);
-          }
-#pragma unroll
-          for (int r = 0; r < kVecRows; ++r) acc[r] = fma(a[r].y, b1, fma(a[r].x, b0, acc[r]));
-        }
-#pragma unroll
-        for (int r = 0; r < kVecRows; ++r) {
-          double v = acc[r];
-#pragma unroll
-          for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-          if (lane == 0 && i0 + r < M) C[(i0 + r) * e.p.sci + j * e.p.scj] = v;
-        }
-      }
-    }
-    return;
-  }
-  for (int64_t i0 = wave * kRows; i0 < M; i0 += nwaves * kRows) {
-    for (int64_t j = nn; j < N; ++j) {
-      double acc[kRows];
-#pragma unroll
-      for (int r = 0; r < kRows; ++r) acc[r] = 0.0;
-      for (int64_t k = lane; k < K; k += 64) {
-        const double b = B[k * e.p.sbk + j * e.p.sbj];
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-          const int64_t i = i0 + r < M ? i0 + r : M - 1;
-          acc[r] = fma(A[i * e.p.sai + k * e.p.sak], b, acc[r]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kRows; ++r) {
-        double v = acc[r];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0 && i0 + r < M) C[(i0 + r) * e.p.sci + j * e.p.scj] = v;
-      }
-    }
-  }
+  if (!kMul && local >= e.ntiles)
+    gemm_edge(g, local - e.ntiles, lds);
+  else
+    gemm_tile<T, kMul>(g, (int64_t)(local / e.ntx) * T, (int64_t)(local % e.ntx) * T, lds);
 }
 
 }  // namespace
 
-hipError_t launch_gemm_edge_cols(const GemmDesc *d, int nprob, int64_t tn, int nblk, char *ws,
-                                 char *out, hipStream_t st) {
-  if (nprob <= 0 || nblk <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gemm_edge_cols, dim3((unsigned)(nblk * nprob)), dim3(256), 0, st, d, nprob,
-                     tn, ws, out);
-  return hipGetLastError();
+namespace {
+
+bool has_mul(const GemmProb &q) { return q.mr != nullptr || q.mt != nullptr; }
+
+// Tile of a set of problems.  32 x 32 where 64 x 64 tiles would be too few for
+// the 256 compute units to hide a workgroup's serial chain of k-tiles (measured
+// per stage of a square solve, 64 / 32: n = 200 9 / 6 us, 515 17 / 11, 1024 30 /
+// 27, 1700 125 / 110; n = 2048, 1024 tiles, 157 / 160; n = 3000 437 / 533), or
+// where they would cover much more than the outputs (blocks of 96: the n = 185
+// cube's per-slice products 70 / 52 us); a 32 x 32 tile reads its operands
+// twice as often, about 15 % of its time.
+template <typename Get>
+int pick_tile(int64_t count, Get get) {
+  double t64 = 0.0, t32 = 0.0;
+  for (int64_t i = 0; i < count; ++i) {
+    const GemmProb &q = get(i);
+    const int64_t m = main_extent(q.M), n = main_extent(q.N);
+    t64 += (double)((m + 63) / 64) * (double)((n + 63) / 64);
+    t32 += (double)((m + 31) / 32) * (double)((n + 31) / 32);
+  }
+  return t64 <= 800.0 || 1.15 * t32 < 4.0 * t64 ? 32 : 64;
 }
 
-static bool has_mul(const GemmProb &q) { return q.mr != nullptr || q.mt != nullptr; }
+}  // namespace
 
 bool gemm_operands_ok(const GemmProb &q) {
-  return q.sak == 1 && q.sbj == 1 && q.K % GBK == 0 && !(q.sai & 1) && !(q.sbk & 1) &&
-         !((uintptr_t)q.A & 15) && !((uintptr_t)q.B & 15) && q.M >= 1 && q.N >= 1;
+  return q.sak == 1 && q.sbj == 1 && q.K % 16 == 0 && !(q.sai & 1) && !(q.sbk & 1) &&
+         !((uintptr_t)q.A & 15) && !((uintptr_t)q.B & 15) && q.M >= 1 && q.N >= 1 &&
+         !(has_mul(q) && (main_extent(q.M) != q.M || main_extent(q.N) != q.N));
 }
 
-int gemm_tiles(const GemmProb &q, int *ntx) {
-  *ntx = (int)((q.N + GBN - 1) / GBN);
-  return *ntx * (int)((q.M + GBM - 1) / GBM);
-}
-
-hipError_t launch_gemm_table(const GemmDesc *d, const int *tile_map, int ntiles, char *ws,
-                             char *out, hipStream_t st, bool mul, hipEvent_t ev0,
-                             hipEvent_t ev1) {
-  if (ntiles <= 0) return hipSuccess;
-  const auto kern = mul ? k_gemm_table<true> : k_gemm_table<false>;
+hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map, char *ws,
+                             char *out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (t.units <= 0) return hipSuccess;
+  auto kern = t.mul ? k_gemm_table<64, true> : k_gemm_table<64, false>;
+  if (t.T == 32) kern = t.mul ? k_gemm_table<32, true> : k_gemm_table<32, false>;
   if (ev0 != nullptr)
-    hipExtLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(256), 0, st, ev0, ev1, 0, d, tile_map,
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)t.units), dim3(256), 0, st, ev0, ev1, 0, d, tile_map,
                           ws, out);
   else
-    hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(256), 0, st, d, tile_map, ws, out);
+    hipLaunchKernelGGL(kern, dim3((unsigned)t.units), dim3(256), 0, st, d, tile_map, ws, out);
   return hipGetLastError();
 }
 
-std::vector<int> gemm_table_map(const std::vector<GemmDesc> &tab) {
-  // every tile of every problem, longest k-range first (workgroups start in
-  // id order, so the short tiles fill the tail); ties keep table order
-  struct T {
+bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map) {
+  map.clear();
+  t = GemmTable{};
+  if (tab.empty()) return true;
+  t.mul = has_mul(tab[0].p);
+  t.T = pick_tile((int64_t)tab.size(), [&](int64_t i) -> const GemmProb & { return tab[(size_t)i].p; });
+  // edge units, then every tile of every problem, longest k-range first (workgroups start
+  // in id order, so the short tiles fill the tail); ties keep table order
+  struct Unit {
     int64_t work;
     int prob, local;
   };
-  std::vector<T> tiles;
+  std::vector<Unit> units;
   for (size_t k = 0; k < tab.size(); ++k) {
-    int ntx = 0;
-    const int nt = gemm_tiles(tab[k].p, &ntx);
-    for (int l = 0; l < nt; ++l) {
+    GemmDesc &e = tab[k];
+    if (!gemm_operands_ok(e.p) || has_mul(e.p) != t.mul) return false;
+    const int64_t ntx = (main_extent(e.p.N) + t.T - 1) / t.T, nty = (main_extent(e.p.M) + t.T - 1) / t.T;
+    e.ntx = (int)ntx;
+    e.ntiles = (int)(ntx * nty);
+    for (int l = 0; l < e.ntiles; ++l) {
       int64_t klo, khi;
-      tile_krange(tab[k].p, l % ntx, l / ntx, &klo, &khi);
-      tiles.push_back(T{khi > klo ? khi - klo : 0, (int)k, l});
+      tile_krange(e.p, e.p.klim_host, l / ntx * t.T, l % ntx * t.T, t.T, &klo, &khi);
+      units.push_back(Unit{khi - klo, (int)k, l});
     }
+    for (int u = 0; u < edge_units(e.p); ++u)
+      units.push_back(Unit{(int64_t)1 << 40, (int)k, e.ntiles + u});
   }
-  std::stable_sort(tiles.begin(), tiles.end(), [](const T &a, const T &b) { return a.work > b.work; });
-  std::vector<int> map;
-  map.reserve(2 * tiles.size());
-  for (const T &t : tiles) {
-    map.push_back(t.prob);
-    map.push_back(t.local);
+  std::stable_sort(units.begin(), units.end(),
+                   [](const Unit &a, const Unit &b) { return a.work > b.work; });
+  t.units = (int)units.size();
+  map.reserve(2 * units.size());
+  for (const Unit &u : units) {
+    map.push_back(u.prob);
+    map.push_back(u.local);
   }
-  return map;
+  return true;
 }
 
 hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0,
                        hipEvent_t ev1) {
   if (count <= 0) return hipSuccess;
   if (count > 4) return hipErrorInvalidValue;
+  const int T = pick_tile(count, [&](int64_t i) -> const GemmProb & { return probs[i]; });
   GemmBatch b{};
-  int64_t mt = 1, nt = 1;
+  int64_t mt = 1, nt = 1, edge = 0;
+  const GemmProb &f = probs[0];
+  bool same = true;
   for (int i = 0; i < count; ++i) {
     const GemmProb &q = probs[i];
     // contiguous operands, 16-byte aligned, K padded to the k-tile
     if (!gemm_operands_ok(q)) return hipErrorInvalidValue;
-    if (has_mul(q) != has_mul(probs[0])) return hipErrorInvalidValue;
-    b.p[i] = probs[i];
-    mt = probs[i].M > mt * GBM ? (probs[i].M + GBM - 1) / GBM : mt;
-    nt = probs[i].N > nt * GBN ? (probs[i].N + GBN - 1) / GBN : nt;
+    if (has_mul(q) != has_mul(f)) return hipErrorInvalidValue;
+    b.p[i] = q;
+    mt = std::max(mt, (main_extent(q.M) + T - 1) / T);
+    nt = std::max(nt, (main_extent(q.N) + T - 1) / T);
+    edge = std::max(edge, (int64_t)edge_units(q));
+    same = same && q.kside == f.kside && q.khigh == f.khigh;
   }
-  // Longest-first order when every problem has the same one-sided
-  // triangular structure: the k-range of a tile then shrinks along one tile
-  // index (triB: klo grows with the column tile, triBu: khi grows with it;
-  // triA / triAu likewise with the row tile).
-  const GemmProb &f = probs[0];
-  bool same = true;
-  for (int i = 1; i < count; ++i) {
-    const GemmProb &q = probs[i];
-    same = same && q.triA == f.triA && q.triB == f.triB && q.triAu == f.triAu &&
-           q.triBu == f.triBu;
-  }
-  const bool rowwise = f.triA || f.triAu, colwise = f.triB || f.triBu;
-  if (same && colwise && !rowwise && !(f.triB && f.triBu))
-    b.order = f.triB ? 1 : 2;
-  else if (same && rowwise && !colwise && !(f.triA && f.triAu))
-    b.order = f.triA ? 3 : 4;
-  dim3 grid((unsigned)nt, (unsigned)mt, (unsigned)count);
-  const auto kern = has_mul(f) ? k_gemm<true> : k_gemm<false>;
+  // longest k-range first: lower limits grow, so the first tiles are the
+  // longest; upper limits grow too, so there the last ones are
+  if (same && f.kside == 2) b.order = f.khigh ? 2 : 1;
+  if (same && f.kside == 1) b.order = f.khigh ? 4 : 3;
+  b.count = count;
+  b.mt = (int)mt;
+  b.nt = (int)nt;
+  b.nedge = (int)(edge * count);
+  const int64_t wgs = (edge + mt * nt) * count;
+  if (wgs > (int64_t)1 << 30) return hipErrorInvalidValue;
+  auto kern = has_mul(f) ? k_gemm<64, true> : k_gemm<64, false>;
+  if (T == 32) kern = has_mul(f) ? k_gemm<32, true> : k_gemm<32, false>;
+  const dim3 grid((unsigned)wgs);
   if (ev0 != nullptr)
     hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, st, ev0, ev1, 0, b);
   else

@@ -324,20 +324,6 @@ struct CylSolveGroup {
 // rp, overwritten), X1 receives yhat (rows of parity wp).
 hipError_t launch_cyl_solve(double *X0, double *X1, const double *fac, const CylSolveGroup *grp,
                             int ngroups, int64_t m, int64_t mp, hipStream_t st);
-// Cylinder: the thin edges of the r output map of one (slot, part, z parity)
-// problem U_blk = Pr X0_blk (Pr ro x mp row-major, PrT its transpose, X0_blk
-// rows of stride mobar in the workspace at byte offset b_off, U_blk at
-// element offset c_off with row stride ldc and column stride 2): the rows
-// ro_main.. (every column) and the columns mo_main.. of the rows above
-// ro_main, at most 8 of each, mp <= 256.  One workgroup per problem.
-struct CylEdge {
-  const double *Pr, *PrT;
-  int64_t b_off, c_off;
-};
-hipError_t launch_cyl_redge(const CylEdge *d, int nprob, char *ws, double *U, int64_t mp,
-                            int64_t ro, int64_t ro_main, int64_t mo, int64_t mo_main,
-                            int64_t mobar, int64_t ldc, hipStream_t st);
-
 // U ((n+2) x (n+2) Chebyshev, natural order) += coefficients of u_bc.
 hipError_t launch_bc_lift_out(double *U, const double *bc, const double *corner, int64_t n,
                               hipStream_t st);
@@ -346,18 +332,18 @@ hipError_t launch_bc_lift_out(double *U, const double *bc, const double *corner,
 //   C(i,j) = sum_k A(i,k) B(k,j),  A(i,k) = A[i*sai + k], B(k,j) = B[k*sbk + j],
 //   C(i,j) at C[i*sci + j*scj]  (sak and sbj must be 1; K a multiple of 16;
 //   A, B 16-byte aligned with even row strides).
-// Triangular structure: when triA, A(i,k) = 0 for k < i + offA; when triB,
-// B(k,j) = 0 for k < j + offB; k-tiles below the first nonzero are skipped.
+constexpr int kGemmGroup = 64;  // rows or columns that share one k limit
 struct GemmProb {
   const double *A;
   const double *B;
   double *C;
   int64_t M, N, K;
   int64_t sai, sak, sbk, sbj, sci, scj;
-  int triA, offA, triB, offB;
-  // upper bounds: when triAu, A(i,k) = 0 for k > i + offAu; when triBu,
-  // B(k,j) = 0 for k > j + offBu; k-tiles above the last nonzero are skipped.
-  int triAu, offAu, triBu, offBu;
+  // Limited k-range: kside 1: A(i,k) = 0, kside 2: B(k,j) = 0 for k below
+  // (khigh 0) or from (khigh 1) klim[x / kGemmGroup], x = i or j; klim
+  // nondecreasing, a device table (klim_host: the same values on the host).
+  int kside, khigh;
+  const int *klim, *klim_host;
   // Multiplier of the eigenbasis solve, when mr is non-null: C(i,j) becomes
   //   (acc - sum_q lr[4i+q] lc[4j+q]) (1 - mr[2i+1] mc[2j+1]) / (mr[2i] + mc[2j]),
   // the lr / lc term (the Dirichlet lift) only when lr is non-null.
@@ -365,6 +351,9 @@ struct GemmProb {
   const double *mr, *mc, *lr, *lc;
   // Cube: a tabulated multiplier instead, mt indexed like C (mr null).
   const double *mt;
+  // Rows M .. Mz - 1 of C are cleared where M has edge rows (1 to 4 past a
+  // multiple of 32): they are the k-padding of the next product.
+  int64_t Mz;
 };
 hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
@@ -402,45 +391,30 @@ hipError_t launch_transpose(const double *in, int64_t ldi, double *out, int64_t 
 hipError_t launch_scale_rows(const double *in, const double *sinv, int s, int64_t m, int64_t rows,
                              int64_t ld, double *out, hipStream_t st);
 
+// Whether an extent has edge rows or columns: 1 to 4 past a multiple of 32.
+__host__ __device__ inline bool gemm_has_edge(int64_t x) {
+  return x > 32 && x % 32 >= 1 && x % 32 <= 4;
+}
 // The launcher's operand requirements (also for table-driven problems, with
-// offsets in place of pointers) and the tile count of one problem (ntx: its
-// column tiles).
+// offsets in place of pointers).
 bool gemm_operands_ok(const GemmProb &q);
-int gemm_tiles(const GemmProb &q, int *ntx);
 
 // Table-driven GEMM over many problems in one launch.  Each pointer of a
 // descriptor's GemmProb is absolute (base id 0), a byte offset from `ws`
-// (1) or from `out` (2).  Workgroup g computes tile (local % ntx, local /
-// ntx) of problem tile_map[2g], local = tile_map[2g + 1].
+// (1) or from `out` (2).  gemm_table (host) picks the tile, fills every
+// descriptor's tile counts and the workgroup map, (problem, unit) pairs; false
+// if a problem does not meet the launcher's requirements.
 struct GemmDesc {
   GemmProb p;
   int abase, bbase, cbase;
-  int tile_start;  // first tile of this problem in table order (host bookkeeping)
-  int ntx;
+  int ntiles, ntx;  // set by gemm_table
 };
-// mul: every problem of the table has a multiplier (else none does).
-hipError_t launch_gemm_table(const GemmDesc *d, const int *tile_map, int ntiles, char *ws,
-                             char *out, hipStream_t st, bool mul = false, hipEvent_t ev0 = nullptr,
+struct GemmTable {
+  int T = 0, units = 0;
+  bool mul = false;
+};
+bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map);
+hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map, char *ws,
+                             char *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
-// Host: the tile map of a table, (problem, local tile) pairs for every tile
-// of every problem, longest k-range (after the triangular skips) first.
-std::vector<int> gemm_table_map(const std::vector<GemmDesc> &tab);
-// Output tile of the MFMA GEMMs (rows and columns).
-constexpr int kGemmTile = 128;
-// The columns tn.. (a thin edge past whole tiles, whose MFMA tiles would be
-// almost empty) of every row of each table problem, in plain FP64 FMAs:
-// one wavefront per row with coalesced loads along k and a fixed-order sum
-// across the wavefront; problems without triangular structure only; nblk
-// workgroups of 4 wavefronts per problem, interleaved (workgroup b serves
-// problem b % nprob), 4 rows per wavefront iteration (8 on the vector path
-// for k-contiguous, 16-byte aligned rows).
-hipError_t launch_gemm_edge_cols(const GemmDesc *d, int nprob, int64_t tn, int nblk, char *ws,
-                                 char *out, hipStream_t st);
-// Leading extent of a dimension split off a thin edge: x less its last
-// partial tile when that tile holds at most 8 rows or columns, else x.
-inline int64_t gemm_main_extent(int64_t x) {
-  const int64_t r = x % kGemmTile;
-  return x > kGemmTile && r != 0 && r <= 8 ? x - r : x;
-}
-
 }  // namespace fps

@@ -132,10 +132,12 @@ struct fps_plan {
   bool zeig = false;
   std::vector<double> zlam[2], zp, zq;
   std::vector<int> zoff, zJ, zrJmax;
-  int64_t mqc[2] = {0, 0};  // output parity sizes rounded up to even
-  fps::detail::DeviceBuf d_mt;                // multiplier of every mode [npad]^3
+  // Cube layout: parity blocks of cmp[s] (rounded up to 16), cnp per axis; output
+  // parity sizes rounded up to even.
+  int64_t cmp[2] = {0, 0}, cnp = 0, mqc[2] = {0, 0};
+  fps::detail::DeviceBuf d_mt;                // multiplier of every mode [cnp]^3
   fps::detail::DeviceBuf d_gy_in, d_gy_out;   // mode-y GEMM tables (input / output map)
-  int gy_tiles[2] = {0, 0};
+  fps::GemmTable t_gy[2];
   fps::detail::DeviceBuf d_gy_map_in, d_gy_map_out;
   int64_t off_ZR = 0, off_RX = 0;
   // 2-D plans whose chains have more than two chunks: fps_adi_native runs one
@@ -202,6 +204,9 @@ int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *
 int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
 // A stage of products on st, timed like a sweep when the plan's timing is on.
 fps_status run_products(fps_plan *pl, const fps::GemmProb *g, int cnt, hipStream_t st);
+// Lengths along which products run: rounded up to the k-tile (the arrays are
+// padded with zeros beyond).
+inline int64_t k_round(int64_t x) { return (x + 15) / 16 * 16; }
 // Entries per axis of the solve's output.
 inline int64_t out_extent(const fps_plan *pl) {
   return pl->out_basis == FPS_OUT_NATIVE ? pl->n : pl->n + 2;

@@ -31,7 +31,7 @@ namespace {
 // C = A B for one block of zero-padded, contiguous operands.
 hipError_t product(const double *A, int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
                    int64_t M, int64_t N, int64_t K, hipStream_t st) {
-  fps::GemmProb g{A, B, C, M, N, K, lda, 1, ldb, 1, ldc, 1, 0, 0, 0, 0, 0, 0, 0, 0};
+  fps::GemmProb g{A, B, C, M, N, K, lda, 1, ldb, 1, ldc, 1};
   return fps::launch_gemm(&g, 1, st);
 }
 
