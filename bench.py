@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -49,16 +50,37 @@ def sweep_traffic(n):
     return (t["half_step_1"] + t["half_step_2"]) / 2.0
 
 
+def output_zero_share(n, s):
+    """Share of the output map's parity-s block that the products skip: the
+    coefficients k of mode x that decay like J_k(x) below 2e-19, by groups of 64."""
+    m, mo = (n - s + 1) // 2, (n + 3 - s) // 2
+    cut = 0
+    for b0 in range(0, mo, 64):
+        k, lo = float(2 * b0 + s), 0.0
+        hi = k
+        for _ in range(60 if k > 0 else 0):
+            x = 0.5 * (lo + hi)
+            t = x / k
+            if k * (math.acosh(1.0 / t) - math.sqrt(1.0 - t * t)) >= 43.0:
+                lo = x
+            else:
+                hi = x
+        a = min(m, max(0, math.floor(lo / math.pi - 0.5 * (s + 1))))
+        cut += (a // 32 * 32) * min(64, mo - b0)
+    return cut / (m * mo)
+
+
 def product_flops(n):
     """Operations of the four product launches of one Chebyshev-output square
     solve, per launch: the parity blocks' dense products (m modes and mo
-    output coefficients per parity)."""
+    output coefficients per parity), less the skipped zeros of the output map."""
     m = ((n + 1) // 2, n // 2)
     mo = ((n + 3) // 2, (n + 2) // 2)
+    z = [1.0 - output_zero_share(n, s) for s in (0, 1)]
     st = [(s, t) for s in (0, 1) for t in (0, 1)]
     return [sum(2.0 * m[s] * m[t] * m[t] for s, t in st), sum(2.0 * m[s] * m[s] * m[t] for s, t in st),
-            sum(2.0 * m[s] * m[t] * mo[t] for s, t in st),
-            sum(2.0 * m[s] * mo[s] * mo[t] for s, t in st)]
+            sum(2.0 * m[s] * m[t] * mo[t] * z[t] for s, t in st),
+            sum(2.0 * m[s] * mo[s] * mo[t] * z[s] for s, t in st)]
 
 
 def product_roofline(n, times_ms):

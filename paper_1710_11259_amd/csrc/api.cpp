@@ -288,6 +288,15 @@ fps::BcLiftConst bc_lift_const() {
   return k;
 }
 
+// The k-range of a product with Wo (or its transpose) on side `side`.
+void limit_k(fps::GemmProb &g, int side, const std::vector<int> &host, const DeviceBuf &dev,
+             int high) {
+  g.kside = side;
+  g.khigh = high;
+  g.klim = (const int *)dev.p;
+  g.klim_host = host.data();
+}
+
 // U_st = Wo_s Y^_st Wo_t^T into the strided view of U.
 int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::GemmProb *g2) {
   const fps::Layout &L = pl->L;
@@ -309,6 +318,8 @@ int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::G
                               Tst, ms, mo[t], mt, npad, 1, mot, 1, mot, 1};
       g2[cnt] = fps::GemmProb{(const double *)pl->d_Wo[s].p, Tst, U + s * N + t, mo[s], mo[t],
                               ms, L.mp[s], 1, mot, 1, 2 * N, 2};
+      limit_k(g1[cnt], 2, pl->klo[t], pl->d_klo[t], 0);
+      limit_k(g2[cnt], 1, pl->klo[s], pl->d_klo[s], 0);
       ++cnt;
     }
   return cnt;
@@ -806,6 +817,8 @@ int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *
       g2[cnt] = fps::GemmProb{(const double *)pl->d_WoT[s2].p, Tst, G + rs * npad + rt, ms, mt, mos,
                               mop[s2], 1, mt, 1, npad, 1, 0, 0, nullptr, nullptr, mr + 2 * rs,
                               mc + 2 * rt, nullptr, nullptr};
+      limit_k(g1[cnt], 2, pl->khi[t], pl->d_khi[t], 1);
+      limit_k(g2[cnt], 1, pl->khi[s2], pl->d_khi[s2], 1);
       ++cnt;
     }
   return cnt;

@@ -382,6 +382,8 @@ hipError_t launch_nested_factors(const double *lam, const double *q, const int *
 hipError_t launch_nested_multiplier(const double *lam, const double *p, const double *q,
                                     const double *r, int J, double *mt, int64_t npad,
                                     hipStream_t st);
+// W[i][j] = 0 for j < klo[i / 64] (rows x ld).
+hipError_t launch_zero_below(double *W, const int *klo, int64_t rows, int64_t ld, hipStream_t st);
 // H = 1.5 I - 0.5 H (n x n, contiguous).
 hipError_t launch_polar_factor(double *H, int64_t n, hipStream_t st);
 // out = in^T, rows x cols multiples of 64.

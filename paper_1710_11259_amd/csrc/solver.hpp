@@ -97,6 +97,10 @@ struct fps_plan {
   // d_mc: the multiplier's row and column factors, [npad][2].
   fps::detail::DeviceBuf d_Wi[2], d_WiT[2], d_Wo[2], d_WoT[2];
   fps::detail::DeviceBuf d_mr, d_mc;
+  // Where Wo is zero (spectral.cpp): row group g of 64 output coefficients has
+  // no entries below mode klo[g], and mode group h none from row khi[h] on.
+  std::vector<int> klo[2], khi[2];
+  fps::detail::DeviceBuf d_klo[2], d_khi[2];
   std::vector<double> lam;
   // Lift map V^T S^-1 C~(T_k'') by parity (mp x mop) and V^T of the lift's
   // linear factors ([npad][2]), only with FPS_PLAN_DIRICHLET.

@@ -108,6 +108,11 @@ __global__ void k_polar_factor(double *__restrict__ H, int64_t n) {
   H[i * n + j] = (i == j ? 1.5 : 0.0) - 0.5 * H[i * n + j];
 }
 
+__global__ void k_zero_below(double *__restrict__ W, const int *__restrict__ klo, int64_t ld) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
+  if (j < ld && j < klo[i / kGemmGroup]) W[i * ld + j] = 0.0;
+}
+
 // out[j][i] = in[i][j] through a 64 x 64 LDS tile (both sides in 512-byte
 // runs); rows and cols multiples of 64.
 __global__ __launch_bounds__(256) void k_transpose(const double *__restrict__ in, int64_t ldi,
@@ -237,6 +242,12 @@ hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(k_tridiag_vectors, dim3((unsigned)((m + 63) / 64)), dim3(64), 0, st, d, e,
                      (int)m, lam, Dp, Dm, V, ld);
+  return hipGetLastError();
+}
+
+hipError_t launch_zero_below(double *W, const int *klo, int64_t rows, int64_t ld, hipStream_t st) {
+  hipLaunchKernelGGL(k_zero_below, dim3((unsigned)((ld + 255) / 256), (unsigned)rows), dim3(256), 0,
+                     st, W, klo, ld);
   return hipGetLastError();
 }
 

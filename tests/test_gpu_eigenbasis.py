@@ -62,6 +62,22 @@ def test_adjoint_of_a_loose_solve():
         assert abs(a - b) <= 1e-13 * scale
 
 
+# Sizes at which the output map's zeros (modes below a row's limit) are skipped,
+# by both tiles, with edge rows (n = 1025: 513 and 513 coefficients) and without;
+# undecayed data, so that every coefficient weighs the same.
+@pytest.mark.parametrize("n,out", [(300, "cheb"), (700, "native"), (1025, "cheb"), (1800, "cheb")])
+def test_skipped_zeros_of_the_output_map(n, out):
+    from oracle import adjoint
+    rng = np.random.default_rng(n)
+    p = fps.plan(n, tol=1e-13, out=out, tight=True)
+    F = rng.standard_normal((n, n))
+    parity.check(_run(p, F), square.poisson_square(F, out=out), 1e-12, f"solve n={n}")
+    if out == "cheb":
+        Ub = rng.standard_normal(p.out_shape())
+        Fb = fps.solve_adjoint(p, torch.from_numpy(Ub).cuda()).cpu().numpy()
+        parity.check(Fb, adjoint.vjp_square(Ub), 1e-12, f"adjoint n={n}")
+
+
 # The cube's multiplier against the iterations written out with dense solves.
 # Their matrices K = -A~^-1 have condition 30 n^4, so the oracle carries
 # 30 n^4 eps (1.4e-11 at n = 8) and the bound is 1e-9; the truncation being
