@@ -464,35 +464,41 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
   if (tab.empty()) return true;
   t.mul = has_mul(tab[0].p);
   t.T = pick_tile((int64_t)tab.size(), [&](int64_t i) -> const GemmProb & { return tab[(size_t)i].p; });
-  // edge units, then every tile of every problem, longest k-range first (workgroups start
-  // in id order, so the short tiles fill the tail); ties keep table order
+  // Problem by problem, the one with the longest tiles first (workgroups start in
+  // id order, so the short tiles fill the tail, and the tiles in flight share
+  // their problem's operands in the caches: ordered by k-range across the 64
+  // blocks of 16 solves at n = 2048, every column of tiles read them anew);
+  // within a problem its edge units, then its tiles, longest k-range first.
   struct Unit {
     int64_t work;
-    int prob, local;
+    int local;
   };
-  std::vector<Unit> units;
+  std::vector<std::vector<Unit>> units(tab.size());
+  std::vector<int> by((size_t)tab.size());
   for (size_t k = 0; k < tab.size(); ++k) {
     GemmDesc &e = tab[k];
+    by[k] = (int)k;
     if (!gemm_operands_ok(e.p) || has_mul(e.p) != t.mul) return false;
     const int64_t ntx = (main_extent(e.p.N) + t.T - 1) / t.T, nty = (main_extent(e.p.M) + t.T - 1) / t.T;
     e.ntx = (int)ntx;
     e.ntiles = (int)(ntx * nty);
+    std::vector<Unit> &u = units[k];
     for (int l = 0; l < e.ntiles; ++l) {
       int64_t klo, khi;
       tile_krange(e.p, e.p.klim_host, l / ntx * t.T, l % ntx * t.T, t.T, &klo, &khi);
-      units.push_back(Unit{khi - klo, (int)k, l});
+      u.push_back(Unit{khi - klo, l});
     }
-    for (int u = 0; u < edge_units(e.p); ++u)
-      units.push_back(Unit{(int64_t)1 << 40, (int)k, e.ntiles + u});
+    std::stable_sort(u.begin(), u.end(), [](const Unit &a, const Unit &b) { return a.work > b.work; });
+    for (int i = 0; i < edge_units(e.p); ++i) u.insert(u.begin(), Unit{u.back().work, e.ntiles + i});
+    t.units += (int)u.size();
   }
-  std::stable_sort(units.begin(), units.end(),
-                   [](const Unit &a, const Unit &b) { return a.work > b.work; });
-  t.units = (int)units.size();
-  map.reserve(2 * units.size());
-  for (const Unit &u : units) {
-    map.push_back(u.prob);
-    map.push_back(u.local);
-  }
+  std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return tab[a].p.K > tab[b].p.K; });
+  map.reserve(2 * (size_t)t.units);
+  for (int k : by)
+    for (const Unit &u : units[(size_t)k]) {
+      map.push_back(k);
+      map.push_back(u.local);
+    }
   return true;
 }
 
