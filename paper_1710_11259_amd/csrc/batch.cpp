@@ -37,6 +37,10 @@ struct fps_batch {
   // batches) the adjoint's input map g1, g2 and output map g1, g2
   DeviceBuf d_gd[8], d_gmap[8];
   fps::GemmTable gt[8];
+  // the problems small enough for chains (n <= 128; forward 0, adjoint 1): one
+  // launch each; the products and permutations below hold the others
+  DeviceBuf d_chain[2];
+  int nchain[2] = {0, 0}, chain_nb[2] = {2, 2};
   // the permutations of F (0) and of the adjoint's cotangent (1) as one
   // launch each (elem_ok; else, for very large batches, one per problem)
   bool elem_ok = false;
@@ -53,11 +57,21 @@ namespace {
 
 bool valid_batch(const fps_batch *b) { return b != nullptr && b->magic == kBatchMagic; }
 
+// Whether the plan's solves run as chains.
+bool chained(const fps_plan *pl) { return pl->L.n <= kChainMax; }
+
+fps_status run_chains(const fps_batch *bt, int t, const double *in, double *out, hipStream_t st) {
+  FPS_HIP(fps::launch_chain_table((const fps::ChainDesc *)bt->d_chain[t].p, bt->nchain[t],
+                                  bt->chain_nb[t], 1, in, nullptr, out, st));
+  return FPS_OK;
+}
+
 // GEMM tables of the coefficient maps: the single-problem builders run on
 // synthetic base pointers (the problem's workspace offset, its U offset in
 // bytes), so every workspace or output operand comes out as an offset.
 fps_status build_gemm_tables(fps_batch *bt) {
   std::vector<fps::GemmDesc> tab[8];
+  std::vector<fps::ChainDesc> chain[2];
   const bool refined = bt->prec == FPS_FP32_REFINED;
   for (int b = 0; b < bt->count; ++b) {
     const fps_plan *pl = bt->plan_of(b);
@@ -65,6 +79,24 @@ fps_status build_gemm_tables(fps_batch *bt) {
     fps::GemmProb g[8][4];
     double *Usyn = (double *)(intptr_t)(bt->u_off[b] * (int64_t)sizeof(double));
     double *Fsyn = (double *)(intptr_t)(bt->f_off[b] * (int64_t)sizeof(double));
+    fps::ChainDesc cd[4];
+    int nb = 0;
+    if (const int c = solve_chain(pl, Fsyn, Usyn, nullptr, nullptr, cd, &nb)) {
+      for (int i = 0; i < c; ++i) {
+        cd[i].ibase = 2;
+        cd[i].obase = 3;
+        chain[0].push_back(cd[i]);
+      }
+      bt->chain_nb[0] = std::max(bt->chain_nb[0], nb);
+      const int ca = refined ? 0 : adjoint_chain(pl, Usyn, Fsyn, cd, &nb);
+      for (int i = 0; i < ca; ++i) {
+        cd[i].ibase = 2;
+        cd[i].obase = 3;
+        chain[1].push_back(cd[i]);
+        bt->chain_nb[1] = std::max(bt->chain_nb[1], nb);
+      }
+      continue;
+    }
     const int c_in = rhs_gemms(pl, wsyn, g[0], g[1]);
     const int c_out = out_gemms(pl, Usyn, wsyn, g[2], g[3]);
     const int c_ain = refined ? 0 : adj_in_gemms(pl, wsyn, g[4], g[5]);
@@ -79,6 +111,13 @@ fps_status build_gemm_tables(fps_batch *bt) {
         tab[t].push_back(fps::GemmDesc{g[t][i], ids[t][0], ids[t][1], ids[t][2]});
       }
     }
+  }
+  for (int t = 0; t < 2; ++t) {
+    for (const fps::ChainDesc &e : chain[t])
+      if (!fps::chain_ok(e, bt->chain_nb[t], 1)) return fail(FPS_E_STATE, "internal: batched chain");
+    const fps_status s = upload(bt->d_chain[t], chain[t]);
+    if (s != FPS_OK) return s;
+    bt->nchain[t] = (int)chain[t].size();
   }
   for (int t = 0; t < 8; ++t) {
     if (tab[t].empty()) continue;
@@ -105,6 +144,7 @@ fps_status build_elem_tables(fps_batch *bt) {
     const fps::Layout &L = pl->L;
     const bool native = bt->out_basis == FPS_OUT_NATIVE;
     const int64_t *mop = native ? L.mp : pl->mop;
+    if (chained(pl)) continue;
     for (int t = 0; t < 2; ++t) {
       fps::ElemDesc e{};
       e.n = t ? out_extent(pl) : L.n;
@@ -118,7 +158,7 @@ fps_status build_elem_tables(fps_batch *bt) {
       const int64_t nwg = (int64_t)e.nbx * e.npad;
       if (!fps::elem_launch_fits((int64_t)map[t].size() + nwg)) return FPS_OK;
       e.wg_start = (int)map[t].size();
-      map[t].insert(map[t].end(), (size_t)nwg, k);
+      map[t].insert(map[t].end(), (size_t)nwg, (int)ed[t].size());
       ed[t].push_back(e);
     }
   }
@@ -142,6 +182,7 @@ fps_status permute_all(const fps_batch *bt, int t, const double *in, char *w, hi
   }
   for (int b = 0; b < bt->count; ++b) {
     const fps_plan *pl = bt->plan_of(b);
+    if (chained(pl)) continue;
     const fps::Layout &L = pl->L;
     const int64_t *mop = bt->out_basis == FPS_OUT_NATIVE ? L.mp : pl->mop;
     char *wb = w + bt->ws_off[b];
@@ -254,6 +295,7 @@ fps_status fps_batch_solve(fps_batch *bt, const double *F, double *U, void *ws, 
   fps_status s;
   if ((s = permute_all(bt, 0, F, w, st)) != FPS_OK) return s;
   if (bt->has_n1) FPS_HIP(fps::launch_fill(U, bt->out_entries, 0.0, st));
+  if ((s = run_chains(bt, 0, F, U, st)) != FPS_OK) return s;
   for (int t = 0; t < 4; ++t)
     FPS_HIP(fps::launch_gemm_table(bt->gt[t], (const fps::GemmDesc *)bt->d_gd[t].p,
                                    (const int *)bt->d_gmap[t].p, w, (char *)U, st));
@@ -271,6 +313,7 @@ fps_status fps_batch_solve_adjoint(fps_batch *bt, const double *Ubar, double *Fb
   char *w = (char *)ws;
   fps_status s;
   if ((s = permute_all(bt, 1, Ubar, w, st)) != FPS_OK) return s;
+  if ((s = run_chains(bt, 1, Ubar, Fbar, st)) != FPS_OK) return s;
   for (int t = 4; t < 8; ++t)
     FPS_HIP(fps::launch_gemm_table(bt->gt[t], (const fps::GemmDesc *)bt->d_gd[t].p,
                                    (const int *)bt->d_gmap[t].p, w, (char *)Fbar, st));

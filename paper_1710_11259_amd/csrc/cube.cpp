@@ -82,11 +82,9 @@ fps_status launch_probs(fps_plan *pl, const std::vector<fps::GemmProb> &probs, h
 // One table launch, timed like run_products.
 fps_status run_table(fps_plan *pl, const fps::GemmTable &g, const DeviceBuf &d, const DeviceBuf &map,
                      char *w, char *out, hipStream_t st) {
-  const bool t = pl->ev_used * 2 + 1 < (int64_t)pl->ev.size();
-  FPS_HIP(fps::launch_gemm_table(g, (const fps::GemmDesc *)d.p, (const int *)map.p, w, out, st,
-                                 t ? pl->ev[2 * pl->ev_used] : nullptr,
-                                 t ? pl->ev[2 * pl->ev_used + 1] : nullptr));
-  if (t) ++pl->ev_used;
+  hipEvent_t e0 = next_event(pl, 0), e1 = next_event(pl, 1);
+  FPS_HIP(fps::launch_gemm_table(g, (const fps::GemmDesc *)d.p, (const int *)map.p, w, out, st, e0, e1));
+  if (e0) ++pl->ev_used;
   return FPS_OK;
 }
 
@@ -207,6 +205,95 @@ fps_status zeig_shifts(fps_plan *pl, double ea, double eb) {
   return FPS_OK;
 }
 
+// Tables of the chains that replace the per-axis products of a cube with blocks of
+// at most 128 entries (n <= 256), three launches: every z-slice of F to its x and
+// y maps in G, every strip of columns of G along z through the input map, the
+// multiplier and the output map to O0, every z-slice of O0 to its x and y
+// output maps in U.
+fps_status upload_chains(fps_plan *pl) {
+  const fps::Layout &L = pl->L;
+  const bool native = pl->out_basis == FPS_OUT_NATIVE;
+  const int64_t n = L.n, N = out_extent(pl), npad = pl->cnp, *mp = pl->cmp, plane = npad * npad;
+  const int64_t *mo = native ? L.m : L.mo, *mop = native ? L.mp : pl->mop;
+  const int nb = pl->cnb;
+  auto at = [](int64_t off, int64_t elem) { return (double *)(intptr_t)(off + 8 * elem); };
+  auto map = [&](fps::ChainDesc &e, int i, bool out, int s) {
+    e.m[i] = (const double *)(out ? pl->d_WoT[s].p : pl->d_WiT[s].p);
+    e.ld[i] = (int)(out ? mop[s] : L.mp[s]);
+    e.k[i] = (int)mp[s];
+    e.n[i] = (int)(out ? mo[s] : mp[s]);
+  };
+  std::vector<fps::ChainDesc> d[3];
+  // slices, in and out: natural position zn is row zn / 2 of parity zn % 2
+  for (int io = 0; io < 2; ++io)
+    for (int64_t zn = 0; zn < (io ? N : n); ++zn) {
+      const int sz = zn & 1;
+      if (L.m[sz] == 0) continue;
+      for (int sy = 0; sy < 2; ++sy)
+        for (int sx = 0; sx < 2; ++sx) {
+          if (L.m[sy] == 0 || L.m[sx] == 0) continue;
+          fps::ChainDesc e{};
+          map(e, 0, io, sx);
+          map(e, 1, io, sy);
+          e.in_r = (int)L.m[sy];
+          e.in_c = (int)L.m[sx];
+          const int64_t slice = sz * (io ? pl->mqc[0] : mp[0]) + zn / 2;
+          const int64_t blk = (slice * npad + sy * mp[0]) * npad + sx * mp[0];
+          if (io) {
+            e.in = at(pl->off_O0, blk);
+            e.ibase = 1;
+            e.in_rs = npad;
+            e.in_cs = 1;
+            e.out = at(0, (zn * N + sy) * N + sx);
+            e.obase = 3;
+            e.out_rs = 2 * N;
+            e.out_cs = 2;
+            e.out_r = (int)mo[sy];
+            e.out_c = (int)mo[sx];
+          } else {
+            e.in = at(0, (zn * n + sy) * n + sx);
+            e.ibase = 2;
+            e.in_rs = 2 * n;
+            e.in_cs = 2;
+            e.out = at(pl->off_G, blk);
+            e.obase = 1;
+            e.out_rs = npad;
+            e.out_cs = 1;
+            e.out_r = (int)mp[sy];
+            e.out_c = (int)mp[sx];
+          }
+          d[2 * io].push_back(e);
+        }
+    }
+  // strips along z
+  const int64_t S = 32 * nb;
+  for (int sz = 0; sz < 2; ++sz)
+    for (int64_t c = 0; c < plane && L.m[sz] > 0; c += S) {
+      fps::ChainDesc e{};
+      map(e, 1, false, sz);
+      map(e, 3, true, sz);
+      e.in = at(pl->off_G, sz * mp[0] * plane + c);
+      e.out = at(pl->off_O0, sz * pl->mqc[0] * plane + c);
+      e.ibase = e.obase = 1;
+      e.in_rs = e.out_rs = e.mt_rs = plane;
+      e.in_cs = e.out_cs = 1;
+      e.in_r = (int)L.m[sz];
+      e.out_r = (int)mo[sz];
+      e.in_c = e.out_c = e.mcols = (int)std::min(S, plane - c);
+      e.mt = (const double *)pl->d_mt.p + sz * mp[0] * plane + c;
+      d[1].push_back(e);
+    }
+  for (int t = 0; t < 3; ++t) {
+    for (const fps::ChainDesc &e : d[t])
+      if (!fps::chain_ok(e, nb, t == 1 ? 2 : 0)) return fail(FPS_E_STATE, "internal: cube chain");
+    if (t != 1) fps::chain_order(d[t]);
+    const fps_status s = upload(pl->d_cchain[t], d[t]);
+    if (s != FPS_OK) return s;
+    pl->cchain_count[t] = (int)d[t].size();
+  }
+  return FPS_OK;
+}
+
 }  // namespace
 
 fps_status cube_plan_build(fps_plan *pl) {
@@ -294,6 +381,8 @@ fps_status cube_plan_upload(fps_plan *pl) {
                                           (const double *)ey.p, J1, (double *)pl->d_mt.p, npad, st));
   }
   FPS_HIP(hipStreamSynchronize(st));
+  pl->cnb = fps::chain_size(mp[0]);
+  if (pl->cnb > 0) return upload_chains(pl);
   // per-slice products: y on the way in, y (the last, into U) on the way out
   const Dims full{{npad, npad, npad}, {mp[0], mp[0], mp[0]}};
   const double *Wi[2] = {(const double *)pl->d_Wi[0].p, (const double *)pl->d_Wi[1].p};
@@ -343,6 +432,17 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
   const int64_t ldo[2] = {mop[0], mop[1]};
   const Dims full{{npad, npad, npad}, {mp0, mp0, mp0}};
   fps_status s;
+  if (pl->cnb > 0) {
+    const int64_t N = out_extent(pl);
+    if (L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N * N, 0.0, st));  // no odd modes: n = 1
+    for (int t = 0; t < 3; ++t) {
+      hipEvent_t e0 = next_event(pl, 0), e1 = next_event(pl, 1);
+      FPS_HIP(fps::launch_chain_table((const fps::ChainDesc *)pl->d_cchain[t].p, pl->cchain_count[t],
+                                      pl->cnb, t == 1 ? 2 : 0, F, w, U, st, e0, e1));
+      if (e0) ++pl->ev_used;
+    }
+    return FPS_OK;
+  }
   // in: x, y, z (the multiplier in the last product's epilogue)
   FPS_HIP(fps::launch_permute3_in(F, G, L.n, npad, mp0, st));
   std::vector<fps::GemmProb> px, pz, qz, qx;
@@ -357,8 +457,6 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
   const int64_t mq = pl->mqc[0] + pl->mqc[1], mb0 = pl->mqc[0];
   const Dims d1{{mq, npad, npad}, {mb0, mp0, mp0}};
   const Dims d2{{mq, npad, mq}, {mb0, mp0, mb0}};
-  const int64_t N = out_extent(pl);
-  if (L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N * N, 0.0, st));  // no odd modes: n = 1
   mode_probs(Y, full, O0, d1, 0, Wo, ldi, WoT, ldo, No, K, qz);
   if ((s = launch_probs(pl, qz, st)) != FPS_OK) return s;
   mode_probs(O0, d1, RX, d2, 2, Wo, ldi, WoT, ldo, No, K, qx);

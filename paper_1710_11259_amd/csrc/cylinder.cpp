@@ -31,6 +31,7 @@ struct CylPlan {
   int64_t n = 0, nt = 0, m = 0, mp = 0, npad = 0;
   int64_t mo = 0, mop = 0, mobar = 0;  // z output per parity (n/2 + 1), padded
   int64_t ro = 0;                      // r output rows per parity ((n + 4) / 2)
+  int64_t ldi = 0, ldo = 0;            // row strides of the z maps
   int64_t nk = 0;                      // distinct |k|: 0 .. nt/2
   std::vector<int> slot_idx, slot_group, slot_kabs;  // internal slot -> mode
   fps::detail::DeviceBuf d_slot_idx;
@@ -39,9 +40,12 @@ struct CylPlan {
   fps::detail::DeviceBuf d_fac;               // [nk][8][mp][npad]
   fps::detail::DeviceBuf d_win[2], d_wout[2];  // z maps (mp x mp, mp x mop)
   fps::detail::DeviceBuf d_rin[4], d_rout[4];  // r maps per group (mp x mp, ro x mp)
+  // n <= 256: block size of the chains (0: products), their r maps per group in
+  // transposed form, and their tables (modes in, modes out)
+  int nb = 0, nchain[2] = {0, 0};
+  fps::detail::DeviceBuf d_rinT[4], d_routT[4], d_chain[2];
   fps::detail::DeviceBuf d_tin, d_tin_map, d_tout, d_tout_map;
   fps::GemmTable t_in, t_out;
-  int n_tout = 0;
   int64_t off_X0 = 0, off_X1 = 0, ws_bytes = 0;
   int64_t x0_elems = 0;
 };
@@ -218,6 +222,70 @@ bool band_lu(const std::vector<ld> &Pb, const std::vector<ld> &Qb, ld lambda, in
   return true;
 }
 
+// Tables of the chains of a cylinder with n <= 256: per mode, part and z parity the
+// F rows of the mode's parity through the z and r maps into X0, and the solved
+// block of X1 through the output maps into U (whose rows of the other parity
+// are zero).
+fps_status upload_chains(CylPlan *c) {
+  const int64_t n = c->n, mp = c->mp, npad = c->npad;
+  std::vector<fps::ChainDesc> in, out;
+  auto map = [](fps::ChainDesc &e, int i, const fps::detail::DeviceBuf &m, int64_t ld, int64_t k,
+                int64_t len) {
+    e.m[i] = (const double *)m.p;
+    e.ld[i] = (int)ld;
+    e.k[i] = (int)k;
+    e.n[i] = (int)len;
+  };
+  for (size_t sl = 0; sl < c->slot_idx.size(); ++sl) {
+    const int g = c->slot_group[sl];
+    int rp, wp, mpow;
+    group_par(g, &rp, &wp, &mpow);
+    const int outp = (mpow + wp) & 1;
+    for (int part = 0; part < 2; ++part)
+      for (int s = 0; s < 2; ++s) {
+        const int64_t blk = ((int64_t)sl * 2 + part) * npad, mode = (int64_t)c->slot_idx[sl] * 2 + part;
+        fps::ChainDesc a{}, b{};
+        map(a, 0, c->d_win[s], c->ldi, mp, mp);
+        map(a, 1, c->d_rinT[g], c->ldi, mp, mp);
+        a.in = (const double *)(intptr_t)(((mode * n + rp) * n + s) * 8);
+        a.ibase = 2;
+        a.in_rs = 2 * n;
+        a.in_cs = 2;
+        a.out = (double *)(intptr_t)(c->off_X0 + ((blk + rp * mp) * npad + s * mp) * 8);
+        a.obase = 1;
+        a.out_rs = npad;
+        a.out_cs = 1;
+        a.out_r = a.out_c = (int)mp;
+        map(b, 0, c->d_wout[s], c->ldo, mp, c->mo);
+        map(b, 1, c->d_routT[g], c->ldo, mp, c->ro);
+        b.in = (const double *)(intptr_t)(c->off_X1 + ((blk + wp * mp) * npad + s * mp) * 8);
+        b.ibase = 1;
+        b.in_rs = npad;
+        b.in_cs = 1;
+        b.out = (double *)(intptr_t)((mode * (n + 4) * (n + 2) + outp * (n + 2) + s) * 8);
+        b.obase = 3;
+        b.out_rs = 2 * (n + 2);
+        b.out_cs = 2;
+        b.out_r = (int)c->ro;
+        b.out_c = (int)c->mo;
+        b.zoff = (int)(outp ? -(n + 2) : n + 2);
+        a.in_r = a.in_c = b.in_r = b.in_c = (int)c->m;
+        in.push_back(a);
+        out.push_back(b);
+      }
+  }
+  std::vector<fps::ChainDesc> *d[2] = {&in, &out};
+  for (int t = 0; t < 2; ++t) {
+    for (const fps::ChainDesc &e : *d[t])
+      if (!fps::chain_ok(e, c->nb, 0)) return fail(FPS_E_STATE, "internal: cylinder chain");
+    fps::chain_order(*d[t]);
+    const fps_status s = upload(c->d_chain[t], *d[t]);
+    if (s != FPS_OK) return s;
+    c->nchain[t] = (int)d[t]->size();
+  }
+  return FPS_OK;
+}
+
 }  // namespace
 
 fps_status cyl_plan_build(fps_plan *pl, int64_t nt) {
@@ -238,6 +306,8 @@ fps_status cyl_plan_build(fps_plan *pl, int64_t nt) {
   c->mop = k_round(c->mo);
   c->mobar = 2 * c->mop;
   c->ro = (n + 4) / 2;
+  c->ldi = (c->mp + 31) / 32 * 32;
+  c->ldo = (c->ro + 31) / 32 * 32;
   c->nk = nt / 2 + 1;
   // slots sorted by group
   for (int g = 0; g < 4; ++g)
@@ -275,20 +345,23 @@ fps_status cyl_plan_upload(fps_plan *pl) {
     lam[s] = d;
   }
   fps_status st;
-  // z maps: W_in = -Rs^T V (mp x mp, B operand), W_out = V^T P^T (mp x mop)
+  c->nb = fps::chain_size(mp);
+  // z maps: W_in = -Rs^T V (B operand), W_out = V^T P^T, rows padded to the tiles
+  // of the chains that read them
+  const int64_t ldi = c->ldi, ldo = c->ldo;
   for (int s = 0; s < 2; ++s) {
-    std::vector<double> win((size_t)(mp * mp), 0.0), wout((size_t)(mp * c->mop), 0.0);
+    std::vector<double> win((size_t)(mp * ldi), 0.0), wout((size_t)(mp * ldo), 0.0);
     for (int64_t b = 0; b < m; ++b)      // Chebyshev z index (row of W_in)
       for (int64_t j = 0; j < m; ++j) {  // eigen index
         long double acc = 0.0L;
         for (int64_t a = 0; a < m; ++a) acc += (long double)Rs[s][(size_t)(a * m + b)] * V[s][(size_t)(a * m + j)];
-        win[(size_t)(b * mp + j)] = (double)(-acc);
+        win[(size_t)(b * ldi + j)] = (double)(-acc);
       }
     for (int64_t j = 0; j < m; ++j)
       for (int64_t o = 0; o < c->mo; ++o) {
         long double acc = 0.0L;
         for (int64_t a = 0; a < m; ++a) acc += V[s][(size_t)(a * m + j)] * (long double)P[s][(size_t)(o * m + a)];
-        wout[(size_t)(j * c->mop + o)] = (double)acc;
+        wout[(size_t)(j * ldo + o)] = (double)acc;
       }
     if ((st = upload(c->d_win[s], win)) != FPS_OK || (st = upload(c->d_wout[s], wout)) != FPS_OK) return st;
   }
@@ -336,8 +409,18 @@ fps_status cyl_plan_upload(fps_plan *pl) {
       }
       for (int64_t o = 0; o < c->ro; ++o) rout[(size_t)(o * mp + b)] = (double)t[(size_t)(2 * o + outp)];
     }
-    if ((st = upload(c->d_rin[g], rin)) != FPS_OK || (st = upload(c->d_rout[g], rout)) != FPS_OK)
+    if (c->nb > 0) {
+      std::vector<double> rinT((size_t)(mp * ldi), 0.0), routT((size_t)(mp * ldo), 0.0);
+      for (int64_t b = 0; b < m; ++b) {
+        for (int64_t a = 0; a < m; ++a) rinT[(size_t)(b * ldi + a)] = rin[(size_t)(a * mp + b)];
+        for (int64_t o = 0; o < c->ro; ++o) routT[(size_t)(b * ldo + o)] = rout[(size_t)(o * mp + b)];
+      }
+      if ((st = upload(c->d_rinT[g], rinT)) != FPS_OK || (st = upload(c->d_routT[g], routT)) != FPS_OK)
+        return st;
+    } else if ((st = upload(c->d_rin[g], rin)) != FPS_OK ||
+               (st = upload(c->d_rout[g], rout)) != FPS_OK) {
       return st;
+    }
   }
   // banded LU factors per (|k|, z column)
   {
@@ -385,6 +468,7 @@ fps_status cyl_plan_upload(fps_plan *pl) {
   c->ngroups = (int)groups.size();
   if ((st = upload(c->d_slot_idx, c->slot_idx)) != FPS_OK || (st = upload(c->d_groups, groups)) != FPS_OK)
     return st;
+  if (c->nb > 0) return upload_chains(c);
   // r-map GEMM tables (workspace / output offsets)
   const int64_t nt = c->nt, N2 = (n + 4) * (n + 2);
   std::vector<fps::GemmDesc> tin, tout;
@@ -439,6 +523,20 @@ fps_status cyl_solve(fps_plan *pl, const double *F, double *U, char *w, hipStrea
   const int64_t n = c->n, nt = c->nt, mp = c->mp, npad = c->npad;
   double *X0 = (double *)(w + c->off_X0), *X1 = (double *)(w + c->off_X1);
   const int64_t rows = nt * 2 * npad;
+  auto chain = [&](int t) {
+    return fps::launch_chain_table((const fps::ChainDesc *)c->d_chain[t].p, c->nchain[t], c->nb, 0, F,
+                                   w, U, st);
+  };
+  auto solve = [&] {
+    return fps::launch_cyl_solve(X0, X1, (const double *)c->d_fac.p,
+                                 (const fps::CylSolveGroup *)c->d_groups.p, c->ngroups, c->m, mp, st);
+  };
+  if (c->nb > 0) {
+    FPS_HIP(chain(0));
+    FPS_HIP(solve());
+    FPS_HIP(chain(1));
+    return FPS_OK;
+  }
   // 1. F -> X0 [slot][part][r][z], parity-blocked, zero padded
   FPS_HIP(fps::launch_cyl_permute_in(F, X0, (const int *)c->d_slot_idx.p, n, nt, mp, st));
   // 2. z map: X1 = X0 W_in (per z parity block)
@@ -446,21 +544,20 @@ fps_status cyl_solve(fps_plan *pl, const double *F, double *U, char *w, hipStrea
     fps::GemmProb q[2];
     for (int s = 0; s < 2; ++s)
       q[s] = fps::GemmProb{X0 + s * mp, (const double *)c->d_win[s].p, X1 + s * mp, rows, mp, mp,
-                           npad, 1, mp, 1, npad, 1};
+                           npad, 1, c->ldi, 1, npad, 1};
     FPS_HIP(fps::launch_gemm(q, 2, st));
   }
   // 3. r map: X0[rp block] = R_g X1[rp block]
   FPS_HIP(fps::launch_gemm_table(c->t_in, (const fps::GemmDesc *)c->d_tin.p,
                                  (const int *)c->d_tin_map.p, w, nullptr, st));
   // 4. banded solves: X1[wp block] = yhat
-  FPS_HIP(fps::launch_cyl_solve(X0, X1, (const double *)c->d_fac.p,
-                                (const fps::CylSolveGroup *)c->d_groups.p, c->ngroups, c->m, mp, st));
+  FPS_HIP(solve());
   // 5. z output map: X0 [slot][part][r][zout] = X1 W_out
   {
     fps::GemmProb q[2];
     for (int s = 0; s < 2; ++s)
       q[s] = fps::GemmProb{X1 + s * mp, (const double *)c->d_wout[s].p, X0 + s * c->mop, rows,
-                           c->mo, mp, npad, 1, c->mop, 1, c->mobar, 1};
+                           c->mo, mp, npad, 1, c->ldo, 1, c->mobar, 1};
     FPS_HIP(fps::launch_gemm(q, 2, st));
   }
   // 6. r output map into U (rows of the other parity stay zero)

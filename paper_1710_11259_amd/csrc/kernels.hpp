@@ -419,4 +419,39 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
 hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map, char *ws,
                              char *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
+// Chains of products on one LDS-resident block (chain.hip), blocks of up to S =
+// 32 nb (nb = 2, 3, 4).  The block is in[r * in_rs + c * in_cs] for r < in_r, c <
+// in_c, zero beyond.  Matrix i is m[i][k * ld + output index], k[i] its inner length
+// (a multiple of 16), n[i] its output length (up to S, that of the last ones up to
+// S + 2); ld covers n rounded up to the tiles that read it: 32, or S + 16 past S.
+//   mode 0: X m0, m1^T X.        1: X m0, m1^T X, multiplier, X m2, m3^T X.
+//   mode 2: m1^T X, multiplier, m3^T X (mcols columns, any number of them).
+// The multiplier is that of GemmProb (mode 1: mr, mc, lr, lc; mode 2: mt with row
+// stride mt_rs), applied to rows < n[1], columns < mcols.  The result goes to
+// out[r * out_rs + c * out_cs] for r < out_r, c < out_c (mode 0: and a zero zoff
+// elements from it, if zoff is not 0).  in / out are absolute (base 0) or byte
+// offsets from the workspace (1), the solve's input (2) or output (3).
+struct ChainDesc {
+  const double *in;
+  double *out;
+  const double *m[4];
+  const double *mr, *mc, *lr, *lc, *mt;
+  int64_t in_rs, out_rs, mt_rs;
+  int in_cs, out_cs, in_r, in_c, out_r, out_c, mcols;
+  int ld[4], k[4], n[4];
+  int ibase, obase, zoff;
+};
+// Blocks of up to `len` per side need nb = chain_size(len) (0: too large).
+inline int chain_size(int64_t len) { return len <= 64 ? 2 : len <= 96 ? 3 : len <= 128 ? 4 : 0; }
+bool chain_ok(const ChainDesc &d, int nb, int mode);
+// Table order: consecutive descriptors 2q, 2q + 1 (the two column parities of the
+// same rows, which share cache lines) 8 apart, on one die at the same time.
+void chain_order(std::vector<ChainDesc> &d);
+hipError_t launch_chain_table(const ChainDesc *d, int count, int nb, int mode, const double *in,
+                              char *ws, double *out, hipStream_t st, hipEvent_t ev0 = nullptr,
+                              hipEvent_t ev1 = nullptr);
+// Mode 1 on up to 4 blocks given by value (nb 2 or 3).
+hipError_t launch_chain(const ChainDesc *d, int count, int nb, hipStream_t st,
+                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+
 }  // namespace fps

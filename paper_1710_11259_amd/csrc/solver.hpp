@@ -144,6 +144,11 @@ struct fps_plan {
   fps::GemmTable t_gy[2];
   fps::detail::DeviceBuf d_gy_map_in, d_gy_map_out;
   int64_t off_ZR = 0, off_RX = 0;
+  // Cube plans whose blocks fit one workgroup's LDS (n <= 256): block size of the
+  // chains (0: per-axis products) and their tables (slices in, strips along z,
+  // slices out).
+  int cnb = 0, cchain_count[3] = {0, 0, 0};
+  fps::detail::DeviceBuf d_cchain[3];
   // 2-D plans whose chains have more than two chunks: fps_adi_native runs one
   // row-parity block's sweeps on the plan's own stream zside, the other's on
   // the caller's, joined by the events zfork / zjoin.  zlock is held while one
@@ -208,9 +213,22 @@ int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *
 int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
 // A stage of products on st, timed like a sweep when the plan's timing is on.
 fps_status run_products(fps_plan *pl, const fps::GemmProb *g, int cnt, hipStream_t st);
+// Start / stop events of the next timed launch (null when timing is off or its
+// pairs are used up); the launch then counts one in ev_used.
+inline hipEvent_t next_event(const fps_plan *pl, int i) {
+  return pl->ev_used * 2 + 1 < (int64_t)pl->ev.size() ? pl->ev[2 * pl->ev_used + i] : nullptr;
+}
 // Lengths along which products run: rounded up to the k-tile (the arrays are
 // padded with zeros beyond).
 inline int64_t k_round(int64_t x) { return (x + 15) / 16 * 16; }
+// The blocks of a square or rectangle solve small enough for one launch of
+// chains (n <= kChainMax: its adjoint's blocks, of up to n / 2 + 2 entries, and
+// the four workgroups of a single solve still pay there): up to 4 (returns their count, 0 for larger plans) from F
+// (or the adjoint's cotangent) to U (Fbar); nb the block size.
+constexpr int64_t kChainMax = 128;
+int solve_chain(const fps_plan *pl, const double *F, double *U, const double *lr, const double *lc,
+                fps::ChainDesc *d, int *nb);
+int adjoint_chain(const fps_plan *pl, const double *Ubar, double *Fbar, fps::ChainDesc *d, int *nb);
 // Entries per axis of the solve's output.
 inline int64_t out_extent(const fps_plan *pl) {
   return pl->out_basis == FPS_OUT_NATIVE ? pl->n : pl->n + 2;
