@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "device.hpp"
 #include "kernels.hpp"
 
 namespace fps {
@@ -403,9 +404,15 @@ __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restric
   const int local = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x + 1]);
   const GemmDesc &e = d[k];
   GemmProb g = e.p;
-  g.A = rebase(g.A, e.abase, ws, out);
-  g.B = rebase(g.B, e.bbase, ws, out);
-  g.C = (double *)rebase(g.C, e.cbase, ws, out);
+  g.A = as_global(rebase(g.A, e.abase, ws, out));
+  g.B = as_global(rebase(g.B, e.bbase, ws, out));
+  g.C = as_global((double *)rebase(g.C, e.cbase, ws, out));
+  g.klim = as_global(g.klim);
+  g.mr = as_global(g.mr);
+  g.mc = as_global(g.mc);
+  g.lr = as_global(g.lr);
+  g.lc = as_global(g.lc);
+  g.mt = as_global(g.mt);
   if (!kMul && local >= e.ntiles)
     gemm_edge(g, local - e.ntiles, lds);
   else
