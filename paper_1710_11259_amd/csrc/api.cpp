@@ -358,7 +358,6 @@ int solve_chain(const fps_plan *pl, const double *F, double *U, const double *lr
       e.mc = (const double *)pl->d_mc.p + 2 * t * L.mp[0];
       e.lr = lr ? lr + 4 * s * L.mp[0] : nullptr;
       e.lc = lc ? lc + 4 * t * L.mp[0] : nullptr;
-      e.mcols = kt;
       e.out = U + s * N + t;
       e.out_rs = 2 * N;
       e.out_cs = 2;
@@ -398,7 +397,6 @@ int adjoint_chain(const fps_plan *pl, const double *Ubar, double *Fbar, fps::Cha
       }
       e.mr = (const double *)pl->d_mr.p + 2 * s * L.mp[0];
       e.mc = (const double *)pl->d_mc.p + 2 * t * L.mp[0];
-      e.mcols = kt;
       e.out = Fbar + s * n + t;
       e.out_rs = 2 * n;
       e.out_cs = 2;

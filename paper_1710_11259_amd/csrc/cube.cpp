@@ -210,6 +210,7 @@ fps_status zeig_shifts(fps_plan *pl, double ea, double eb) {
 // y maps in G, every strip of columns of G along z through the input map, the
 // multiplier and the output map to O0, every z-slice of O0 to its x and y
 // output maps in U.
+constexpr int kChainMode[3] = {0, 2, 3};
 fps_status upload_chains(fps_plan *pl) {
   const fps::Layout &L = pl->L;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
@@ -220,16 +221,19 @@ fps_status upload_chains(fps_plan *pl) {
   auto map = [&](fps::ChainDesc &e, int i, bool out, int s) {
     e.m[i] = (const double *)(out ? pl->d_WoT[s].p : pl->d_WiT[s].p);
     e.ld[i] = (int)(out ? mop[s] : L.mp[s]);
-    e.k[i] = (int)mp[s];
+    e.k[i] = (int)((mp[s] + 31) / 32 * 32);
     e.n[i] = (int)(out ? mo[s] : mp[s]);
   };
   std::vector<fps::ChainDesc> d[3];
-  // slices, in and out: natural position zn is row zn / 2 of parity zn % 2
+  // slices, in and out: natural position zn is row zn / 2 of parity zn % 2.  The
+  // units of one slice and row parity read the same rows.
+  int group[2] = {1, 1};
   for (int io = 0; io < 2; ++io)
     for (int64_t zn = 0; zn < (io ? N : n); ++zn) {
       const int sz = zn & 1;
       if (L.m[sz] == 0) continue;
-      for (int sy = 0; sy < 2; ++sy)
+      for (int sy = 0; sy < 2; ++sy) {
+        const size_t first = d[2 * io].size();
         for (int sx = 0; sx < 2; ++sx) {
           if (L.m[sy] == 0 || L.m[sx] == 0) continue;
           fps::ChainDesc e{};
@@ -262,11 +266,14 @@ fps_status upload_chains(fps_plan *pl) {
             e.out_r = (int)mp[sy];
             e.out_c = (int)mp[sx];
           }
-          d[2 * io].push_back(e);
+          for (e.r0 = 0; e.r0 < std::min(e.n[1], 32 * nb); e.r0 += fps::chain_part(nb))
+            d[2 * io].push_back(e);
         }
+        group[io] = std::max(group[io], (int)(d[2 * io].size() - first));
+      }
     }
   // strips along z
-  const int64_t S = 32 * nb;
+  const int64_t S = fps::chain_part(nb);
   for (int sz = 0; sz < 2; ++sz)
     for (int64_t c = 0; c < plane && L.m[sz] > 0; c += S) {
       fps::ChainDesc e{};
@@ -279,14 +286,14 @@ fps_status upload_chains(fps_plan *pl) {
       e.in_cs = e.out_cs = 1;
       e.in_r = (int)L.m[sz];
       e.out_r = (int)mo[sz];
-      e.in_c = e.out_c = e.mcols = (int)std::min(S, plane - c);
+      e.in_c = e.out_c = (int)std::min(S, plane - c);
       e.mt = (const double *)pl->d_mt.p + sz * mp[0] * plane + c;
       d[1].push_back(e);
     }
   for (int t = 0; t < 3; ++t) {
     for (const fps::ChainDesc &e : d[t])
-      if (!fps::chain_ok(e, nb, t == 1 ? 2 : 0)) return fail(FPS_E_STATE, "internal: cube chain");
-    if (t != 1) fps::chain_order(d[t]);
+      if (!fps::chain_ok(e, nb, kChainMode[t])) return fail(FPS_E_STATE, "internal: cube chain");
+    if (t != 1) fps::chain_order(d[t], group[t / 2]);
     const fps_status s = upload(pl->d_cchain[t], d[t]);
     if (s != FPS_OK) return s;
     pl->cchain_count[t] = (int)d[t].size();
@@ -438,7 +445,7 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
     for (int t = 0; t < 3; ++t) {
       hipEvent_t e0 = next_event(pl, 0), e1 = next_event(pl, 1);
       FPS_HIP(fps::launch_chain_table((const fps::ChainDesc *)pl->d_cchain[t].p, pl->cchain_count[t],
-                                      pl->cnb, t == 1 ? 2 : 0, F, w, U, st, e0, e1));
+                                      pl->cnb, kChainMode[t], F, w, U, st, e0, e1));
       if (e0) ++pl->ev_used;
     }
     return FPS_OK;

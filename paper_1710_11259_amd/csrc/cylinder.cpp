@@ -229,6 +229,7 @@ bool band_lu(const std::vector<ld> &Pb, const std::vector<ld> &Qb, ld lambda, in
 fps_status upload_chains(CylPlan *c) {
   const int64_t n = c->n, mp = c->mp, npad = c->npad;
   std::vector<fps::ChainDesc> in, out;
+  const int k = (int)((mp + 31) / 32 * 32);
   auto map = [](fps::ChainDesc &e, int i, const fps::detail::DeviceBuf &m, int64_t ld, int64_t k,
                 int64_t len) {
     e.m[i] = (const double *)m.p;
@@ -245,8 +246,8 @@ fps_status upload_chains(CylPlan *c) {
       for (int s = 0; s < 2; ++s) {
         const int64_t blk = ((int64_t)sl * 2 + part) * npad, mode = (int64_t)c->slot_idx[sl] * 2 + part;
         fps::ChainDesc a{}, b{};
-        map(a, 0, c->d_win[s], c->ldi, mp, mp);
-        map(a, 1, c->d_rinT[g], c->ldi, mp, mp);
+        map(a, 0, c->d_win[s], c->ldi, k, mp);
+        map(a, 1, c->d_rinT[g], c->ldi, k, mp);
         a.in = (const double *)(intptr_t)(((mode * n + rp) * n + s) * 8);
         a.ibase = 2;
         a.in_rs = 2 * n;
@@ -256,8 +257,8 @@ fps_status upload_chains(CylPlan *c) {
         a.out_rs = npad;
         a.out_cs = 1;
         a.out_r = a.out_c = (int)mp;
-        map(b, 0, c->d_wout[s], c->ldo, mp, c->mo);
-        map(b, 1, c->d_routT[g], c->ldo, mp, c->ro);
+        map(b, 0, c->d_wout[s], c->ldo, k, c->mo);
+        map(b, 1, c->d_routT[g], c->ldo, k, c->ro);
         b.in = (const double *)(intptr_t)(c->off_X1 + ((blk + wp * mp) * npad + s * mp) * 8);
         b.ibase = 1;
         b.in_rs = npad;
@@ -270,15 +271,19 @@ fps_status upload_chains(CylPlan *c) {
         b.out_c = (int)c->mo;
         b.zoff = (int)(outp ? -(n + 2) : n + 2);
         a.in_r = a.in_c = b.in_r = b.in_c = (int)c->m;
-        in.push_back(a);
-        out.push_back(b);
+        for (int r = 0; r < std::min(b.n[1], 32 * c->nb); r += fps::chain_part(c->nb)) {
+          a.r0 = b.r0 = r;
+          if (r < a.n[1]) in.push_back(a);
+          out.push_back(b);
+        }
       }
   }
   std::vector<fps::ChainDesc> *d[2] = {&in, &out};
   for (int t = 0; t < 2; ++t) {
     for (const fps::ChainDesc &e : *d[t])
-      if (!fps::chain_ok(e, c->nb, 0)) return fail(FPS_E_STATE, "internal: cylinder chain");
-    fps::chain_order(*d[t]);
+      if (!fps::chain_ok(e, c->nb, 3 * t)) return fail(FPS_E_STATE, "internal: cylinder chain");
+    // the two z parities of a mode and part share F's (or U's) lines
+    fps::chain_order(*d[t], (int)(d[t]->size() / (c->slot_idx.size() * 2)));
     const fps_status s = upload(c->d_chain[t], *d[t]);
     if (s != FPS_OK) return s;
     c->nchain[t] = (int)d[t]->size();
@@ -350,7 +355,7 @@ fps_status cyl_plan_upload(fps_plan *pl) {
   // of the chains that read them
   const int64_t ldi = c->ldi, ldo = c->ldo;
   for (int s = 0; s < 2; ++s) {
-    std::vector<double> win((size_t)(mp * ldi), 0.0), wout((size_t)(mp * ldo), 0.0);
+    std::vector<double> win((size_t)(ldi * ldi), 0.0), wout((size_t)(ldi * ldo), 0.0);
     for (int64_t b = 0; b < m; ++b)      // Chebyshev z index (row of W_in)
       for (int64_t j = 0; j < m; ++j) {  // eigen index
         long double acc = 0.0L;
@@ -410,7 +415,7 @@ fps_status cyl_plan_upload(fps_plan *pl) {
       for (int64_t o = 0; o < c->ro; ++o) rout[(size_t)(o * mp + b)] = (double)t[(size_t)(2 * o + outp)];
     }
     if (c->nb > 0) {
-      std::vector<double> rinT((size_t)(mp * ldi), 0.0), routT((size_t)(mp * ldo), 0.0);
+      std::vector<double> rinT((size_t)(ldi * ldi), 0.0), routT((size_t)(ldi * ldo), 0.0);
       for (int64_t b = 0; b < m; ++b) {
         for (int64_t a = 0; a < m; ++a) rinT[(size_t)(b * ldi + a)] = rin[(size_t)(a * mp + b)];
         for (int64_t o = 0; o < c->ro; ++o) routT[(size_t)(b * ldo + o)] = rout[(size_t)(o * mp + b)];
@@ -524,7 +529,7 @@ fps_status cyl_solve(fps_plan *pl, const double *F, double *U, char *w, hipStrea
   double *X0 = (double *)(w + c->off_X0), *X1 = (double *)(w + c->off_X1);
   const int64_t rows = nt * 2 * npad;
   auto chain = [&](int t) {
-    return fps::launch_chain_table((const fps::ChainDesc *)c->d_chain[t].p, c->nchain[t], c->nb, 0, F,
+    return fps::launch_chain_table((const fps::ChainDesc *)c->d_chain[t].p, c->nchain[t], c->nb, 3 * t, F,
                                    w, U, st);
   };
   auto solve = [&] {

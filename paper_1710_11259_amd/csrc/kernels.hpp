@@ -420,15 +420,18 @@ hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *t
                              char *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
 // Chains of products on one LDS-resident block (chain.hip), blocks of up to S =
-// 32 nb (nb = 2, 3, 4).  The block is in[r * in_rs + c * in_cs] for r < in_r, c <
+// 32 nb (nb = 2, 3, 4).  The block X is in[r * in_rs + c * in_cs] for r < in_r, c <
 // in_c, zero beyond.  Matrix i is m[i][k * ld + output index], k[i] its inner length
-// (a multiple of 16), n[i] its output length (up to S, that of the last ones up to
-// S + 2); ld covers n rounded up to the tiles that read it: 32, or S + 16 past S.
-//   mode 0: X m0, m1^T X.        1: X m0, m1^T X, multiplier, X m2, m3^T X.
-//   mode 2: m1^T X, multiplier, m3^T X (mcols columns, any number of them).
+// (a multiple of 16, in modes 0, 2 and 3 of 32), n[i] its output length (up to S,
+// that of the last ones up to S + 2); ld covers n rounded up to the tiles that read
+// it: 32, or S + 16 past S.
+//   mode 0: rows r0 .. r0 + chain_part(nb) of m1^T X m0, in_cs 2 and out_cs 1.
+//   mode 3: the same, in_cs 1 and out_cs 2; the last rows below S bring those past it.
+//   mode 1: m3^T (multiplier of m1^T X m0) m2.
+//   mode 2: m3^T (multiplier of m1^T X), up to chain_part(nb) columns.
 // The multiplier is that of GemmProb (mode 1: mr, mc, lr, lc; mode 2: mt with row
-// stride mt_rs), applied to rows < n[1], columns < mcols.  The result goes to
-// out[r * out_rs + c * out_cs] for r < out_r, c < out_c (mode 0: and a zero zoff
+// stride mt_rs), applied to rows < n[1], columns < n[0] (in_c).  The result goes to
+// out[r * out_rs + c * out_cs] for r < out_r, c < out_c (mode 3: and a zero zoff
 // elements from it, if zoff is not 0).  in / out are absolute (base 0) or byte
 // offsets from the workspace (1), the solve's input (2) or output (3).
 struct ChainDesc {
@@ -437,16 +440,17 @@ struct ChainDesc {
   const double *m[4];
   const double *mr, *mc, *lr, *lc, *mt;
   int64_t in_rs, out_rs, mt_rs;
-  int in_cs, out_cs, in_r, in_c, out_r, out_c, mcols;
+  int in_cs, out_cs, in_r, in_c, out_r, out_c, r0;
   int ld[4], k[4], n[4];
   int ibase, obase, zoff;
 };
 // Blocks of up to `len` per side need nb = chain_size(len) (0: too large).
 inline int chain_size(int64_t len) { return len <= 64 ? 2 : len <= 96 ? 3 : len <= 128 ? 4 : 0; }
+constexpr int chain_part(int nb) { return nb >= 3 ? 32 : 64; }
 bool chain_ok(const ChainDesc &d, int nb, int mode);
-// Table order: consecutive descriptors 2q, 2q + 1 (the two column parities of the
-// same rows, which share cache lines) 8 apart, on one die at the same time.
-void chain_order(std::vector<ChainDesc> &d);
+// Table order: runs of `group` descriptors that share operands, of which d holds
+// one after another, 8 apart: on one die at the same time.
+void chain_order(std::vector<ChainDesc> &d, int group);
 hipError_t launch_chain_table(const ChainDesc *d, int count, int nb, int mode, const double *in,
                               char *ws, double *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                               hipEvent_t ev1 = nullptr);
