@@ -37,126 +37,147 @@ __global__ __launch_bounds__(256) void k_cyl_permute_in(const double *__restrict
   dst[mp + a] = v1;
 }
 
-// One z column of one |k| group: the banded systems (Q_k + lambda_j P_k)
-// yhat = rhs of the group's right-hand sides (up to kCylRhs), sharing the
-// factors fac[((kabs * 8 + t) * mp + a) * npad + zpos], t: pivot offset,
+// One z column of half a |k| group: the banded systems (Q_k + lambda_j P_k)
+// yhat = rhs of its kCylRhs / 2 right-hand sides (real and imaginary part), with
+// the factors fac[((kabs * 8 + t) * mp + a) * npad + zpos], t: pivot offset,
 // two multipliers, 1/u_aa, four superdiagonal entries of U.  rhs: X0 rows
 // of parity rp (column zpos, stride npad), overwritten by the forward
 // substitution; yhat: X1 rows of parity wp (zeros beyond m and for padded
-// columns).  The factors and right-hand sides of kCylStep consecutive steps
-// are loaded before they are used.
-constexpr int kCylStep = 8;
+// columns).
+//
+// Bound by HBM and by latency: 270 MB of factors and 134 MB a pass over the right-hand
+// sides at 256 x 256, in 1032 wavefronts that each walk 256 dependent steps.  The
+// factors and right-hand sides of kCylStep steps are loaded while the steps before
+// are computed.  The halves of a group (one wavefront each) use the same factors,
+// so their workgroups are 8 apart: on one die, sharing its L2.
+constexpr int kCylStep = 8, kHalf = kCylRhs / 2;
 
-__global__ __launch_bounds__(64) void k_cyl_solve(double *__restrict__ X0,
-                                                  double *__restrict__ X1,
-                                                  const double *__restrict__ fac,
-                                                  const CylSolveGroup *__restrict__ grp, int64_t m,
-                                                  int64_t mp) {
-  const int64_t npad = 2 * mp;
-  const int64_t zpos = (int64_t)blockIdx.x * 64 + threadIdx.x;
+struct CylForward {
+  double pv[kCylStep], l1[kCylStep], l2[kCylStep], nb[kHalf][kCylStep];
+};
+struct CylBackward {
+  double iu[kCylStep], u[4][kCylStep], bv[kHalf][kCylStep];
+};
+
+__global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
+                                                     double *__restrict__ X1,
+                                                     const double *__restrict__ fac,
+                                                     const CylSolveGroup *__restrict__ grp, int m,
+                                                     int mp, int nzb, int nunits) {
+  const int npad = 2 * mp;
+  const int id = blockIdx.x, unit = (id >> 4) * 8 + (id & 7), half = (id >> 3) & 1;
+  if (unit >= nunits) return;
+  const int zpos = unit % nzb * 64 + threadIdx.x;
   if (zpos >= npad) return;
-  const CylSolveGroup &e = grp[blockIdx.y];
-  double *b[kCylRhs], *x[kCylRhs];
-  bool use[kCylRhs];
+  const CylSolveGroup &e = grp[unit / nzb];
+  const int *sp = e.sp + half * kHalf;
+  if (sp[0] < 0) return;  // the parts of a slot come in pairs
+  double *b[kHalf], *x[kHalf];
 #pragma unroll
-  for (int r = 0; r < kCylRhs; ++r) {
-    use[r] = e.sp[r] >= 0;
-    const int64_t sp = use[r] ? e.sp[r] : e.sp[0];  // unused: recomputed, never stored
-    b[r] = X0 + (sp * npad + e.rp * mp) * npad + zpos;
-    x[r] = X1 + (sp * npad + e.wp * mp) * npad + zpos;
+  for (int r = 0; r < kHalf; ++r) {
+    b[r] = X0 + ((int64_t)sp[r] * npad + e.rp * mp) * npad + zpos;
+    x[r] = X1 + ((int64_t)sp[r] * npad + e.wp * mp) * npad + zpos;
   }
-  const int s = zpos >= mp ? 1 : 0;
-  if (zpos - (s ? mp : 0) >= m) {
-    for (int64_t a = 0; a < mp; ++a)
+  if (zpos - (zpos >= mp ? mp : 0) >= m) {
+    for (int a = 0; a < mp; ++a)
 #pragma unroll
-      for (int r = 0; r < kCylRhs; ++r)
-        if (use[r]) x[r][a * npad] = 0.0;
+      for (int r = 0; r < kHalf; ++r) x[r][(int64_t)a * npad] = 0.0;
     return;
   }
   const double *f0 = fac + ((int64_t)e.kabs * 8 * mp) * npad + zpos;
-  const int64_t fs = mp * npad;  // between factor fields
-  double w0[kCylRhs], w1[kCylRhs], w2[kCylRhs];
+  const int64_t fs = (int64_t)mp * npad;  // between factor fields
+
+  auto load_fwd = [&](CylForward &q, int a0) {
 #pragma unroll
-  for (int r = 0; r < kCylRhs; ++r) {
+    for (int t = 0; t < kCylStep; ++t) {
+      const int a = min(a0 + t, m - 1);
+      const double *f = f0 + (int64_t)a * npad;
+      q.pv[t] = f[0];
+      q.l1[t] = f[fs];
+      q.l2[t] = f[2 * fs];
+#pragma unroll
+      for (int r = 0; r < kHalf; ++r) q.nb[r][t] = b[r][(int64_t)min(a0 + t + 3, m - 1) * npad];
+    }
+  };
+  double w0[kHalf], w1[kHalf], w2[kHalf];
+#pragma unroll
+  for (int r = 0; r < kHalf; ++r) {
     w0[r] = b[r][0];
     w1[r] = m > 1 ? b[r][npad] : 0.0;
     w2[r] = m > 2 ? b[r][2 * npad] : 0.0;
   }
-  for (int64_t a0 = 0; a0 < m; a0 += kCylStep) {
-    double pv[kCylStep], l1[kCylStep], l2[kCylStep], nb[kCylRhs][kCylStep];
+  auto run_fwd = [&](const CylForward &q, int a0) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
-      const int64_t a = a0 + t;
-      const double *f = f0 + (a < m ? a : 0) * npad;
-      pv[t] = f[0];
-      l1[t] = f[fs];
-      l2[t] = f[2 * fs];
-#pragma unroll
-      for (int r = 0; r < kCylRhs; ++r) nb[r][t] = a + 3 < m ? b[r][(a + 3) * npad] : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < kCylStep; ++t) {
-      const int64_t a = a0 + t;
+      const int a = a0 + t;
       if (a >= m) break;
-      const int p = (int)pv[t];
+      const int p = (int)q.pv[t];
 #pragma unroll
-      for (int r = 0; r < kCylRhs; ++r) {
-        if (p == 1) {
-          const double tt = w0[r];
-          w0[r] = w1[r];
-          w1[r] = tt;
-        } else if (p == 2) {
-          const double tt = w0[r];
-          w0[r] = w2[r];
-          w2[r] = tt;
-        }
-        w1[r] -= l1[t] * w0[r];
-        w2[r] -= l2[t] * w0[r];
-        if (use[r]) b[r][a * npad] = w0[r];
+      for (int r = 0; r < kHalf; ++r) {
+        const double v0 = p == 1 ? w1[r] : p == 2 ? w2[r] : w0[r];
+        w1[r] = (p == 1 ? w0[r] : w1[r]) - q.l1[t] * v0;
+        w2[r] = (p == 2 ? w0[r] : w2[r]) - q.l2[t] * v0;
+        b[r][(int64_t)a * npad] = v0;
         w0[r] = w1[r];
         w1[r] = w2[r];
-        w2[r] = nb[r][t];
+        w2[r] = a + 3 < m ? q.nb[r][t] : 0.0;
       }
     }
+  };
+  // (loads run ahead of the stores: those of step a are at rows past a + 2)
+  CylForward fa, fb;
+  load_fwd(fa, 0);
+  for (int a0 = 0; a0 < m; a0 += 2 * kCylStep) {
+    load_fwd(fb, a0 + kCylStep);
+    run_fwd(fa, a0);
+    load_fwd(fa, a0 + 2 * kCylStep);
+    run_fwd(fb, a0 + kCylStep);
   }
-  double x1[kCylRhs], x2[kCylRhs], x3[kCylRhs], x4[kCylRhs];
-#pragma unroll
-  for (int r = 0; r < kCylRhs; ++r) x1[r] = x2[r] = x3[r] = x4[r] = 0.0;
-  for (int64_t a1 = m - 1; a1 >= 0; a1 -= kCylStep) {
-    double iu[kCylStep], u1[kCylStep], u2[kCylStep], u3[kCylStep], u4[kCylStep];
-    double bv[kCylRhs][kCylStep];
+
+  auto load_bwd = [&](CylBackward &q, int a1) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
-      const int64_t a = a1 - t >= 0 ? a1 - t : 0;
-      const double *f = f0 + a * npad;
-      iu[t] = f[3 * fs];
-      u1[t] = f[4 * fs];
-      u2[t] = f[5 * fs];
-      u3[t] = f[6 * fs];
-      u4[t] = f[7 * fs];
+      const int a = max(a1 - t, 0);
+      const double *f = f0 + (int64_t)a * npad;
+      q.iu[t] = f[3 * fs];
 #pragma unroll
-      for (int r = 0; r < kCylRhs; ++r) bv[r][t] = b[r][a * npad];
+      for (int i = 0; i < 4; ++i) q.u[i][t] = f[(4 + i) * fs];
+#pragma unroll
+      for (int r = 0; r < kHalf; ++r) q.bv[r][t] = b[r][(int64_t)a * npad];
     }
+  };
+  double x1[kHalf], x2[kHalf], x3[kHalf], x4[kHalf];
+#pragma unroll
+  for (int r = 0; r < kHalf; ++r) x1[r] = x2[r] = x3[r] = x4[r] = 0.0;
+  auto run_bwd = [&](const CylBackward &q, int a1) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
-      const int64_t a = a1 - t;
+      const int a = a1 - t;
       if (a < 0) break;
 #pragma unroll
-      for (int r = 0; r < kCylRhs; ++r) {
-        const double v =
-            (bv[r][t] - u1[t] * x1[r] - u2[t] * x2[r] - u3[t] * x3[r] - u4[t] * x4[r]) * iu[t];
-        if (use[r]) x[r][a * npad] = v;
+      for (int r = 0; r < kHalf; ++r) {
+        const double v = (q.bv[r][t] - q.u[0][t] * x1[r] - q.u[1][t] * x2[r] - q.u[2][t] * x3[r] -
+                          q.u[3][t] * x4[r]) *
+                         q.iu[t];
+        x[r][(int64_t)a * npad] = v;
         x4[r] = x3[r];
         x3[r] = x2[r];
         x2[r] = x1[r];
         x1[r] = v;
       }
     }
+  };
+  CylBackward ba, bb;
+  load_bwd(ba, m - 1);
+  for (int a1 = m - 1; a1 >= 0; a1 -= 2 * kCylStep) {
+    load_bwd(bb, a1 - kCylStep);
+    run_bwd(ba, a1);
+    load_bwd(ba, a1 - 2 * kCylStep);
+    run_bwd(bb, a1 - kCylStep);
   }
-  for (int64_t a = m; a < mp; ++a)
+  for (int a = m; a < mp; ++a)
 #pragma unroll
-    for (int r = 0; r < kCylRhs; ++r)
-      if (use[r]) x[r][a * npad] = 0.0;
+    for (int r = 0; r < kHalf; ++r) x[r][(int64_t)a * npad] = 0.0;
 }
 
 }  // namespace
@@ -173,10 +194,11 @@ hipError_t launch_cyl_permute_in(const double *F, double *X0, const int *slot_id
 
 hipError_t launch_cyl_solve(double *X0, double *X1, const double *fac, const CylSolveGroup *grp,
                             int ngroups, int64_t m, int64_t mp, hipStream_t st) {
-  const int64_t npad = 2 * mp;
   if (ngroups <= 0) return hipSuccess;
-  dim3 grid((unsigned)((npad + 63) / 64), (unsigned)ngroups);
-  hipLaunchKernelGGL(k_cyl_solve, grid, dim3(64), 0, st, X0, X1, fac, grp, m, mp);
+  const int64_t nzb = (2 * mp + 63) / 64, units = nzb * ngroups;
+  // n <= 512, n_theta <= 1024: at most 8 x 513 units
+  hipLaunchKernelGGL(k_cyl_solve, dim3((unsigned)((units + 7) / 8 * 16)), dim3(64), 0, st, X0, X1, fac,
+                     grp, (int)m, (int)mp, (int)nzb, (int)units);
   return hipGetLastError();
 }
 
