@@ -328,11 +328,11 @@ int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::G
 int solve_chain(const fps_plan *pl, const double *F, double *U, const double *lr, const double *lc,
                 fps::ChainDesc *d, int *nb) {
   const fps::Layout &L = pl->L;
-  if (L.n > kChainMax) return 0;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
   const int64_t n = L.n, N = out_extent(pl), *mo = native ? L.m : L.mo;
   const int64_t *mop = native ? L.mp : pl->mop;
-  *nb = fps::chain_size(k_round(L.m[0]));
+  if (!forward_chained(pl)) return 0;
+  *nb = mo[0] <= 48 ? 3 : mo[0] <= 64 ? 4 : 5;
   int cnt = 0;
   for (int s = 0; s < 2; ++s)
     for (int t = 0; t < 2; ++t) {
@@ -370,10 +370,10 @@ int solve_chain(const fps_plan *pl, const double *F, double *U, const double *lr
 
 int adjoint_chain(const fps_plan *pl, const double *Ubar, double *Fbar, fps::ChainDesc *d, int *nb) {
   const fps::Layout &L = pl->L;
-  if (L.n > kChainMax) return 0;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
   const int64_t n = L.n, N = out_extent(pl), *mo = native ? L.m : L.mo;
-  *nb = fps::chain_size(k_round(mo[0]));
+  if (!adjoint_chained(pl)) return 0;
+  *nb = mo[0] <= 48 ? 3 : 4;
   int cnt = 0;
   for (int s = 0; s < 2; ++s)
     for (int t = 0; t < 2; ++t) {

@@ -37,10 +37,10 @@ struct fps_batch {
   // batches) the adjoint's input map g1, g2 and output map g1, g2
   DeviceBuf d_gd[8], d_gmap[8];
   fps::GemmTable gt[8];
-  // the problems small enough for chains (n <= 128; forward 0, adjoint 1): one
+  // the problems small enough for chains (forward 0, adjoint 1): one
   // launch each; the products and permutations below hold the others
   DeviceBuf d_chain[2];
-  int nchain[2] = {0, 0}, chain_nb[2] = {2, 2};
+  int nchain[2] = {0, 0}, chain_nb[2] = {3, 3};
   // the permutations of F (0) and of the adjoint's cotangent (1) as one
   // launch each (elem_ok; else, for very large batches, one per problem)
   bool elem_ok = false;
@@ -57,8 +57,8 @@ namespace {
 
 bool valid_batch(const fps_batch *b) { return b != nullptr && b->magic == kBatchMagic; }
 
-// Whether the plan's solves run as chains.
-bool chained(const fps_plan *pl) { return pl->L.n <= kChainMax; }
+// Whether the plan's solves (t 0) or adjoints (1) run as chains.
+bool chained(const fps_plan *pl, int t) { return t ? adjoint_chained(pl) : forward_chained(pl); }
 
 fps_status run_chains(const fps_batch *bt, int t, const double *in, double *out, hipStream_t st) {
   FPS_HIP(fps::launch_chain_table((const fps::ChainDesc *)bt->d_chain[t].p, bt->nchain[t],
@@ -80,27 +80,22 @@ fps_status build_gemm_tables(fps_batch *bt) {
     double *Usyn = (double *)(intptr_t)(bt->u_off[b] * (int64_t)sizeof(double));
     double *Fsyn = (double *)(intptr_t)(bt->f_off[b] * (int64_t)sizeof(double));
     fps::ChainDesc cd[4];
-    int nb = 0;
-    if (const int c = solve_chain(pl, Fsyn, Usyn, nullptr, nullptr, cd, &nb)) {
+    for (int t = 0; t < (refined ? 1 : 2); ++t) {
+      int nb = 0;
+      const int c = t ? adjoint_chain(pl, Usyn, Fsyn, cd, &nb)
+                      : solve_chain(pl, Fsyn, Usyn, nullptr, nullptr, cd, &nb);
       for (int i = 0; i < c; ++i) {
         cd[i].ibase = 2;
         cd[i].obase = 3;
-        chain[0].push_back(cd[i]);
+        chain[t].push_back(cd[i]);
       }
-      bt->chain_nb[0] = std::max(bt->chain_nb[0], nb);
-      const int ca = refined ? 0 : adjoint_chain(pl, Usyn, Fsyn, cd, &nb);
-      for (int i = 0; i < ca; ++i) {
-        cd[i].ibase = 2;
-        cd[i].obase = 3;
-        chain[1].push_back(cd[i]);
-        bt->chain_nb[1] = std::max(bt->chain_nb[1], nb);
-      }
-      continue;
+      if (c > 0) bt->chain_nb[t] = std::max(bt->chain_nb[t], nb);
     }
-    const int c_in = rhs_gemms(pl, wsyn, g[0], g[1]);
-    const int c_out = out_gemms(pl, Usyn, wsyn, g[2], g[3]);
-    const int c_ain = refined ? 0 : adj_in_gemms(pl, wsyn, g[4], g[5]);
-    const int c_aout = refined ? 0 : adj_out_gemms(pl, Fsyn, wsyn, g[6], g[7]);
+    const bool fwd = !chained(pl, 0), adj = !refined && !chained(pl, 1);
+    const int c_in = fwd ? rhs_gemms(pl, wsyn, g[0], g[1]) : 0;
+    const int c_out = fwd ? out_gemms(pl, Usyn, wsyn, g[2], g[3]) : 0;
+    const int c_ain = adj ? adj_in_gemms(pl, wsyn, g[4], g[5]) : 0;
+    const int c_aout = adj ? adj_out_gemms(pl, Fsyn, wsyn, g[6], g[7]) : 0;
     // base ids (A, B, C): ws-relative 1, absolute 0, output-relative 2
     static const int ids[8][3] = {{1, 0, 1}, {0, 1, 1}, {1, 0, 1}, {0, 1, 2},
                                   {1, 0, 1}, {0, 1, 1}, {1, 0, 1}, {0, 1, 2}};
@@ -144,8 +139,8 @@ fps_status build_elem_tables(fps_batch *bt) {
     const fps::Layout &L = pl->L;
     const bool native = bt->out_basis == FPS_OUT_NATIVE;
     const int64_t *mop = native ? L.mp : pl->mop;
-    if (chained(pl)) continue;
     for (int t = 0; t < 2; ++t) {
+      if (chained(pl, t)) continue;
       fps::ElemDesc e{};
       e.n = t ? out_extent(pl) : L.n;
       e.npad = t ? mop[0] + mop[1] : L.npad;
@@ -182,7 +177,7 @@ fps_status permute_all(const fps_batch *bt, int t, const double *in, char *w, hi
   }
   for (int b = 0; b < bt->count; ++b) {
     const fps_plan *pl = bt->plan_of(b);
-    if (chained(pl)) continue;
+    if (chained(pl, t)) continue;
     const fps::Layout &L = pl->L;
     const int64_t *mop = bt->out_basis == FPS_OUT_NATIVE ? L.mp : pl->mop;
     char *wb = w + bt->ws_off[b];

@@ -7,7 +7,7 @@
 // between), cylinder modes (z and r maps) and whole square solves up to n = 128.
 // Against one product launch per axis: cube n = 256 775 -> 490 us, n = 185 297 ->
 // 180 us, n = 128 111 -> 53 us, cylinder 256 x 256 1031 -> 562 us (its z map then
-// also ran over the r parity that a mode has not), square n = 64 22.6 -> 14.2 us.
+// also ran over the r parity that a mode has not), square n = 64 22.6 -> 8.6 us.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -25,169 +25,9 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
 
-// Square solves: block of up to S x S (S = 32 NB), NB^2 wavefronts, each 32 x 32 of the output
-// as 2 x 2 MFMA blocks (v_mfma_f64_16x16x4f64: lane l supplies A[l % 16][l / 16]
-// and B[l / 16][l % 16], accumulator register r holds C[4r + l / 16][l % 16]).
-// X lives in LDS with two columns of padding: 16 rows at one k then fall on
-// distinct banks.  The other operand is read from global memory in its
-// transposed form [k][row or column], 128 contiguous bytes per k.
-// 1 or 2 output rows or columns past S (the output maps have m + 1 or m + 2) are
-// 16-wide extra tiles, a tenth of the products more: wavefront w takes the
-// extra tiles w, w + NB^2, ...
-template <int NB>
-struct Chain {
-  static constexpr int S = 32 * NB, P = S + 2, kThreads = 64 * NB * NB, kLds = S * P + 16;
-  static constexpr int kWaves = NB * NB, kSlots = NB == 2 ? 3 : 2;  // extra tiles per wavefront
-};
-
 struct Lane {
   int l15, l4, wave, wy, wx;
 };
-
-// acc += X[r0 .. r0 + 16 RB)[0 .. K) W[0 .. K)[c0 .. c0 + 16 CB): X from LDS as the
-// left operand, W [k][column] from global memory, loaded 4 k-steps ahead.
-template <int P, int RB, int CB>
-__device__ __forceinline__ void mul_right(const double *X, const double *__restrict__ W, int ldw,
-                                          int K, int r0, int c0, const Lane &l, dbl4 (&acc)[RB][CB]) {
-  const double *xa = X + (r0 + l.l15) * P + l.l4;
-  const uint32_t wo = l.l4 * ldw + l.l15;  // the lane's part of the address
-  const double *wu = W + c0;               // the wavefront's
-  double b[4][CB];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int c = 0; c < CB; ++c) b[u][c] = (wu + (4 * u) * ldw + 16 * c)[wo];
-#pragma unroll 1
-  for (int ks = 0; ks < K; ks += 16) {
-    const int nx = ks + 16 < K ? ks + 16 : ks;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      double a[RB], bv[CB];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) a[r] = xa[r * 16 * P + ks + 4 * u];
-#pragma unroll
-      for (int c = 0; c < CB; ++c) {
-        bv[c] = b[u][c];
-        b[u][c] = (wu + (nx + 4 * u) * ldw + 16 * c)[wo];
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], bv[c], acc[r][c], 0, 0, 0);
-    }
-  }
-}
-
-// acc += W^T[r0 ..)[0 .. K) X[0 .. K)[c0 ..): W [k][row] from global memory as the left
-// operand, X from LDS.
-template <int P, int RB, int CB>
-__device__ __forceinline__ void mul_left(const double *X, const double *__restrict__ W, int ldw,
-                                         int K, int r0, int c0, const Lane &l, dbl4 (&acc)[RB][CB]) {
-  const uint32_t wo = l.l4 * ldw + l.l15;
-  const double *wu = W + r0;
-  const double *xb = X + l.l4 * P + c0 + l.l15;
-  double a[4][RB];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int r = 0; r < RB; ++r) a[u][r] = (wu + (4 * u) * ldw + 16 * r)[wo];
-#pragma unroll 1
-  for (int ks = 0; ks < K; ks += 16) {
-    const int nx = ks + 16 < K ? ks + 16 : ks;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      double av[RB], b[CB];
-#pragma unroll
-      for (int c = 0; c < CB; ++c) b[c] = xb[(ks + 4 * u) * P + 16 * c];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        av[r] = a[u][r];
-        a[u][r] = (wu + (nx + 4 * u) * ldw + 16 * r)[wo];
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r)
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[r], b[c], acc[r][c], 0, 0, 0);
-    }
-  }
-}
-
-// The eigenbasis multiplier of entry (i, j), as in the product kernels.
-__device__ __forceinline__ double multiplier(const ChainDesc &d, int i, int j, double v) {
-  if (d.lr != nullptr) {
-    const double *r = d.lr + 4 * i, *c = d.lc + 4 * j;
-    v -= fma(r[3], c[3], fma(r[2], c[2], fma(r[1], c[1], r[0] * c[0])));
-  }
-  const dbl2 r = *(const dbl2 *)(d.mr + 2 * i), c = *(const dbl2 *)(d.mc + 2 * j);
-  return v * (fma(-r.y, c.y, 1.0) / (r.x + c.x));
-}
-
-// One product step of the chain on X: right (X W) or left (W^T X), with rows x
-// cols outputs; the result goes to `put(r, c, value)`, for this lane's row r + l4
-// and column c + l15, after every wavefront has read X.
-template <int NB, bool kLeft, typename Put>
-__device__ __forceinline__ void step(double *X, const double *W, int ldw, int K, int rows, int cols,
-                                     const Lane &l, Put put) {
-  using C = Chain<NB>;
-  dbl4 acc[2][2], ext[C::kSlots];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = dbl4{0.0, 0.0, 0.0, 0.0};
-  const int r0 = l.wy * 32, c0 = l.wx * 32;
-  const bool mine = r0 < rows && c0 < cols;  // uniform per wavefront
-  if (mine) {
-    if constexpr (kLeft)
-      mul_left<C::P, 2, 2>(X, W, ldw, K, r0, c0, l, acc);
-    else
-      mul_right<C::P, 2, 2>(X, W, ldw, K, r0, c0, l, acc);
-  }
-  // extra tiles: columns past S (one per 16 rows), rows past S (one per 16
-  // columns; left products only), and the corner
-  const int nec = cols > C::S ? 2 * NB : 0, ner = rows > C::S ? 2 * NB : 0;
-  const int next = nec + ner + (nec && ner ? 1 : 0);
-  auto extra = [&](int t, int *r, int *c) {
-    *r = t < nec ? 16 * t : C::S;
-    *c = t < nec ? C::S : t < nec + ner ? 16 * (t - nec) : C::S;
-  };
-#pragma unroll
-  for (int s = 0; s < C::kSlots; ++s) {
-    const int t = l.wave + s * C::kWaves;
-    ext[s] = dbl4{0.0, 0.0, 0.0, 0.0};
-    if (t < next) {
-      int r, c;
-      extra(t, &r, &c);
-      dbl4 e[1][1] = {{dbl4{0.0, 0.0, 0.0, 0.0}}};
-      if constexpr (kLeft)
-        mul_left<C::P, 1, 1>(X, W, ldw, K, r, c, l, e);
-      else
-        mul_right<C::P, 1, 1>(X, W, ldw, K, r, c, l, e);
-      ext[s] = e[0][0];
-    }
-  }
-  __syncthreads();
-  if (mine) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          put(r0 + a * 16 + 4 * r, c0 + b * 16, acc[a][b][r]);
-  }
-#pragma unroll
-  for (int s = 0; s < C::kSlots; ++s) {
-    const int t = l.wave + s * C::kWaves;
-    if (t < next) {
-      int er, ec;
-      extra(t, &er, &ec);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) put(er + 4 * r, ec, ext[s][r]);
-    }
-  }
-}
 
 // Where the offsets of a table's blocks start (unused for blocks given by value).
 struct Bases {
@@ -223,66 +63,171 @@ __device__ __forceinline__ dbl2 at2(const double *p, uint32_t bytes) {
   return *(const dbl2 *)((const char *)p + bytes);
 }
 
-// A whole square solve: right, left, multiplier, right, left.
-template <int NB, bool kTable>
+// A whole square solve, m3^T (multiplier of m1^T X m0) m2, of blocks of up to 64 with
+// outputs of up to 16 TT: a wavefront per 16 x 16 tile (v_mfma_f64_16x16x4f64: lane l
+// supplies A[l % 16][l / 16] and B[l / 16][l % 16], accumulator register r holds
+// C[4r + l / 16][l % 16]), 16 of them at most; the first wavefronts also take the
+// tiles left over at TT = 5.  Bound by latency: the four products of n = 64 are 0.25 us
+// each, a load from another die's cache or HBM takes 1 to 2.  So the first product
+// reads F straight into the matrix unit's layout, the other operand of the next
+// product is loaded into registers while the current one runs, and the results go
+// to two LDS buffers in turn, one barrier each.  n = 64: 14.2 us with 32 x 32 tiles that
+// waited for every operand -> 8.6.
+template <int TT>
+struct Chain {
+  static constexpr int P = 16 * TT + 2;  // 16 rows at one k on distinct banks
+  static constexpr int kWaves = TT * TT < 16 ? TT * TT : 16, kThreads = 64 * kWaves;
+  static constexpr int kSlots = (TT * TT + kWaves - 1) / kWaves;
+};
+constexpr int kChainK = 64, kSteps = kChainK / 4;
+
+// Row / column of the wavefront's tile in a product with rows x cols outputs; false
+// if there is none.
+__device__ __forceinline__ bool chain_tile(int i, int rows, int cols, int *r, int *c) {
+  const int nx = (cols + 15) >> 4;
+  *r = i / nx * 16;
+  *c = i % nx * 16;
+  return *r < rows;
+}
+
+// w = W[k][w0 + l15] of k = 4u + l4, for k < K (a multiple of 16).
+__device__ __forceinline__ void chain_load(const double *W, int ldw, int K, int w0, const Lane &l,
+                                           double (&w)[kSteps]) {
+  const uint32_t o = 8 * (l.l4 * ldw + l.l15);
+#pragma unroll
+  for (int u = 0; u < kSteps; ++u)
+    if ((u & ~3) * 4 < K) w[u] = at(W + w0 + 4 * u * ldw, o);
+}
+
+// The tile X W (kLeft W^T X) with X from LDS.
+template <int P, bool kLeft>
+__device__ __forceinline__ dbl4 chain_mul(const double *X, const double (&w)[kSteps], int K, int r,
+                                          int c, const Lane &l) {
+  const double *x = kLeft ? X + l.l4 * P + c + l.l15 : X + (r + l.l15) * P + l.l4;
+  dbl4 acc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int v = 0; v < kSteps; v += 4)
+    if (4 * v < K) {
+#pragma unroll
+      for (int u = v; u < v + 4; ++u) {
+        const double t = x[4 * u * (kLeft ? P : 1)];
+        acc = kLeft ? __builtin_amdgcn_mfma_f64_16x16x4f64(w[u], t, acc, 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f64_16x16x4f64(t, w[u], acc, 0, 0, 0);
+      }
+    }
+  return acc;
+}
+
+template <int TT, bool kTable>
 __device__ __forceinline__ void solve_block(const ChainDesc &e, const Bases &u) {
-  using C = Chain<NB>;
-  __shared__ __align__(16) double X[C::kLds];
+  using C = Chain<TT>;
+  constexpr int P = C::P;
+  __shared__ __align__(16) double X[2][16 * TT * P];
   const int tid = threadIdx.x;
   Lane l;
   l.l15 = tid & 15;
   l.l4 = (tid & 63) >> 4;
   l.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  l.wy = l.wave / NB;
-  l.wx = l.wave % NB;
-  static_assert(C::S * C::S == 16 * C::kThreads, "one block is 16 elements per thread");
-  // thread t holds column t % S of rows t / S + 2 NB i
-  const int tr = tid / C::S, tc = tid % C::S;
   const double *in = rebase<kTable>(e.in, e.ibase, u);
-  const uint32_t off = (uint32_t)(tr * (int)e.in_rs + tc * e.in_cs);
+  double *out = (double *)rebase<kTable>(e.out, e.obase, u);
+  double wa[kSteps], wb[kSteps];
+  int r, c;
+  auto keep = [&](double *Y, const dbl4 &acc) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int r = i * 2 * NB;
-    X[(r + tr) * C::P + tc] = tr + r < e.in_r && tc < e.in_c ? (in + r * e.in_rs)[off] : 0.0;
+    for (int q = 0; q < 4; ++q) Y[(r + 4 * q + l.l4) * P + c + l.l15] = acc[q];
+  };
+  // slots past the first (TT = 5) load their W when they come to it
+  // 1: X m0, X straight from the input (zero beyond in_r, in_c)
+#pragma unroll
+  for (int s = 0; s < C::kSlots; ++s)
+    if (chain_tile(l.wave + s * C::kWaves, e.k[1], e.n[0], &r, &c)) {
+      double x[kSteps];
+      const int row = r + l.l15;
+      const double *p = in + (int64_t)min(row, e.in_r - 1) * e.in_rs;
+#pragma unroll
+      for (int v = 0; v < kSteps; ++v)
+        if ((v & ~3) * 4 < e.k[0]) x[v] = p[min(4 * v + l.l4, e.in_c - 1) * e.in_cs];
+      chain_load(e.m[0], e.ld[0], e.k[0], c, l, wa);
+      if (s == 0) {
+        int r1, c1;
+        if (chain_tile(l.wave, e.n[1], e.n[0], &r1, &c1)) chain_load(e.m[1], e.ld[1], e.k[1], r1, l, wb);
+      }
+      dbl4 acc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int v = 0; v < kSteps; ++v)
+        if ((v & ~3) * 4 < e.k[0])
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(
+              row < e.in_r && 4 * v + l.l4 < e.in_c ? x[v] : 0.0, wa[v], acc, 0, 0, 0);
+      keep(X[0], acc);
+    }
+  // 2: m1^T X and the multiplier (as in the product kernels)
+  if (chain_tile(l.wave, e.k[3], e.n[2], &r, &c)) chain_load(e.m[2], e.ld[2], e.k[2], c, l, wa);
+  dbl2 fr[4], fc;
+  if (chain_tile(l.wave, e.n[1], e.n[0], &r, &c)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) fr[q] = *(const dbl2 *)(e.mr + 2 * (r + 4 * q + l.l4));
+    fc = *(const dbl2 *)(e.mc + 2 * (c + l.l15));
   }
   __syncthreads();
-  double *Xl = X + l.l4 * C::P + l.l15;  // this lane's entry of a 4 x 16 patch
-  auto keep = [&](int r, int c, double x) {
-    if (r + 4 <= C::S && c + l.l15 < C::P) Xl[r * C::P + c] = x;
-  };
-  auto keep_mul = [&](int r, int c, double x) {
-    const int i = r + l.l4, j = c + l.l15;
-    if (r + 4 <= C::S && j < C::S)
-      Xl[r * C::P + c] = i < e.n[1] && j < e.n[0] ? multiplier(e, i, j, x) : 0.0;
-  };
-  double *out = (double *)rebase<kTable>(e.out, e.obase, u);
-  const uint32_t oo = (uint32_t)(l.l4 * (int)e.out_rs + l.l15 * e.out_cs);
-  auto store = [&](int r, int c, double x) {
-    if (r + l.l4 < e.out_r && c + l.l15 < e.out_c)
-      (out + r * e.out_rs + (int64_t)c * e.out_cs)[oo] = x;
-  };
-  step<NB, false>(X, e.m[0], e.ld[0], e.k[0], e.k[1], e.n[0], l, keep);
+#pragma unroll
+  for (int s = 0; s < C::kSlots; ++s)
+    if (chain_tile(l.wave + s * C::kWaves, e.n[1], e.n[0], &r, &c)) {
+      if (s > 0) {
+        chain_load(e.m[1], e.ld[1], e.k[1], r, l, wb);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) fr[q] = *(const dbl2 *)(e.mr + 2 * (r + 4 * q + l.l4));
+        fc = *(const dbl2 *)(e.mc + 2 * (c + l.l15));
+      }
+      dbl4 acc = chain_mul<P, true>(X[0], wb, e.k[1], r, c, l);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double v = acc[q];
+        if (e.lr != nullptr) {
+          const double *a = e.lr + 4 * (r + 4 * q + l.l4), *b = e.lc + 4 * (c + l.l15);
+          v -= fma(a[3], b[3], fma(a[2], b[2], fma(a[1], b[1], a[0] * b[0])));
+        }
+        acc[q] = v * (fma(-fr[q].y, fc.y, 1.0) / (fr[q].x + fc.x));
+      }
+      keep(X[1], acc);
+    }
+  // 3: X m2
+  if (chain_tile(l.wave, e.n[3], e.n[2], &r, &c)) chain_load(e.m[3], e.ld[3], e.k[3], r, l, wb);
   __syncthreads();
-  step<NB, true>(X, e.m[1], e.ld[1], e.k[1], e.n[1], e.n[0], l, keep_mul);
+#pragma unroll
+  for (int s = 0; s < C::kSlots; ++s)
+    if (chain_tile(l.wave + s * C::kWaves, e.k[3], e.n[2], &r, &c)) {
+      if (s > 0) chain_load(e.m[2], e.ld[2], e.k[2], c, l, wa);
+      keep(X[0], chain_mul<P, false>(X[1], wa, e.k[2], r, c, l));
+    }
   __syncthreads();
-  step<NB, false>(X, e.m[2], e.ld[2], e.k[2], e.k[3], e.n[2], l, keep);
-  __syncthreads();
-  step<NB, true>(X, e.m[3], e.ld[3], e.k[3], e.n[3], e.n[2], l, store);
+  // 4: m3^T X
+#pragma unroll
+  for (int s = 0; s < C::kSlots; ++s)
+    if (chain_tile(l.wave + s * C::kWaves, e.n[3], e.n[2], &r, &c)) {
+      if (s > 0) chain_load(e.m[3], e.ld[3], e.k[3], r, l, wb);
+      const dbl4 acc = chain_mul<P, true>(X[0], wb, e.k[3], r, c, l);
+      const int j = c + l.l15;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = r + 4 * q + l.l4;
+        if (i < e.out_r && j < e.out_c) out[i * e.out_rs + (int64_t)j * e.out_cs] = acc[q];
+      }
+    }
 }
 
-template <int NB>
-__global__ __launch_bounds__(Chain<NB>::kThreads, NB == 3 ? 5 : 4) void k_chain_table(
-    const ChainDesc *__restrict__ d, Bases u) {
-  solve_block<NB, true>(table_entry(d[blockIdx.x]), u);
+template <int TT>
+__global__ __launch_bounds__(Chain<TT>::kThreads) void k_chain_table(const ChainDesc *__restrict__ d,
+                                                                     Bases u) {
+  solve_block<TT, true>(table_entry(d[blockIdx.x]), u);
 }
 
 struct ChainBatch {
   ChainDesc d[4];
 };
 
-template <int NB>
-__global__ __launch_bounds__(Chain<NB>::kThreads, NB == 3 ? 5 : 4) void k_chain(ChainBatch b) {
-  solve_block<NB, false>(b.d[blockIdx.x], Bases{});
+template <int TT>
+__global__ __launch_bounds__(Chain<TT>::kThreads) void k_chain(ChainBatch b) {
+  solve_block<TT, false>(b.d[blockIdx.x], Bases{});
 }
 
 // Slabs and strips: two products of one block of up to S x S, S = 32 NB, split so
@@ -646,28 +591,30 @@ hipError_t run(K kern, unsigned grid, unsigned block, hipStream_t st, hipEvent_t
 }  // namespace
 
 bool chain_ok(const ChainDesc &d, int nb, int mode) {
-  const int S = 32 * nb;
-  const int step = mode == 1 ? 16 : 32;
+  const int S = mode == 1 ? 16 * nb : 32 * nb, step = mode == 1 ? 16 : 32;
+  const int K = mode == 1 && S > kChainK ? kChainK : S;
   auto mat = [&](int i, int most) {
-    return d.m[i] != nullptr && d.k[i] >= step && d.k[i] <= S && d.k[i] % step == 0 && d.n[i] >= 1 &&
-           d.n[i] <= most && d.ld[i] >= (d.n[i] > S ? S + 16 : (d.n[i] + 31) / 32 * 32);
+    const int cover = mode == 1 ? (d.n[i] + 15) / 16 * 16 : d.n[i] > S ? S + 16 : (d.n[i] + 31) / 32 * 32;
+    return d.m[i] != nullptr && d.k[i] >= step && d.k[i] <= K && d.k[i] % step == 0 && d.n[i] >= 1 &&
+           d.n[i] <= most && d.ld[i] >= cover;
   };
   // the lanes' address parts are 32-bit
-  if (S * d.in_rs >= (int64_t)1 << 31 || 16 * d.out_rs >= (int64_t)1 << 31) return false;
-  if (nb < 2 || nb > 4 || d.in_r > S || d.in_c > S || d.in_r < 1 || d.in_c < 1) return false;
-  if (mode == 0 ? d.in_cs != 2 || d.out_cs != 1 || d.out_c % 2 || d.out_rs % 2 || d.zoff != 0
-                : mode == 3 ? d.in_cs != 1 || d.out_cs != 2
-                            : mode == 2 && (d.in_cs != 1 || d.out_cs != 1 || d.in_c % 2 || d.mt_rs % 2))
-    return false;
-  if (mode == 0 || mode == 3)
-    return mat(0, S + 2) && mat(1, S + 2) && d.in_r <= d.k[1] && d.in_c <= d.k[0] && d.r0 >= 0 &&
-           d.r0 % chain_part(nb) == 0 && d.r0 < d.n[1] && d.r0 < S &&
-           (mode == 3 || (d.n[0] <= S && d.n[1] <= S));
+  if (8 * S * d.in_rs >= (int64_t)1 << 31) return false;
+  if (d.in_r > S || d.in_c > S || d.in_r < 1 || d.in_c < 1) return false;
   if (mode == 1)
-    return d.mr != nullptr && d.mc != nullptr && mat(0, S) && mat(1, S) && mat(2, S + 2) &&
-           mat(3, S + 2) && d.in_r <= d.k[1] && d.in_c <= d.k[0] && d.zoff == 0;
-  return mode == 2 && d.mt != nullptr && mat(1, S) && mat(3, S + 2) && d.in_r <= d.k[1] &&
-         d.k[3] <= d.ld[1] && d.in_c <= chain_part(nb) && d.out_c <= d.in_c && d.zoff == 0;
+    return (nb == 3 || nb == 4 || nb == 5) && d.mr != nullptr && d.mc != nullptr && mat(0, K) &&
+           mat(1, K) && mat(2, S) && mat(3, S) && d.in_r <= d.k[1] && d.in_c <= d.k[0] &&
+           d.k[2] == (d.n[0] + 15) / 16 * 16 && d.k[3] == (d.n[1] + 15) / 16 * 16;
+  if (nb < 2 || nb > 4) return false;
+  if (mode == 2)
+    return d.mt != nullptr && mat(1, S) && mat(3, S + 2) && d.in_r <= d.k[1] && d.k[3] <= d.ld[1] &&
+           d.in_c <= chain_part(nb) && d.out_c <= d.in_c && d.in_cs == 1 && d.out_cs == 1 &&
+           d.in_c % 2 == 0 && d.mt_rs % 2 == 0 && d.zoff == 0;
+  if (mode == 0 ? d.in_cs != 2 || d.out_cs != 1 || d.out_c % 2 || d.zoff != 0 || d.n[0] > S || d.n[1] > S
+                : mode != 3 || d.in_cs != 1 || d.out_cs != 2)
+    return false;
+  return mat(0, S + 2) && mat(1, S + 2) && d.in_r <= d.k[1] && d.in_c <= d.k[0] && d.r0 >= 0 &&
+         d.r0 % chain_part(nb) == 0 && d.r0 < d.n[1] && d.r0 < S;
 }
 
 void chain_order(std::vector<ChainDesc> &d, int group) {
@@ -692,8 +639,9 @@ hipError_t launch_chain_table(const ChainDesc *d, int count, int nb, int mode, c
   FPS_UNITS(2, 2);
   FPS_UNITS(3, 1);
   FPS_UNITS(4, 1);
-  FPS_CHAIN(2, 1, k_chain_table<2>, Chain<2>::kThreads);
   FPS_CHAIN(3, 1, k_chain_table<3>, Chain<3>::kThreads);
+  FPS_CHAIN(4, 1, k_chain_table<4>, Chain<4>::kThreads);
+  FPS_CHAIN(5, 1, k_chain_table<5>, Chain<5>::kThreads);
 #undef FPS_UNITS
 #undef FPS_CHAIN
   return hipErrorInvalidValue;
@@ -701,14 +649,15 @@ hipError_t launch_chain_table(const ChainDesc *d, int count, int nb, int mode, c
 
 hipError_t launch_chain(const ChainDesc *d, int count, int nb, hipStream_t st, hipEvent_t ev0,
                         hipEvent_t ev1) {
-  if (count < 1 || count > 4 || (nb != 2 && nb != 3)) return hipErrorInvalidValue;
+  if (count < 1 || count > 4) return hipErrorInvalidValue;
   ChainBatch b{};
   for (int i = 0; i < count; ++i) {
     if (!chain_ok(d[i], nb, 1)) return hipErrorInvalidValue;
     b.d[i] = d[i];
   }
-  return nb == 2 ? run(k_chain<2>, (unsigned)count, Chain<2>::kThreads, st, ev0, ev1, b)
-                 : run(k_chain<3>, (unsigned)count, Chain<3>::kThreads, st, ev0, ev1, b);
+  if (nb == 3) return run(k_chain<3>, (unsigned)count, Chain<3>::kThreads, st, ev0, ev1, b);
+  if (nb == 4) return run(k_chain<4>, (unsigned)count, Chain<4>::kThreads, st, ev0, ev1, b);
+  return run(k_chain<5>, (unsigned)count, Chain<5>::kThreads, st, ev0, ev1, b);
 }
 
 }  // namespace fps

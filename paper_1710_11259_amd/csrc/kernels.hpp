@@ -419,15 +419,17 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
 hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map, char *ws,
                              char *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
-// Chains of products on one LDS-resident block (chain.hip), blocks of up to S =
-// 32 nb (nb = 2, 3, 4).  The block X is in[r * in_rs + c * in_cs] for r < in_r, c <
-// in_c, zero beyond.  Matrix i is m[i][k * ld + output index], k[i] its inner length
-// (a multiple of 16, in modes 0, 2 and 3 of 32), n[i] its output length (up to S,
-// that of the last ones up to S + 2); ld covers n rounded up to the tiles that read
-// it: 32, or S + 16 past S.
+// Chains of products on one LDS-resident block (chain.hip).  The block X is in[r *
+// in_rs + c * in_cs] for r < in_r, c < in_c, zero beyond.  Matrix i is m[i][k * ld +
+// output index], k[i] its inner length (padded), n[i] its output length; ld covers n
+// rounded up to the tiles that read it.
+//   mode 1: m3^T (multiplier of m1^T X m0) m2; blocks of up to 64, outputs of up to
+//           16 nb (nb = 3, 4, 5); k multiples of 16, ld of n's next one.
+//   Modes 0, 2 and 3 with blocks of up to S = 32 nb (nb = 2, 3, 4), k multiples of 32,
+//   n of the last matrices up to S + 2 but in mode 0, ld at least n rounded up to 32,
+//   or S + 16 past S:
 //   mode 0: rows r0 .. r0 + chain_part(nb) of m1^T X m0, in_cs 2 and out_cs 1.
 //   mode 3: the same, in_cs 1 and out_cs 2; the last rows below S bring those past it.
-//   mode 1: m3^T (multiplier of m1^T X m0) m2.
 //   mode 2: m3^T (multiplier of m1^T X), up to chain_part(nb) columns.
 // The multiplier is that of GemmProb (mode 1: mr, mc, lr, lc; mode 2: mt with row
 // stride mt_rs), applied to rows < n[1], columns < n[0] (in_c).  The result goes to
@@ -444,7 +446,8 @@ struct ChainDesc {
   int ld[4], k[4], n[4];
   int ibase, obase, zoff;
 };
-// Blocks of up to `len` per side need nb = chain_size(len) (0: too large).
+// Slabs and strips of blocks of up to `len` per side need nb = chain_size(len) (0: too
+// large).
 inline int chain_size(int64_t len) { return len <= 64 ? 2 : len <= 96 ? 3 : len <= 128 ? 4 : 0; }
 constexpr int chain_part(int nb) { return nb >= 3 ? 32 : 64; }
 bool chain_ok(const ChainDesc &d, int nb, int mode);
@@ -454,7 +457,7 @@ void chain_order(std::vector<ChainDesc> &d, int group);
 hipError_t launch_chain_table(const ChainDesc *d, int count, int nb, int mode, const double *in,
                               char *ws, double *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                               hipEvent_t ev1 = nullptr);
-// Mode 1 on up to 4 blocks given by value (nb 2 or 3).
+// Mode 1 on up to 4 blocks given by value.
 hipError_t launch_chain(const ChainDesc *d, int count, int nb, hipStream_t st,
                         hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 

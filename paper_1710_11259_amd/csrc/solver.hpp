@@ -221,11 +221,15 @@ inline hipEvent_t next_event(const fps_plan *pl, int i) {
 // Lengths along which products run: rounded up to the k-tile (the arrays are
 // padded with zeros beyond).
 inline int64_t k_round(int64_t x) { return (x + 15) / 16 * 16; }
-// The blocks of a square or rectangle solve small enough for one launch of
-// chains (n <= kChainMax: its adjoint's blocks, of up to n / 2 + 2 entries, and
-// the four workgroups of a single solve still pay there): up to 4 (returns their count, 0 for larger plans) from F
-// (or the adjoint's cotangent) to U (Fbar); nb the block size.
-constexpr int64_t kChainMax = 128;
+// Squares and rectangles solved in one launch of chains: blocks, and inner lengths of
+// the products, of at most 64 (n <= 128; an adjoint's first products run over the
+// output's coefficients, so n <= 126 unless they are native).
+inline bool forward_chained(const fps_plan *pl) { return pl->L.m[0] <= 64; }
+inline bool adjoint_chained(const fps_plan *pl) {
+  return (pl->out_basis == FPS_OUT_NATIVE ? pl->L.m[0] : pl->L.mo[0]) <= 64;
+}
+// Their blocks: up to 4 (returns the count, 0 for other plans) from F (or the adjoint's
+// cotangent) to U (Fbar); nb for launch_chain.
 int solve_chain(const fps_plan *pl, const double *F, double *U, const double *lr, const double *lc,
                 fps::ChainDesc *d, int *nb);
 int adjoint_chain(const fps_plan *pl, const double *Ubar, double *Fbar, fps::ChainDesc *d, int *nb);
