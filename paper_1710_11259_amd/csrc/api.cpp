@@ -244,33 +244,49 @@ fps_status check_solve_args(fps_plan *pl, const void *a, const void *b, void *ws
   return FPS_OK;
 }
 
-// Y^_st = (Wi_s F_st Wi_t^T) o multiplier for the four parity blocks.
-int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2, const double *lr,
-              const double *lc) {
+namespace {
+
+// T_s = A_s X_s, X_s the rows of parity s of an array of N x N entries in natural order:
+// A_s [rows_s][row stride lda], T_s [rows_s][2 c0] with its even columns in the first
+// half, c0 = the even half's length rounded up.
+fps::GemmProb natural_product(const double *A, int64_t lda, int64_t rows, int64_t krows,
+                              const double *X, int64_t N, int s, double *T, int64_t c0) {
+  fps::GemmProb g{A, X + s * N, T, rows, 2 * c0, k_round(krows), lda, 1, 2 * N, 1, 2 * c0, 1};
+  g.split = c0;
+  g.cols = N;
+  g.krows = krows;
+  return g;
+}
+
+}  // namespace
+
+// Y^_st = (Wi_s F_st Wi_t^T) o multiplier for the four parity blocks, from F in natural
+// order: g1 (cnt1 products) by row parity, g2 (returned count) by block.  (A pass that
+// sorted F into the blocks first took 0.48 of 5.95 ms for a batch of 256, 5 of 97 us
+// at n = 1024.)
+int rhs_gemms(const fps_plan *pl, const double *F, char *ws, fps::GemmProb *g1, int *cnt1,
+              fps::GemmProb *g2, const double *lr, const double *lc) {
   const fps::Layout &L = pl->L;
-  const int64_t npad = L.npad;
+  const int64_t npad = L.npad, k0 = k_round(L.m[0]);
   double *G = (double *)(ws + pl->off_G);
-  const double *GT = (const double *)(ws + pl->off_GT);
-  double *Tb = (double *)(ws + pl->off_O0);
+  double *T = (double *)(ws + pl->off_O0);
   const double *mr = (const double *)pl->d_mr.p, *mc = (const double *)pl->d_mc.p;
   int cnt = 0;
-  int64_t toff = 0;
-  for (int s = 0; s < 2; ++s)
+  *cnt1 = 0;
+  for (int s = 0; s < 2; ++s) {
+    const int64_t ms = k_round(L.m[s]), rs = s * L.mp[0];
+    if (ms == 0) continue;
+    g1[(*cnt1)++] = natural_product((const double *)pl->d_Wi[s].p, L.mp[s], ms, L.m[s], F, L.n, s, T, k0);
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = k_round(L.m[s]), mt = k_round(L.m[t]), rs = s * L.mp[0], rt = t * L.mp[0];
-      if (ms == 0 || mt == 0) continue;
-      double *Tst = Tb + toff;
-      toff += ms * mt;
-      // T_st = F_st Wi_t^T
-      g1[cnt] = fps::GemmProb{GT + rs * npad + rt, (const double *)pl->d_WiT[t].p, Tst, ms, mt, mt,
-                              npad, 1, L.mp[t], 1, mt, 1};
-      // Y^_st = Wi_s T_st, multiplied
-      g2[cnt] = fps::GemmProb{(const double *)pl->d_Wi[s].p, Tst, G + rs * npad + rt, ms, mt, ms,
-                              L.mp[s], 1, mt, 1, npad, 1, 0, 0, nullptr, nullptr,
-                              mr + 2 * rs, mc + 2 * rt, lr ? lr + 4 * rs : nullptr,
-                              lc ? lc + 4 * rt : nullptr};
-      ++cnt;
+      const int64_t mt = k_round(L.m[t]), rt = t * L.mp[0];
+      if (mt == 0) continue;
+      g2[cnt++] = fps::GemmProb{T + t * k0, (const double *)pl->d_WiT[t].p, G + rs * npad + rt, ms, mt,
+                                mt, 2 * k0, 1, L.mp[t], 1, npad, 1, 0, 0, nullptr, nullptr,
+                                mr + 2 * rs, mc + 2 * rt, lr ? lr + 4 * rs : nullptr,
+                                lc ? lc + 4 * rt : nullptr};
     }
+    T += ms * 2 * k0;
+  }
   return cnt;
 }
 
@@ -414,9 +430,25 @@ static fps_status run_chain(fps_plan *pl, const fps::ChainDesc *d, int cnt, int 
   return FPS_OK;
 }
 
-// The whole 2-D solve on st: one launch of chains up to n = 128 (n = 64: 23 us in
-// five launches before), else F permuted into the GT region, the two input
-// products (with the multiplier), the two output products.  bc: Dirichlet
+// Whether a one-launch solve may write `out` while it reads `in`: no overlap, or the
+// same n x n array (every block then reads just the entries that it later writes).
+bool chain_in_out(const double *in, int64_t n_in, const double *out, int64_t n_out) {
+  const uintptr_t a = (uintptr_t)in, b = (uintptr_t)out;
+  return a + n_in * sizeof(double) <= b || b + n_out * sizeof(double) <= a ||
+         (a == b && n_in == n_out);
+}
+
+// n = 1 has no odd modes: the entries of the 3 x 3 U that no product writes.
+fps_status clear_n1(const fps_plan *pl, double *U, hipStream_t st) {
+  if (out_extent(pl) != 3) return FPS_OK;
+  FPS_HIP(fps::launch_fill(U + 1, 1, 0.0, st));
+  FPS_HIP(fps::launch_fill(U + 3, 3, 0.0, st));
+  FPS_HIP(fps::launch_fill(U + 7, 1, 0.0, st));
+  return FPS_OK;
+}
+
+// The whole 2-D solve on st: one launch of chains up to n = 128, else the two input
+// products (the multiplier in the second) and the two output products.  bc: Dirichlet
 // traces or null.
 fps_status solve_2d(fps_plan *pl, const double *F, const double *bc, double *U, char *w,
                     hipStream_t st) {
@@ -432,20 +464,20 @@ fps_status solve_2d(fps_plan *pl, const double *F, const double *bc, double *U, 
                                     pl->sy2, st));
   }
   const int64_t N = out_extent(pl);
-  if (L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N, 0.0, st));  // no odd modes: n = 1
   fps_status s;
   fps::ChainDesc chain[4];
   int nb = 0;
   int cnt = solve_chain(pl, F, U, lr, lc, chain, &nb);
-  if (cnt > 0) {
+  if (cnt > 0 && (L.n == 1 || chain_in_out(F, L.n * L.n, U, N * N))) {
     if ((s = run_chain(pl, chain, cnt, nb, st)) != FPS_OK) return s;
+    if (L.n == 1 && (s = clear_n1(pl, U, st)) != FPS_OK) return s;
     if (bc) FPS_HIP(fps::launch_bc_lift_out(U, bc, corner, L.n, st));
     return FPS_OK;
   }
-  FPS_HIP(fps::launch_permute_in(F, (double *)(w + pl->off_GT), L.n, L.npad, L.mp[0], st));
   fps::GemmProb g1[4], g2[4];
-  cnt = rhs_gemms(pl, w, g1, g2, lr, lc);
-  if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
+  int cnt1 = 0;
+  cnt = rhs_gemms(pl, F, w, g1, &cnt1, g2, lr, lc);
+  if ((s = run_products(pl, g1, cnt1, st)) != FPS_OK) return s;
   if ((s = run_products(pl, g2, cnt, st)) != FPS_OK) return s;
   cnt = out_gemms(pl, U, w, g1, g2);
   if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
@@ -885,40 +917,34 @@ namespace detail {
 // multiplier is the same (diagonal in the eigenbasis), so the cotangent goes
 // through Wo^T, the multiplier and Wi^T.
 //
-// Ybar^_st = (Wo_s^T Ubar_st Wo_t) o multiplier, from Ubar in the
-// parity-blocked layout (X region), into G.
-int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *g2) {
+// Ybar^_st = (Wo_s^T Ubar_st Wo_t) o multiplier, from Ubar in natural order, into G.
+int adj_in_gemms(const fps_plan *pl, const double *Ubar, char *w, fps::GemmProb *g1, int *cnt1,
+                 fps::GemmProb *g2) {
   const fps::Layout &L = pl->L;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
   const int64_t *mo = native ? L.m : L.mo, *mop = native ? L.mp : pl->mop;
-  const int64_t npad = L.npad, mo0 = mop[0], mobar = mop[0] + mop[1];
-  const double *Up = (const double *)(w + pl->off_X);
+  const int64_t npad = L.npad, k0 = k_round(mo[0]);
   const double *mr = (const double *)pl->d_mr.p, *mc = (const double *)pl->d_mc.p;
   double *G = (double *)(w + pl->off_G);
-  double *Tt = (double *)(w + pl->off_O0);  // temporaries mop_s x mp_t
+  double *T = (double *)(w + pl->off_O0);
   int cnt = 0;
-  int64_t toff = 0;
-  for (int s2 = 0; s2 < 2; ++s2)
+  *cnt1 = 0;
+  for (int s = 0; s < 2; ++s) {
+    const int64_t ms = k_round(L.m[s]), rs = s * L.mp[0];
+    if (L.m[s] == 0) continue;
+    fps::GemmProb &g = g1[(*cnt1)++];
+    g = natural_product((const double *)pl->d_WoT[s].p, mop[s], ms, mo[s], Ubar, out_extent(pl), s, T, k0);
+    limit_k(g, 1, pl->khi[s], pl->d_khi[s], 1);
     for (int t = 0; t < 2; ++t) {
-      const int64_t ms = k_round(L.m[s2]), mt = k_round(L.m[t]);
-      const int64_t mos = k_round(mo[s2]), mot = k_round(mo[t]);
-      const int64_t rs = s2 * L.mp[0], rt = t * L.mp[0];
-      if (L.m[s2] == 0 || L.m[t] == 0) continue;
-      double *Tst = Tt + toff;
-      toff += mos * mt;
-      g1[cnt] = fps::GemmProb{Up + (s2 * mo0) * mobar + t * mo0, (const double *)pl->d_Wo[t].p,
-                              Tst, mos, mt, mot, mobar, 1, L.mp[t], 1, mt, 1};
-      if (fps::gemm_has_edge(mo[s2])) {  // rows mo .. mos - 1 are zero: cleared
-        g1[cnt].M = mo[s2];
-        g1[cnt].Mz = mos;
-      }
-      g2[cnt] = fps::GemmProb{(const double *)pl->d_WoT[s2].p, Tst, G + rs * npad + rt, ms, mt, mos,
-                              mop[s2], 1, mt, 1, npad, 1, 0, 0, nullptr, nullptr, mr + 2 * rs,
-                              mc + 2 * rt, nullptr, nullptr};
-      limit_k(g1[cnt], 2, pl->khi[t], pl->d_khi[t], 1);
-      limit_k(g2[cnt], 1, pl->khi[s2], pl->d_khi[s2], 1);
-      ++cnt;
+      const int64_t mt = k_round(L.m[t]), rt = t * L.mp[0];
+      if (L.m[t] == 0) continue;
+      g2[cnt] = fps::GemmProb{T + t * k0, (const double *)pl->d_Wo[t].p, G + rs * npad + rt, ms, mt,
+                              k_round(mo[t]), 2 * k0, 1, L.mp[t], 1, npad, 1, 0, 0, nullptr, nullptr,
+                              mr + 2 * rs, mc + 2 * rt, nullptr, nullptr};
+      limit_k(g2[cnt++], 2, pl->khi[t], pl->d_khi[t], 1);
     }
+    T += ms * 2 * k0;
+  }
   return cnt;
 }
 
@@ -958,17 +984,15 @@ fps_status fps_solve_adjoint(fps_plan *pl, const double *Ubar, double *Fbar, voi
     return fail(FPS_E_UNSUPPORTED, "adjoint: square FP64 plans only");
   hipStream_t st = (hipStream_t)stream;
   char *w = (char *)ws;
-  const fps::Layout &L = pl->L;
-  const bool native = pl->out_basis == FPS_OUT_NATIVE;
-  const int64_t *mop = native ? L.mp : pl->mop;
+  const int64_t n = pl->L.n, N = out_extent(pl);
   fps::ChainDesc chain[4];
   int nb = 0;
-  if (const int c = adjoint_chain(pl, Ubar, Fbar, chain, &nb)) return run_chain(pl, chain, c, nb, st);
-  FPS_HIP(fps::launch_permute_in(Ubar, (double *)(w + pl->off_X), out_extent(pl), mop[0] + mop[1],
-                                 mop[0], st));
+  if (n == 1 || chain_in_out(Ubar, N * N, Fbar, n * n))
+    if (const int c = adjoint_chain(pl, Ubar, Fbar, chain, &nb)) return run_chain(pl, chain, c, nb, st);
   fps::GemmProb g1[4], g2[4];
-  int cnt = adj_in_gemms(pl, w, g1, g2);
-  if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;
+  int cnt1 = 0;
+  int cnt = adj_in_gemms(pl, Ubar, w, g1, &cnt1, g2);
+  if ((s = run_products(pl, g1, cnt1, st)) != FPS_OK) return s;
   if ((s = run_products(pl, g2, cnt, st)) != FPS_OK) return s;
   cnt = adj_out_gemms(pl, Fbar, w, g1, g2);
   if ((s = run_products(pl, g1, cnt, st)) != FPS_OK) return s;

@@ -38,15 +38,9 @@ struct fps_batch {
   DeviceBuf d_gd[8], d_gmap[8];
   fps::GemmTable gt[8];
   // the problems small enough for chains (forward 0, adjoint 1): one
-  // launch each; the products and permutations below hold the others
+  // launch each; the products hold the others
   DeviceBuf d_chain[2];
   int nchain[2] = {0, 0}, chain_nb[2] = {3, 3};
-  // the permutations of F (0) and of the adjoint's cotangent (1) as one
-  // launch each (elem_ok; else, for very large batches, one per problem)
-  bool elem_ok = false;
-  DeviceBuf d_ed[2], d_emap[2];
-  int ewg[2] = {0, 0};
-
   ~fps_batch() {
     for (fps_plan *p : sub) fps_plan_destroy(p);
   }
@@ -56,9 +50,6 @@ struct fps_batch {
 namespace {
 
 bool valid_batch(const fps_batch *b) { return b != nullptr && b->magic == kBatchMagic; }
-
-// Whether the plan's solves (t 0) or adjoints (1) run as chains.
-bool chained(const fps_plan *pl, int t) { return t ? adjoint_chained(pl) : forward_chained(pl); }
 
 fps_status run_chains(const fps_batch *bt, int t, const double *in, double *out, hipStream_t st) {
   FPS_HIP(fps::launch_chain_table((const fps::ChainDesc *)bt->d_chain[t].p, bt->nchain[t],
@@ -91,21 +82,21 @@ fps_status build_gemm_tables(fps_batch *bt) {
       }
       if (c > 0) bt->chain_nb[t] = std::max(bt->chain_nb[t], nb);
     }
-    const bool fwd = !chained(pl, 0), adj = !refined && !chained(pl, 1);
-    const int c_in = fwd ? rhs_gemms(pl, wsyn, g[0], g[1]) : 0;
-    const int c_out = fwd ? out_gemms(pl, Usyn, wsyn, g[2], g[3]) : 0;
-    const int c_ain = adj ? adj_in_gemms(pl, wsyn, g[4], g[5]) : 0;
-    const int c_aout = adj ? adj_out_gemms(pl, Fsyn, wsyn, g[6], g[7]) : 0;
-    // base ids (A, B, C): ws-relative 1, absolute 0, output-relative 2
-    static const int ids[8][3] = {{1, 0, 1}, {0, 1, 1}, {1, 0, 1}, {0, 1, 2},
-                                  {1, 0, 1}, {0, 1, 1}, {1, 0, 1}, {0, 1, 2}};
-    const int counts[8] = {c_in, c_in, c_out, c_out, c_ain, c_ain, c_aout, c_aout};
-    for (int t = 0; t < 8; ++t) {
-      const int cnt = counts[t];
-      for (int i = 0; i < cnt; ++i) {
-        tab[t].push_back(fps::GemmDesc{g[t][i], ids[t][0], ids[t][1], ids[t][2]});
-      }
+    int counts[8] = {};
+    if (!forward_chained(pl)) {
+      counts[1] = rhs_gemms(pl, Fsyn, wsyn, g[0], &counts[0], g[1]);
+      counts[2] = counts[3] = out_gemms(pl, Usyn, wsyn, g[2], g[3]);
     }
+    if (!refined && !adjoint_chained(pl)) {
+      counts[5] = adj_in_gemms(pl, Usyn, wsyn, g[4], &counts[4], g[5]);
+      counts[6] = counts[7] = adj_out_gemms(pl, Fsyn, wsyn, g[6], g[7]);
+    }
+    // base ids (A, B, C): absolute 0, relative to ws 1, to the output 2, to the input 3
+    static const int ids[8][3] = {{0, 3, 1}, {1, 0, 1}, {1, 0, 1}, {0, 1, 2},
+                                  {0, 3, 1}, {1, 0, 1}, {1, 0, 1}, {0, 1, 2}};
+    for (int t = 0; t < 8; ++t)
+      for (int i = 0; i < counts[t]; ++i)
+        tab[t].push_back(fps::GemmDesc{g[t][i], ids[t][0], ids[t][1], ids[t][2]});
   }
   for (int t = 0; t < 2; ++t) {
     for (const fps::ChainDesc &e : chain[t])
@@ -126,68 +117,57 @@ fps_status build_gemm_tables(fps_batch *bt) {
   return FPS_OK;
 }
 
-// Tables of the batched permutations (sorted order, largest problems first).
-// Left unbuilt (elem_ok false) when a launch would not fit one 1-D grid of
-// 256-thread workgroups (elem_launch_fits); such batches keep the per-problem
-// launches.
-fps_status build_elem_tables(fps_batch *bt) {
-  std::vector<fps::ElemDesc> ed[2];
-  std::vector<int> map[2];
-  for (int k = 0; k < bt->count; ++k) {
-    const int b = bt->order[k];
-    const fps_plan *pl = bt->plan_of(b);
-    const fps::Layout &L = pl->L;
-    const bool native = bt->out_basis == FPS_OUT_NATIVE;
-    const int64_t *mop = native ? L.mp : pl->mop;
-    for (int t = 0; t < 2; ++t) {
-      if (chained(pl, t)) continue;
-      fps::ElemDesc e{};
-      e.n = t ? out_extent(pl) : L.n;
-      e.npad = t ? mop[0] + mop[1] : L.npad;
-      e.mp0 = t ? mop[0] : L.mp[0];
-      e.src = (t ? bt->u_off[b] : bt->f_off[b]) * (int64_t)sizeof(double);
-      e.sbase = 2;
-      e.dst = bt->ws_off[b] + (t ? pl->off_X : pl->off_GT);
-      e.dbase = 1;
-      e.nbx = (int)((e.npad + 255) / 256);
-      const int64_t nwg = (int64_t)e.nbx * e.npad;
-      if (!fps::elem_launch_fits((int64_t)map[t].size() + nwg)) return FPS_OK;
-      e.wg_start = (int)map[t].size();
-      map[t].insert(map[t].end(), (size_t)nwg, (int)ed[t].size());
-      ed[t].push_back(e);
+// All stages (t 0: of the solve, 1: of the adjoint) in place of the tables where `in`
+// and `out` overlap: every problem's input is consumed before any output is
+// written, one launch per problem and stage.
+fps_status run_overlapping(const fps_batch *bt, int t, const double *in, double *out, char *w,
+                           hipStream_t st) {
+  for (int stage = 0; stage < 4; ++stage)
+    for (int b = 0; b < bt->count; ++b) {
+      const fps_plan *pl = bt->plan_of(b);
+      char *wb = w + bt->ws_off[b];
+      const double *x = in + (t ? bt->u_off[b] : bt->f_off[b]);
+      double *y = out + (t ? bt->f_off[b] : bt->u_off[b]);
+      fps::GemmProb g[4][4];
+      int cnt[4] = {};
+      if (pl->n == 1) {  // its one block: the input kept in the workspace until the end
+        const int64_t n = t ? out_extent(pl) : 1;
+        double *keep = (double *)(wb + pl->off_GT);
+        if (stage == 0) FPS_HIP(hipMemcpyAsync(keep, x, n * n * 8, hipMemcpyDeviceToDevice, st));
+        if (stage < 3) continue;
+        fps::ChainDesc d[4];
+        int nb = 0;
+        const int c = t ? adjoint_chain(pl, keep, y, d, &nb)
+                        : solve_chain(pl, keep, y, nullptr, nullptr, d, &nb);
+        FPS_HIP(fps::launch_chain(d, c, nb, st));
+        const fps_status s = t ? FPS_OK : clear_n1(pl, y, st);
+        if (s != FPS_OK) return s;
+        continue;
+      }
+      if (t == 0) {
+        cnt[1] = rhs_gemms(pl, x, wb, g[0], &cnt[0], g[1]);
+        cnt[2] = cnt[3] = out_gemms(pl, y, wb, g[2], g[3]);
+      } else {
+        cnt[1] = adj_in_gemms(pl, x, wb, g[0], &cnt[0], g[1]);
+        cnt[2] = cnt[3] = adj_out_gemms(pl, y, wb, g[2], g[3]);
+      }
+      FPS_HIP(fps::launch_gemm(g[stage], cnt[stage], st));
     }
-  }
-  fps_status s;
-  for (int t = 0; t < 2; ++t) {
-    bt->ewg[t] = (int)map[t].size();
-    if ((s = upload(bt->d_ed[t], ed[t])) != FPS_OK || (s = upload(bt->d_emap[t], map[t])) != FPS_OK)
-      return s;
-  }
-  bt->elem_ok = true;
   return FPS_OK;
 }
 
-// The permutation of every problem's F (t = 0, into its GT region) or output
-// cotangent (t = 1, into its X region).
-fps_status permute_all(const fps_batch *bt, int t, const double *in, char *w, hipStream_t st) {
-  if (bt->elem_ok) {
-    FPS_HIP(fps::launch_permute_in_batch((const fps::ElemDesc *)bt->d_ed[t].p,
-                                         (const int *)bt->d_emap[t].p, bt->ewg[t], in, w, st));
-    return FPS_OK;
-  }
-  for (int b = 0; b < bt->count; ++b) {
-    const fps_plan *pl = bt->plan_of(b);
-    if (chained(pl, t)) continue;
-    const fps::Layout &L = pl->L;
-    const int64_t *mop = bt->out_basis == FPS_OUT_NATIVE ? L.mp : pl->mop;
-    char *wb = w + bt->ws_off[b];
-    if (t == 0)
-      FPS_HIP(fps::launch_permute_in(in + bt->f_off[b], (double *)(wb + pl->off_GT), L.n, L.npad,
-                                     L.mp[0], st));
-    else
-      FPS_HIP(fps::launch_permute_in(in + bt->u_off[b], (double *)(wb + pl->off_X), out_extent(pl),
-                                     mop[0] + mop[1], mop[0], st));
-  }
+// Enqueues the solve's (t 0) or the adjoint's (1) launches.
+fps_status run_batch(const fps_batch *bt, int t, const double *in, double *out, char *w,
+                     hipStream_t st) {
+  const int64_t n_in = t ? bt->out_entries : bt->in_entries;
+  const int64_t n_out = t ? bt->in_entries : bt->out_entries;
+  if (!chain_in_out(in, n_in, out, n_out)) return run_overlapping(bt, t, in, out, w, st);
+  if (t == 0 && bt->has_n1 && n_in != n_out) FPS_HIP(fps::launch_fill(out, n_out, 0.0, st));
+  const fps_status s = run_chains(bt, t, in, out, st);
+  if (s != FPS_OK) return s;
+  for (int i = 4 * t; i < 4 * t + 4; ++i)
+    FPS_HIP(fps::launch_gemm_table(bt->gt[i], (const fps::GemmDesc *)bt->d_gd[i].p,
+                                   (const int *)bt->d_gmap[i].p, in, w, (char *)out, st));
   return FPS_OK;
 }
 
@@ -258,8 +238,7 @@ fps_status fps_batch_create(fps_batch **out, int dim, int count, const int64_t *
     bt->has_n1 = bt->has_n1 || pl->n == 1;
   }
   if (!(flags & FPS_PLAN_HOST_ONLY)) {
-    fps_status s = build_gemm_tables(bt);
-    if (s == FPS_OK) s = build_elem_tables(bt);
+    const fps_status s = build_gemm_tables(bt);
     if (s != FPS_OK) {
       delete bt;
       return s;
@@ -286,15 +265,7 @@ fps_status fps_batch_solve(fps_batch *bt, const double *F, double *U, void *ws, 
   if (!F || !U || !ws) return fail(FPS_E_ARG, "null pointer argument");
   if (((uintptr_t)ws) % 256 != 0) return fail(FPS_E_ARG, "workspace must be 256-byte aligned");
   hipStream_t st = (hipStream_t)stream;
-  char *w = (char *)ws;
-  fps_status s;
-  if ((s = permute_all(bt, 0, F, w, st)) != FPS_OK) return s;
-  if (bt->has_n1) FPS_HIP(fps::launch_fill(U, bt->out_entries, 0.0, st));
-  if ((s = run_chains(bt, 0, F, U, st)) != FPS_OK) return s;
-  for (int t = 0; t < 4; ++t)
-    FPS_HIP(fps::launch_gemm_table(bt->gt[t], (const fps::GemmDesc *)bt->d_gd[t].p,
-                                   (const int *)bt->d_gmap[t].p, w, (char *)U, st));
-  return FPS_OK;
+  return run_batch(bt, 0, F, U, (char *)ws, st);
 }
 
 fps_status fps_batch_solve_adjoint(fps_batch *bt, const double *Ubar, double *Fbar, void *ws,
@@ -305,14 +276,7 @@ fps_status fps_batch_solve_adjoint(fps_batch *bt, const double *Ubar, double *Fb
   if (((uintptr_t)ws) % 256 != 0) return fail(FPS_E_ARG, "workspace must be 256-byte aligned");
   if (bt->prec != FPS_FP64) return fail(FPS_E_UNSUPPORTED, "batched adjoint: FP64 batches only");
   hipStream_t st = (hipStream_t)stream;
-  char *w = (char *)ws;
-  fps_status s;
-  if ((s = permute_all(bt, 1, Ubar, w, st)) != FPS_OK) return s;
-  if ((s = run_chains(bt, 1, Ubar, Fbar, st)) != FPS_OK) return s;
-  for (int t = 4; t < 8; ++t)
-    FPS_HIP(fps::launch_gemm_table(bt->gt[t], (const fps::GemmDesc *)bt->d_gd[t].p,
-                                   (const int *)bt->d_gmap[t].p, w, (char *)Fbar, st));
-  return FPS_OK;
+  return run_batch(bt, 1, Ubar, Fbar, (char *)ws, st);
 }
 
 void fps_batch_destroy(fps_batch *bt) {

@@ -83,7 +83,8 @@ fps_status launch_probs(fps_plan *pl, const std::vector<fps::GemmProb> &probs, h
 fps_status run_table(fps_plan *pl, const fps::GemmTable &g, const DeviceBuf &d, const DeviceBuf &map,
                      char *w, char *out, hipStream_t st) {
   hipEvent_t e0 = next_event(pl, 0), e1 = next_event(pl, 1);
-  FPS_HIP(fps::launch_gemm_table(g, (const fps::GemmDesc *)d.p, (const int *)map.p, w, out, st, e0, e1));
+  FPS_HIP(fps::launch_gemm_table(g, (const fps::GemmDesc *)d.p, (const int *)map.p, nullptr, w, out, st,
+                                 e0, e1));
   if (e0) ++pl->ev_used;
   return FPS_OK;
 }
@@ -441,8 +442,9 @@ fps_status cube_solve(fps_plan *pl, const double *F, double *U, char *w, hipStre
   fps_status s;
   if (pl->cnb > 0) {
     const int64_t N = out_extent(pl);
-    if (L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N * N, 0.0, st));  // no odd modes: n = 1
     for (int t = 0; t < 3; ++t) {
+      // no odd modes (n = 1): parts of U that no chain writes (F is read by now)
+      if (t == 1 && L.m[1] == 0) FPS_HIP(fps::launch_fill(U, N * N * N, 0.0, st));
       hipEvent_t e0 = next_event(pl, 0), e1 = next_event(pl, 1);
       FPS_HIP(fps::launch_chain_table((const fps::ChainDesc *)pl->d_cchain[t].p, pl->cchain_count[t],
                                       pl->cnb, kChainMode[t], F, w, U, st, e0, e1));

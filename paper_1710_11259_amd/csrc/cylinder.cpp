@@ -554,7 +554,7 @@ fps_status cyl_solve(fps_plan *pl, const double *F, double *U, char *w, hipStrea
   }
   // 3. r map: X0[rp block] = R_g X1[rp block]
   FPS_HIP(fps::launch_gemm_table(c->t_in, (const fps::GemmDesc *)c->d_tin.p,
-                                 (const int *)c->d_tin_map.p, w, nullptr, st));
+                                 (const int *)c->d_tin_map.p, nullptr, w, nullptr, st));
   // 4. banded solves: X1[wp block] = yhat
   FPS_HIP(solve());
   // 5. z output map: X0 [slot][part][r][zout] = X1 W_out
@@ -568,7 +568,7 @@ fps_status cyl_solve(fps_plan *pl, const double *F, double *U, char *w, hipStrea
   // 6. r output map into U (rows of the other parity stay zero)
   FPS_HIP(fps::launch_fill(U, nt * 2 * (n + 4) * (n + 2), 0.0, st));
   FPS_HIP(fps::launch_gemm_table(c->t_out, (const fps::GemmDesc *)c->d_tout.p,
-                                 (const int *)c->d_tout_map.p, w, (char *)U, st));
+                                 (const int *)c->d_tout_map.p, nullptr, w, (char *)U, st));
   return FPS_OK;
 }
 

@@ -31,6 +31,7 @@ namespace {
 // padding.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
 
 // order: tile dispatch order (0: natural; 1 / 2: column tile slowest,
 // ascending / descending; 3 / 4: row tile slowest, ascending / descending), so
@@ -43,6 +44,11 @@ struct GemmBatch {
 };
 
 constexpr int kGroup = kGemmGroup, kBK = 16;
+
+// Kinds of products, one per launch: plain; with the eigenbasis multiplier in the
+// epilogue; of an array in natural order (GemmProb's split), whose rows past the
+// last and whose parity-blocked result cost the plain ones registers.
+enum { kPlain = 0, kMul = 1, kNatural = 2 };
 
 // Extent covered by MFMA tiles: the 1 to 4 rows or columns past a multiple of 32
 // (the output maps have n/2 + 1) would cost a row of almost empty tiles, so
@@ -114,7 +120,7 @@ struct Tile {
 };
 
 // One T x T output tile at (i0, j0) of problem g.
-template <int T, bool kMul>
+template <int T, int kKind>
 __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, const int64_t j0,
                                           double *lds) {
   constexpr int BK = kBK;
@@ -141,22 +147,34 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
   const int64_t arow = i0 + ar < g.M ? i0 + ar : g.M - 1;
   const double *__restrict__ Ap = g.A + arow * g.sai + klo + ak;
   const double *__restrict__ Bp = g.B + (klo + bk) * g.sbk;
-  const int64_t jlast = (g.N - 1) & ~(int64_t)1;  // row strides are even: the pair exists
-  int bcol[QB];
+  // (row strides are even: the pair exists; natural rows may end within one, then
+  // the pair before holds its first column)
+  const int64_t jlast = kKind == kNatural ? g.cols - 2 : (g.N - 1) & ~(int64_t)1;
+  int bcol[QB], brow = (int)klo + bk;
+  bool late[QB];
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
     const int64_t j = j0 + bc + 2 * TB * q;
     bcol[q] = (int)(j < jlast ? j : jlast);
+    late[q] = kKind == kNatural && j > jlast;
   }
 
   dbl2 ra[2][RA / 2], rb[2][QB];
   auto fetch = [&](int r) {
 #pragma unroll
     for (int q = 0; q < RA / 2; ++q) ra[r][q] = *(const dbl2 *)(Ap + 2 * q);
+    if constexpr (kKind == kNatural) {
+      // rows past the last are clamped too: A is zero there
+      const double *Bn = g.B + (brow < (int)g.krows ? brow : (int)g.krows - 1) * g.sbk;
 #pragma unroll
-    for (int q = 0; q < QB; ++q) rb[r][q] = *(const dbl2 *)(Bp + bcol[q]);
+      for (int q = 0; q < QB; ++q) rb[r][q] = *(const dbl2u *)(Bn + bcol[q]);
+      brow += BK;
+    } else {
+#pragma unroll
+      for (int q = 0; q < QB; ++q) rb[r][q] = *(const dbl2 *)(Bp + bcol[q]);
+      Bp += BK * g.sbk;
+    }
     Ap += BK;
-    Bp += BK * g.sbk;
   };
   auto stash = [&](double *st, int r) {
     double *Ad = st + ar * (BK + 1) + ak;
@@ -167,7 +185,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
       Ad[2 * q + 1] = ra[r][q].y;
     }
 #pragma unroll
-    for (int q = 0; q < QB; ++q) *(dbl2 *)(Bd + 2 * TB * q) = rb[r][q];
+    for (int q = 0; q < QB; ++q) {
+      if (kKind == kNatural && late[q]) rb[r][q].x = rb[r][q].y;
+      *(dbl2 *)(Bd + 2 * TB * q) = rb[r][q];
+    }
   };
 
   dbl4 acc[NB][NB];
@@ -240,8 +261,12 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
       for (int r = 0; r < 4; ++r) {
         const int64_t gi = i0 + wy * W + a * 16 + 4 * r + (lane >> 4);
         const int64_t gj = j0 + wx * W + b * 16 + (lane & 15);
-        if (gi < Mm && gj < Nm)
-          g.C[gi * g.sci + gj * g.scj] = kMul ? multiply(g, gi, gj, acc[a][b][r]) : acc[a][b][r];
+        if (gi >= Mm || gj >= Nm) continue;
+        const double v = acc[a][b][r];
+        if constexpr (kKind == kNatural)
+          g.C[gi * g.sci + (gj & 1) * g.split + (gj >> 1)] = gj < g.cols ? v : 0.0;
+        else
+          g.C[gi * g.sci + gj * g.scj] = kKind == kMul ? multiply(g, gi, gj, v) : v;
       }
 }
 
@@ -350,23 +375,24 @@ __device__ __forceinline__ void gemm_edge(const GemmProb &g, int unit, double *l
 
 // Plain products allocate 52 KB, three workgroups per compute unit: four run in
 // step, their first and last k-tiles at the same time (n = 2048: 155 against
-// 141 us per launch).
-template <int T, bool kMul>
+// 141 us per launch).  The products with longer loops or epilogues drift apart by
+// themselves (natural order, n = 4096: 3.65 ms a solve with four, 3.70 with three).
+template <int T, int kKind>
 constexpr int lds_doubles() {
-  return T == 64 && !kMul ? 52 * 128 : Tile<T>::kLds;
+  return T == 64 && kKind == kPlain ? 52 * 128 : Tile<T>::kLds;
 }
 
-template <int T, bool kMul>
+template <int T, int kKind>
 __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
-  __shared__ __align__(16) double lds[lds_doubles<T, kMul>()];
+  __shared__ __align__(16) double lds[lds_doubles<T, kKind>()];
   int L = blockIdx.x;
-  if (!kMul && L < batch.nedge) {
+  if (kKind == kPlain && L < batch.nedge) {
     const int per = batch.nedge / batch.count;
     const GemmProb &g = batch.p[L / per];
     if (L % per < edge_units(g)) gemm_edge(g, L % per, lds);
     return;
   }
-  if (!kMul) L -= batch.nedge;
+  if (kKind == kPlain) L -= batch.nedge;
   const int nt = batch.nt, mt = batch.mt, nz = batch.count;
   int bx, by, z;
   if (batch.order == 0) {
@@ -384,46 +410,49 @@ __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
     z = rem / nt;
     bx = rem % nt;
   }
-  gemm_tile<T, kMul>(batch.p[z], (int64_t)by * T, (int64_t)bx * T, lds);
+  gemm_tile<T, kKind>(batch.p[z], (int64_t)by * T, (int64_t)bx * T, lds);
 }
 
 // Table-driven GEMM: workgroup g computes unit tile_map[2g + 1] of problem
 // tile_map[2g]: its tiles row by row (ntx per row), then its edge units.
 // Operand pointers are rebased per GemmDesc base ids.
-__device__ __forceinline__ const double *rebase(const double *p, int id, char *ws, char *out) {
-  return id == 1 ? (const double *)(ws + (intptr_t)p)
-                 : id == 2 ? (const double *)(out + (intptr_t)p) : p;
+__device__ __forceinline__ const double *rebase(const double *p, int id, char *ws, char *out,
+                                                const char *in) {
+  const char *at = id == 1 ? ws : id == 2 ? out : in;
+  return id == 0 ? p : (const double *)(at + (intptr_t)p);
 }
 
-template <int T, bool kMul>
+template <int T, int kKind>
 __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restrict__ d,
                                                        const int *__restrict__ tile_map, char *ws,
-                                                       char *out) {
-  __shared__ __align__(16) double lds[lds_doubles<T, kMul>()];
+                                                       char *out, const char *in) {
+  __shared__ __align__(16) double lds[lds_doubles<T, kKind>()];
   const int k = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x]);
   const int local = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x + 1]);
   const GemmDesc &e = d[k];
   GemmProb g = e.p;
-  g.A = as_global(rebase(g.A, e.abase, ws, out));
-  g.B = as_global(rebase(g.B, e.bbase, ws, out));
-  g.C = as_global((double *)rebase(g.C, e.cbase, ws, out));
+  g.A = as_global(rebase(g.A, e.abase, ws, out, in));
+  g.B = as_global(rebase(g.B, e.bbase, ws, out, in));
+  g.C = as_global((double *)rebase(g.C, e.cbase, ws, out, in));
   g.klim = as_global(g.klim);
   g.mr = as_global(g.mr);
   g.mc = as_global(g.mc);
   g.lr = as_global(g.lr);
   g.lc = as_global(g.lc);
   g.mt = as_global(g.mt);
-  if (!kMul && local >= e.ntiles)
+  if (kKind == kPlain && local >= e.ntiles)
     gemm_edge(g, local - e.ntiles, lds);
   else
-    gemm_tile<T, kMul>(g, (int64_t)(local / e.ntx) * T, (int64_t)(local % e.ntx) * T, lds);
+    gemm_tile<T, kKind>(g, (int64_t)(local / e.ntx) * T, (int64_t)(local % e.ntx) * T, lds);
 }
 
 }  // namespace
 
 namespace {
 
-bool has_mul(const GemmProb &q) { return q.mr != nullptr || q.mt != nullptr; }
+int kind_of(const GemmProb &q) {
+  return q.split > 0 ? kNatural : q.mr != nullptr || q.mt != nullptr ? kMul : kPlain;
+}
 
 // Tile of a set of problems.  32 x 32 where 64 x 64 tiles would be too few for
 // the 256 compute units to hide a workgroup's serial chain of k-tiles (measured
@@ -447,21 +476,32 @@ int pick_tile(int64_t count, Get get) {
 }  // namespace
 
 bool gemm_operands_ok(const GemmProb &q) {
-  return q.sak == 1 && q.sbj == 1 && q.K % 16 == 0 && !(q.sai & 1) && !(q.sbk & 1) &&
-         !((uintptr_t)q.A & 15) && !((uintptr_t)q.B & 15) && q.M >= 1 && q.N >= 1 &&
-         !(has_mul(q) && (main_extent(q.M) != q.M || main_extent(q.N) != q.N));
+  const int kind = kind_of(q);
+  if (q.sak != 1 || q.sbj != 1 || q.K % 16 != 0 || (q.sai & 1) || ((uintptr_t)q.A & 15) || q.M < 1 ||
+      q.N < 1)
+    return false;
+  if (kind != kPlain && (main_extent(q.M) != q.M || main_extent(q.N) != q.N)) return false;
+  if (kind == kNatural)
+    return q.mr == nullptr && q.mt == nullptr && q.cols >= 2 && q.cols <= q.N && q.N % 2 == 0 &&
+           q.krows >= 1 && q.krows <= q.K && !((uintptr_t)q.B & 7);
+  return !(q.sbk & 1) && !((uintptr_t)q.B & 15);
 }
 
-hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map, char *ws,
-                             char *out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map,
+                             const double *in, char *ws, char *out, hipStream_t st, hipEvent_t ev0,
+                             hipEvent_t ev1) {
   if (t.units <= 0) return hipSuccess;
-  auto kern = t.mul ? k_gemm_table<64, true> : k_gemm_table<64, false>;
-  if (t.T == 32) kern = t.mul ? k_gemm_table<32, true> : k_gemm_table<32, false>;
+  auto kern = t.kind == kMul ? k_gemm_table<64, kMul>
+                             : t.kind == kNatural ? k_gemm_table<64, kNatural> : k_gemm_table<64, kPlain>;
+  if (t.T == 32)
+    kern = t.kind == kMul ? k_gemm_table<32, kMul>
+                          : t.kind == kNatural ? k_gemm_table<32, kNatural> : k_gemm_table<32, kPlain>;
   if (ev0 != nullptr)
     hipExtLaunchKernelGGL(kern, dim3((unsigned)t.units), dim3(256), 0, st, ev0, ev1, 0, d, tile_map,
-                          ws, out);
+                          ws, out, (const char *)in);
   else
-    hipLaunchKernelGGL(kern, dim3((unsigned)t.units), dim3(256), 0, st, d, tile_map, ws, out);
+    hipLaunchKernelGGL(kern, dim3((unsigned)t.units), dim3(256), 0, st, d, tile_map, ws, out,
+                       (const char *)in);
   return hipGetLastError();
 }
 
@@ -469,7 +509,7 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
   map.clear();
   t = GemmTable{};
   if (tab.empty()) return true;
-  t.mul = has_mul(tab[0].p);
+  t.kind = kind_of(tab[0].p);
   t.T = pick_tile((int64_t)tab.size(), [&](int64_t i) -> const GemmProb & { return tab[(size_t)i].p; });
   // Problem by problem, the one with the longest tiles first (workgroups start in
   // id order, so the short tiles fill the tail, and the tiles in flight share
@@ -485,7 +525,7 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
   for (size_t k = 0; k < tab.size(); ++k) {
     GemmDesc &e = tab[k];
     by[k] = (int)k;
-    if (!gemm_operands_ok(e.p) || has_mul(e.p) != t.mul) return false;
+    if (!gemm_operands_ok(e.p) || kind_of(e.p) != t.kind) return false;
     const int64_t ntx = (main_extent(e.p.N) + t.T - 1) / t.T, nty = (main_extent(e.p.M) + t.T - 1) / t.T;
     e.ntx = (int)ntx;
     e.ntiles = (int)(ntx * nty);
@@ -496,7 +536,7 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
       u.push_back(Unit{khi - klo, l});
     }
     std::stable_sort(u.begin(), u.end(), [](const Unit &a, const Unit &b) { return a.work > b.work; });
-    for (int i = 0; i < edge_units(e.p); ++i) u.insert(u.begin(), Unit{u.back().work, e.ntiles + i});
+    for (int i = 0; t.kind == kPlain && i < edge_units(e.p); ++i) u.insert(u.begin(), Unit{u.back().work, e.ntiles + i});
     t.units += (int)u.size();
   }
   std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return tab[a].p.K > tab[b].p.K; });
@@ -517,16 +557,17 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEven
   GemmBatch b{};
   int64_t mt = 1, nt = 1, edge = 0;
   const GemmProb &f = probs[0];
+  const int kind = kind_of(f);
   bool same = true;
   for (int i = 0; i < count; ++i) {
     const GemmProb &q = probs[i];
     // contiguous operands, 16-byte aligned, K padded to the k-tile
     if (!gemm_operands_ok(q)) return hipErrorInvalidValue;
-    if (has_mul(q) != has_mul(f)) return hipErrorInvalidValue;
+    if (kind_of(q) != kind) return hipErrorInvalidValue;
     b.p[i] = q;
     mt = std::max(mt, (main_extent(q.M) + T - 1) / T);
     nt = std::max(nt, (main_extent(q.N) + T - 1) / T);
-    edge = std::max(edge, (int64_t)edge_units(q));
+    if (kind == kPlain) edge = std::max(edge, (int64_t)edge_units(q));
     same = same && q.kside == f.kside && q.khigh == f.khigh;
   }
   // longest k-range first: lower limits grow, so the first tiles are the
@@ -539,8 +580,9 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEven
   b.nedge = (int)(edge * count);
   const int64_t wgs = (edge + mt * nt) * count;
   if (wgs > (int64_t)1 << 30) return hipErrorInvalidValue;
-  auto kern = has_mul(f) ? k_gemm<64, true> : k_gemm<64, false>;
-  if (T == 32) kern = has_mul(f) ? k_gemm<32, true> : k_gemm<32, false>;
+  auto kern = kind == kMul ? k_gemm<64, kMul> : kind == kNatural ? k_gemm<64, kNatural> : k_gemm<64, kPlain>;
+  if (T == 32)
+    kern = kind == kMul ? k_gemm<32, kMul> : kind == kNatural ? k_gemm<32, kNatural> : k_gemm<32, kPlain>;
   const dim3 grid((unsigned)wgs);
   if (ev0 != nullptr)
     hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, st, ev0, ev1, 0, b);

@@ -354,6 +354,11 @@ struct GemmProb {
   // Rows M .. Mz - 1 of C are cleared where M has edge rows (1 to 4 past a
   // multiple of 32): they are the k-padding of the next product.
   int64_t Mz;
+  // split > 0: B is an array in natural order, of `cols` columns and krows rows (A is
+  // zero from k = krows on), 8-byte aligned.  Column j of the product goes to column
+  // j / 2 (even j) or split + j / 2 (odd) of C, zeros from j = cols to N - 1.  Every
+  // problem of one launch or none.
+  int64_t split, cols, krows;
 };
 hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
@@ -403,7 +408,7 @@ bool gemm_operands_ok(const GemmProb &q);
 
 // Table-driven GEMM over many problems in one launch.  Each pointer of a
 // descriptor's GemmProb is absolute (base id 0), a byte offset from `ws`
-// (1) or from `out` (2).  gemm_table (host) picks the tile, fills every
+// (1), from `out` (2) or from `in` (3).  gemm_table (host) picks the tile, fills every
 // descriptor's tile counts and the workgroup map, (problem, unit) pairs; false
 // if a problem does not meet the launcher's requirements.
 struct GemmDesc {
@@ -412,12 +417,11 @@ struct GemmDesc {
   int ntiles, ntx;  // set by gemm_table
 };
 struct GemmTable {
-  int T = 0, units = 0;
-  bool mul = false;
+  int T = 0, units = 0, kind = 0;
 };
 bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map);
-hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map, char *ws,
-                             char *out, hipStream_t st, hipEvent_t ev0 = nullptr,
+hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *tile_map,
+                             const double *in, char *ws, char *out, hipStream_t st, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
 // Chains of products on one LDS-resident block (chain.hip).  The block X is in[r *
 // in_rs + c * in_cs] for r < in_r, c < in_c, zero beyond.  Matrix i is m[i][k * ld +

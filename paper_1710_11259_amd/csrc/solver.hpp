@@ -200,16 +200,16 @@ fps_status spectral_factors_2d(fps_plan *pl);
 fps::BcLiftConst bc_lift_const();
 // The products of one square or rectangle solve, per stage up to 4
 // parity-block problems (returns their count), operands formed from the
-// workspace base `ws` (and U / Fbar).  rhs: g1 then g2 after k_permute_in of F
-// into the GT region, leaving Y^ (the multiplier applied; with lr / lc the
+// workspace base `ws` (and U / Fbar).  rhs: g1 then g2 from F, leaving Y^ (the multiplier applied; with lr / lc the
 // Dirichlet lift subtracted first) in G; out: g1 then g2 to U (whose entries of
 // empty parity blocks the caller clears).  adj_in / adj_out: the same four
-// steps of the adjoint, transposed, from the permuted cotangent in the X
-// region to Fbar.
-int rhs_gemms(const fps_plan *pl, char *ws, fps::GemmProb *g1, fps::GemmProb *g2,
-              const double *lr = nullptr, const double *lc = nullptr);
+// steps of the adjoint, transposed, from the cotangent to Fbar.  The input stages' g1
+// is by row parity (cnt1 products).
+int rhs_gemms(const fps_plan *pl, const double *F, char *ws, fps::GemmProb *g1, int *cnt1,
+              fps::GemmProb *g2, const double *lr = nullptr, const double *lc = nullptr);
 int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::GemmProb *g2);
-int adj_in_gemms(const fps_plan *pl, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
+int adj_in_gemms(const fps_plan *pl, const double *Ubar, char *w, fps::GemmProb *g1, int *cnt1,
+                 fps::GemmProb *g2);
 int adj_out_gemms(const fps_plan *pl, double *Fbar, char *w, fps::GemmProb *g1, fps::GemmProb *g2);
 // A stage of products on st, timed like a sweep when the plan's timing is on.
 fps_status run_products(fps_plan *pl, const fps::GemmProb *g, int cnt, hipStream_t st);
@@ -230,6 +230,8 @@ inline bool adjoint_chained(const fps_plan *pl) {
 }
 // Their blocks: up to 4 (returns the count, 0 for other plans) from F (or the adjoint's
 // cotangent) to U (Fbar); nb for launch_chain.
+bool chain_in_out(const double *in, int64_t n_in, const double *out, int64_t n_out);
+fps_status clear_n1(const fps_plan *pl, double *U, hipStream_t st);
 int solve_chain(const fps_plan *pl, const double *F, double *U, const double *lr, const double *lc,
                 fps::ChainDesc *d, int *nb);
 int adjoint_chain(const fps_plan *pl, const double *Ubar, double *Fbar, fps::ChainDesc *d, int *nb);

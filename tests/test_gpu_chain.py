@@ -62,3 +62,48 @@ def test_cylinder(n):
     U = torch.full(p.out_shape(), float("nan"), dtype=torch.float64, device="cuda")
     u = _host(fps.solve(p, x, out=U))
     parity.check(u[:, 0] + 1j * u[:, 1], cylinder.poisson_cylinder(F), 1e-12, f"cylinder n={n}")
+
+
+# Inputs read in natural order by the first product: odd sizes (the last column
+# stands alone), odd offsets (rows 8-byte aligned only), sizes around the tiles, and
+# values beyond the array that must not matter.
+@pytest.mark.parametrize("n", [129, 130, 191, 257, 515, 1023, 1026])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_natural_input(n, offset):
+    rng = np.random.default_rng(n)
+    p = fps.plan(n, tol=1e-13)
+
+    def padded(x):
+        buf = torch.full((x.size + 64,), float("nan"), dtype=torch.float64, device="cuda")
+        v = buf[offset:offset + x.size].view(x.shape)
+        v.copy_(torch.from_numpy(x))
+        return v
+
+    F = rng.standard_normal((n, n))
+    parity.check(_host(fps.solve(p, padded(F))), square.poisson_square(F), 1e-12, f"solve n={n}")
+    Ub = rng.standard_normal(p.out_shape())
+    parity.check(_host(fps.solve_adjoint(p, padded(Ub))), adjoint.vjp_square(Ub), 1e-12, f"adjoint n={n}")
+
+
+# F and U may overlap in any way: every input is read before an output is written.
+@pytest.mark.parametrize("ns", [[1], [1, 2, 1], [40, 128], [33, 200, 1]])
+@pytest.mark.parametrize("out", ["cheb", "native"])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_overlapping_input_and_output(ns, out, shift):
+    rng = np.random.default_rng(len(ns))
+    b = fps.batch(ns, tol=1e-13, out=out)
+    F = torch.from_numpy(rng.standard_normal(b.in_entries)).cuda()
+    U = fps.batch_solve(b, F)
+    buf = torch.zeros(b.out_entries + 8, dtype=torch.float64, device="cuda")
+    x = buf[shift:shift + b.in_entries]
+    x.copy_(F)
+    y = fps.batch_solve(b, x, out=buf[:b.out_entries])
+    parity.check(_host(y), U.cpu().numpy(), 1e-13, "batch")
+    n = ns[0]
+    p = fps.plan(n, tol=1e-13, out=out)
+    F1 = F[:n * n].view(n, n)
+    U1 = fps.solve(p, F1)
+    x = buf[shift:shift + n * n].view(n, n)
+    x.copy_(F1)
+    y = fps.solve(p, x, out=buf[:U1.numel()].view(U1.shape))
+    parity.check(_host(y), U1.cpu().numpy(), 1e-13, "single")
