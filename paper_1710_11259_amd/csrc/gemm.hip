@@ -373,18 +373,9 @@ __device__ __forceinline__ void gemm_edge(const GemmProb &g, int unit, double *l
     edge_rows<64>(g, (int64_t)(unit - ncu) * 64, Mm, lds);
 }
 
-// Plain products allocate 52 KB, three workgroups per compute unit: four run in
-// step, their first and last k-tiles at the same time (n = 2048: 155 against
-// 141 us per launch).  The products with longer loops or epilogues drift apart by
-// themselves (natural order, n = 4096: 3.65 ms a solve with four, 3.70 with three).
-template <int T, int kKind>
-constexpr int lds_doubles() {
-  return T == 64 && kKind == kPlain ? 52 * 128 : Tile<T>::kLds;
-}
-
 template <int T, int kKind>
 __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
-  __shared__ __align__(16) double lds[lds_doubles<T, kKind>()];
+  __shared__ __align__(16) double lds[Tile<T>::kLds];
   int L = blockIdx.x;
   if (kKind == kPlain && L < batch.nedge) {
     const int per = batch.nedge / batch.count;
@@ -426,7 +417,7 @@ template <int T, int kKind>
 __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restrict__ d,
                                                        const int *__restrict__ tile_map, char *ws,
                                                        char *out, const char *in) {
-  __shared__ __align__(16) double lds[lds_doubles<T, kKind>()];
+  __shared__ __align__(16) double lds[Tile<T>::kLds];
   const int k = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x]);
   const int local = __builtin_amdgcn_readfirstlane(tile_map[2 * blockIdx.x + 1]);
   const GemmDesc &e = d[k];
