@@ -268,8 +268,8 @@ __device__ __forceinline__ dbl2 sum_l4(dbl2 v) {
 // the products need 24 .. 48 of its cycles in every 64 of the matrix unit's (strips
 // 246 -> 208 us a launch).
 
-// acc = W^T[r0 .. r0 + 32)[0 .. K) X[0 .. K)[c0 .. c0 + 32), W [k][row], X [k][column],
-// zero beyond in_r, in_c; K a multiple of 32.  Rows interleaved, columns too if kPair.
+// acc = W^T[r0 .. r0 + 32)[0 .. K) X[0 .. K)[c0 .. c0 + 32), W [k][row] (zeros from k =
+// in_r on), X [k][column], zero beyond in_c; K a multiple of 32.  Rows interleaved, columns too if kPair.
 // X comes from HBM: 8 k-steps (2048 MFMA cycles of the SIMD's wavefronts) ahead, W
 // from the caches: 4.  kExt: ext[c] = the rows S, S + 1 of W^T X in this lane's two
 // columns (all four lanes of a column hold them).
@@ -278,75 +278,89 @@ __device__ __forceinline__ void mul_stream(const double *__restrict__ W, int ldw
                                            const double *__restrict__ X, const ChainDesc &e, int K,
                                            int r0, int c0, const Lane &l, dbl4 (&acc)[2][2],
                                            dbl2 (&ext)[2]) {
-  const uint32_t wo = 8 * (l.l4 * ldw + 2 * l.l15);
+  const uint32_t wo = 8 * (l.l4 * ldw + 2 * l.l15), xwo = 8 * (l.l4 * ldw);
   const double *wu = W + r0;
   const int rs = (int)e.in_rs, cs = e.in_cs;
-  // the last k-step with data, and its rows: later ones read it again (masked)
+  // the last k-step with data, and its rows
   const int last = (e.in_r - 1) & ~3;
-  bool cok[2];
   uint32_t xo[2], xl[2];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const int col = c0 + (kPair ? 2 * l.l15 + c : 16 * c + l.l15);
-    cok[c] = col < e.in_c;
     // (a pair may end one past in_c, in the padding)
-    const int cc = (cok[c] ? col : kPair ? (e.in_c - 1) & ~1 : e.in_c - 1) * cs;
+    const int cc = (col < e.in_c ? col : kPair ? (e.in_c - 1) & ~1 : e.in_c - 1) * cs;
     xo[c] = 8 * (l.l4 * rs + cc);
     xl[c] = 8 * (min(l.l4, e.in_r - 1 - last) * rs + cc);
   }
   dbl2 a[4], b[8], x[4];
-  const uint32_t xwo = 8 * (l.l4 * ldw);
   ext[0] = ext[1] = dbl2{0.0, 0.0};
   auto load_a = [&](int u, int k) {
-    const int kk = (k < K ? k : K - 4) * ldw;
-    a[u] = at2(wu + kk, wo);
-    if constexpr (kExt) x[u] = at2(W + S + kk, xwo);
+    a[u] = at2(wu + k * ldw, wo);
+    if constexpr (kExt) x[u] = at2(W + S + k * ldw, xwo);
   };
-  auto load_b = [&](int u, int k) {
-    const bool z = k >= last;
-    const double *p = X + (z ? last : k) * rs;
+  // kEnd: the k-steps may end or pass the data; those past it read the last row again,
+  // times zeros of W
+  auto load_b = [&](int u, int k, auto end) {
+    const bool z = decltype(end)::value && k >= last;
+    const double *p = X + (int64_t)(z ? last : k) * rs;
+    const uint32_t o0 = z ? xl[0] : xo[0], o1 = z ? xl[1] : xo[1];
     if constexpr (kPair)
-      b[u] = *(const dbl2u *)((const char *)p + (z ? xl[0] : xo[0]));
+      b[u] = *(const dbl2u *)((const char *)p + o0);
     else
-      b[u] = dbl2{at(p, z ? xl[0] : xo[0]), at(p, z ? xl[1] : xo[1])};
+      b[u] = dbl2{at(p, o0), at(p, o1)};
   };
+  using Inner = std::false_type;
+  using End = std::true_type;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
     if (u < 4) load_a(u, 4 * u);
-    load_b(u, 4 * u);
+    load_b(u, 4 * u, End{});
     __builtin_amdgcn_sched_barrier(0);  // in the order of their use, for the waits
   }
 #pragma unroll
   for (int r = 0; r < 2; ++r)
 #pragma unroll
     for (int c = 0; c < 2; ++c) acc[r][c] = dbl4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-  for (int ks = 0; ks < K; ks += 32) {
+  // 8 k-steps, and the loads of the 8 (W: of 4 of them) that follow (kNext)
+  auto chunk = [&](int ks, auto next, auto end) {
+    constexpr bool kNext = decltype(next)::value;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int k = ks + 4 * u;
-      const bool rok = k + l.l4 < e.in_r;
-      const double bv[2] = {rok && cok[0] ? b[u].x : 0.0, rok && cok[1] ? b[u].y : 0.0};
 #pragma unroll
       for (int r = 0; r < 2; ++r)
 #pragma unroll
         for (int c = 0; c < 2; ++c)
-          acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u & 3][r], bv[c], acc[r][c], 0, 0, 0);
+          acc[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u & 3][r], b[u][c], acc[r][c], 0, 0, 0);
       if constexpr (kExt) {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          ext[c].x = fma(x[u & 3].x, bv[c], ext[c].x);
-          ext[c].y = fma(x[u & 3].y, bv[c], ext[c].y);
+          ext[c].x = fma(x[u & 3].x, b[u][c], ext[c].x);
+          ext[c].y = fma(x[u & 3].y, b[u][c], ext[c].y);
         }
       }
       // the next loads go into the registers just read; the barrier keeps them
       // from moving next to their use
       __builtin_amdgcn_sched_barrier(0);
-      load_a(u & 3, k + 16);
-      load_b(u, k + 32);
+      if (kNext || u < 4) load_a(u & 3, k + 16);
+      if constexpr (kNext) load_b(u, k + 32, end);
       __builtin_amdgcn_sched_barrier(0);
     }
-  }
+  };
+  int ks = 0;
+#pragma unroll 1
+  for (; ks + 64 <= e.in_r; ks += 32) chunk(ks, End{}, Inner{});
+#pragma unroll 1
+  for (; ks + 32 < K; ks += 32) chunk(ks, End{}, End{});
+  chunk(ks, Inner{}, Inner{});
+  // columns past in_c took others' data
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+    if (c0 + (kPair ? 2 * l.l15 + c : 16 * c + l.l15) >= e.in_c) {
+      ext[c] = dbl2{0.0, 0.0};
+#pragma unroll
+      for (int r = 0; r < 2; ++r) acc[r][c] = dbl4{0.0, 0.0, 0.0, 0.0};
+    }
   if constexpr (kExt)
     for (int c = 0; c < 2; ++c) ext[c] = sum_l4(ext[c]);
 }
@@ -390,9 +404,7 @@ __device__ __forceinline__ void mul_kept(const double *T, const int (&t)[2], int
     for (int c = 0; c < 2; ++c) o.acc[r][c] = dbl4{0.0, 0.0, 0.0, 0.0};
     o.w[r] = o.t[r] = o.tw[r] = dbl2{0.0, 0.0};
   }
-#pragma unroll 1
-  for (int ks = 0; ks < K; ks += 16) {
-    const int nx = ks + 16 < K ? ks + 16 : ks;
+  auto chunk = [&](int ks, auto next) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       double tv[2], ev[2];
@@ -415,9 +427,13 @@ __device__ __forceinline__ void mul_kept(const double *T, const int (&t)[2], int
           o.tw[r] = dbl2{fma(ev[r], x[u].x, o.tw[r].x), fma(ev[r], x[u].y, o.tw[r].y)};
       }
       __builtin_amdgcn_sched_barrier(0);
-      load(u, nx + 4 * u);
+      if constexpr (decltype(next)::value) load(u, ks + 16 + 4 * u);
     }
-  }
+  };
+  int ks = 0;
+#pragma unroll 1
+  for (; ks + 16 < K; ks += 16) chunk(ks, std::true_type{});
+  chunk(ks, std::false_type{});
 #pragma unroll
   for (int r = 0; r < 2; ++r) {
     if constexpr (kExtW) o.w[r] = sum_l4(o.w[r]);
