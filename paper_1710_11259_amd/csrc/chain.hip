@@ -59,9 +59,30 @@ __device__ __forceinline__ ChainDesc table_entry(const ChainDesc &d) {
 __device__ __forceinline__ double at(const double *p, uint32_t bytes) {
   return *(const double *)((const char *)p + bytes);
 }
-__device__ __forceinline__ dbl2 at2(const double *p, uint32_t bytes) {
-  return *(const dbl2 *)((const char *)p + bytes);
-}
+
+// The same through a buffer descriptor: base, a uniform and the lanes' byte offset are
+// all added by the load.  (From a pointer the compiler adds 64-bit addresses per lane,
+// and vector instructions take the matrix unit's time in FP64.)  `bytes` past the base
+// stay below 2^31 (chain_ok).
+struct Buffer {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit Buffer(const double *p)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0xffffffffu, 0x00027000)) {}
+  __device__ __forceinline__ double load(uint32_t lane, uint32_t uniform) const {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, lane, uniform, 0));
+  }
+  __device__ __forceinline__ void store(double v, uint32_t lane, uint32_t uniform) const {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lane, uniform, 0);
+  }
+  __device__ __forceinline__ void store2(dbl2 v, uint32_t lane, uint32_t uniform) const {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, lane, uniform, 0);
+  }
+  __device__ __forceinline__ dbl2 load2(uint32_t lane, uint32_t uniform) const {
+    return __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(r, lane, uniform, 0));
+  }
+};
 
 // A whole square solve, m3^T (multiplier of m1^T X m0) m2, of blocks of up to 64 with
 // outputs of up to 16 TT: a wavefront per 16 x 16 tile (v_mfma_f64_16x16x4f64: lane l
@@ -279,7 +300,7 @@ __device__ __forceinline__ void mul_stream(const double *__restrict__ W, int ldw
                                            int r0, int c0, const Lane &l, dbl4 (&acc)[2][2],
                                            dbl2 (&ext)[2]) {
   const uint32_t wo = 8 * (l.l4 * ldw + 2 * l.l15), xwo = 8 * (l.l4 * ldw);
-  const double *wu = W + r0;
+  const Buffer wb(W), xb(X);
   const int rs = (int)e.in_rs, cs = e.in_cs;
   // the last k-step with data, and its rows
   const int last = (e.in_r - 1) & ~3;
@@ -295,19 +316,19 @@ __device__ __forceinline__ void mul_stream(const double *__restrict__ W, int ldw
   dbl2 a[4], b[8], x[4];
   ext[0] = ext[1] = dbl2{0.0, 0.0};
   auto load_a = [&](int u, int k) {
-    a[u] = at2(wu + k * ldw, wo);
-    if constexpr (kExt) x[u] = at2(W + S + k * ldw, xwo);
+    a[u] = wb.load2(wo, 8 * (r0 + k * ldw));
+    if constexpr (kExt) x[u] = wb.load2(xwo, 8 * (S + k * ldw));
   };
   // kEnd: the k-steps may end or pass the data; those past it read the last row again,
   // times zeros of W
   auto load_b = [&](int u, int k, auto end) {
     const bool z = decltype(end)::value && k >= last;
-    const double *p = X + (int64_t)(z ? last : k) * rs;
+    const uint32_t row = 8 * (z ? last : k) * rs;
     const uint32_t o0 = z ? xl[0] : xo[0], o1 = z ? xl[1] : xo[1];
     if constexpr (kPair)
-      b[u] = *(const dbl2u *)((const char *)p + o0);
+      b[u] = xb.load2(o0, row);
     else
-      b[u] = dbl2{at(p, o0), at(p, o1)};
+      b[u] = dbl2{xb.load(o0, row), xb.load(o1, row)};
   };
   using Inner = std::false_type;
   using End = std::true_type;
@@ -383,14 +404,15 @@ __device__ __forceinline__ void mul_kept(const double *T, const int (&t)[2], int
                                          const double *__restrict__ W, int ldw, int S, int K, int w0,
                                          const double *te, int P, const Lane &l, Kept &o) {
   const uint32_t wo = 8 * (l.l4 * ldw + (kPair ? 2 : 1) * l.l15), xwo = 8 * (l.l4 * ldw);
+  const Buffer wb(W);
   dbl2 w[4], x[4];
   auto load = [&](int u, int k) {
-    const double *p = W + w0 + k * ldw;
+    const uint32_t row = 8 * (w0 + k * ldw);
     if constexpr (kPair)
-      w[u] = at2(p, wo);
+      w[u] = wb.load2(wo, row);
     else
-      w[u] = dbl2{at(p, wo), at(p + 16, wo)};
-    if constexpr (kExtW) x[u] = at2(W + S + k * ldw, xwo);
+      w[u] = dbl2{wb.load(wo, row), wb.load(wo + 128, row)};
+    if constexpr (kExtW) x[u] = wb.load2(xwo, 8 * (S + k * ldw));
   };
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -511,20 +533,41 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_slab(const Chain
     rows ? second(Ext{}, Ext{}) : second(Ext{}, No{});
   else
     rows ? second(No{}, Ext{}) : second(No{}, No{});
+  const Buffer ob(out);
+  const uint32_t rs = 8 * (uint32_t)e.out_rs, lane = l.l4 * rs + 16 * l.l15;
+  if (r0 + 32 <= e.out_r && c0 + 32 <= e.out_c) {
+    const Buffer zb(out + e.zoff);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = r0 + 16 * a + 4 * r + l.l4;
-      if constexpr (kOut) {
-        store_one(e, out, i, c0 + l.l15, o.acc[a][0][r]);
-        store_one(e, out, i, c0 + 16 + l.l15, o.acc[a][1][r]);
-      } else {  // out_c is even, out_cs 1
-        const int j = c0 + 2 * l.l15;
-        if (i < e.out_r && j < e.out_c)
-          *(dbl2u *)(out + i * e.out_rs + j) = dbl2{o.acc[a][0][r], o.acc[a][1][r]};
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t row = (r0 + 16 * a + 4 * r) * rs + (kOut ? 16 : 8) * c0;
+        if constexpr (kOut) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            ob.store(o.acc[a][c][r], lane, row + 256 * c);
+            if (e.zoff != 0) zb.store(0.0, lane, row + 256 * c);
+          }
+        } else {
+          ob.store2(dbl2{o.acc[a][0][r], o.acc[a][1][r]}, lane, row);
+        }
       }
-    }
+  } else {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = r0 + 16 * a + 4 * r + l.l4;
+        if constexpr (kOut) {
+          store_one(e, out, i, c0 + l.l15, o.acc[a][0][r]);
+          store_one(e, out, i, c0 + 16 + l.l15, o.acc[a][1][r]);
+        } else {  // out_c is even, out_cs 1
+          const int j = c0 + 2 * l.l15;
+          if (i < e.out_r && j < e.out_c)
+            *(dbl2u *)(out + i * e.out_rs + j) = dbl2{o.acc[a][0][r], o.acc[a][1][r]};
+        }
+      }
+  }
   if constexpr (kOut) {
     // lanes l4 = 0, 1 hold the two extra rows or columns each
 #pragma unroll
@@ -562,12 +605,19 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_strip(const Chai
     dbl2 ext[2];
     mul_stream<true, false>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
     const int j = c0 + 2 * l.l15;  // columns j, j + 1 (in_c is even)
+    const Buffer mb(e.mt);
+    const uint32_t mrs = 8 * (uint32_t)e.mt_rs, mlane = 2 * l.l4 * mrs + 8 * j;
+    const bool inner = r0 + 32 <= e.n[1] && c0 + 32 <= e.in_c;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = r0 + 8 * r + 2 * l.l4 + a;
-        const dbl2 f = i < e.n[1] && j < e.in_c ? *(const dbl2 *)(e.mt + i * e.mt_rs + j) : dbl2{0.0, 0.0};
+        dbl2 f{0.0, 0.0};
+        if (inner)
+          f = mb.load2(mlane, (r0 + 8 * r + a) * mrs);
+        else if (i < e.n[1] && j < e.in_c)
+          f = *(const dbl2 *)(e.mt + i * e.mt_rs + j);
         *(dbl2 *)(T + i * C::E + (j ^ (a << 4))) = dbl2{o.acc[a][0][r] * f.x, o.acc[a][1][r] * f.y};
       }
   }
@@ -581,13 +631,25 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_strip(const Chai
     mul_kept<true, true, true, false>(T, t, C::E, e.m[3], e.ld[3], C::S, e.k[3], r0, T, 0, l, o);
   else
     mul_kept<true, true, false, false>(T, t, C::E, e.m[3], e.ld[3], C::S, e.k[3], r0, T, 0, l, o);
+  if (r0 + 32 <= e.out_r && c0 + 32 <= e.out_c) {
+    const Buffer ob(out);
+    const uint32_t rs = 8 * (uint32_t)e.out_rs, lane = 2 * l.l4 * rs + 8 * l.l15;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        store_one(e, out, r0 + 8 * r + 2 * l.l4 + a, c0 + 16 * b + l.l15, o.acc[a][b][r]);
+        for (int r = 0; r < 4; ++r)
+          ob.store(o.acc[a][b][r], lane, (r0 + 8 * r + a) * rs + 8 * (c0 + 16 * b));
+  } else {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          store_one(e, out, r0 + 8 * r + 2 * l.l4 + a, c0 + 16 * b + l.l15, o.acc[a][b][r]);
+  }
   if (rows && l.l4 < 2)
 #pragma unroll
     for (int a = 0; a < 2; ++a)
@@ -615,7 +677,9 @@ bool chain_ok(const ChainDesc &d, int nb, int mode) {
            d.n[i] <= most && d.ld[i] >= cover;
   };
   // the lanes' address parts are 32-bit
-  if (8 * S * d.in_rs >= (int64_t)1 << 31) return false;
+  if (8 * S * d.in_rs >= (int64_t)1 << 31 || 8 * (S + 2) * d.out_rs >= (int64_t)1 << 31 ||
+      8 * S * d.mt_rs >= (int64_t)1 << 31)
+    return false;
   if (d.in_r > S || d.in_c > S || d.in_r < 1 || d.in_c < 1) return false;
   if (mode == 1)
     return (nb == 3 || nb == 4 || nb == 5) && d.mr != nullptr && d.mc != nullptr && mat(0, K) &&
