@@ -60,30 +60,6 @@ __device__ __forceinline__ double at(const double *p, uint32_t bytes) {
   return *(const double *)((const char *)p + bytes);
 }
 
-// The same through a buffer descriptor: base, a uniform and the lanes' byte offset are
-// all added by the load.  (From a pointer the compiler adds 64-bit addresses per lane,
-// and vector instructions take the matrix unit's time in FP64.)  `bytes` past the base
-// stay below 2^31 (chain_ok).
-struct Buffer {
-  __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ explicit Buffer(const double *p)
-      : r(__builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 0xffffffffu, 0x00027000)) {}
-  __device__ __forceinline__ double load(uint32_t lane, uint32_t uniform) const {
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, lane, uniform, 0));
-  }
-  __device__ __forceinline__ void store(double v, uint32_t lane, uint32_t uniform) const {
-    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lane, uniform, 0);
-  }
-  __device__ __forceinline__ void store2(dbl2 v, uint32_t lane, uint32_t uniform) const {
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, lane, uniform, 0);
-  }
-  __device__ __forceinline__ dbl2 load2(uint32_t lane, uint32_t uniform) const {
-    return __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(r, lane, uniform, 0));
-  }
-};
-
 // A whole square solve, m3^T (multiplier of m1^T X m0) m2, of blocks of up to 64 with
 // outputs of up to 16 TT: a wavefront per 16 x 16 tile (v_mfma_f64_16x16x4f64: lane l
 // supplies A[l % 16][l / 16] and B[l / 16][l % 16], accumulator register r holds

@@ -31,7 +31,6 @@ namespace {
 // padding.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
-typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
 
 // order: tile dispatch order (0: natural; 1 / 2: column tile slowest,
 // ascending / descending; 3 / 4: row tile slowest, ascending / descending), so
@@ -145,36 +144,36 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
   const int ar = tid / TA, ak = (tid % TA) * RA;
   const int bk = tid / TB, bc = (tid % TB) * 2;
   const int64_t arow = i0 + ar < g.M ? i0 + ar : g.M - 1;
-  const double *__restrict__ Ap = g.A + arow * g.sai + klo + ak;
-  const double *__restrict__ Bp = g.B + (klo + bk) * g.sbk;
+  const double *Ab = g.A + i0 * g.sai + klo, *Bb = g.B + klo * g.sbk;
+  const uint32_t ao = 8 * ((uint32_t)(arow - i0) * (uint32_t)g.sai + ak);
   // (row strides are even: the pair exists; natural rows may end within one, then
   // the pair before holds its first column)
   const int64_t jlast = kKind == kNatural ? g.cols - 2 : (g.N - 1) & ~(int64_t)1;
-  int bcol[QB], brow = (int)klo + bk;
+  uint32_t bo[QB], bl[QB];
   bool late[QB];
+  // natural rows past the last are clamped too (A is zero there), in the last k-tile
+  const int whole = kKind == kNatural ? (int)(g.krows - klo) / BK : 0;
+  const int lrow = kKind == kNatural ? (int)(g.krows - klo) - whole * BK - 1 : 0;
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
-    const int64_t j = j0 + bc + 2 * TB * q;
-    bcol[q] = (int)(j < jlast ? j : jlast);
+    const int64_t j = j0 + bc + 2 * TB * q, jc = j < jlast ? j : jlast;
+    bo[q] = 8 * ((uint32_t)bk * (uint32_t)g.sbk + (uint32_t)jc);
+    bl[q] = 8 * ((uint32_t)(bk < lrow ? bk : lrow) * (uint32_t)g.sbk + (uint32_t)jc);
     late[q] = kKind == kNatural && j > jlast;
   }
 
   dbl2 ra[2][RA / 2], rb[2][QB];
+  int tile = 0;
   auto fetch = [&](int r) {
+    const Buffer A(Ab), B(Bb);
 #pragma unroll
-    for (int q = 0; q < RA / 2; ++q) ra[r][q] = *(const dbl2 *)(Ap + 2 * q);
-    if constexpr (kKind == kNatural) {
-      // rows past the last are clamped too: A is zero there
-      const double *Bn = g.B + (brow < (int)g.krows ? brow : (int)g.krows - 1) * g.sbk;
+    for (int q = 0; q < RA / 2; ++q) ra[r][q] = A.load2(ao + 16 * q, 0);
+    const bool last = kKind == kNatural && tile >= whole;
 #pragma unroll
-      for (int q = 0; q < QB; ++q) rb[r][q] = *(const dbl2u *)(Bn + bcol[q]);
-      brow += BK;
-    } else {
-#pragma unroll
-      for (int q = 0; q < QB; ++q) rb[r][q] = *(const dbl2 *)(Bp + bcol[q]);
-      Bp += BK * g.sbk;
-    }
-    Ap += BK;
+    for (int q = 0; q < QB; ++q) rb[r][q] = B.load2(last ? bl[q] : bo[q], 0);
+    Ab += BK;
+    Bb += BK * g.sbk;
+    ++tile;
   };
   auto stash = [&](double *st, int r) {
     double *Ad = st + ar * (BK + 1) + ak;
@@ -252,6 +251,23 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
       __syncthreads();
       mma(L::kStage);
     }
+  }
+  const int64_t ri = i0 + wy * W, cj = j0 + wx * W;
+  if (kKind != kMul && ri + W <= Mm && cj + W <= (kKind == kNatural && g.cols < Nm ? g.cols : Nm)) {
+    // whole tiles: columns 16 b + l15, natural ones by parity
+    const int l15 = lane & 15, l4 = lane >> 4;
+    const uint32_t rs = 8 * (uint32_t)g.sci, cs = 8 * (uint32_t)g.scj;
+    const Buffer C(g.C + ri * g.sci + (kKind == kNatural ? cj / 2 : cj * g.scj));
+    const uint32_t co = l4 * rs + (kKind == kNatural ? 8 * ((l15 & 1) * (uint32_t)g.split + (l15 >> 1))
+                                                      : l15 * cs);
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          C.store(acc[a][b][r], co, (16 * a + 4 * r) * rs + (kKind == kNatural ? 64 * b : 16 * b * cs));
+    return;
   }
 #pragma unroll
   for (int a = 0; a < NB; ++a)
@@ -468,6 +484,10 @@ int pick_tile(int64_t count, Get get) {
 
 bool gemm_operands_ok(const GemmProb &q) {
   const int kind = kind_of(q);
+  // 32-bit byte offsets within a tile
+  if (64 * q.sai >= (int64_t)1 << 28 || 64 * q.sbk + q.N >= (int64_t)1 << 28 ||
+      64 * (q.sci + q.scj) >= (int64_t)1 << 28)
+    return false;
   if (q.sak != 1 || q.sbj != 1 || q.K % 16 != 0 || (q.sai & 1) || ((uintptr_t)q.A & 15) || q.M < 1 ||
       q.N < 1)
     return false;
