@@ -146,18 +146,19 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
   const int64_t arow = i0 + ar < g.M ? i0 + ar : g.M - 1;
   const double *Ab = g.A + i0 * g.sai + klo, *Bb = g.B + klo * g.sbk;
   const uint32_t ao = 8 * ((uint32_t)(arow - i0) * (uint32_t)g.sai + ak);
-  // (row strides are even: the pair exists; natural rows may end within one, then
-  // the pair before holds its first column)
+  const int nk = (int)((khi - klo + BK - 1) / BK);
+  // Columns past N are clamped to the last pair (row strides are even: it exists).
+  // Of a natural array the rows past the last are clamped (A is zero there), and the
+  // columns past it only in the last k-tile, as before that they lie in the rows that
+  // follow; the row may end within a pair, then the pair before holds its first column.
   const int64_t jlast = kKind == kNatural ? g.cols - 2 : (g.N - 1) & ~(int64_t)1;
+  const int lrow = kKind == kNatural ? (int)(g.krows - klo) - (nk - 1) * BK - 1 : 0;
   uint32_t bo[QB], bl[QB];
   bool late[QB];
-  // natural rows past the last are clamped too (A is zero there), in the last k-tile
-  const int whole = kKind == kNatural ? (int)(g.krows - klo) / BK : 0;
-  const int lrow = kKind == kNatural ? (int)(g.krows - klo) - whole * BK - 1 : 0;
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
     const int64_t j = j0 + bc + 2 * TB * q, jc = j < jlast ? j : jlast;
-    bo[q] = 8 * ((uint32_t)bk * (uint32_t)g.sbk + (uint32_t)jc);
+    bo[q] = 8 * ((uint32_t)bk * (uint32_t)g.sbk + (uint32_t)(kKind == kNatural ? j : jc));
     bl[q] = 8 * ((uint32_t)(bk < lrow ? bk : lrow) * (uint32_t)g.sbk + (uint32_t)jc);
     late[q] = kKind == kNatural && j > jlast;
   }
@@ -168,14 +169,14 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
     const Buffer A(Ab), B(Bb);
 #pragma unroll
     for (int q = 0; q < RA / 2; ++q) ra[r][q] = A.load2(ao + 16 * q, 0);
-    const bool last = kKind == kNatural && tile >= whole;
+    const bool last = kKind == kNatural && tile == nk - 1;
 #pragma unroll
     for (int q = 0; q < QB; ++q) rb[r][q] = B.load2(last ? bl[q] : bo[q], 0);
     Ab += BK;
     Bb += BK * g.sbk;
     ++tile;
   };
-  auto stash = [&](double *st, int r) {
+  auto stash = [&](double *st, int r, bool last) {
     double *Ad = st + ar * (BK + 1) + ak;
     double *Bd = st + L::kA + bk * (T + 2) + bc;
 #pragma unroll
@@ -185,7 +186,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
     }
 #pragma unroll
     for (int q = 0; q < QB; ++q) {
-      if (kKind == kNatural && late[q]) rb[r][q].x = rb[r][q].y;
+      if (kKind == kNatural && last && late[q]) rb[r][q].x = rb[r][q].y;
       *(dbl2 *)(Bd + 2 * TB * q) = rb[r][q];
     }
   };
@@ -227,29 +228,36 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
   // reads and this tile's reads before the stash that follows.  The loads of
   // tile t + 2 are issued before the products of tile t, so a load has two
   // k-tiles to arrive.
-  const int nk = (int)((khi - klo + BK - 1) / BK);
   if (nk > 0) {
     fetch(0);
-    stash(lds, 0);
+    stash(lds, 0, nk == 1);
     if (nk > 1) fetch(1);
     __syncthreads();
     int t = 0;
 #pragma unroll 1
-    for (; t + 2 < nk; t += 2) {
+    for (; t + 3 < nk; t += 2) {
       fetch(0);
       mma(0);
-      stash(lds + L::kStage, 1);
+      stash(lds + L::kStage, 1, false);
       __syncthreads();
-      if (t + 3 < nk) fetch(1);
+      fetch(1);
       mma(L::kStage);
-      stash(lds, 0);
+      stash(lds, 0, false);
       __syncthreads();
     }
+    // 1, 2 or 3 k-tiles are left, the last of all among them
+    const int rest = nk - t;
+    if (rest == 3) fetch(0);
     mma(0);
-    if (t + 1 < nk) {
-      stash(lds + L::kStage, 1);
+    if (rest > 1) {
+      stash(lds + L::kStage, 1, rest == 2);
       __syncthreads();
       mma(L::kStage);
+    }
+    if (rest == 3) {
+      stash(lds, 0, true);
+      __syncthreads();
+      mma(0);
     }
   }
   const int64_t ri = i0 + wy * W, cj = j0 + wx * W;
@@ -421,7 +429,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
 }
 
 // Table-driven GEMM: workgroup g computes unit tile_map[2g + 1] of problem
-// tile_map[2g]: its tiles row by row (ntx per row), then its edge units.
+// tile_map[2g]: the tile at rows 32 (u >> 16), columns 32 (u >> 1 & 0x7fff), a 32 x 32 one
+// if u is odd, or edge unit -1 - u.
 // Operand pointers are rebased per GemmDesc base ids.
 __device__ __forceinline__ const double *rebase(const double *p, int id, char *ws, char *out,
                                                 const char *in) {
@@ -447,10 +456,15 @@ __global__ __launch_bounds__(256, 2) void k_gemm_table(const GemmDesc *__restric
   g.lr = as_global(g.lr);
   g.lc = as_global(g.lc);
   g.mt = as_global(g.mt);
-  if (kKind == kPlain && local >= e.ntiles)
-    gemm_edge(g, local - e.ntiles, lds);
+  if (kKind == kPlain && local < 0) {
+    gemm_edge(g, -1 - local, lds);
+    return;
+  }
+  const int64_t i0 = (local >> 16) * 32, j0 = ((local >> 1) & 0x7fff) * 32;
+  if (T == 32 || (local & 1))
+    gemm_tile<32, kKind>(g, i0, j0, lds);
   else
-    gemm_tile<T, kKind>(g, (int64_t)(local / e.ntx) * T, (int64_t)(local % e.ntx) * T, lds);
+    gemm_tile<64, kKind>(g, i0, j0, lds);
 }
 
 }  // namespace
@@ -527,6 +541,9 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
   // their problem's operands in the caches: ordered by k-range across the 64
   // blocks of 16 solves at n = 2048, every column of tiles read them anew);
   // within a problem its edge units, then its tiles, longest k-range first.
+  // Tables of 64 x 64 tiles cover the last 32 rows or columns of a problem (past a
+  // multiple of 64) by 32 x 32 ones: a batch's blocks have any multiple of 16 (256
+  // problems of n = 32 .. 1024: 5.27 -> 5.14 ms).
   struct Unit {
     int64_t work;
     int local;
@@ -534,20 +551,28 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
   std::vector<std::vector<Unit>> units(tab.size());
   std::vector<int> by((size_t)tab.size());
   for (size_t k = 0; k < tab.size(); ++k) {
-    GemmDesc &e = tab[k];
+    const GemmProb &q = tab[k].p;
     by[k] = (int)k;
-    if (!gemm_operands_ok(e.p) || kind_of(e.p) != t.kind) return false;
-    const int64_t ntx = (main_extent(e.p.N) + t.T - 1) / t.T, nty = (main_extent(e.p.M) + t.T - 1) / t.T;
-    e.ntx = (int)ntx;
-    e.ntiles = (int)(ntx * nty);
+    if (!gemm_operands_ok(q) || kind_of(q) != t.kind) return false;
+    const int64_t M = main_extent(q.M), N = main_extent(q.N);
+    if (M >= (int64_t)32 << 15 || N >= (int64_t)32 << 15) return false;
     std::vector<Unit> &u = units[k];
-    for (int l = 0; l < e.ntiles; ++l) {
+    auto add = [&](int64_t i0, int64_t j0, int T) {
+      if (i0 >= M || j0 >= N) return;
       int64_t klo, khi;
-      tile_krange(e.p, e.p.klim_host, l / ntx * t.T, l % ntx * t.T, t.T, &klo, &khi);
-      u.push_back(Unit{khi - klo, l});
-    }
+      tile_krange(q, q.klim_host, i0, j0, T, &klo, &khi);
+      u.push_back(Unit{(khi - klo) * T * T, (int)((i0 / 32) << 16 | (j0 / 32) << 1 | (T < t.T ? 1 : 0))});
+    };
+    for (int64_t i0 = 0; i0 < M; i0 += t.T)
+      for (int64_t j0 = 0; j0 < N; j0 += t.T) {
+        if (t.T == 32 || (M - i0 > 32 && N - j0 > 32)) {
+          add(i0, j0, t.T);
+        } else {
+          for (int c = 0; c < 4; ++c) add(i0 + (c >> 1) * 32, j0 + (c & 1) * 32, 32);
+        }
+      }
     std::stable_sort(u.begin(), u.end(), [](const Unit &a, const Unit &b) { return a.work > b.work; });
-    for (int i = 0; t.kind == kPlain && i < edge_units(e.p); ++i) u.insert(u.begin(), Unit{u.back().work, e.ntiles + i});
+    for (int i = 0; t.kind == kPlain && i < edge_units(q); ++i) u.insert(u.begin(), Unit{0, -1 - i});
     t.units += (int)u.size();
   }
   std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return tab[a].p.K > tab[b].p.K; });

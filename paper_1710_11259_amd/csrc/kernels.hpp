@@ -408,13 +408,12 @@ bool gemm_operands_ok(const GemmProb &q);
 
 // Table-driven GEMM over many problems in one launch.  Each pointer of a
 // descriptor's GemmProb is absolute (base id 0), a byte offset from `ws`
-// (1), from `out` (2) or from `in` (3).  gemm_table (host) picks the tile, fills every
-// descriptor's tile counts and the workgroup map, (problem, unit) pairs; false
+// (1), from `out` (2) or from `in` (3).  gemm_table (host) picks the tile and fills the
+// workgroup map, (problem, unit) pairs; false
 // if a problem does not meet the launcher's requirements.
 struct GemmDesc {
   GemmProb p;
   int abase, bbase, cbase;
-  int ntiles, ntx;  // set by gemm_table
 };
 struct GemmTable {
   int T = 0, units = 0, kind = 0;
