@@ -305,7 +305,7 @@ fps::BcLiftConst bc_lift_const() {
 }
 
 // The k-range of a product with Wo (or its transpose) on side `side`.
-void limit_k(fps::GemmProb &g, int side, const std::vector<int> &host, const DeviceBuf &dev,
+void limit_k(fps::GemmProb &g, int side, const std::vector<int> &host, const DeviceView &dev,
              int high) {
   g.kside = side;
   g.khigh = high;
@@ -666,8 +666,7 @@ fps_status plan2d_build(fps_plan *pl) {
     fps_status s;
     if ((s = upload(pl->d_tab, pl->tab)) != FPS_OK || (s = upload(pl->d_ctab, pl->ctab)) != FPS_OK ||
         (s = upload(pl->d_l1, pl->l1)) != FPS_OK || (s = upload(pl->d_sinv, pl->sinv)) != FPS_OK ||
-        (s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) ? lift : nullptr)) != FPS_OK ||
-        (s = spectral_factors_2d(pl)) != FPS_OK)
+        (s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) ? lift : nullptr)) != FPS_OK)
       return s;
     // chains of more than two chunks: the two row-parity halves of the ADI
     // run on two streams (run_adi)

@@ -363,14 +363,18 @@ struct GemmProb {
 hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
 
-// Plan-time passes of the eigenbasis form (spectral.hip).  Eigenpairs of the
-// negative definite tridiagonal T whose negated diagonal is d, coupling e (e2
-// = e^2; device arrays of m): lam[a] ascending from the most negative, V the
+// Plan-time passes of the eigenbasis form (spectral.hip).  Eigenpairs of two
+// negative definite tridiagonals T (m 0: none) whose negated diagonal is d, coupling e
+// (e2 = e^2; device arrays of m): lam[a] ascending from the most negative, V the
 // orthonormal-to-m-eps vectors as columns (row length ld); [lo, hi] encloses
 // sigma(-T); Dp, Dm scratch of V's shape, V zeroed by the caller.
-hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2, int64_t m,
-                              double lo, double hi, double *lam, double *Dp, double *Dm, double *V,
-                              int64_t ld, hipStream_t st);
+struct TridiagEig {
+  const double *d, *e, *e2;
+  double *lam, *Dp, *Dm, *V;
+  int64_t ld;
+  int m;
+};
+hipError_t launch_tridiag_eig(const TridiagEig *p, double lo, double hi, hipStream_t st);
 // Cube multipliers -(1 - eps) / (lz ly + lz lx + ly lx) by storage position
 // [npad]^3 (cube.cpp states the iterations).  z-eigenbasis: eps = ey[z][y]
 // ex[z][x], the error factors of slice z's shifts p / q[off[z] .. off[z+1] - 1]

@@ -39,6 +39,11 @@ struct DeviceBuf {
   }
 };
 
+// A table within another allocation.
+struct DeviceView {
+  void *p = nullptr;
+};
+
 }  // namespace detail
 }  // namespace fps
 
@@ -95,16 +100,17 @@ struct fps_plan {
   // V^T S^-1 R (mp x mp) and Wo = P S^-1 V (mop x mp; native output S^-1 V,
   // mp x mp).  lam: eigenvalues by storage position (-1 on padding); d_mr /
   // d_mc: the multiplier's row and column factors, [npad][2].
-  fps::detail::DeviceBuf d_Wi[2], d_WiT[2], d_Wo[2], d_WoT[2];
-  fps::detail::DeviceBuf d_mr, d_mc;
+  fps::detail::DeviceBuf d_maps;  // holds them and the tables below
+  fps::detail::DeviceView d_Wi[2], d_WiT[2], d_Wo[2], d_WoT[2];
+  fps::detail::DeviceView d_mr, d_mc;
   // Where Wo is zero (spectral.cpp): row group g of 64 output coefficients has
   // no entries below mode klo[g], and mode group h none from row khi[h] on.
   std::vector<int> klo[2], khi[2];
-  fps::detail::DeviceBuf d_klo[2], d_khi[2];
+  fps::detail::DeviceView d_klo[2], d_khi[2];
   std::vector<double> lam;
   // Lift map V^T S^-1 C~(T_k'') by parity (mp x mop) and V^T of the lift's
   // linear factors ([npad][2]), only with FPS_PLAN_DIRICHLET.
-  fps::detail::DeviceBuf d_lift[2], d_lina;
+  fps::detail::DeviceView d_lift[2], d_lina;
 
   // sweep timing diagnostics
   std::vector<hipEvent_t> ev;  // pairs
@@ -196,7 +202,6 @@ struct RefineRound {
 std::vector<RefineRound> refine_schedule(double tol, bool dirichlet);
 // Eigenbasis maps (spectral.cpp).
 fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift);
-fps_status spectral_factors_2d(fps_plan *pl);
 fps::BcLiftConst bc_lift_const();
 // The products of one square or rectangle solve, per stage up to 4
 // parity-block problems (returns their count), operands formed from the

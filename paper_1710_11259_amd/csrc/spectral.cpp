@@ -30,19 +30,14 @@ namespace detail {
 namespace {
 
 // C = A B for one block of zero-padded, contiguous operands.
-hipError_t product(const double *A, int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
-                   int64_t M, int64_t N, int64_t K, hipStream_t st) {
-  fps::GemmProb g{A, B, C, M, N, K, lda, 1, ldb, 1, ldc, 1};
-  return fps::launch_gemm(&g, 1, st);
+fps::GemmProb product(const double *A, int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
+                      int64_t M, int64_t N, int64_t K) {
+  return fps::GemmProb{A, B, C, M, N, K, lda, 1, ldb, 1, ldc, 1};
 }
 
-// rows x cols (row-major) zero-padded to rp x cp.
-std::vector<double> padded(const std::vector<double> &M, int64_t rows, int64_t cols, int64_t rp,
-                           int64_t cp) {
-  std::vector<double> out((size_t)(rp * cp), 0.0);
-  for (int64_t i = 0; i < rows; ++i)
-    std::copy(M.begin() + i * cols, M.begin() + (i + 1) * cols, out.begin() + i * cp);
-  return out;
+// rows x cols (row-major) into zeros with row stride cp.
+void padded(const std::vector<double> &M, int64_t rows, int64_t cols, int64_t cp, double *out) {
+  for (int64_t i = 0; i < rows; ++i) std::copy(M.begin() + i * cols, M.begin() + (i + 1) * cols, out + i * cp);
 }
 
 // Zeros of Wo.  Mode a of parity s is u = cos or sin of x y, x = (pi / 2)
@@ -77,113 +72,20 @@ void wo_zeros(int s, int64_t rows, int64_t modes, std::vector<int> &klo, std::ve
         khi[(size_t)h] = (int)std::min(rows, (g + 1) * fps::kGemmGroup);
 }
 
-fps_status alloc(DeviceBuf &b, int64_t doubles) {
-  if (hipMalloc(&b.p, (size_t)doubles * 8) != hipSuccess)
-    return fail(FPS_E_NOMEM, "hipMalloc of a plan table failed");
-  return FPS_OK;
-}
-
-}  // namespace
-
-// Eigenpairs of the parity blocks of A~ and the merged maps, in both
-// orientations (d_Wi / d_WiT, d_Wo / d_WoT); pl->lam gets the eigenvalues by
-// storage position.  The plan's L, Rs, P, mop and sinv are set; lift (or null)
-// holds the Dirichlet lift map S^-1 C~(T_k''), merged the same way.
-fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift) {
-  const fps::Layout &L = pl->L;
-  const bool native = pl->out_basis == FPS_OUT_NATIVE;
-  const double n = (double)pl->n;
-  hipStream_t st = nullptr;
-  fps_status s;
-  pl->lam.assign((size_t)L.npad, -1.0);
-  std::vector<double> v0((size_t)L.npad, 0.0);  // first row of each V_s
-  for (int sp = 0; sp < 2; ++sp) {
-    const int64_t m = L.m[sp], mp = L.mp[sp], mop = native ? mp : pl->mop[sp];
-    if (m == 0) continue;
-    std::vector<double> d((size_t)m), e((size_t)m, 0.0), e2((size_t)m, 0.0);
-    for (int64_t k = 0; k < m; ++k) {
-      d[(size_t)k] = -fps::atilde_diag(2 * k + sp);
-      if (k + 1 < m) e[(size_t)k] = fps::atilde_off(2 * k + sp);
-      e2[(size_t)k] = e[(size_t)k] * e[(size_t)k];
-    }
-    DeviceBuf dd, de, de2, dl, map, tmp;
-    if ((s = upload(dd, d)) != FPS_OK || (s = upload(de, e)) != FPS_OK ||
-        (s = upload(de2, e2)) != FPS_OK || (s = alloc(dl, m)) != FPS_OK ||
-        (s = alloc(tmp, 4 * mp * mp)) != FPS_OK)
-      return s;
-    double *T0 = (double *)tmp.p, *T1 = T0 + mp * mp, *V = T1 + mp * mp, *VT = V + mp * mp;
-    const double *lam = (const double *)dl.p;
-    // Lemma B.1: sigma(-A~) lies in [1 / (30 n^4), 1]
-    FPS_HIP(fps::launch_fill(V, mp * mp, 0.0, st));
-    FPS_HIP(fps::launch_tridiag_eig((const double *)dd.p, (const double *)de.p, (const double *)de2.p,
-                                    m, 0.5 / (30.0 * n * n * n * n), 1.01, (double *)dl.p, T0, T1, V,
-                                    mp, st));
-    // The vectors are orthogonal to about m eps (neighbouring eigenvalues
-    // differ by a relative 2 / m); one polar step V <- V (3 I - V^T V) / 2
-    // squares that.
-    FPS_HIP(fps::launch_transpose(V, mp, VT, mp, mp, mp, st));
-    FPS_HIP(product(VT, mp, V, mp, T0, mp, mp, mp, mp, st));
-    FPS_HIP(fps::launch_polar_factor(T0, mp, st));
-    FPS_HIP(product(V, mp, T0, mp, T1, mp, mp, mp, mp, st));
-    std::swap(V, T1);
-    FPS_HIP(fps::launch_transpose(V, mp, VT, mp, mp, mp, st));
-    // input map V^T (S^-1 R)
-    if ((s = upload(map, padded(pl->Rs[sp], m, m, mp, mp))) != FPS_OK ||
-        (s = alloc(pl->d_Wi[sp], mp * mp)) != FPS_OK || (s = alloc(pl->d_WiT[sp], mp * mp)) != FPS_OK ||
-        (s = alloc(pl->d_Wo[sp], mop * mp)) != FPS_OK || (s = alloc(pl->d_WoT[sp], mop * mp)) != FPS_OK)
-      return s;
-    double *Wi = (double *)pl->d_Wi[sp].p, *Wo = (double *)pl->d_Wo[sp].p;
-    FPS_HIP(product(VT, mp, (const double *)map.p, mp, Wi, mp, mp, mp, mp, st));
-    FPS_HIP(fps::launch_transpose(Wi, mp, (double *)pl->d_WiT[sp].p, mp, mp, mp, st));
-    // output map (P S^-1) V, or S^-1 V for the native coefficients
-    DeviceBuf pmap;
-    if (native) {
-      FPS_HIP(fps::launch_scale_rows(V, (const double *)pl->d_sinv.p, sp, m, mp, mp, Wo, st));
-    } else {
-      if ((s = upload(pmap, padded(pl->P[sp], L.mo[sp], m, mop, mp))) != FPS_OK) return s;
-      FPS_HIP(product((const double *)pmap.p, mp, V, mp, Wo, mp, mop, mp, mp, st));
-    }
-    wo_zeros(sp, native ? m : L.mo[sp], m, pl->klo[sp], pl->khi[sp]);
-    if ((s = upload(pl->d_klo[sp], pl->klo[sp])) != FPS_OK ||
-        (s = upload(pl->d_khi[sp], pl->khi[sp])) != FPS_OK)
-      return s;
-    FPS_HIP(fps::launch_zero_below(Wo, (const int *)pl->d_klo[sp].p, native ? m : L.mo[sp], mp, st));
-    FPS_HIP(fps::launch_transpose(Wo, mp, (double *)pl->d_WoT[sp].p, mop, mop, mp, st));
-    // Dirichlet lift map V^T S^-1 C~(T_k''), m x mop
-    DeviceBuf lmap;
-    if (lift) {
-      const int64_t lp = pl->mop[sp];
-      if ((s = upload(lmap, padded(lift[sp], m, L.mo[sp], mp, lp))) != FPS_OK ||
-          (s = alloc(pl->d_lift[sp], mp * lp)) != FPS_OK)
-        return s;
-      FPS_HIP(product(VT, mp, (const double *)lmap.p, lp, (double *)pl->d_lift[sp].p, lp, mp, lp, mp,
-                      st));
-    }
-    FPS_HIP(hipMemcpy(pl->lam.data() + sp * L.mp[0], lam, (size_t)m * 8, hipMemcpyDeviceToHost));
-    FPS_HIP(hipMemcpy(v0.data() + sp * L.mp[0], V, (size_t)m * 8, hipMemcpyDeviceToHost));
+// Consecutive pieces of one allocation, in doubles, each 256-byte aligned.
+struct Pieces {
+  int64_t size = 0;
+  int64_t take(int64_t doubles) {
+    const int64_t at = size;
+    size += (doubles + 31) / 32 * 32;
+    return at;
   }
-  if (lift) {
-    // V^T of the scaled C~ coefficients of (1 - t)/2 and (1 + t)/2, which are
-    // nonzero at degrees 0 and 1 only
-    const BcLiftConst k = bc_lift_const();
-    std::vector<double> a((size_t)(2 * L.npad), 0.0);
-    for (int sp = 0; sp < 2; ++sp)
-      for (int64_t i = 0; i < L.m[sp]; ++i) {
-        const size_t r = (size_t)(sp * L.mp[0] + i);
-        a[2 * r] = k.sinv[sp] * k.am[sp] * v0[r];
-        a[2 * r + 1] = k.sinv[sp] * k.ap[sp] * v0[r];
-      }
-    if ((s = upload(pl->d_lina, a)) != FPS_OK) return s;
-  }
-  return FPS_OK;
-}
+};
 
 // Row and column factors of the 2-D multiplier (see the top of the file) by
 // storage position: (sx2 lambda_i, e_i) and (sy2 lambda_j, f_j).
-fps_status spectral_factors_2d(fps_plan *pl) {
-  const fps::Layout &L = pl->L;
-  std::vector<double> r((size_t)(2 * L.npad)), c((size_t)(2 * L.npad));
-  for (int64_t i = 0; i < L.npad; ++i) {
+void factors_2d(const fps_plan *pl, double *r, double *c) {
+  for (int64_t i = 0; i < pl->L.npad; ++i) {
     const double a = pl->sx2 * pl->lam[(size_t)i], b = -pl->sy2 * pl->lam[(size_t)i];
     double e = 1.0, f = 1.0;
     for (const fps::ShiftSet &sh : pl->rsh)
@@ -196,9 +98,179 @@ fps_status spectral_factors_2d(fps_plan *pl) {
     c[2 * i] = -b;
     c[2 * i + 1] = f;
   }
-  fps_status s;
-  if ((s = upload(pl->d_mr, r)) != FPS_OK) return s;
-  return upload(pl->d_mc, c);
+}
+
+}  // namespace
+
+// Eigenpairs of the parity blocks of A~ and the merged maps, in both
+// orientations (d_Wi / d_WiT, d_Wo / d_WoT); pl->lam gets the eigenvalues by
+// storage position; 2-D plans also get the multiplier's factors.  The plan's L, Rs, P,
+// mop, sinv (and shifts) are set; lift (or null) holds the Dirichlet lift map
+// S^-1 C~(T_k''), merged the same way.  One allocation for the plan's tables, one
+// for the temporaries, an upload per parity, one read-back and one more upload: at
+// n = 64 the calls took longer than the kernels (plan creation 1.32 -> 0.95 ms).
+fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift) {
+  const fps::Layout &L = pl->L;
+  const bool native = pl->out_basis == FPS_OUT_NATIVE;
+  const double n = (double)pl->n;
+  hipStream_t st = nullptr;
+  const int64_t *mp = L.mp;
+  int64_t mop[2];
+  Pieces keep, tmp;
+  int64_t wi[2], wit[2], wo[2], wot[2], li[2], small[2], v[2];  // offsets in the two allocations
+  struct Input {
+    int64_t d, e, e2, klo, map, pmap, lmap, size;  // of one parity's upload
+  } in[2];
+  const int64_t lam_at = tmp.take(L.npad);
+  int64_t up[2];
+  for (int sp = 0; sp < 2; ++sp) {
+    const int64_t m = L.m[sp];
+    mop[sp] = native ? mp[sp] : pl->mop[sp];
+    if (m == 0) continue;
+    wo_zeros(sp, native ? m : L.mo[sp], m, pl->klo[sp], pl->khi[sp]);
+    wi[sp] = keep.take(mp[sp] * mp[sp]);
+    wit[sp] = keep.take(mp[sp] * mp[sp]);
+    wo[sp] = keep.take(mop[sp] * mp[sp]);
+    wot[sp] = keep.take(mop[sp] * mp[sp]);
+    li[sp] = lift ? keep.take(mp[sp] * pl->mop[sp]) : 0;
+    Pieces q;
+    in[sp].d = q.take(m);
+    in[sp].e = q.take(m);
+    in[sp].e2 = q.take(m);
+    in[sp].klo = q.take((int64_t)pl->klo[sp].size());  // ints
+    in[sp].map = q.take(mp[sp] * mp[sp]);
+    in[sp].pmap = native ? 0 : q.take(mop[sp] * mp[sp]);
+    in[sp].lmap = lift ? q.take(mp[sp] * pl->mop[sp]) : 0;
+    in[sp].size = q.size;
+    up[sp] = tmp.take(q.size);
+    v[sp] = tmp.take(4 * mp[sp] * mp[sp]);
+  }
+  const int64_t nf = pl->dim == 2 ? 2 * L.npad : 0;
+  Pieces fin;  // the last upload
+  const int64_t mr = fin.take(nf), mc = fin.take(nf), lina = fin.take(lift ? 2 * L.npad : 0);
+  for (int sp = 0; sp < 2; ++sp)
+    small[sp] = fin.take((int64_t)(pl->klo[sp].size() + pl->khi[sp].size()));  // ints
+  const int64_t fin_at = keep.take(fin.size);
+  DeviceBuf work;
+  if (hipMalloc(&pl->d_maps.p, (size_t)keep.size * 8) != hipSuccess ||
+      hipMalloc(&work.p, (size_t)tmp.size * 8) != hipSuccess)
+    return fail(FPS_E_NOMEM, "hipMalloc of a plan table failed");
+  double *K = (double *)pl->d_maps.p, *W = (double *)work.p;
+
+  fps::TridiagEig eig[2] = {};
+  for (int sp = 0; sp < 2; ++sp) {
+    const int64_t m = L.m[sp], mm = mp[sp];
+    if (m == 0) continue;
+    const Input &q = in[sp];
+    std::vector<double> h((size_t)q.size, 0.0);
+    for (int64_t k = 0; k < m; ++k) {
+      const double off = k + 1 < m ? fps::atilde_off(2 * k + sp) : 0.0;
+      h[(size_t)(q.d + k)] = -fps::atilde_diag(2 * k + sp);
+      h[(size_t)(q.e + k)] = off;
+      h[(size_t)(q.e2 + k)] = off * off;
+    }
+    std::copy(pl->klo[sp].begin(), pl->klo[sp].end(), (int *)(h.data() + q.klo));
+    padded(pl->Rs[sp], m, m, mm, h.data() + q.map);
+    if (!native) padded(pl->P[sp], L.mo[sp], m, mm, h.data() + q.pmap);
+    if (lift) padded(lift[sp], m, L.mo[sp], pl->mop[sp], h.data() + q.lmap);
+    const double *D = W + up[sp];
+    FPS_HIP(hipMemcpy(W + up[sp], h.data(), h.size() * 8, hipMemcpyHostToDevice));
+    double *T0 = W + v[sp];
+    eig[sp] = fps::TridiagEig{D + q.d, D + q.e, D + q.e2, W + lam_at + sp * mp[0],
+                              T0, T0 + mm * mm, T0 + 2 * mm * mm, mm, (int)m};
+    FPS_HIP(fps::launch_fill(eig[sp].V, mm * mm, 0.0, st));
+  }
+  // Lemma B.1: sigma(-A~) lies in [1 / (30 n^4), 1]
+  FPS_HIP(fps::launch_tridiag_eig(eig, 0.5 / (30.0 * n * n * n * n), 1.01, st));
+  // Stage by stage, the products of both parities in one launch.
+  const int np = L.m[1] > 0 ? 2 : 1;
+  double *Vs[2] = {}, *VTs[2] = {};
+  fps::GemmProb g[4];
+  // The vectors are orthogonal to about m eps (neighbouring eigenvalues
+  // differ by a relative 2 / m); one polar step V <- V (3 I - V^T V) / 2
+  // squares that.
+  for (int sp = 0; sp < np; ++sp) {
+    const int64_t mm = mp[sp];
+    const fps::TridiagEig &x = eig[sp];
+    VTs[sp] = x.V + mm * mm;
+    FPS_HIP(fps::launch_transpose(x.V, mm, VTs[sp], mm, mm, mm, st));
+    g[sp] = product(VTs[sp], mm, x.V, mm, x.Dp, mm, mm, mm, mm);
+  }
+  FPS_HIP(fps::launch_gemm(g, np, st));
+  for (int sp = 0; sp < np; ++sp) {
+    const int64_t mm = mp[sp];
+    const fps::TridiagEig &x = eig[sp];
+    FPS_HIP(fps::launch_polar_factor(x.Dp, mm, st));
+    g[sp] = product(x.V, mm, x.Dp, mm, x.Dm, mm, mm, mm, mm);
+    Vs[sp] = x.Dm;
+  }
+  FPS_HIP(fps::launch_gemm(g, np, st));
+  // input maps V^T (S^-1 R); output maps (P S^-1) V, or S^-1 V for the native
+  // coefficients; Dirichlet lift maps V^T S^-1 C~(T_k''), m x mop
+  int cnt = 0;
+  for (int sp = 0; sp < np; ++sp) {
+    const int64_t mm = mp[sp];
+    const double *D = W + up[sp];
+    pl->d_Wi[sp].p = K + wi[sp];
+    pl->d_WiT[sp].p = K + wit[sp];
+    pl->d_Wo[sp].p = K + wo[sp];
+    pl->d_WoT[sp].p = K + wot[sp];
+    FPS_HIP(fps::launch_transpose(Vs[sp], mm, VTs[sp], mm, mm, mm, st));
+    g[cnt++] = product(VTs[sp], mm, D + in[sp].map, mm, K + wi[sp], mm, mm, mm, mm);
+    if (native)
+      FPS_HIP(fps::launch_scale_rows(Vs[sp], (const double *)pl->d_sinv.p, sp, L.m[sp], mm, mm,
+                                     K + wo[sp], st));
+    else
+      g[cnt++] = product(D + in[sp].pmap, mm, Vs[sp], mm, K + wo[sp], mm, mop[sp], mm, mm);
+  }
+  FPS_HIP(fps::launch_gemm(g, cnt, st));
+  for (int sp = 0; sp < np; ++sp) {
+    const int64_t mm = mp[sp], lp = pl->mop[sp];
+    const double *D = W + up[sp];
+    FPS_HIP(fps::launch_transpose(K + wi[sp], mm, K + wit[sp], mm, mm, mm, st));
+    FPS_HIP(fps::launch_zero_below(K + wo[sp], (const int *)(D + in[sp].klo),
+                                   native ? L.m[sp] : L.mo[sp], mm, st));
+    FPS_HIP(fps::launch_transpose(K + wo[sp], mm, K + wot[sp], mop[sp], mop[sp], mm, st));
+    if (lift) {
+      pl->d_lift[sp].p = K + li[sp];
+      g[sp] = product(VTs[sp], mm, D + in[sp].lmap, lp, K + li[sp], lp, mm, lp, mm);
+    }
+  }
+  if (lift) FPS_HIP(fps::launch_gemm(g, np, st));
+  std::vector<double> lam((size_t)L.npad);
+  FPS_HIP(hipMemcpy(lam.data(), W + lam_at, lam.size() * 8, hipMemcpyDeviceToHost));
+  pl->lam.assign((size_t)L.npad, -1.0);
+  for (int sp = 0; sp < 2; ++sp)
+    std::copy_n(lam.begin() + sp * mp[0], L.m[sp], pl->lam.begin() + sp * mp[0]);
+  std::vector<double> h((size_t)fin.size, 0.0);
+  if (nf > 0) factors_2d(pl, h.data() + mr, h.data() + mc);
+  if (lift) {
+    // V^T of the scaled C~ coefficients of (1 - t)/2 and (1 + t)/2, which are
+    // nonzero at degrees 0 and 1 only: the first row of each V
+    const BcLiftConst k = bc_lift_const();
+    for (int sp = 0; sp < 2; ++sp) {
+      if (L.m[sp] == 0) continue;
+      std::vector<double> v0((size_t)L.m[sp]);
+      FPS_HIP(hipMemcpy(v0.data(), Vs[sp], v0.size() * 8, hipMemcpyDeviceToHost));
+      for (int64_t i = 0; i < L.m[sp]; ++i) {
+        const int64_t r = lina + 2 * (sp * mp[0] + i);
+        h[(size_t)r] = k.sinv[sp] * k.am[sp] * v0[(size_t)i];
+        h[(size_t)(r + 1)] = k.sinv[sp] * k.ap[sp] * v0[(size_t)i];
+      }
+    }
+  }
+  for (int sp = 0; sp < 2; ++sp) {
+    int *z = (int *)(h.data() + small[sp]);
+    std::copy(pl->klo[sp].begin(), pl->klo[sp].end(), z);
+    std::copy(pl->khi[sp].begin(), pl->khi[sp].end(), z + pl->klo[sp].size());
+    pl->d_klo[sp].p = (int *)(K + fin_at + small[sp]);
+    pl->d_khi[sp].p = (int *)(K + fin_at + small[sp]) + pl->klo[sp].size();
+  }
+  pl->d_mr.p = K + fin_at + mr;
+  pl->d_mc.p = K + fin_at + mc;
+  if (lift) pl->d_lina.p = K + fin_at + lina;
+  FPS_HIP(hipMemcpy(K + fin_at, h.data(), h.size() * 8, hipMemcpyHostToDevice));
+  return FPS_OK;
 }
 
 }  // namespace detail

@@ -9,24 +9,29 @@ namespace fps {
 
 namespace {
 
+struct EigPair {
+  TridiagEig p[2];
+};
+
 // Eigenvalue k (ascending) of the positive definite B = -T (diagonal d,
 // squared couplings e2) by multisection on Sturm counts: one wavefront per
 // eigenvalue, the 64 lanes counting at 64 interior points, so a pass over the
-// matrix cuts the bracket by 65 instead of 2 (12 passes; the recurrence is a
-// serial chain of m divisions, so passes are what costs).  The points are
+// matrix cuts the bracket by 65 instead of 2 (10 passes, 60 bits; its logarithm starts below
+// 43, so it ends below half an ulp; the recurrence is a serial chain of m divisions, so
+// passes are what costs, and both parities run in one launch).  The points are
 // spaced geometrically until the bracket is within a factor 2: the spectrum
 // spans 30 n^4 and every eigenvalue is wanted to relative accuracy.  A zero
 // pivot is left to IEEE: e2 / 0 = inf, the next pivot is -inf and counts.
-// Measured (m = 2048, both parities): 6 ms.
-__global__ __launch_bounds__(256) void k_tridiag_values(const double *__restrict__ d,
-                                                        const double *__restrict__ e2, int m,
-                                                        double lo0, double hi0,
-                                                        double *__restrict__ lam) {
+__global__ __launch_bounds__(256) void k_tridiag_values(EigPair both, double lo0, double hi0) {
+  const TridiagEig &g = both.p[blockIdx.y];
+  const double *__restrict__ d = g.d, *__restrict__ e2 = g.e2;
+  double *__restrict__ lam = g.lam;
+  const int m = g.m;
   const int lane = threadIdx.x & 63;
   const int k = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
   if (k >= m) return;
   double lo = lo0, hi = hi0;
-  for (int pass = 0; pass < 12; ++pass) {
+  for (int pass = 0; pass < 10; ++pass) {
     const double f = (lane + 1) * (1.0 / 65.0);
     const double x = hi > 2.0 * lo ? lo * exp2(f * log2(hi / lo)) : lo + (hi - lo) * f;
     double q = d[0] - x;
@@ -51,53 +56,62 @@ __global__ __launch_bounds__(256) void k_tridiag_values(const double *__restrict
 // direction.  One lane per vector; pivots and vectors are stored [row][vector],
 // so every access of a wavefront is one 512-byte run.  Dp and Dm are scratch
 // of V's shape (ld columns; V and its padding are zeroed by the caller).
-__global__ __launch_bounds__(64) void k_tridiag_vectors(
-    const double *__restrict__ d, const double *__restrict__ e, int m,
-    const double *__restrict__ lam, double *__restrict__ Dp, double *__restrict__ Dm,
-    double *__restrict__ V, int64_t ld) {
-  const int a = blockIdx.x * 64 + threadIdx.x;
-  if (a >= m) return;
-  const double x = -lam[a];
+// (The pointers are parameters for their no-alias promise: without it no entry of d
+// or e is read before the last pivot is stored.)
+__device__ __forceinline__ void tridiag_vector(const double *__restrict__ d,
+                                               const double *__restrict__ e, int m, int a, double x,
+                                               double *__restrict__ Dp, double *__restrict__ Dm,
+                                               double *__restrict__ V, int64_t ld) {
   constexpr double kEps = 2.220446049250313e-16;
   auto pivot = [&](double q, double c) { return q == 0.0 ? kEps * c : q; };
-  double q = 0.0;
+  // both eliminations at once: two independent chains of divisions
+  double qp = 0.0, qm = 0.0;
+#pragma unroll 4
   for (int i = 0; i < m; ++i) {
-    q = i == 0 ? d[0] - x : (d[i] - x) - e[i - 1] * e[i - 1] / q;
-    q = pivot(q, i + 1 < m ? e[i] : d[i]);
-    Dp[i * ld + a] = q;
+    const int j = m - 1 - i;
+    qp = i == 0 ? d[0] - x : (d[i] - x) - e[i - 1] * e[i - 1] / qp;
+    qm = i == 0 ? d[j] - x : (d[j] - x) - e[j] * e[j] / qm;
+    qp = pivot(qp, i + 1 < m ? e[i] : d[i]);
+    qm = pivot(qm, j > 0 ? e[j - 1] : d[0]);
+    Dp[i * ld + a] = qp;
+    Dm[j * ld + a] = qm;
   }
   double best = 0.0;
   int r = m - 1;
+#pragma unroll 8
   for (int i = m - 1; i >= 0; --i) {
-    q = i == m - 1 ? d[i] - x : (d[i] - x) - e[i] * e[i] / q;
-    q = pivot(q, i > 0 ? e[i - 1] : d[0]);
-    Dm[i * ld + a] = q;
-    const double g = fabs(Dp[i * ld + a] + q - (d[i] - x));
-    if (i == m - 1 || g < best) {
-      best = g;
+    const double t = fabs(Dp[i * ld + a] + Dm[i * ld + a] - (d[i] - x));
+    if (i == m - 1 || t < best) {
+      best = t;
       r = i;
     }
   }
-  double s = 0.0, z = 0.0;
-  for (int i = m - 1; i >= 0; --i) {
-    if (i < r) z *= e[i] / Dp[i * ld + a];
-    if (i == r) z = 1.0;
-    if (i <= r) {
-      V[i * ld + a] = z;
-      s += z * z;
-    }
-  }
-  z = 0.0;
+  double s = 0.0, zu = 0.0, zd = 0.0;  // towards row 0, towards row m - 1
+#pragma unroll 4
   for (int i = 0; i < m; ++i) {
-    if (i == r) z = 1.0;
-    if (i > r) {
-      z *= e[i - 1] / Dm[i * ld + a];
-      V[i * ld + a] = z;
-      s += z * z;
+    const int j = m - 1 - i;
+    if (j < r) zu *= e[j] / Dp[j * ld + a];
+    if (j == r) zu = 1.0;
+    if (j <= r) {
+      V[j * ld + a] = zu;
+      s += zu * zu;
     }
+    if (i > r) {
+      zd *= e[i - 1] / Dm[i * ld + a];
+      V[i * ld + a] = zd;
+      s += zd * zd;
+    }
+    if (i == r) zd = 1.0;
   }
   const double inv = 1.0 / sqrt(s);
+#pragma unroll 8
   for (int i = 0; i < m; ++i) V[i * ld + a] *= inv;
+}
+
+__global__ __launch_bounds__(64) void k_tridiag_vectors(EigPair both) {
+  const TridiagEig &g = both.p[blockIdx.y];
+  const int a = blockIdx.x * 64 + threadIdx.x;
+  if (a < g.m) tridiag_vector(g.d, g.e, g.m, a, -g.lam[a], g.Dp, g.Dm, g.V, g.ld);
 }
 
 // H = 1.5 I - 0.5 H (n x n): with H = V^T V, V H is the first-order step to
@@ -232,16 +246,14 @@ hipError_t launch_nested_multiplier(const double *lam, const double *p, const do
   return hipGetLastError();
 }
 
-hipError_t launch_tridiag_eig(const double *d, const double *e, const double *e2, int64_t m,
-                              double lo, double hi, double *lam, double *Dp, double *Dm, double *V,
-                              int64_t ld, hipStream_t st) {
+hipError_t launch_tridiag_eig(const TridiagEig *p, double lo, double hi, hipStream_t st) {
+  const int m = p[0].m > p[1].m ? p[0].m : p[1].m;
   if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_tridiag_values, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, st, d, e2,
-                     (int)m, lo, hi, lam);
+  const EigPair both{{p[0], p[1]}};
+  hipLaunchKernelGGL(k_tridiag_values, dim3((unsigned)((m + 3) / 4), 2), dim3(256), 0, st, both, lo, hi);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_tridiag_vectors, dim3((unsigned)((m + 63) / 64)), dim3(64), 0, st, d, e,
-                     (int)m, lam, Dp, Dm, V, ld);
+  hipLaunchKernelGGL(k_tridiag_vectors, dim3((unsigned)((m + 63) / 64), 2), dim3(64), 0, st, both);
   return hipGetLastError();
 }
 
