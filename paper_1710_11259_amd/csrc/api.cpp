@@ -100,8 +100,8 @@ fps_status for_row_blocks(fps_plan *pl, hipStream_t st, Body body) {
 // half-step solves along those rows (chain blocks r0 / 64 ..), the second
 // along every column but only over those rows, and each half-step's carries
 // are those of its own chains and positions.
-hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void *Gterm, int g_f32,
-                    int f32, void *O0, void *O1, char *ws, int64_t r0, int64_t r1, int c0, int c1,
+hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const double *Gterm,
+                    double *O0, double *O1, char *ws, int64_t r0, int64_t r1, int c0, int c1,
                     int s, hipStream_t s2) {
   const fps::Layout &L = pl->L;
   const int J = sh.J;
@@ -119,7 +119,6 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
   A0.npad = L.npad;
   A0.ncols = L.npad;
   A0.ld = L.npad;
-  A0.nbatch = 1;
   A0.mp0 = L.mp[0];
   A0.mp1 = L.mp[1];
   A0.mstride = L.mstride;
@@ -135,8 +134,7 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
       A.blk0 = (int)(r0 / 64);
       A.blk1 = (int)(r1 / 64);
     }
-    A.in = j == 0 ? Gterm : (const void *)O1;
-    A.in_f32 = j == 0 ? g_f32 : f32;
+    A.in = j == 0 ? Gterm : O1;
     A.in_scale = j == 0 ? -1.0 : 1.0;
     A.ab_prev = j == 0 ? nullptr : ab;
     A.tab_prev = j == 0 ? nullptr : pl->tab_dev(pl->tab2(base + j - 1));
@@ -144,7 +142,6 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
     A.l1 = pl->l1_dev(pl->tab1(base + j));
     A.sigma = s1;
     A.out = O0;
-    A.out_f32 = f32;
     A.out_mode = 2;
     if (fused && j > 0) {
       A.ab_prev = nullptr;
@@ -156,7 +153,7 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
     hipError_t e = timed_sweep(pl, A, s2, true);
     if (e == hipSuccess && !fused)
       e = fps::launch_reduce(lv, pl->ctab_dev(pl->tab1(base + j)), ab2, -A.sigma, L.npad, nc0,
-                             nc1, L.ncmax, s2, 1, 0, 0, r0, r1, 0, 2);
+                             nc1, L.ncmax, s2, r0, r1, 0, 2);
     if (e != hipSuccess) return e;
     fps::SweepArgs B = A0;
     if (!whole) {
@@ -165,7 +162,6 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
     }
     const bool last = j == J - 1;
     B.in = O0;
-    B.in_f32 = f32;
     B.in_scale = 1.0;
     B.ab_prev = ab2;
     B.tab_prev = A.tab;
@@ -177,18 +173,16 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
     }
     B.lv = lv2;
     B.g = Gterm;
-    B.g_f32 = g_f32;
     B.sg = 1.0;
     B.tab = pl->tab_dev(pl->tab2(base + j));
     B.l1 = pl->l1_dev(pl->tab2(base + j));
     B.sigma = last ? 0.0 : (pl->rect ? p[j + 1] - q[j] : p[j] + p[j + 1]);
     B.out = O1;
-    B.out_f32 = f32;
     B.out_mode = last ? 1 : 2;
     e = timed_sweep(pl, B, s2);
     if (e == hipSuccess && (!fused || last))
       e = fps::launch_reduce(lv2, pl->ctab_dev(pl->tab2(base + j)), ab, last ? 1.0 : -B.sigma,
-                             L.npad, nc0, nc1, L.ncmax, s2, 1, 0, 0, 0, L.npad,
+                             L.npad, nc0, nc1, L.ncmax, s2, 0, L.npad,
                              whole ? 0 : s, whole ? 2 : s + 1);
     if (e != hipSuccess) return e;
     sigma_prev = B.sigma;
@@ -198,10 +192,8 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
 
 // Runs the 2J half-sweeps of Algorithm 2 with the shifts `sh`, whose step j
 // uses the plan's tables of step base + j.  `Gterm` is the right-hand side G
-// (parity-blocked, npad x npad) of storage type g_f32; O0, O1 are the
-// ping-pong arrays (room for npad^2 doubles each), in G's layout.  With f32 set every step stores its outputs in float (refinement
-// rounds, including the final chunk-local solution: a later round corrects
-// its rounding, and the last round's correction is small), else in double.
+// (parity-blocked, npad x npad); O0, O1 are the
+// ping-pong arrays (room for npad^2 doubles each), in G's layout.
 // Leaves the final chunk-local solution in O1 and its chunk carries in ab,
 // to finalize with the tables of the last second half-step
 // (pl->tab2(base + J - 1)).
@@ -221,10 +213,10 @@ hipError_t adi_part(fps_plan *pl, const fps::ShiftSet &sh, int base, const void 
 // (q_j = -p_j, T1_j = T2_j = A~ + p_j) the coefficients are 2 p_j and
 // p_j + p_{j+1}.  After every half-step the chunk carries are resolved,
 // and the next half-step folds them in.
-fps_status run_adi(fps_plan *pl, const fps::ShiftSet &sh, int base, const void *Gterm, int g_f32,
-                   int f32, void *O0, void *O1, char *ws, hipStream_t st) {
+fps_status run_adi(fps_plan *pl, const fps::ShiftSet &sh, int base, const double *Gterm,
+                   double *O0, double *O1, char *ws, hipStream_t st) {
   return for_row_blocks(pl, st, [&](int64_t r0, int64_t r1, int c0, int c1, int s, hipStream_t s2) {
-    return adi_part(pl, sh, base, Gterm, g_f32, f32, O0, O1, ws, r0, r1, c0, c1, s, s2);
+    return adi_part(pl, sh, base, Gterm, O0, O1, ws, r0, r1, c0, c1, s, s2);
   });
 }
 
@@ -898,12 +890,13 @@ fps_status fps_adi_native(fps_plan *pl, const double *G, double *Y, void *ws, vo
   const fps::Layout &L = pl->L;
   double *Gp = (double *)(w + pl->off_G);
   FPS_HIP(fps::launch_permute_in(G, Gp, L.n, L.npad, L.mp[0], st));
-  if ((s = run_adi(pl, pl->shifts, 0, Gp, 0, 0, w + pl->off_O0, w + pl->off_O1, w, st)) != FPS_OK)
+  if ((s = run_adi(pl, pl->shifts, 0, Gp, (double *)(w + pl->off_O0),
+                   (double *)(w + pl->off_O1), w, st)) != FPS_OK)
     return s;
   const int J = pl->shifts.J;
-  FPS_HIP(fps::launch_finalize<double>((double *)(w + pl->off_O1), (double *)(w + pl->off_ab),
-                                       pl->tab_dev(pl->tab2(J - 1)), Y, 1, nullptr, L.n, L.npad, L.mp[0],
-                                       L.mstride, L.ncmax, st));
+  FPS_HIP(fps::launch_finalize((double *)(w + pl->off_O1), (double *)(w + pl->off_ab),
+                               pl->tab_dev(pl->tab2(J - 1)), Y, nullptr, L.n, L.npad, L.mp[0],
+                               L.mstride, L.ncmax, st));
   return FPS_OK;
 }
 

@@ -10,7 +10,6 @@
 #include <numeric>
 #include <vector>
 
-#include "launch_limits.hpp"
 #include "solver.hpp"
 
 using namespace fps::detail;

@@ -342,7 +342,7 @@ __device__ __forceinline__ void edge_columns(const GemmProb &g, int64_t i, int64
 }
 
 // Row units: kCols columns x (256 / kCols) parts of k, the parts' sums added in
-// order; the last lanes clear rows M .. Mz - 1.
+// order.
 template <int kCols>
 __device__ __forceinline__ void edge_rows(const GemmProb &g, int64_t j0, int64_t Mm, double *lds) {
   constexpr int kParts = 256 / kCols;
@@ -374,7 +374,6 @@ __device__ __forceinline__ void edge_rows(const GemmProb &g, int64_t j0, int64_t
     for (int u = 0; u < kParts; ++u) v += lds[e * 256 + u * kCols + tid % kCols];
     g.C[(Mm + e) * g.sci + j * g.scj] = v;
   }
-  for (int64_t i = g.M + part; i < g.Mz; i += kParts) g.C[i * g.sci + j * g.scj] = 0.0;
 }
 
 __device__ __forceinline__ void gemm_edge(const GemmProb &g, int unit, double *lds) {

@@ -10,28 +10,22 @@
 
 namespace fps {
 
-// One ADI half-sweep.  Chains run down the storage rows of a parity-blocked
-// array (npad rows = chain positions of both parities, row stride ld), one
-// chain per storage column (ncols of them); nbatch such arrays (e.g. the
-// z-slices of a cube) are swept together, batch b at offset b * bstride.
+// One FP64 half-sweep of Algorithm 2 (fps_adi_native).  Chains run down the storage
+// rows of a parity-blocked array (npad rows = chain positions of both parities, row
+// stride ld), one chain per storage column (ncols of them).
 //   input  v = in_scale * in + (carry correction of the producing pass)
-//   rhs    r = v + sg * g (g non-null, og == 0) or v; with `pre` non-null, r is
-//          first multiplied along the chain by the tridiagonal stencil with
-//          diagonal pre[row] and coupling pre[npad + row] (rows row, row + 1)
+//   rhs    r = v + sg * g (g non-null) or v
 //   solve  x = T^-1 r along each chain (per parity), T the pass's
 //          tridiagonal (tables)
-//   output out_mode 0: v + og * g - sigma x stored transposed (requires
-//          ncols == ld == npad; the next pass then solves along the other
-//          index); 1: x in place orientation; 2: v + og * g - sigma x in place
+//   output out_mode 0: v - sigma x stored transposed (requires
+//          ncols == ld == npad); 1: x in place orientation; 2: v - sigma x in place
 //          orientation; 3: x stored transposed (as mode 0).  Chunk-level
 //          carries are not applied by the
 //          producer: it leaves its chunk boundary values in `lv`;
 //          launch_reduce turns them into carries, which the consumer (the
-//          next sweep, or a finalize kernel) folds in.
-// A g array enters either the right-hand side (sg, og == 0) or, on stencil
-// passes only, the output base (og, sg == 0).
+//          next sweep, or k_finalize) folds in.
 struct SweepArgs {
-  const void *in;          // [npad rows][ld], storage type in_f32
+  const double *in;        // [npad rows][ld]
   double in_scale;
   const double *ab_prev;   // producer's chunk carries [2][ncmax][npad][2] (producer chains = npad), or null
   const double *tab_prev;  // producer's per-position tables (its shift) [2][kNTab][mstride]
@@ -43,31 +37,20 @@ struct SweepArgs {
   const double *lv_prev;
   const double *ctab_prev;
   double carry_scale;
-  const void *g;           // G term, same layout as `in`, or nullptr
-  double sg, og;
+  const double *g;         // G term, same layout as `in`, or nullptr
+  double sg;
   const double *tab;       // this pass's tables [2][kNTab][mstride]
   const double *l1;        // this pass's segment-carry combinations [2][ncmax][kL1]
   double sigma;
-  void *out;               // storage type out_f32
+  double *out;
   double *lv;              // chunk boundary values [ncmax][2][2][ncols]
-  const double *pre;       // stencil [2][npad] or nullptr (float64 storage only)
-  double pre_shift;        // added to the stencil's diagonal
   int out_mode;
   int64_t npad, mp0, mp1, mstride, ncmax;
   int64_t ncols, ld;       // chains, row stride (elements)
-  int nbatch;              // arrays swept together (>= 1)
-  int64_t bstride;         // elements between arrays (in, g, out)
-  int64_t lvb, abb;        // doubles between the arrays' lv / ab_prev blocks
   int nc0, nc1;
-  // Storage types (0: double, 1: float; arithmetic is double throughout).
-  // Supported: without g, in/out = d/d, f/d, f/f; with g, in/g/out =
-  // d/d/d, d/f/d, f/f/d, f/f/f.  Stencil passes: d/d or f/f without g,
-  // d/d/d or f/f/f with g in the right-hand side, d/d/d with g in the
-  // output base.
-  int in_f32, g_f32, out_f32;
-  // Single launches: the chain blocks (64 chains) blk0 .. blk1-1 and chunk
+  // The chain blocks (64 chains) blk0 .. blk1-1 and chunk
   // rows (parity-0 chunks first) chk0 .. chk1-1 only; blk1 = 0 / chk1 = 0
-  // take all of them.  Batched launches take all.
+  // take all of them.
   int blk0, blk1, chk0, chk1;
 };
 
@@ -78,84 +61,21 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st, hipEvent_t ev0 = nul
 
 // Row-chain half-sweep: the same pass along the storage rows of `in`
 // (chains = rows, positions = columns, ncols = npad chains), stored in the
-// same layout (out_mode 1: x, 2: v - sigma x); no g term or stencil, single
-// arrays; in/out storage d/d, f/d or f/f.  The producer's carries fold in
+// same layout (out_mode 1: x, 2: v - sigma x); no g term.  The producer's carries fold in
 // as in launch_sweep with the producer's chains along the columns; its
 // chunk boundary values go to lv ([ncmax][2][2][npad], chains = rows).
 // Equals launch_sweep on the transposed arrays bit for bit.
 hipError_t launch_sweep_rows(const SweepArgs &a, hipStream_t st, hipEvent_t ev0 = nullptr,
                              hipEvent_t ev1 = nullptr);
 
-// Batched sweeps over several independent problems in one launch.  The
-// workspace pointers of each descriptor's SweepArgs (in, g, out, lv,
-// ab_prev) hold byte offsets from `base`; tab, tab_prev, l1 and pre are
-// device pointers; ab_prev is used iff tab_prev is non-null.  With a stencil
-// (`types.pre` non-null) every descriptor must carry one.  Workgroup g runs
-// block (local % nbx, local / nbx), local = g - wg_start, of problem
-// wg_prob[g].  Storage types and the presence of g come from `types` /
-// `with_g` and must be those of every descriptor.
-struct BatchSweep {
-  SweepArgs a;
-  int wg_start, nbx;
-};
-// wg_base: the launch runs workgroups wg_base .. wg_base + nwg - 1 of the map.
-hipError_t launch_sweep_batch(const SweepArgs &types, bool with_g, const BatchSweep *d,
-                              const int *wg_prob, int nwg, char *base, hipStream_t st,
-                              int wg_base = 0, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// LDS-resident slice ADI of the z-eigenbasis cube (zeig_lds.hip): for
-// every sorted slice k (slice[k] its storage slice, J[k] its steps, 0 for the
-// inactive slices, whose Y^ is zeroed), the J[k] steps of the batched slice
-// sweeps' pass form (x solve with tables tab0[k] + 2j, y solve with tables
-// tab0[k] + 2j + 1 and the stencil pre = A~ + mu[k], the identity at the last
-// step; sigmas sig[sig0[k] + 2j], sig[sig0[k] + 2j + 1]) on G^ (npad^3,
-// [z][y][x]), writing Y^ = -(the final y solve) for all four parity blocks of
-// the slice.  Needs parity blocks of at most 128 (zeig_lds_fits).  The chains are solved in chunks of kZeigLdsChunk
-// positions with the chunk multipliers tab32 ([table][2][BF2, Bk2][mstride])
-// and ctab32 ([table][2][F2last, BF2first, Bk2first][mstride /
-// kZeigLdsChunk]) of fps::build_chunk_tables.
-constexpr int kZeigLdsChunk = 16;
-//
-// The nested cube's inner ADI (`nested`) runs the same kernel with the
-// stencil pre = A~ in both solves (the last y solve keeps it), mu = 0, both
-// solves of step j on table tab0_all + j, every slice k in storage slice k
-// with J_all steps and the sigmas sig[2j], sig[2j + 1], writing +(the final
-// y solve).  Null per-slice arrays take these uniform values (slice k, mu 0,
-// sig0 0); tab0_all / J_all >= 0 replace tab0[] / J[].
-struct ZeigLdsArgs {
-  const double *G;
-  double *Y;
-  const double *tab, *tab32, *ctab32, *pre, *mu, *sig;
-  const int *slice, *J, *tab0, *sig0;
-  int64_t npad, mp0, mstride, ncmax;
-  int m0, m1;
-  int tab0_all = -1, J_all = -1;
-  // nested: Y receives cy x + cr G + cb B instead of x (B null: cy x)
-  const double *B = nullptr;
-  double cy = 1.0, cr = 0.0, cb = 0.0;
-};
-bool zeig_lds_fits(int64_t m0, int64_t m1);
-hipError_t launch_zeig_lds(const ZeigLdsArgs &a, int nslices, hipStream_t st,
-                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, bool nested = false);
-
-// Batched row-chain sweeps (launch_sweep_rows per problem): every
-// descriptor is a single array whose chains are its storage rows, with
-// out_mode 0 (v - sigma x) or 3 (x), stored in the input's layout; no g term
-// or stencil; in/out storage d/d, f/d or f/f from `types`.  Workgroup g runs
-// chain block local % nbx and chunk row local / nbx of problem wg_prob[g].
-hipError_t launch_sweep_batch_rows(const SweepArgs &types, const BatchSweep *d, const int *wg_prob,
-                                   int nwg, char *base, hipStream_t st, int wg_base = 0,
-                                   hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-
 // Chunk carries: for every chain, the forward and backward carry into each
 // chunk, scaled by `scale`, into ab [2][ncmax][nchains][2] (ctab: the
-// per-chunk coefficients [2][kNCTab][ncmax] of the producing pass's shift);
-// nbatch blocks of lv / ab at strides lvb / abb.
+// per-chunk coefficients [2][kNCTab][ncmax] of the producing pass's shift).
 // Only the chains r_lo .. r_hi-1 (r_hi < 0: all) of the parities s_lo ..
 // s_hi-1 are resolved.
 hipError_t launch_reduce(const double *lv, const double *ctab, double *ab, double scale,
                          int64_t nchains, int nc0, int nc1, int64_t ncmax, hipStream_t st,
-                         int nbatch = 1, int64_t lvb = 0, int64_t abb = 0, int64_t r_lo = 0,
-                         int64_t r_hi = -1, int s_lo = 0, int s_hi = 2);
+                         int64_t r_lo = 0, int64_t r_hi = -1, int s_lo = 0, int s_hi = 2);
 
 // Shape of the chunk-carry kernels for chains of up to ncmax chunks: each
 // chain on a segment of 2 to 16 lanes (the least power of two that holds
@@ -169,124 +89,20 @@ inline int reduce_lanes(int64_t ncmax) {
 }
 inline int reduce_chains(int64_t ncmax) { return kReduceThreads / reduce_lanes(ncmax); }
 
-// Batched launch_reduce: lv_off / ab_off are byte offsets from `base`; the
-// workgroups of one problem are (chain block b, parity s) -> local index
-// s * nbx + b with nbx = ceil(npad / reduce_chains(ncmax_max)), flattened as for
-// BatchSweep; ncmax_max bounds every problem's ncmax (lanes per chain).
-struct BatchReduce {
-  int64_t lv_off, ab_off;
-  const double *ctab;
-  double scale;
-  int64_t npad, ncmax;
-  int nc0, nc1;
-  int wg_start, nbx;
-};
-// wg_base: the launch runs workgroups wg_base .. wg_base + nwg - 1 of the map.
-hipError_t launch_reduce_batch(const BatchReduce *d, const int *wg_prob, int nwg, int64_t ncmax_max,
-                               char *base, hipStream_t st, int wg_base = 0);
-
-// Y_perm[r][col] = x[r][col] + carries (final pass, non-transposed; x of
-// storage type T).
-// mode 0: write Y in the parity-blocked layout (npad x npad, ld npad);
-// mode 1: write the natural-order n x n array, entry (i,j) times
-//         sinv_i * sinv_j when `sinv` is non-null;
-// mode 2: add Y into the parity-blocked FP64 array `out`.
-// Only the parity-blocked rows r0 .. r1-1 (r1 < 0: all) are finalized.
-template <typename T>
-hipError_t launch_finalize(const T *x, const double *ab, const double *tab, double *out, int mode,
+// Y = x[r][col] + carries (final pass, non-transposed): the natural-order n x n array
+// `out`, entry (i, j) times sinv_i * sinv_j when `sinv` is non-null.
+hipError_t launch_finalize(const double *x, const double *ab, const double *tab, double *out,
                            const double *sinv, int64_t n, int64_t npad, int64_t mp0,
-                           int64_t mstride, int64_t ncmax, hipStream_t st, int64_t r0 = 0,
-                           int64_t r1 = -1);
-
-// Residual of the symmetric Sylvester equation in the parity-blocked layout,
-// r = G - (A~ Y + Y A~) (Y null: r = G), in FP64, stored in float as r and,
-// with rT non-null, r^T.  A~ acts along each parity block as a tridiagonal stencil with
-// diagonal dv[] and coupling ev[] (ev[k] couples positions k and k+1).
-// For a rectangle the operator is ax A~ Y + ay Y A~ (ax = sx2, ay = sy2).
-// Only the rows r0 .. r1-1 (multiples of 64; r1 < 0: all) are formed (rT
-// only with all rows); rows across a zero coupling are not read.
-hipError_t launch_residual(const double *G, const double *Y, const double *dv, const double *ev,
-                           float *r, float *rT, int64_t npad, hipStream_t st, double ax = 1.0,
-                           double ay = 1.0, int64_t r0 = 0, int64_t r1 = -1);
+                           int64_t mstride, int64_t ncmax, hipStream_t st);
 
 // natural n x n (ld n) -> parity-blocked npad x npad (zero padding); with
 // `sinv` non-null, entry (i, j) is multiplied by sinv[i] * sinv[j].
 hipError_t launch_permute_in(const double *src, double *dst, int64_t n, int64_t npad, int64_t mp0,
                              hipStream_t st, const double *sinv = nullptr);
 
-// parity-blocked npad x npad -> natural n x n, entry (i, j) times
-// sinv[i] * sinv[j] when sinv is non-null.
-hipError_t launch_permute_out(const double *src, double *dst, int64_t n, int64_t npad, int64_t mp0,
-                              const double *sinv, hipStream_t st);
-
-// One problem of a batched element-wise launch (launch_permute_in,
-// launch_residual or launch_finalize for many problems at once, each
-// workgroup doing what the single-problem launch's workgroup does).
-// Workgroups wg_start .. of the launch belong to this problem, nbx per row
-// of its own grid (permute-in, finalize: ceil(npad / 256) per row, npad
-// rows; residual: npad / 64 tiles per row of tiles).  src / dst
-// are byte offsets from the base named by sbase / dbase (0: absolute, 1:
-// workspace, 2: the input F); ab is a workspace offset, tab and ev device
-// pointers.  The residual takes G at src, Y at ab, r at dst, the stencil's
-// diagonal at tab and its coupling at ev.
-struct ElemDesc {
-  int64_t src, dst, ab;
-  const double *tab, *ev;
-  int64_t n, npad, mp0, mstride, ncmax;
-  int sbase, dbase;
-  int wg_start, nbx;
-};
-// F of every problem into its parity-blocked layout (no sinv).
-hipError_t launch_permute_in_batch(const ElemDesc *d, const int *wg_prob, int nwg, const double *in,
-                                   char *ws, hipStream_t st);
-// launch_residual (ax = ay = 1) for every problem; with_y false: r = G.
-hipError_t launch_residual_batch(const ElemDesc *d, const int *wg_prob, int nwg, bool with_y,
-                                 char *ws, hipStream_t st);
-// launch_finalize with mode 0 or 2 (no sinv), the input x in float when
-// x_f32 is set, else in double.
-hipError_t launch_finalize_batch(const ElemDesc *d, const int *wg_prob, int nwg, int mode, char *ws,
-                                 hipStream_t st, int x_f32 = 0);
-
 // Cube (npad^3 arrays [z][y][x], every axis parity-blocked):
 // natural n^3 -> parity-blocked npad^3 (zero padding).
 hipError_t launch_permute3_in(const double *src, double *dst, int64_t n, int64_t npad, int64_t mp0,
-                              hipStream_t st);
-// parity-blocked (row length ld, parity-1 blocks at mb0 on every axis) ->
-// natural N^3, times sinv_i sinv_j sinv_k when sinv is non-null.
-hipError_t launch_permute3_out(const double *src, double *dst, int64_t N, int64_t ld, int64_t mb0,
-                               const double *sinv, hipStream_t st);
-// After a z-fiber sweep: R = x + chunk carries (ab over the npad^2 (y, x)
-// chains, tab of the sweep's shift), stored as R[z][y][x] and, unless RT is
-// null, R^T[z][x][y].
-hipError_t launch_cube_zfinal(const double *x, const double *ab, const double *tab, double *R,
-                              double *RT, int64_t npad, int64_t mp0, int64_t mstride,
-                              int64_t ncmax, hipStream_t st);
-// Per-slice finalization with a table per slice: v = scale (x[z] + chunk
-// carries of slice z) when tabs[z] is non-null, else 0; out[z] = v, or
-// out[z] += v with `add` (x of storage type T).
-template <typename T>
-hipError_t launch_slice_final(const T *x, const double *ab, const double *const *tabs, double *out,
-                              double scale, int add, int64_t npad, int64_t mp0, int64_t mstride,
-                              int64_t ncmax, hipStream_t st);
-// z-eigenbasis cube, refinement: the negated residual of every slice
-// equation, q_z = G_z + A~ Y_z A~ + mu[z] (A~ Y_z + Y_z A~) (Y null: q = G),
-// FP64 arithmetic, stored in float; dv / ev the A~ stencil of
-// launch_residual; nslices arrays of npad x npad at stride npad^2.
-hipError_t launch_zeig_residual(const double *G, const double *Y, const double *dv, const double *ev,
-                                const double *mu, float *q, int64_t npad, int64_t nslices,
-                                hipStream_t st);
-// After a row solve of every slice that left x in place (float, chunk
-// carries pending in ab at the per-slice stride 2 ncmax npad 2, tables tab
-// shared by the slices): v = x + carries stored in float both as outT (x's
-// orientation) and out (transposed).
-hipError_t launch_slice_xfinal(const float *x, const double *ab, const double *tab, float *outT,
-                               float *out, int64_t npad, int64_t mp0, int64_t mstride,
-                               int64_t ncmax, int64_t nslices, hipStream_t st);
-// After the last per-slice sweep (chains = x, positions = y, ab per slice):
-// out = cy (x + chunk carries) + cr R + cb B; ab null: x is complete.
-hipError_t launch_cube_ifinal(const double *x, const double *ab, const double *tab,
-                              const double *R, const double *B, double *out, double cy, double cr,
-                              double cb, int64_t npad, int64_t mp0, int64_t mstride, int64_t ncmax,
                               hipStream_t st);
 hipError_t launch_fill(double *dst, int64_t count, double v, hipStream_t st);
 
@@ -351,9 +167,6 @@ struct GemmProb {
   const double *mr, *mc, *lr, *lc;
   // Cube: a tabulated multiplier instead, mt indexed like C (mr null).
   const double *mt;
-  // Rows M .. Mz - 1 of C are cleared where M has edge rows (1 to 4 past a
-  // multiple of 32): they are the k-padding of the next product.
-  int64_t Mz;
   // split > 0: B is an array in natural order, of `cols` columns and krows rows (A is
   // zero from k = krows on), 8-byte aligned.  Column j of the product goes to column
   // j / 2 (even j) or split + j / 2 (odd) of C, zeros from j = cols to N - 1.  Every

@@ -151,33 +151,17 @@ __device__ __forceinline__ void reduce_block(const double *__restrict__ lv,
                                 scale, nc, lane);
 }
 
-// Grid: (ceil((r_hi - r_lo) / (kReduceThreads / kL)), parities s_lo ..,
-// batch); workgroup of kReduceThreads threads, chain-major.
+// Grid: (ceil((r_hi - r_lo) / (kReduceThreads / kL)), parities s_lo ..); workgroup of kReduceThreads threads, chain-major.
 template <int kL, int kQ>
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(
     const double *__restrict__ lv, const double *__restrict__ ctab, double *__restrict__ ab,
-    double scale, int64_t nchains, int nc0, int nc1, int64_t ncmax, int64_t lvb, int64_t abb,
+    double scale, int64_t nchains, int nc0, int nc1, int64_t ncmax,
     int64_t r_lo, int64_t r_hi, int s_lo) {
   const int s = (int)blockIdx.y + s_lo;
   const int nc = s ? nc1 : nc0;
-  const int64_t z = blockIdx.z;
-  reduce_block<kL, kQ>(lv + z * lvb, ctab + (int64_t)s * kNCTab * ncmax, ab + z * abb, scale,
+  reduce_block<kL, kQ>(lv, ctab + (int64_t)s * kNCTab * ncmax, ab, scale,
                        nchains, nc, ncmax, s,
                        r_lo + (int64_t)blockIdx.x * (kReduceThreads / kL), r_hi);
-}
-
-template <int kL, int kQ>
-__global__ __launch_bounds__(kReduceThreads) void k_reduce_batch(
-    const BatchReduce *__restrict__ d, const int *__restrict__ wg_prob, char *base, int wg_base) {
-  const int g = (int)blockIdx.x + wg_base;
-  const int k = __builtin_amdgcn_readfirstlane(wg_prob[g]);
-  const BatchReduce &e = d[k];
-  const int local = g - e.wg_start;
-  const int s = local / e.nbx;
-  const int nc = s ? e.nc1 : e.nc0;
-  reduce_block<kL, kQ>((const double *)(base + e.lv_off), e.ctab + (int64_t)s * kNCTab * e.ncmax,
-                       (double *)(base + e.ab_off), e.scale, e.npad, nc, e.ncmax, s,
-                       (int64_t)(local % e.nbx) * (kReduceThreads / kL), e.npad);
 }
 
 // Kernel shape for chains of up to ncmax chunks: lanes per chain, and the
@@ -214,32 +198,17 @@ void reduce_shape(int64_t ncmax, int *lanes, int *kq) {
 
 hipError_t launch_reduce(const double *lv, const double *ctab, double *ab, double scale,
                          int64_t nchains, int nc0, int nc1, int64_t ncmax, hipStream_t st,
-                         int nbatch, int64_t lvb, int64_t abb, int64_t r_lo, int64_t r_hi,
-                         int s_lo, int s_hi) {
+                         int64_t r_lo, int64_t r_hi, int s_lo, int s_hi) {
   if (r_hi < 0) r_hi = nchains;
   if (r_lo < 0 || r_hi > nchains || s_lo < 0 || s_hi > 2) return hipErrorInvalidValue;
   if (r_lo >= r_hi || s_lo >= s_hi) return hipSuccess;
   const int chains = reduce_chains(ncmax);
-  dim3 grid((unsigned)((r_hi - r_lo + chains - 1) / chains), (unsigned)(s_hi - s_lo),
-            (unsigned)(nbatch > 0 ? nbatch : 1));
+  dim3 grid((unsigned)((r_hi - r_lo + chains - 1) / chains), (unsigned)(s_hi - s_lo));
   int lanes, kq;
   reduce_shape(ncmax, &lanes, &kq);
 #define FPS_LAUNCH(L, Q)                                                                    \
   hipLaunchKernelGGL((k_reduce<L, Q>), grid, dim3(kReduceThreads), 0, st, lv, ctab, ab, \
-                     scale, nchains, nc0, nc1, ncmax, lvb, abb, r_lo, r_hi, s_lo)
-  FPS_WITH_REDUCE_SHAPE(lanes, kq, FPS_LAUNCH);
-#undef FPS_LAUNCH
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_batch(const BatchReduce *d, const int *wg_prob, int nwg, int64_t ncmax_max,
-                               char *base, hipStream_t st, int wg_base) {
-  if (nwg <= 0) return hipSuccess;
-  int lanes, kq;
-  reduce_shape(ncmax_max, &lanes, &kq);
-#define FPS_LAUNCH(L, Q)                                                                     \
-  hipLaunchKernelGGL((k_reduce_batch<L, Q>), dim3((unsigned)nwg), dim3(kReduceThreads), 0, \
-                     st, d, wg_prob, base, wg_base)
+                     scale, nchains, nc0, nc1, ncmax, r_lo, r_hi, s_lo)
   FPS_WITH_REDUCE_SHAPE(lanes, kq, FPS_LAUNCH);
 #undef FPS_LAUNCH
   return hipGetLastError();
