@@ -1,8 +1,8 @@
 """Benchmark: square Poisson solve (F_T -> U), n = 4096, FP64, on one MI355X.
 
-One step = one full solve through the C ABI: Chebyshev -> C~ input map,
-the 2J ADI half-sweeps of Algorithm 2, and the output map to the (n+2)^2
-Chebyshev coefficients.  Inputs are resident in HBM before timing starts.
+One step = one full solve through the C ABI: the J-step iterate of Algorithm 2 from
+the n^2 Chebyshev coefficients of F to the (n+2)^2 of U, as four dense products in
+the eigenbasis of A~.  Inputs are resident in HBM before timing starts.
 Prints one JSON line.
 """
 from __future__ import annotations
@@ -20,34 +20,6 @@ sys.path.insert(0, ROOT)
 METRIC = "dof/s, square Poisson n=4096 at rel err ≤1e-12; % of HBM roofline"
 HBM_PEAK_GBS = 8000.0
 FP64_MFMA_PEAK_TFLOPS = 78.6  # dense FP64 matrix peak of MI355X
-# Calibrated HBM traffic of the sweep kernels per launch (rocprofv3
-# FETCH_SIZE x1.9999 + WRITE_SIZE x1.0000, see profiles/sweep_square_n4096.md
-# and profiles/sweep_square_n10000.md), valid only for the sweep source
-# (sweep.hip) with this sha256 (the counters were taken on the same device
-# code).
-SWEEP_SOURCES = ("sweep.hip",)
-SWEEP_TRAFFIC = {"sha256": "26523be850a96aee6cae29ca6125c86917afec02f83fb7294da6db3a9528f947",
-                 4096: {"half_step_1": 277.6e6, "half_step_2": 413.0e6},
-                 10000: {"half_step_1": 1764.2e6, "half_step_2": 2529.8e6}}
-
-
-def sweep_sources_sha():
-    import hashlib
-    h = hashlib.sha256()
-    for f in SWEEP_SOURCES:
-        with open(os.path.join(ROOT, "paper_1710_11259_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
-    return h.hexdigest()
-
-
-def sweep_traffic(n):
-    """Counter-measured HBM bytes per sweep launch at size n, mean of the two
-    half-steps, or None when the sources changed since the counters were
-    taken (or no counters exist for n)."""
-    if sweep_sources_sha() != SWEEP_TRAFFIC["sha256"] or n not in SWEEP_TRAFFIC:
-        return None
-    t = SWEEP_TRAFFIC[n]
-    return (t["half_step_1"] + t["half_step_2"]) / 2.0
 
 
 def output_zero_share(n, s):
@@ -121,7 +93,7 @@ def bench_sweeps(fps, torch, plan, G, ws):
             "avg_launch_us": {"half_step_1": round(t1 * 1e6, 2), "half_step_2": round(t2 * 1e6, 2)},
             "achieved_GBs": round((b1 + b2) / (t1 + t2) / 1e9, 1),
             "frac": round((b1 + b2) / (t1 + t2) / 1e9 / HBM_PEAK_GBS, 4),
-            "traffic": sweep_traffic(n), "launches_timed": len(t)}
+            "traffic": None, "launches_timed": len(t)}
 
 
 def copy_rate(torch, dev, mib=1024, reps=5):
@@ -524,24 +496,15 @@ def bench_cylinder(fps, workloads, torch, n=256, n_theta=256, steps=5, check=Tru
     ms = e0.elapsed_time(e1) / steps
     ms_g, same_g = graph_timing(fps, torch, p, F, U, steps)
     dof = float(n) * n * n_theta
-    # Whole-solve rooflines.  MFMA: the four maps, 6 n_theta n^3 flops (z in and
-    # out 2 n_theta n^3 each, r in and out n_theta n^3 each, parity blocks).
-    # HBM: every stage reads its operands and writes its result once: the
-    # permutation (F, X), the z and r input maps (2 X each), the banded solves
-    # (factor table + 2 X), the z output map (X + X_out), the r output map
-    # (X_out + U) and the fill of U; X = 2 n_theta npad^2 doubles, X_out with
-    # the padded z output width.
-    m = n // 2
-    mp = (m + 63) // 64 * 64
-    npad = 2 * mp
-    mobar = 2 * ((m + 1 + 63) // 64 * 64)
-    X = 2.0 * n_theta * npad * npad * 8
-    Xo = X * mobar / npad
-    Fb = 2.0 * n_theta * n * n * 8
-    Ub = 2.0 * n_theta * (n + 4) * (n + 2) * 8
-    fac = (n_theta // 2 + 1) * 8.0 * mp * npad * 8
-    hbm = (Fb + X) + 2 * X + 2 * X + (fac + 2 * X) + (X + Xo) + (Xo + Ub) + Ub
-    flops = 6.0 * n_theta * float(n) ** 3
+    # Whole-solve rooflines.  MFMA: the four maps of the modes' own r parity (n <=
+    # 256), 4 n_theta n^3 flops (z and r, in and out, n_theta n^3 each, parity
+    # blocks).  HBM: every stage reads its operands and writes its result once: F's
+    # rows of one parity, right-hand sides written, the banded solves reading the
+    # factor table and the right-hand sides twice and writing them and the solution,
+    # the solution read, U written.
+    x = float(n_theta) * 2 * (n // 2) * n * 8
+    flops = 4.0 * n_theta * float(n) ** 3
+    hbm = 2 * x + (n_theta // 2 + 1) * 8.0 * (n // 2) * n * 8 + 4 * x + x + U.numel() * 8.0
     res = {"n": n, "n_theta": n_theta, "dof": dof, "ms_per_solve": ms,
            "dof_per_s": dof / (ms * 1e-3), "plan_s": round(t_plan, 2),
            "hip_graph": {"ms_per_solve": ms_g, "dof_per_s": dof / (ms_g * 1e-3),
@@ -615,8 +578,8 @@ def bench_adjoint(fps, workloads, torch, tol, n=2048, batch=16, steps=3, check=T
     """Differentiation form: one forward and one backward pass of the autograd
     solve over a batch of 16 right-hand sides at n = 2048, for the quadratic
     loss ||U(F) - U*||^2 (U* the solution for a fixed target right-hand side).
-    The backward pass is the adjoint solve (the same ADI sweeps between the
-    transposed coefficient maps); nothing is stored from the forward pass."""
+    The backward pass is the adjoint solve (the transposed products in reverse
+    order); nothing is stored from the forward pass."""
     import numpy as np
     F_host, Fstar, _ = workloads.adjoint_case(n, batch, n_dirs=1)
     p = fps.plan(n, tol=tol, tight=tight)
@@ -641,15 +604,14 @@ def bench_adjoint(fps, workloads, torch, tol, n=2048, batch=16, steps=3, check=T
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
     dof = float(batch) * n * n
-    # algorithmic sweep bytes: 40 B per dof per ADI iteration, forward and backward
-    sweep_bytes = 2.0 * batch * p.J * 40.0 * n * n
+    flops = 2.0 * batch * sum(product_flops(n))  # eight product launches
     res = {"n": n, "batch": batch, "J": p.J, "ms_per_fwd_bwd": ms,
            "dof_per_s": dof / (ms * 1e-3),
-           "sweep_bytes_algorithmic": sweep_bytes,
-           "sweep_bytes_rate_GBs": round(sweep_bytes / (ms * 1e-3) / 1e9, 1),
+           "product_flops": flops,
+           "product_TFLOPs_whole_step": round(flops / (ms * 1e-3) / 1e12, 2),
            "method": "autograd Function over one fps_batch: forward fps_batch_solve, backward "
-                     "fps_batch_solve_adjoint (the sweeps of all problems in one launch per "
-                     "half-step)"}
+                     "fps_batch_solve_adjoint (the products of all problems in one launch per "
+                     "stage)"}
     if check:
         from oracle import adjoint
         Ub = (2.0 * (U[0] - Ustar)).detach().cpu().numpy()
