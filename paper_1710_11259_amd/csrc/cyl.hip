@@ -45,54 +45,39 @@ __global__ __launch_bounds__(256) void k_cyl_permute_in(const double *__restrict
 // substitution; yhat: X1 rows of parity wp (zeros beyond m and for padded
 // columns).
 //
-// Bound by HBM and by latency: 270 MB of factors and 134 MB a pass over the right-hand
+// Bound by HBM and by latency: 170 MB of factors and 134 MB a pass over the right-hand
 // sides at 256 x 256, in 1032 wavefronts that each walk 256 dependent steps.  The
 // factors and right-hand sides of kCylStep steps are loaded while the steps before
 // are computed.  The halves of a group (one wavefront each) use the same factors,
 // so their workgroups are 8 apart: on one die, sharing its L2.
+//
+// Piv: false where none of the wavefront's 64 columns was factored with a row
+// exchange (CylSolveGroup::pivots): the pivot offsets and the last two
+// superdiagonals are then zero and are not read, 3 of the 8 fields: 101 MB of 806 at
+// 256 x 256, the solve of the whole cylinder 523 -> 495 us.  At n = 64 and 256 the
+// matrices with |k| != 2 need no exchange, those with |k| = 2 in few columns.
 constexpr int kCylStep = 8, kHalf = kCylRhs / 2;
 
+template <bool Piv>
 struct CylForward {
-  double pv[kCylStep], l1[kCylStep], l2[kCylStep], nb[kHalf][kCylStep];
+  double pv[Piv ? kCylStep : 1], l1[kCylStep], l2[kCylStep], nb[kHalf][kCylStep];
 };
+template <bool Piv>
 struct CylBackward {
-  double iu[kCylStep], u[4][kCylStep], bv[kHalf][kCylStep];
+  double iu[kCylStep], u[Piv ? 4 : 2][kCylStep], bv[kHalf][kCylStep];
 };
 
-__global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
-                                                     double *__restrict__ X1,
-                                                     const double *__restrict__ fac,
-                                                     const CylSolveGroup *__restrict__ grp, int m,
-                                                     int mp, int nzb, int nunits) {
-  const int npad = 2 * mp;
-  const int id = blockIdx.x, unit = (id >> 4) * 8 + (id & 7), half = (id >> 3) & 1;
-  if (unit >= nunits) return;
-  const int zpos = unit % nzb * 64 + threadIdx.x;
-  if (zpos >= npad) return;
-  const CylSolveGroup &e = grp[unit / nzb];
-  const int *sp = e.sp + half * kHalf;
-  if (sp[0] < 0) return;  // the parts of a slot come in pairs
-  double *b[kHalf], *x[kHalf];
-#pragma unroll
-  for (int r = 0; r < kHalf; ++r) {
-    b[r] = X0 + ((int64_t)sp[r] * npad + e.rp * mp) * npad + zpos;
-    x[r] = X1 + ((int64_t)sp[r] * npad + e.wp * mp) * npad + zpos;
-  }
-  if (zpos - (zpos >= mp ? mp : 0) >= m) {
-    for (int a = 0; a < mp; ++a)
-#pragma unroll
-      for (int r = 0; r < kHalf; ++r) x[r][(int64_t)a * npad] = 0.0;
-    return;
-  }
-  const double *f0 = fac + ((int64_t)e.kabs * 8 * mp) * npad + zpos;
+template <bool Piv>
+__device__ void cyl_columns(double *const (&b)[kHalf], double *const (&x)[kHalf],
+                            const double *__restrict__ f0, int m, int mp, int npad) {
   const int64_t fs = (int64_t)mp * npad;  // between factor fields
 
-  auto load_fwd = [&](CylForward &q, int a0) {
+  auto load_fwd = [&](CylForward<Piv> &q, int a0) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
       const int a = min(a0 + t, m - 1);
       const double *f = f0 + (int64_t)a * npad;
-      q.pv[t] = f[0];
+      if constexpr (Piv) q.pv[t] = f[0];
       q.l1[t] = f[fs];
       q.l2[t] = f[2 * fs];
 #pragma unroll
@@ -106,12 +91,12 @@ __global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
     w1[r] = m > 1 ? b[r][npad] : 0.0;
     w2[r] = m > 2 ? b[r][2 * npad] : 0.0;
   }
-  auto run_fwd = [&](const CylForward &q, int a0) {
+  auto run_fwd = [&](const CylForward<Piv> &q, int a0) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
       const int a = a0 + t;
       if (a >= m) break;
-      const int p = (int)q.pv[t];
+      const int p = Piv ? (int)q.pv[Piv ? t : 0] : 0;
 #pragma unroll
       for (int r = 0; r < kHalf; ++r) {
         const double v0 = p == 1 ? w1[r] : p == 2 ? w2[r] : w0[r];
@@ -125,7 +110,7 @@ __global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
     }
   };
   // (loads run ahead of the stores: those of step a are at rows past a + 2)
-  CylForward fa, fb;
+  CylForward<Piv> fa, fb;
   load_fwd(fa, 0);
   for (int a0 = 0; a0 < m; a0 += 2 * kCylStep) {
     load_fwd(fb, a0 + kCylStep);
@@ -134,14 +119,14 @@ __global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
     run_fwd(fb, a0 + kCylStep);
   }
 
-  auto load_bwd = [&](CylBackward &q, int a1) {
+  auto load_bwd = [&](CylBackward<Piv> &q, int a1) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
       const int a = max(a1 - t, 0);
       const double *f = f0 + (int64_t)a * npad;
       q.iu[t] = f[3 * fs];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) q.u[i][t] = f[(4 + i) * fs];
+      for (int i = 0; i < (Piv ? 4 : 2); ++i) q.u[i][t] = f[(4 + i) * fs];
 #pragma unroll
       for (int r = 0; r < kHalf; ++r) q.bv[r][t] = b[r][(int64_t)a * npad];
     }
@@ -149,25 +134,27 @@ __global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
   double x1[kHalf], x2[kHalf], x3[kHalf], x4[kHalf];
 #pragma unroll
   for (int r = 0; r < kHalf; ++r) x1[r] = x2[r] = x3[r] = x4[r] = 0.0;
-  auto run_bwd = [&](const CylBackward &q, int a1) {
+  auto run_bwd = [&](const CylBackward<Piv> &q, int a1) {
 #pragma unroll
     for (int t = 0; t < kCylStep; ++t) {
       const int a = a1 - t;
       if (a < 0) break;
 #pragma unroll
       for (int r = 0; r < kHalf; ++r) {
-        const double v = (q.bv[r][t] - q.u[0][t] * x1[r] - q.u[1][t] * x2[r] - q.u[2][t] * x3[r] -
-                          q.u[3][t] * x4[r]) *
-                         q.iu[t];
+        double v = q.bv[r][t] - q.u[0][t] * x1[r] - q.u[1][t] * x2[r];
+        if constexpr (Piv) {
+          v = v - q.u[2][t] * x3[r] - q.u[3][t] * x4[r];
+          x4[r] = x3[r];
+          x3[r] = x2[r];
+        }
+        v *= q.iu[t];
         x[r][(int64_t)a * npad] = v;
-        x4[r] = x3[r];
-        x3[r] = x2[r];
         x2[r] = x1[r];
         x1[r] = v;
       }
     }
   };
-  CylBackward ba, bb;
+  CylBackward<Piv> ba, bb;
   load_bwd(ba, m - 1);
   for (int a1 = m - 1; a1 >= 0; a1 -= 2 * kCylStep) {
     load_bwd(bb, a1 - kCylStep);
@@ -175,7 +162,37 @@ __global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
     load_bwd(ba, a1 - 2 * kCylStep);
     run_bwd(bb, a1 - kCylStep);
   }
-  for (int a = m; a < mp; ++a)
+}
+
+__global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
+                                                     double *__restrict__ X1,
+                                                     const double *__restrict__ fac,
+                                                     const CylSolveGroup *__restrict__ grp, int m,
+                                                     int mp, int nzb, int nunits) {
+  const int npad = 2 * mp;
+  const int id = blockIdx.x, unit = (id >> 4) * 8 + (id & 7), half = (id >> 3) & 1;
+  if (unit >= nunits) return;
+  const int zb = unit % nzb, zpos = zb * 64 + threadIdx.x;
+  if (zpos >= npad) return;
+  const CylSolveGroup &e = grp[unit / nzb];
+  const int *sp = e.sp + half * kHalf;
+  if (sp[0] < 0) return;  // the parts of a slot come in pairs
+  double *b[kHalf], *x[kHalf];
+#pragma unroll
+  for (int r = 0; r < kHalf; ++r) {
+    b[r] = X0 + ((int64_t)sp[r] * npad + e.rp * mp) * npad + zpos;
+    x[r] = X1 + ((int64_t)sp[r] * npad + e.wp * mp) * npad + zpos;
+  }
+  int a = 0;
+  if (zpos - (zpos >= mp ? mp : 0) < m) {
+    const double *f0 = fac + ((int64_t)e.kabs * 8 * mp) * npad + zpos;
+    if (e.pivots >> zb & 1)
+      cyl_columns<true>(b, x, f0, m, mp, npad);
+    else
+      cyl_columns<false>(b, x, f0, m, mp, npad);
+    a = m;
+  }
+  for (; a < mp; ++a)
 #pragma unroll
     for (int r = 0; r < kHalf; ++r) x[r][(int64_t)a * npad] = 0.0;
 }

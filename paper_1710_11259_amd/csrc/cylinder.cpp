@@ -428,6 +428,7 @@ fps_status cyl_plan_upload(fps_plan *pl) {
     }
   }
   // banded LU factors per (|k|, z column)
+  std::vector<unsigned> pivots((size_t)c->nk, 0u);  // npad <= 512: 8 blocks of columns
   {
     std::vector<double> fac((size_t)(c->nk * 8 * mp * npad), 0.0);
     for (int64_t kabs = 0; kabs < c->nk; ++kabs) {
@@ -440,6 +441,8 @@ fps_status cyl_plan_upload(fps_plan *pl) {
           for (int t = 0; t < 8; ++t) f[t] = fac.data() + ((kabs * 8 + t) * mp) * npad + zpos;
           if (!band_lu(Pb, Qb, lam[s][(size_t)j], m, f, npad))
             return fail(FPS_E_STATE, "internal: singular cylinder mode matrix");
+          for (int64_t a = 0; a < m; ++a)
+            if (f[0][a * npad] != 0.0) pivots[(size_t)kabs] |= 1u << (zpos / 64);
         }
     }
     if ((st = upload(c->d_fac, fac)) != FPS_OK) return st;
@@ -458,6 +461,7 @@ fps_status cyl_plan_upload(fps_plan *pl) {
         e.kabs = kabs;
         e.rp = rp;
         e.wp = wp;
+        e.pivots = pivots[(size_t)kabs];
         gid[kabs] = (int)groups.size();
         groups.push_back(e);
       }

@@ -133,6 +133,7 @@ constexpr int kCylRhs = 4;
 struct CylSolveGroup {
   int sp[kCylRhs];
   int kabs, rp, wp;
+  unsigned pivots;  // bit b: a row exchange in some z column of 64 b .. 64 b + 63
 };
 // Cylinder: the banded r-solves of every (|k| group, z column) with the
 // plan's LU factors (see cylinder.cpp), one thread applying them to all the
