@@ -48,8 +48,10 @@ __global__ __launch_bounds__(256) void k_cyl_permute_in(const double *__restrict
 // Bound by HBM and by latency: 170 MB of factors and 134 MB a pass over the right-hand
 // sides at 256 x 256, in 1032 wavefronts that each walk 256 dependent steps.  The
 // factors and right-hand sides of kCylStep steps are loaded while the steps before
-// are computed.  The halves of a group (one wavefront each) use the same factors,
-// so their workgroups are 8 apart: on one die, sharing its L2.
+// are computed.  The halves of a group (one wavefront each) use the same factors.
+// paired: they are one workgroup, so that one of them finds what the other has read
+// in the compute unit's cache; else their workgroups are 8 apart, on one die, sharing
+// its L2.
 //
 // Piv: false where none of the wavefront's 64 columns was factored with a row
 // exchange (CylSolveGroup::pivots): the pivot offsets and the last two
@@ -164,15 +166,16 @@ __device__ void cyl_columns(double *const (&b)[kHalf], double *const (&x)[kHalf]
   }
 }
 
-__global__ __launch_bounds__(64, 1) void k_cyl_solve(double *__restrict__ X0,
-                                                     double *__restrict__ X1,
-                                                     const double *__restrict__ fac,
-                                                     const CylSolveGroup *__restrict__ grp, int m,
-                                                     int mp, int nzb, int nunits) {
+__global__ __launch_bounds__(128, 1) void k_cyl_solve(double *__restrict__ X0,
+                                                      double *__restrict__ X1,
+                                                      const double *__restrict__ fac,
+                                                      const CylSolveGroup *__restrict__ grp, int m,
+                                                      int mp, int nzb, int nunits, int paired) {
   const int npad = 2 * mp;
-  const int id = blockIdx.x, unit = (id >> 4) * 8 + (id & 7), half = (id >> 3) & 1;
+  const int id = blockIdx.x, unit = paired ? id : (id >> 4) * 8 + (id & 7);
+  const int half = paired ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (id >> 3) & 1;
   if (unit >= nunits) return;
-  const int zb = unit % nzb, zpos = zb * 64 + threadIdx.x;
+  const int zb = unit % nzb, zpos = zb * 64 + (threadIdx.x & 63);
   if (zpos >= npad) return;
   const CylSolveGroup &e = grp[unit / nzb];
   const int *sp = e.sp + half * kHalf;
@@ -214,8 +217,14 @@ hipError_t launch_cyl_solve(double *X0, double *X1, const double *fac, const Cyl
   if (ngroups <= 0) return hipSuccess;
   const int64_t nzb = (2 * mp + 63) / 64, units = nzb * ngroups;
   // n <= 512, n_theta <= 1024: at most 8 x 513 units
-  hipLaunchKernelGGL(k_cyl_solve, dim3((unsigned)((units + 7) / 8 * 16)), dim3(64), 0, st, X0, X1, fac,
-                     grp, (int)m, (int)mp, (int)nzb, (int)units);
+  // Pairs from two units per compute unit on: 496 -> 481 us for the whole solve at
+  // 256 x 256 (516 units), 161 against 161 at 200 x 96 (196 units).  With fewer units
+  // the halves are faster apart, on more compute units: 118 against 123 us at 256 x 64
+  // (132 units), 22.5 against 24.4 at 64 x 64 (33 units).
+  const int paired = units >= 512;
+  const unsigned grid = (unsigned)(paired ? units : (units + 7) / 8 * 16);
+  hipLaunchKernelGGL(k_cyl_solve, dim3(grid), dim3(paired ? 128 : 64), 0, st, X0, X1, fac, grp,
+                     (int)m, (int)mp, (int)nzb, (int)units, paired);
   return hipGetLastError();
 }
 

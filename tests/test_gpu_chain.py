@@ -122,3 +122,19 @@ def test_cylinder_modes_with_row_exchanges(n):
         Uk = (cylinder.solve_mode(np.ascontiguousarray(Fk.real), k)
               + 1j * cylinder.solve_mode(np.ascontiguousarray(Fk.imag), k))
         parity.check(u[k + 3, 0] + 1j * u[k + 3, 1], Uk, 1e-12, f"cylinder n={n} mode {k}")
+
+
+# Banded solves on both sides of 512 units, from which the halves of a |k| group share
+# a workgroup: 3 blocks of columns, the last one partly past the padded size, times
+# 170 and 171 groups, of which k = 0 and -n_theta / 2 have one half alone.
+@pytest.mark.parametrize("nt", [338, 340])
+def test_cylinder_many_modes(nt):
+    n = 130
+    F = workloads.cylinder_rhs(n, nt, seed=nt)
+    x = torch.from_numpy(np.ascontiguousarray(np.stack([F.real, F.imag], axis=1))).cuda()
+    u = _host(fps.solve(fps.plan_cylinder(n, nt), x))
+    for k in (0, -1, 2, -2, 57, nt // 2 - 1, -(nt // 2)):
+        Fk = F[k + nt // 2]
+        Uk = (cylinder.solve_mode(np.ascontiguousarray(Fk.real), k)
+              + 1j * cylinder.solve_mode(np.ascontiguousarray(Fk.imag), k))
+        parity.check(u[k + nt // 2, 0] + 1j * u[k + nt // 2, 1], Uk, 1e-12, f"mode {k}")
