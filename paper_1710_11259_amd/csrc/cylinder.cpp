@@ -270,6 +270,7 @@ fps_status upload_chains(CylPlan *c) {
         b.out_r = (int)c->ro;
         b.out_c = (int)c->mo;
         b.zoff = (int)(outp ? -(n + 2) : n + 2);
+        b.zcol = s;
         a.in_r = a.in_c = b.in_r = b.in_c = (int)c->m;
         for (int r = 0; r < std::min(b.n[1], 32 * c->nb); r += fps::chain_part(c->nb)) {
           a.r0 = b.r0 = r;

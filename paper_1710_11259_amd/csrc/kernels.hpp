@@ -255,8 +255,10 @@ hipError_t launch_gemm_table(const GemmTable &t, const GemmDesc *d, const int *t
 // The multiplier is that of GemmProb (mode 1: mr, mc, lr, lc; mode 2: mt with row
 // stride mt_rs), applied to rows < n[1], columns < n[0] (in_c).  The result goes to
 // out[r * out_rs + c * out_cs] for r < out_r, c < out_c (mode 3: and a zero zoff
-// elements from it, if zoff is not 0).  in / out are absolute (base 0) or byte
-// offsets from the workspace (1), the solve's input (2) or output (3).
+// elements from it, if zoff is not 0; out is column zcol of its row, and the table
+// holds the same block for column 1 - zcol, which shares the writing of the zeros).
+// in / out are absolute (base 0) or byte offsets from the workspace (1), the solve's
+// input (2) or output (3).
 struct ChainDesc {
   const double *in;
   double *out;
@@ -265,7 +267,7 @@ struct ChainDesc {
   int64_t in_rs, out_rs, mt_rs;
   int in_cs, out_cs, in_r, in_c, out_r, out_c, r0;
   int ld[4], k[4], n[4];
-  int ibase, obase, zoff;
+  int ibase, obase, zoff, zcol;
 };
 // Slabs and strips of blocks of up to `len` per side need nb = chain_size(len) (0: too
 // large).
