@@ -499,12 +499,13 @@ def bench_cylinder(fps, workloads, torch, n=256, n_theta=256, steps=5, check=Tru
     # Whole-solve rooflines.  MFMA: the four maps of the modes' own r parity (n <=
     # 256), 4 n_theta n^3 flops (z and r, in and out, n_theta n^3 each, parity
     # blocks).  HBM: every stage reads its operands and writes its result once: F's
-    # rows of one parity, right-hand sides written, the banded solves reading the
-    # factor table and the right-hand sides twice and writing them and the solution,
-    # the solution read, U written.
+    # rows of one parity, right-hand sides written, the banded solves reading five
+    # fields of the factor table (the other three only where rows were exchanged) and
+    # the right-hand sides twice and writing them and the solution, the solution read,
+    # U written.
     x = float(n_theta) * 2 * (n // 2) * n * 8
     flops = 4.0 * n_theta * float(n) ** 3
-    hbm = 2 * x + (n_theta // 2 + 1) * 8.0 * (n // 2) * n * 8 + 4 * x + x + U.numel() * 8.0
+    hbm = 2 * x + (n_theta // 2 + 1) * 5.0 * (n // 2) * n * 8 + 4 * x + x + U.numel() * 8.0
     res = {"n": n, "n_theta": n_theta, "dof": dof, "ms_per_solve": ms,
            "dof_per_s": dof / (ms * 1e-3), "plan_s": round(t_plan, 2),
            "hip_graph": {"ms_per_solve": ms_g, "dof_per_s": dof / (ms_g * 1e-3),
