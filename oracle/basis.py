@@ -83,8 +83,8 @@ def cheb_T(n: int, x: np.ndarray) -> np.ndarray:
     return np.cos(np.outer(np.arange(n), np.arccos(x)))
 
 
-def cheb_to_ct(n: int) -> np.ndarray:
-    """R with R[i, k] = int T_k(x) C~_i(x) (1-x^2) dx, i.e. column k holds the
+def cheb_to_ct(n: int, dtype=np.float64) -> np.ndarray:
+    """R (in float64, or to extended precision with dtype np.longdouble) with R[i, k] = int T_k(x) C~_i(x) (1-x^2) dx, i.e. column k holds the
     C~ coefficients of T_k (orthonormality of C~ under (1-x^2), footnote of
     Sec. 3.1), for i, k < n, entrywise from the Gegenbauer connection formula
     (DLMF 18.18.16) in the limit that gives T_k (DLMF 18.7.25), mu = 3/2:
@@ -95,20 +95,20 @@ def cheb_to_ct(n: int) -> np.ndarray:
     few accurately known factors (relative accuracy of a few eps; Gauss-Jacobi
     quadrature of the integrals in float64 leaves absolute errors ~ eps that
     grow relative to the small entries with n: 9e-14 relative at n = 512)."""
-    R = np.zeros((n, n))
+    R = np.zeros((n, n), dtype=dtype)
     if n == 0:
         return R
     ld = np.longdouble
     mu = ld(1.5)
     j = np.arange(1, n + 1).astype(ld)
     # A(1) = 1/(mu (mu+1)), A(j+1)/A(j) = j/(mu + j + 1); index j - 1
-    A = np.cumprod(np.concatenate([[1 / (mu * (mu + 1))], j[:-1] / (mu + j[:-1] + 1)])).astype(np.float64)
+    A = np.cumprod(np.concatenate([[1 / (mu * (mu + 1))], j[:-1] / (mu + j[:-1] + 1)])).astype(dtype)
     l_ = np.arange(n).astype(ld)
     # B(0) = 1, B(l+1)/B(l) = (l - mu)/(l + 1)
-    B = np.cumprod(np.concatenate([[ld(1)], (l_[:-1] - mu) / (l_[:-1] + 1)])).astype(np.float64)
-    i_all = np.arange(n, dtype=np.float64)
+    B = np.cumprod(np.concatenate([[ld(1)], (l_[:-1] - mu) / (l_[:-1] + 1)])).astype(dtype)
+    i_all = np.arange(n, dtype=dtype)
     nu = np.sqrt((i_all + 1.5) / ((i_all + 1) * (i_all + 2)))
-    RT = np.zeros((n, n))  # row k holds column k (returned transposed, no copy)
+    RT = np.zeros((n, n), dtype=dtype)  # row k holds column k (returned transposed, no copy)
     RT[0, 0] = 1 / nu[0]   # T_0 = C^(mu)_0
     for k in range(1, n):
         l = np.arange(k // 2 + 1)
@@ -132,8 +132,8 @@ def dct_matrix(N: int) -> np.ndarray:
     return C
 
 
-def recombined_to_cheb(n: int) -> np.ndarray:
-    """P (n+2) x n with column i = Chebyshev coefficients of (1-x^2) C~_i(x)
+def recombined_to_cheb(n: int, dtype=np.float64) -> np.ndarray:
+    """P (n+2) x n (dtype as for cheb_to_ct) with column i = Chebyshev coefficients of (1-x^2) C~_i(x)
     (the expansion (3.2)), entrywise from a closed form:
       * C^(3/2)_i = P'_{i+1} (NIST 18.9.19 with lambda = 1/2) and
         (1-x^2) P'_{i+1} = (i+1)(i+2)/(2i+3) (P_i - P_{i+2}) (Legendre P),
@@ -150,20 +150,21 @@ def recombined_to_cheb(n: int) -> np.ndarray:
     grows with n: 3.4e-14 relative at n = 512)."""
     N = n + 2
     if n == 0:
-        return np.zeros((N, n))
+        return np.zeros((N, n), dtype=dtype)
     # L(m) for integer m = 0 .. n+1 by the ratio recurrence, in extended precision
     ld = np.longdouble
     m = np.arange(n + 2)
     ratios = (m[:-1].astype(ld) + ld(0.5)) / (m[:-1].astype(ld) + 1)
-    L = np.concatenate([[np.sqrt(ld(np.pi))], np.sqrt(ld(np.pi)) * np.cumprod(ratios)]).astype(np.float64)
-    PT = np.zeros((n, N))  # row i holds column i (returned transposed, no copy)
+    pi = 4 * np.arctan(ld(1)) if dtype is ld else np.pi
+    L = np.concatenate([[np.sqrt(ld(pi))], np.sqrt(ld(pi)) * np.cumprod(ratios)]).astype(dtype)
+    PT = np.zeros((n, N), dtype=dtype)  # row i holds column i (returned transposed, no copy)
     for i in range(n):
-        nu = np.sqrt((i + 1.5) / ((i + 1) * (i + 2)))
+        nu = np.sqrt((dtype(i) + 1.5) / ((i + 1) * (i + 2)))
         k = np.arange(i % 2, i + 1, 2)
         a, b = (i - k) // 2, (i + k) // 2
-        w = np.where(k == 0, 1.0, 2.0) / np.pi
+        w = np.where(k == 0, dtype(1.0), dtype(2.0)) / pi
         PT[i, k] = nu * (i + 1) * (i + 2) / 4 * w * L[a] * L[b] / ((a + 1.0) * (b + 1.0))
-        PT[i, i + 2] = -nu * (i + 1) * (i + 2) / (2 * i + 3) * (2 / np.pi) * L[0] * L[i + 2]
+        PT[i, i + 2] = -nu * (i + 1) * (i + 2) / (2 * i + 3) * (2 / pi) * L[0] * L[i + 2]
     return PT.T
 
 

@@ -614,10 +614,7 @@ fps_status plan2d_build(fps_plan *pl) {
     }
     fps::build_sweep_tables_ab(pl->L, alpha, beta, pl->tab, pl->ctab, nullptr, pl->l1);
   }
-  fps::build_conversions(pl->L, pl->Rs, pl->P);
   for (int s = 0; s < 2; ++s) pl->mop[s] = (pl->L.mo[s] + fps::kPad - 1) / fps::kPad * fps::kPad;
-  pl->sinv.resize(n);
-  for (int64_t i = 0; i < n; ++i) pl->sinv[i] = 1.0 / std::sqrt((double)(i + 1) * (double)(i + 2));
 
   const fps::Layout &L = pl->L;
   const int64_t sq = align256(L.npad * L.npad * 8);
@@ -640,9 +637,7 @@ fps_status plan2d_build(fps_plan *pl) {
   if (prec == FPS_FP32_REFINED) {
     pl->ws_bytes += sq;  // kept: workspaces of a plan size stay interchangeable
   }
-  std::vector<double> lift[2];
   if (flags & FPS_PLAN_DIRICHLET) {
-    fps::build_lift_map(L, lift);
     pl->off_bc = pl->ws_bytes;
     pl->ws_bytes += align256((4 * L.npad + 8) * 8);
   }
@@ -657,8 +652,8 @@ fps_status plan2d_build(fps_plan *pl) {
   if (!(flags & FPS_PLAN_HOST_ONLY)) {
     fps_status s;
     if ((s = upload(pl->d_tab, pl->tab)) != FPS_OK || (s = upload(pl->d_ctab, pl->ctab)) != FPS_OK ||
-        (s = upload(pl->d_l1, pl->l1)) != FPS_OK || (s = upload(pl->d_sinv, pl->sinv)) != FPS_OK ||
-        (s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) ? lift : nullptr)) != FPS_OK)
+        (s = upload(pl->d_l1, pl->l1)) != FPS_OK ||
+        (s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) != 0)) != FPS_OK)
       return s;
     // chains of more than two chunks: the two row-parity halves of the ADI
     // run on two streams (run_adi)

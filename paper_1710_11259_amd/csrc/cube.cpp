@@ -315,14 +315,11 @@ fps_status cube_plan_build(fps_plan *pl) {
   enclosure(pl, &ea, &eb);
   const fps_status s = pl->zeig ? zeig_shifts(pl, ea, eb) : nested_shifts(pl, ea, eb);
   if (s != FPS_OK) return s;
-  fps::build_conversions(L, pl->Rs, pl->P);
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
   for (int sp = 0; sp < 2; ++sp) {
     pl->mop[sp] = (L.mo[sp] + fps::kPad - 1) / fps::kPad * fps::kPad;
     pl->mqc[sp] = ((native ? L.m[sp] : L.mo[sp]) + 1) / 2 * 2;
   }
-  pl->sinv.resize(n);
-  for (int64_t i = 0; i < n; ++i) pl->sinv[i] = 1.0 / std::sqrt((double)(i + 1) * (double)(i + 2));
   // Workspace: six arrays of (up to) npad^3 (input stages in G / O0 / O1, Y^ in ZR,
   // output stages in O0..O1 and RX..RX + 1), then what the chunk carries of
   // npad^2 chains would take (kept, so that workspaces allocated for a plan
@@ -348,8 +345,7 @@ fps_status cube_plan_upload(fps_plan *pl) {
   const fps::Layout &L = pl->L;
   const int64_t npad = pl->cnp, *mp = pl->cmp;
   fps_status s;
-  if ((s = upload(pl->d_sinv, pl->sinv)) != FPS_OK || (s = spectral_build(pl, nullptr)) != FPS_OK)
-    return s;
+  if ((s = spectral_build(pl, false)) != FPS_OK) return s;
   // the multiplier of every mode
   hipStream_t st = nullptr;
   DeviceBuf lam, ey, ex, p, q, off, mu;

@@ -177,18 +177,43 @@ struct GemmProb {
 hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
 
-// Plan-time passes of the eigenbasis form (spectral.hip).  Eigenpairs of two
-// negative definite tridiagonals T (m 0: none) whose negated diagonal is d, coupling e
-// (e2 = e^2; device arrays of m): lam[a] ascending from the most negative, V the
-// orthonormal-to-m-eps vectors as columns (row length ld); [lo, hi] encloses
-// sigma(-T); Dp, Dm scratch of V's shape, V zeroed by the caller.
+// Plan-time passes of the eigenbasis form (spectral.hip).  Values of about 2^-100
+// relative accuracy, the unevaluated sums p[i] + p[lo + i].
+struct PairArray {
+  double *p;
+  int64_t lo;
+};
+// Eigenpairs of two negative definite tridiagonals T (m 0: none) whose negated diagonal is d
+// and coupling e (e[m - 1] = 0; e2 = e^2 in double; device arrays of m): lam[a] ascending
+// from the most negative, V the orthonormal vectors as columns (row length ld, rows and
+// columns from m on unwritten); [lo, hi] encloses sigma(-T); cp, cm scratch of V's shape.
 struct TridiagEig {
-  const double *d, *e, *e2;
-  double *lam, *Dp, *Dm, *V;
+  PairArray d, e;
+  const double *e2;
+  double *lam;
+  PairArray cp, cm, V;
   int64_t ld;
   int m;
 };
 hipError_t launch_tridiag_eig(const TridiagEig *p, double lo, double hi, hipStream_t st);
+// M[a][b] = row[a] col[b] t[b - a + rows - 1] u[a + b] (planner's MapTables) for a < rows, b <
+// cols, zeros up to prows x ld; up to 4 of them.
+struct MapEntries {
+  PairArray row, col, t, u, M;
+  int64_t rows, cols, prows, ld;
+};
+hipError_t launch_map_entries(const MapEntries *m, int count, hipStream_t st);
+// W = V^T M (rows x cols, contiguous) and, if WT is not null, its transpose, rounded once
+// from the pairs; V as above, M with row length cols, rows and cols multiples of 64.
+// zlo (or null): W[a][j] = 0 for a < zlo[j / kGemmGroup].  Up to 4 of them.
+struct MapProduct {
+  PairArray V, M;
+  int64_t ldv, rows, cols;
+  int m;
+  const int *zlo;
+  double *W, *WT;
+};
+hipError_t launch_map_products(const MapProduct *p, int count, hipStream_t st);
 // Cube multipliers -(1 - eps) / (lz ly + lz lx + ly lx) by storage position
 // [npad]^3 (cube.cpp states the iterations).  z-eigenbasis: eps = ey[z][y]
 // ex[z][x], the error factors of slice z's shifts p / q[off[z] .. off[z+1] - 1]
@@ -205,17 +230,6 @@ hipError_t launch_nested_factors(const double *lam, const double *q, const int *
 hipError_t launch_nested_multiplier(const double *lam, const double *p, const double *q,
                                     const double *r, int J, double *mt, int64_t npad,
                                     hipStream_t st);
-// W[i][j] = 0 for j < klo[i / 64] (rows x ld).
-hipError_t launch_zero_below(double *W, const int *klo, int64_t rows, int64_t ld, hipStream_t st);
-// H = 1.5 I - 0.5 H (n x n, contiguous).
-hipError_t launch_polar_factor(double *H, int64_t n, hipStream_t st);
-// out = in^T, rows x cols multiples of 64.
-hipError_t launch_transpose(const double *in, int64_t ldi, double *out, int64_t ldo, int64_t rows,
-                            int64_t cols, hipStream_t st);
-// out[i][j] = sinv[2i + s] in[i][j] for i < m, 0 for the other rows.
-hipError_t launch_scale_rows(const double *in, const double *sinv, int s, int64_t m, int64_t rows,
-                             int64_t ld, double *out, hipStream_t st);
-
 // Whether an extent has edge rows or columns: 1 to 4 past a multiple of 32.
 __host__ __device__ inline bool gemm_has_edge(int64_t x) {
   return x > 32 && x % 32 >= 1 && x % 32 <= 4;

@@ -150,6 +150,16 @@ double atilde_off(int64_t i) {
   return 1.0 / ((2 * x + 5) * std::sqrt((2 * x + 3) * (2 * x + 7)));
 }
 
+long double atilde_diag_ld(int64_t i) {
+  const long double x = (long double)i;
+  return -2.0L / ((2 * x + 1) * (2 * x + 5));
+}
+
+long double atilde_off_ld(int64_t i) {
+  const long double x = (long double)i;
+  return 1.0L / ((2 * x + 5) * std::sqrt((2 * x + 3) * (2 * x + 7)));
+}
+
 namespace {
 
 // Number of eigenvalues below x of the parity-s block of A~ (m positions):
@@ -463,123 +473,129 @@ void build_sweep_tables_ab(const Layout &L, const std::vector<double> &alpha,
   }
 }
 
+namespace {
+
+// Empty tables of a rows x cols map; row[a] = 1 / sqrt((i+1)(i+2)) times nu_i^e, i = 2a + s,
+// with nu_i = sqrt((i + 3/2)/((i+1)(i+2))): C~_i = nu_i C^(3/2)_i.
+MapTables empty_map(int64_t rows, int64_t cols, int s, int e) {
+  MapTables M;
+  M.rows = rows;
+  M.cols = cols;
+  M.row.resize((size_t)rows);
+  for (int64_t a = 0; a < rows; ++a) {
+    const long double i = (long double)(2 * a + s), w = (i + 1) * (i + 2);
+    M.row[(size_t)a] = e == 0 ? 1.0L / std::sqrt(w) : e > 0 ? std::sqrt(i + 1.5L) / w : 1.0L / std::sqrt(i + 1.5L);
+  }
+  M.col.assign((size_t)cols, 1.0L);
+  M.t.assign((size_t)(rows + cols), 0.0L);
+  M.u.assign((size_t)(rows + cols), 0.0L);
+  return M;
+}
+
+}  // namespace
+
+// T_k = (k/2) sum_l A(k-l) B(l) (i + 3/2) C^(3/2)_i, i = k - 2l, A(j) = (j-1)!/(3/2)_{j+1},
+// B(l) = (-3/2)_l / l! (Gegenbauer connection, DLMF 18.18.16, in the limit that gives T_k,
+// 18.7.25); l = b - a and k - l = a + b + s.  T_0 = C^(3/2)_0: A(0) stands for 2/3 and k/2
+// for 1 there.
+MapTables input_map(const Layout &L, int s) {
+  const int64_t m = L.m[s];
+  MapTables M = empty_map(m, m, s, -1);
+  for (int64_t a = 0; a < m; ++a) {
+    const int64_t k = 2 * a + s;
+    M.row[(size_t)a] *= (long double)k + 1.5L;
+    M.col[(size_t)a] = k == 0 ? 1.0L : 0.5L * (long double)k;
+  }
+  long double B = 1.0L;
+  for (int64_t l = 0; l < m; ++l) {
+    M.t[(size_t)(l + m - 1)] = B;
+    B *= ((long double)l - 1.5L) / (long double)(l + 1);
+  }
+  long double A = 2.0L / 3.0L;  // A(0)
+  for (int64_t j = 0; j < 2 * m + s; ++j) {
+    if (j >= s) M.u[(size_t)(j - s)] = A;
+    A = j == 0 ? 1.0L / (1.5L * 2.5L) : A * (long double)j / ((long double)j + 2.5L);
+  }
+  return M;
+}
+
+// C^(3/2)_i = P'_{i+1} and (1-x^2) P'_{i+1} = (i+1)(i+2)/(2i+3) (P_i - P_{i+2}) (Legendre P);
+// P_j = sum_k (2 - [k = 0])/pi g((j-k)/2) g((j+k)/2) T_k with g(z) = Gamma(z+1/2)/Gamma(z+1)
+// (DLMF 18.18.16 at 1/2, in the limit that gives T_k), and g(z+1) = g(z)(z+1/2)/(z+1) joins the
+// two terms: with h(z) = g(z)/(z+1) the coefficient of T_k, k = 2b + s, is
+//   nu_i (i+1)(i+2)/4 (2 - [k = 0])/pi h(a - b) h(a + b + s),
+// and that of T_{i+2}, which has one term only, the same with -2 g(0) for h(-1).
+MapTables output_map(const Layout &L, int s) {
+  const int64_t m = L.m[s], mo = L.mo[s];
+  MapTables M = empty_map(m, mo, s, 1);
+  const long double pi = std::acos(-1.0L), g0 = std::sqrt(pi);
+  for (int64_t a = 0; a < m; ++a) {
+    const long double i = (long double)(2 * a + s);
+    M.row[(size_t)a] *= 0.25L * (i + 1) * (i + 2);
+  }
+  for (int64_t b = 0; b < mo; ++b) M.col[(size_t)b] = (2 * b + s == 0 ? 1.0L : 2.0L) / pi;
+  long double g = g0;
+  for (int64_t z = 0; z < m + mo + s; ++z) {
+    const long double h = g / (long double)(z + 1);
+    if (z < m) M.t[(size_t)(m - 1 - z)] = h;
+    if (z >= s) M.u[(size_t)(z - s)] = h;
+    g *= ((long double)z + 0.5L) / (long double)(z + 1);
+  }
+  M.t[(size_t)m] = -2.0L * g0;
+  return M;
+}
+
+MapTables native_map(const Layout &L, int s) {
+  const int64_t m = L.m[s];
+  MapTables M = empty_map(m, m, s, 0);
+  M.t[(size_t)(m - 1)] = 1.0L;
+  M.u.assign(M.u.size(), 1.0L);
+  return M;
+}
+
+// T''_k = 2k C^(2)_{k-2} (d/dx T_k = k C^(1)_{k-1}, d/dx C^(l)_j = 2l C^(l+1)_{j-1});
+// C^(lam)_j = sum_l c_{j,l} C^(mu)_{j-2l} with (DLMF 18.18.16)
+//   c_{j,l} = (lam-mu)_l (lam)_{j-l} (mu + j - 2l) / ((mu)_{j-l+1} l!),
+// lam = 2, mu = 3/2, all positive; l = b - a - 1 and j - l = a + b + s - 1.
+MapTables lift_map(const Layout &L, int s) {
+  const int64_t m = L.m[s], mo = L.mo[s];
+  const long double lam = 2.0L, mu = 1.5L;
+  MapTables M = empty_map(m, mo, s, -1);
+  for (int64_t a = 0; a < m; ++a) M.row[(size_t)a] *= (long double)(2 * a + s) + mu;
+  for (int64_t b = 0; b < mo; ++b) M.col[(size_t)b] = 2.0L * (long double)(2 * b + s);
+  long double f = 1.0L;
+  for (int64_t l = 0; l + 1 < mo; ++l) {
+    M.t[(size_t)(l + m)] = f;
+    f *= (lam - mu + (long double)l) / (long double)(l + 1);
+  }
+  long double g = 1.0L / mu;
+  for (int64_t z = 0; z < m + mo - 1; ++z) {
+    M.u[(size_t)(z + 1 - s)] = g;
+    g *= (lam + (long double)z) / (mu + (long double)(z + 1));
+  }
+  return M;
+}
+
 void build_conversions(const Layout &L, std::vector<double> Rs[2], std::vector<double> P[2]) {
-  const int64_t n = L.n, N = n + 2;
-  auto beta = [](int64_t i) -> long double {
-    const long double x = (long double)i;
-    return std::sqrt((x + 1) * (x + 3) / ((2 * x + 3) * (2 * x + 5)));
-  };
-  auto sc = [](int64_t i) -> long double {
-    const long double x = (long double)i;
-    return std::sqrt((x + 1) * (x + 2));
-  };
   for (int s = 0; s < 2; ++s) {
-    Rs[s].assign((size_t)L.m[s] * L.m[s], 0.0);
-    P[s].assign((size_t)L.mo[s] * L.m[s], 0.0);
-  }
-  // Input map: C~ coefficients of T_k by T_{k+1} = 2 x T_k - T_{k-1}, with
-  // multiplication by x in the C~ basis: x C~_i = beta_i C~_{i+1} + beta_{i-1} C~_{i-1}.
-  {
-    std::vector<long double> prev(n + 1, 0.0L), cur(n + 1, 0.0L), nxt(n + 1, 0.0L);
-    auto emit = [&](int64_t k, const std::vector<long double> &v) {
-      const int s = (int)(k & 1);
-      const int64_t b = k >> 1, ms = L.m[s];
-      for (int64_t i = s; i <= k; i += 2) Rs[s][(size_t)(i >> 1) * ms + b] = (double)(v[i] / sc(i));
-    };
-    auto jx = [&](const std::vector<long double> &v, int64_t deg, std::vector<long double> &w) {
-      // w = x * v for v with nonzeros at indices <= deg (same parity as deg)
-      for (int64_t i = 0; i <= deg + 1 && i <= n; ++i) w[i] = 0.0L;
-      for (int64_t i = deg & 1; i <= deg; i += 2) {
-        if (i + 1 <= n) w[i + 1] += beta(i) * v[i];
-        if (i >= 1) w[i - 1] += beta(i - 1) * v[i];
-      }
-    };
-    cur[0] = 2.0L / std::sqrt(3.0L);
-    emit(0, cur);
-    if (n > 1) {
-      jx(cur, 0, nxt);
-      std::swap(prev, cur);
-      std::swap(cur, nxt);
-      emit(1, cur);
-    }
-    for (int64_t k = 1; k + 1 < n; ++k) {
-      jx(cur, k, nxt);
-      for (int64_t i = (k + 1) & 1; i <= k + 1; i += 2) nxt[i] = 2.0L * nxt[i] - prev[i];
-      std::swap(prev, cur);
-      std::swap(cur, nxt);
-      emit(k + 1, cur);
-    }
-  }
-  // Output map: Chebyshev coefficients of phi_i = (1-x^2) C~_i by the same
-  // three-term recurrence, phi_{i+1} = (x phi_i - beta_{i-1} phi_{i-1}) / beta_i,
-  // with x T_0 = T_1 and x T_k = (T_{k+1} + T_{k-1}) / 2.
-  {
-    std::vector<long double> prev(N + 1, 0.0L), cur(N + 1, 0.0L), nxt(N + 1, 0.0L);
-    auto emit = [&](int64_t i, const std::vector<long double> &v) {
-      const int s = (int)(i & 1);
-      const int64_t b = i >> 1, ms = L.m[s];
-      for (int64_t k = s; k <= std::min(i + 2, N - 1); k += 2)
-        P[s][(size_t)(k >> 1) * ms + b] = (double)(v[k] / sc(i));
-    };
-    auto xt = [&](const std::vector<long double> &v, int64_t deg, std::vector<long double> &w) {
-      for (int64_t k = 0; k <= deg + 1 && k <= N; ++k) w[k] = 0.0L;
-      for (int64_t k = deg & 1; k <= deg; k += 2) {
-        if (k == 0) {
-          w[1] += v[0];
-        } else {
-          if (k + 1 <= N) w[k + 1] += 0.5L * v[k];
-          w[k - 1] += 0.5L * v[k];
-        }
-      }
-    };
-    const long double h = std::sqrt(3.0L) / 4.0L;
-    cur[0] = h;
-    cur[2] = -h;
-    emit(0, cur);
-    if (n > 1) {
-      xt(cur, 2, nxt);
-      for (int64_t k = 0; k <= 3; ++k) nxt[k] /= beta(0);
-      std::swap(prev, cur);
-      std::swap(cur, nxt);
-      emit(1, cur);
-    }
-    for (int64_t i = 1; i + 1 < n; ++i) {
-      xt(cur, i + 2, nxt);
-      const long double bi = beta(i), bm = beta(i - 1);
-      for (int64_t k = (i + 1) & 1; k <= i + 3; k += 2) nxt[k] = (nxt[k] - bm * prev[k]) / bi;
-      std::swap(prev, cur);
-      std::swap(cur, nxt);
-      emit(i + 1, cur);
+    const int64_t m = L.m[s], mo = L.mo[s];
+    Rs[s].assign((size_t)(m * m), 0.0);
+    P[s].assign((size_t)(mo * m), 0.0);
+    const MapTables in = input_map(L, s), out = output_map(L, s);
+    for (int64_t a = 0; a < m; ++a) {
+      for (int64_t b = a; b < m; ++b) Rs[s][(size_t)(a * m + b)] = (double)in.at(a, b);
+      for (int64_t b = 0; b <= std::min(a + 1, mo - 1); ++b) P[s][(size_t)(b * m + a)] = (double)out.at(a, b);
     }
   }
 }
 
 void build_lift_map(const Layout &L, std::vector<double> Ms[2]) {
-  const int64_t n = L.n, N = n + 2;
-  for (int s = 0; s < 2; ++s) Ms[s].assign((size_t)L.m[s] * L.mo[s], 0.0);
-  // T''_k = 2k C^(2)_{k-2} (d/dx T_k = k C^(1)_{k-1}, d/dx C^(l)_j = 2l C^(l+1)_{j-1});
-  // C^(lam)_j = sum_l c_{j,l} C^(mu)_{j-2l} with (DLMF 18.18.16)
-  //   c_{j,l} = (lam-mu)_l (lam)_{j-l} (mu + j - 2l) / ((mu)_{j-l+1} l!),
-  // lam = 2, mu = 3/2; C^(3/2)_i = C~_i / nu_i, nu_i = sqrt((i+3/2)/((i+1)(i+2))).
-  const long double lam = 2.0L, mu = 1.5L;
-  long double u0 = 1.0L / mu;  // (lam)_j / (mu)_{j+1} at j = 0
-  for (int64_t k = 2; k < N; ++k) {
-    const int64_t j = k - 2;
-    if (j > 0) u0 *= (lam + (long double)(j - 1)) / (mu + (long double)j);
-    const int s = (int)(k & 1);
-    long double u = u0;
-    for (int64_t l = 0; 2 * l <= j; ++l) {
-      const int64_t i = j - 2 * l;
-      if (i < n) {
-        const long double x = (long double)i;
-        const long double nu = std::sqrt((x + 1.5L) / ((x + 1.0L) * (x + 2.0L)));
-        const long double sc = std::sqrt((x + 1.0L) * (x + 2.0L));
-        Ms[s][(size_t)(i >> 1) * L.mo[s] + (k >> 1)] =
-            (double)(2.0L * (long double)k * u * (mu + x) / (nu * sc));
-      }
-      u *= (lam - mu + (long double)l) / (long double)(l + 1) * (mu + (long double)(j - l)) /
-           (lam + (long double)(j - l - 1));
-    }
+  for (int s = 0; s < 2; ++s) {
+    const int64_t m = L.m[s], mo = L.mo[s];
+    Ms[s].assign((size_t)(m * mo), 0.0);
+    const MapTables M = lift_map(L, s);
+    for (int64_t a = 0; a < m; ++a)
+      for (int64_t b = a + 1; b < mo; ++b) Ms[s][(size_t)(a * mo + b)] = (double)M.at(a, b);
   }
 }
 

@@ -93,6 +93,8 @@ void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam);
 // diagonal at index i, and coupling between i and i+2.
 double atilde_diag(int64_t i);
 double atilde_off(int64_t i);
+long double atilde_diag_ld(int64_t i);
+long double atilde_off_ld(int64_t i);
 
 // Tables for the shifted solves (A~ + p I) along chains of one parity.
 // pos:   [J][2][kNTab][mstride]; chunk: [J][2][kNCTab][ncmax];
@@ -125,21 +127,34 @@ void build_sweep_tables_ab(const Layout &L, const std::vector<double> &alpha,
 void build_chunk_tables(const Layout &L, const std::vector<double> &pos, int64_t chunk,
                         std::vector<double> &out_pos, std::vector<double> &out_chunk);
 
-// Conversion maps split by parity (row-major, float64):
-//   Rs[s]: m[s] x m[s], Rs[s][a][b] = R[2a+s][2b+s] / sqrt((2a+s+1)(2a+s+2)),
-//          R[i][k] = C~_i coefficient of T_k (upper triangular).
-//   P[s]:  mo[s] x m[s], P[s][a][b] = Chebyshev coefficient 2a+s of
-//          (1-x^2) C~_{2b+s}(x) / sqrt((2b+s+1)(2b+s+2)).
-void build_conversions(const Layout &L, std::vector<double> Rs[2], std::vector<double> P[2]);
+// Coefficient maps split by parity, in closed form: entry (a, b) of every one is
+//   row[a] col[b] t[b - a + rows - 1] u[a + b],
+// from four tables in extended precision.  (Products of tables: the entries are as
+// accurate as the tables, where three-term recurrences over the degrees lost up to
+// 5e-16 of a column's largest entry at n = 4096.)
+struct MapTables {
+  int64_t rows = 0, cols = 0;
+  std::vector<long double> row, col, t, u;
+  long double at(int64_t a, int64_t b) const {
+    return row[(size_t)a] * col[(size_t)b] * t[(size_t)(b - a + rows - 1)] * u[(size_t)(a + b)];
+  }
+};
+// S^-1 R: C~_{2a+s} coefficient of T_{2b+s} / sqrt((2a+s+1)(2a+s+2)), m[s] x m[s],
+// upper triangular.
+MapTables input_map(const Layout &L, int s);
+// (P S^-1)^T: Chebyshev coefficient 2b+s of (1-x^2) C~_{2a+s} / sqrt((2a+s+1)(2a+s+2)),
+// m[s] x mo[s], zero for b > a + 1.
+MapTables output_map(const Layout &L, int s);
+// S^-1 alone, m[s] x m[s]: the native coefficients.
+MapTables native_map(const Layout &L, int s);
+// Dirichlet lift (Sec. 6.1): C~_{2a+s} coefficient of T''_{2b+s} / sqrt((2a+s+1)(2a+s+2)),
+// m[s] x mo[s], nonzero only for b > a.  Applied to a trace g it gives S^-1 C~(g'')
+// without forming g'' (whose C~ projection cancels heavily for rough g).
+MapTables lift_map(const Layout &L, int s);
 
-// Dirichlet lift map (Sec. 6.1): the scaled C~ coefficients of the second
-// derivative of each Chebyshev polynomial, split by parity (row-major,
-// float64, m[s] x mo[s]):
-//   Ms[s][a][b] = C~_{2a+s} coefficient of T''_{2b+s} / sqrt((2a+s+1)(2a+s+2)),
-// nonzero only for b > a.  From T''_k = 2k C^(2)_{k-2} and the Gegenbauer
-// connection C^(2) -> C^(3/2) (all coefficients positive), accumulated in
-// extended precision.  Applying it to a trace g gives S^-1 C~(g'') without
-// forming g'' (whose C~ projection cancels heavily for rough g).
+// The same maps in float64 (row-major): Rs[s] the input map, P[s] the output map
+// (mo[s] x m[s]), Ms[s] the lift map.
+void build_conversions(const Layout &L, std::vector<double> Rs[2], std::vector<double> P[2]);
 void build_lift_map(const Layout &L, std::vector<double> Ms[2]);
 
 }  // namespace fps

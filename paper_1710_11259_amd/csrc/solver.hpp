@@ -89,12 +89,10 @@ struct fps_plan {
   int tab2(int j) const { return rect ? 2 * j + 1 : j; }
   fps::Layout L;
   std::vector<double> tab, ctab, l1;  // host sweep tables
-  std::vector<double> Rs[2], P[2];  // host conversion maps (unpadded)
   int64_t mop[2] = {0, 0};          // output parity lengths padded to 64
-  std::vector<double> sinv;         // 1/sqrt((i+1)(i+2))
 
   // device copies
-  fps::detail::DeviceBuf d_tab, d_ctab, d_l1, d_sinv;
+  fps::detail::DeviceBuf d_tab, d_ctab, d_l1;
   // Coefficient maps merged with the eigenvectors V of A~ (spectral.cpp), by
   // parity, zero-padded to multiples of 64, in both orientations: Wi =
   // V^T S^-1 R (mp x mp) and Wo = P S^-1 V (mop x mp; native output S^-1 V,
@@ -201,7 +199,7 @@ struct RefineRound {
 };
 std::vector<RefineRound> refine_schedule(double tol, bool dirichlet);
 // Eigenbasis maps (spectral.cpp).
-fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift);
+fps_status spectral_build(fps_plan *pl, bool lift);
 fps::BcLiftConst bc_lift_const();
 // The products of one square or rectangle solve, per stage up to 4
 // parity-block problems (returns their count), operands formed from the

@@ -14,8 +14,7 @@
 // array through HBM.  At n = 4096 (J = 96) the passes took 10.7 ms of 13.3;
 // the extra 2 n^3 take 2.3 ms.  The passes grow as n^2 log n, the products as
 // n^3, and at the largest size accepted (n = 16384) the products still take
-// less.  One orthogonal transform each way also leaves less rounding than 2J
-// sweeps (n = 4096: 2e-15 against 3e-14).
+// less.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,25 +28,13 @@ namespace detail {
 
 namespace {
 
-// C = A B for one block of zero-padded, contiguous operands.
-fps::GemmProb product(const double *A, int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
-                      int64_t M, int64_t N, int64_t K) {
-  return fps::GemmProb{A, B, C, M, N, K, lda, 1, ldb, 1, ldc, 1};
-}
-
-// rows x cols (row-major) into zeros with row stride cp.
-void padded(const std::vector<double> &M, int64_t rows, int64_t cols, int64_t cp, double *out) {
-  for (int64_t i = 0; i < rows; ++i) std::copy(M.begin() + i * cols, M.begin() + (i + 1) * cols, out + i * cp);
-}
-
 // Zeros of Wo.  Mode a of parity s is u = cos or sin of x y, x = (pi / 2)
 // (2a + s + 1), as far as it is resolved, so its Chebyshev coefficient of
 // index k is ~ J_k(x), which beyond k = x falls like
 // exp(-k (acosh(k/x) - sqrt(1 - (x/k)^2))); its C~ coefficients are
 // ~ J_{k+3/2}(x).  Entries below exp(-43) = 2e-19 of their column are taken as
-// zero: 0.004 of an ulp of what the mode contributes, while the rounding of the
-// eigenvectors leaves ~1e-17 there (LAPACK's vectors have at most 1e-30 in this
-// region, n = 200 ... 4096).  A mode with coefficients to drop at some k <= n + 1
+// zero: 0.004 of an ulp of what the mode contributes (LAPACK's vectors have at most
+// 1e-30 in this region, n = 200 ... 4096).  A mode with coefficients to drop at some k <= n + 1
 // is resolved to better than that.  The share of zeros is 17 % at n = 200, 26 %
 // at 1000 and 29 % at 4096.
 void wo_zeros(int s, int64_t rows, int64_t modes, std::vector<int> &klo, std::vector<int> &khi) {
@@ -100,50 +87,93 @@ void factors_2d(const fps_plan *pl, double *r, double *c) {
   }
 }
 
+// Extended-precision values as pairs in a host image of doubles: h at `at`, l
+// v.size() further on.
+void put_pairs(std::vector<double> &h, int64_t at, const std::vector<long double> &v) {
+  for (size_t i = 0; i < v.size(); ++i) {
+    h[(size_t)at + i] = (double)v[i];
+    h[(size_t)at + v.size() + i] = (double)(v[i] - (long double)(double)v[i]);
+  }
+}
+
+// A map's tables in the upload image, its entries' place among the temporaries.
+struct MapAt {
+  fps::MapTables tab;
+  int64_t row, col, t, u;
+  void place(Pieces &q) {
+    row = q.take(2 * (int64_t)tab.row.size());
+    col = q.take(2 * (int64_t)tab.col.size());
+    t = q.take(2 * (int64_t)tab.t.size());
+    u = q.take(2 * (int64_t)tab.u.size());
+  }
+  void put(std::vector<double> &h) const {
+    put_pairs(h, row, tab.row);
+    put_pairs(h, col, tab.col);
+    put_pairs(h, t, tab.t);
+    put_pairs(h, u, tab.u);
+  }
+  // entries M, zero-padded to prows x ld
+  fps::MapEntries entries(double *W, double *M, int64_t prows, int64_t ld) const {
+    auto pair = [&](int64_t at, const std::vector<long double> &v) {
+      return fps::PairArray{W + at, (int64_t)v.size()};
+    };
+    return fps::MapEntries{pair(row, tab.row), pair(col, tab.col), pair(t, tab.t), pair(u, tab.u),
+                           fps::PairArray{M, prows * ld}, tab.rows, tab.cols, prows, ld};
+  }
+};
+
 }  // namespace
 
 // Eigenpairs of the parity blocks of A~ and the merged maps, in both
 // orientations (d_Wi / d_WiT, d_Wo / d_WoT); pl->lam gets the eigenvalues by
-// storage position; 2-D plans also get the multiplier's factors.  The plan's L, Rs, P,
-// mop, sinv (and shifts) are set; lift (or null) holds the Dirichlet lift map
-// S^-1 C~(T_k''), merged the same way.  One allocation for the plan's tables, one
-// for the temporaries, an upload per parity, one read-back and one more upload: at
-// n = 64 the calls took longer than the kernels (plan creation 1.32 -> 0.95 ms).
-fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift) {
+// storage position; 2-D plans also get the multiplier's factors.  The plan's L, mop
+// (and shifts) are set; lift: also the Dirichlet lift map, merged the same way.  The maps'
+// closed forms (MapTables) are tables of O(n), so the uploads are short and everything of
+// O(n^2) or more is formed on the device, in pairs of doubles until its one
+// rounding.  One allocation for the plan's tables, one for the temporaries, two uploads
+// and one read-back: at n = 64 the calls take longer than the kernels.
+fps_status spectral_build(fps_plan *pl, bool lift) {
   const fps::Layout &L = pl->L;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
   const double n = (double)pl->n;
   hipStream_t st = nullptr;
   const int64_t *mp = L.mp;
+  const int np = L.m[1] > 0 ? 2 : 1;
   int64_t mop[2];
   Pieces keep, tmp;
-  int64_t wi[2], wit[2], wo[2], wot[2], li[2], small[2], v[2];  // offsets in the two allocations
-  struct Input {
-    int64_t d, e, e2, klo, map, pmap, lmap, size;  // of one parity's upload
-  } in[2];
-  const int64_t lam_at = tmp.take(L.npad);
-  int64_t up[2];
-  for (int sp = 0; sp < 2; ++sp) {
+  int64_t wi[2], wit[2], wo[2], wot[2], li[2], small[2];  // offsets in the two allocations
+  int64_t d[2], e[2], e2[2], klo[2], v[2], s0[2], s1[2];
+  MapAt in[2], out[2], lm[2];
+  for (int sp = 0; sp < np; ++sp) {
     const int64_t m = L.m[sp];
     mop[sp] = native ? mp[sp] : pl->mop[sp];
-    if (m == 0) continue;
     wo_zeros(sp, native ? m : L.mo[sp], m, pl->klo[sp], pl->khi[sp]);
     wi[sp] = keep.take(mp[sp] * mp[sp]);
     wit[sp] = keep.take(mp[sp] * mp[sp]);
     wo[sp] = keep.take(mop[sp] * mp[sp]);
     wot[sp] = keep.take(mop[sp] * mp[sp]);
     li[sp] = lift ? keep.take(mp[sp] * pl->mop[sp]) : 0;
-    Pieces q;
-    in[sp].d = q.take(m);
-    in[sp].e = q.take(m);
-    in[sp].e2 = q.take(m);
-    in[sp].klo = q.take((int64_t)pl->klo[sp].size());  // ints
-    in[sp].map = q.take(mp[sp] * mp[sp]);
-    in[sp].pmap = native ? 0 : q.take(mop[sp] * mp[sp]);
-    in[sp].lmap = lift ? q.take(mp[sp] * pl->mop[sp]) : 0;
-    in[sp].size = q.size;
-    up[sp] = tmp.take(q.size);
-    v[sp] = tmp.take(4 * mp[sp] * mp[sp]);
+    // the upload, at the front of the temporaries
+    d[sp] = tmp.take(2 * m);
+    e[sp] = tmp.take(2 * m);
+    e2[sp] = tmp.take(m);
+    klo[sp] = tmp.take((int64_t)pl->klo[sp].size());  // ints
+    in[sp].tab = fps::input_map(L, sp);
+    in[sp].place(tmp);
+    out[sp].tab = native ? fps::native_map(L, sp) : fps::output_map(L, sp);
+    out[sp].place(tmp);
+    if (!lift) continue;
+    lm[sp].tab = fps::lift_map(L, sp);
+    lm[sp].place(tmp);
+  }
+  const int64_t up = tmp.size;
+  const int64_t lam_at = tmp.take(L.npad);
+  for (int sp = 0; sp < np; ++sp) {
+    // vectors; the eliminations' ratios, then the maps' entries
+    const int64_t wide = std::max(mp[sp], pl->mop[sp]);
+    v[sp] = tmp.take(2 * mp[sp] * mp[sp]);
+    s0[sp] = tmp.take(2 * mp[sp] * wide);
+    s1[sp] = tmp.take(2 * mp[sp] * wide);
   }
   const int64_t nf = pl->dim == 2 ? 2 * L.npad : 0;
   Pieces fin;  // the last upload
@@ -157,101 +187,72 @@ fps_status spectral_build(fps_plan *pl, const std::vector<double> *lift) {
     return fail(FPS_E_NOMEM, "hipMalloc of a plan table failed");
   double *K = (double *)pl->d_maps.p, *W = (double *)work.p;
 
+  std::vector<double> h((size_t)up, 0.0);
   fps::TridiagEig eig[2] = {};
-  for (int sp = 0; sp < 2; ++sp) {
-    const int64_t m = L.m[sp], mm = mp[sp];
-    if (m == 0) continue;
-    const Input &q = in[sp];
-    std::vector<double> h((size_t)q.size, 0.0);
-    for (int64_t k = 0; k < m; ++k) {
-      const double off = k + 1 < m ? fps::atilde_off(2 * k + sp) : 0.0;
-      h[(size_t)(q.d + k)] = -fps::atilde_diag(2 * k + sp);
-      h[(size_t)(q.e + k)] = off;
-      h[(size_t)(q.e2 + k)] = off * off;
-    }
-    std::copy(pl->klo[sp].begin(), pl->klo[sp].end(), (int *)(h.data() + q.klo));
-    padded(pl->Rs[sp], m, m, mm, h.data() + q.map);
-    if (!native) padded(pl->P[sp], L.mo[sp], m, mm, h.data() + q.pmap);
-    if (lift) padded(lift[sp], m, L.mo[sp], pl->mop[sp], h.data() + q.lmap);
-    const double *D = W + up[sp];
-    FPS_HIP(hipMemcpy(W + up[sp], h.data(), h.size() * 8, hipMemcpyHostToDevice));
-    double *T0 = W + v[sp];
-    eig[sp] = fps::TridiagEig{D + q.d, D + q.e, D + q.e2, W + lam_at + sp * mp[0],
-                              T0, T0 + mm * mm, T0 + 2 * mm * mm, mm, (int)m};
-    FPS_HIP(fps::launch_fill(eig[sp].V, mm * mm, 0.0, st));
-  }
-  // Lemma B.1: sigma(-A~) lies in [1 / (30 n^4), 1]
-  FPS_HIP(fps::launch_tridiag_eig(eig, 0.5 / (30.0 * n * n * n * n), 1.01, st));
-  // Stage by stage, the products of both parities in one launch.
-  const int np = L.m[1] > 0 ? 2 : 1;
-  double *Vs[2] = {}, *VTs[2] = {};
-  fps::GemmProb g[4];
-  // The vectors are orthogonal to about m eps (neighbouring eigenvalues
-  // differ by a relative 2 / m); one polar step V <- V (3 I - V^T V) / 2
-  // squares that.
-  for (int sp = 0; sp < np; ++sp) {
-    const int64_t mm = mp[sp];
-    const fps::TridiagEig &x = eig[sp];
-    VTs[sp] = x.V + mm * mm;
-    FPS_HIP(fps::launch_transpose(x.V, mm, VTs[sp], mm, mm, mm, st));
-    g[sp] = product(VTs[sp], mm, x.V, mm, x.Dp, mm, mm, mm, mm);
-  }
-  FPS_HIP(fps::launch_gemm(g, np, st));
-  for (int sp = 0; sp < np; ++sp) {
-    const int64_t mm = mp[sp];
-    const fps::TridiagEig &x = eig[sp];
-    FPS_HIP(fps::launch_polar_factor(x.Dp, mm, st));
-    g[sp] = product(x.V, mm, x.Dp, mm, x.Dm, mm, mm, mm, mm);
-    Vs[sp] = x.Dm;
-  }
-  FPS_HIP(fps::launch_gemm(g, np, st));
-  // input maps V^T (S^-1 R); output maps (P S^-1) V, or S^-1 V for the native
-  // coefficients; Dirichlet lift maps V^T S^-1 C~(T_k''), m x mop
+  fps::MapEntries me[4];
   int cnt = 0;
   for (int sp = 0; sp < np; ++sp) {
-    const int64_t mm = mp[sp];
-    const double *D = W + up[sp];
+    const int64_t m = L.m[sp], mm = mp[sp];
+    std::vector<long double> diag((size_t)m), off((size_t)m);
+    for (int64_t k = 0; k < m; ++k) {
+      diag[(size_t)k] = -fps::atilde_diag_ld(2 * k + sp);
+      off[(size_t)k] = k + 1 < m ? fps::atilde_off_ld(2 * k + sp) : 0.0L;
+      h[(size_t)(e2[sp] + k)] = (double)(off[(size_t)k] * off[(size_t)k]);
+    }
+    put_pairs(h, d[sp], diag);
+    put_pairs(h, e[sp], off);
+    std::copy(pl->klo[sp].begin(), pl->klo[sp].end(), (int *)(h.data() + klo[sp]));
+    in[sp].put(h);
+    out[sp].put(h);
+    if (lift) lm[sp].put(h);
+    const int64_t sq = mm * mm;
+    eig[sp] = fps::TridiagEig{{W + d[sp], m}, {W + e[sp], m}, W + e2[sp], W + lam_at + sp * mp[0],
+                              {W + s0[sp], sq}, {W + s1[sp], sq}, {W + v[sp], sq}, mm, (int)m};
+    me[cnt++] = in[sp].entries(W, W + s0[sp], mm, mm);
+    me[cnt++] = out[sp].entries(W, W + s1[sp], mm, mop[sp]);
+  }
+  FPS_HIP(hipMemcpy(W, h.data(), h.size() * 8, hipMemcpyHostToDevice));
+  // Lemma B.1: sigma(-A~) lies in [1 / (30 n^4), 1]
+  FPS_HIP(fps::launch_tridiag_eig(eig, 0.5 / (30.0 * n * n * n * n), 1.01, st));
+  // Wi = V^T (S^-1 R); Wo^T = V^T (P S^-1)^T, or V^T S^-1 for the native coefficients
+  FPS_HIP(fps::launch_map_entries(me, cnt, st));
+  fps::MapProduct mq[4];
+  for (int i = 0; i < cnt; ++i) {
+    const int sp = i / 2;
+    double *w[4] = {K + wi[sp], K + wit[sp], K + wot[sp], K + wo[sp]};
+    mq[i] = fps::MapProduct{eig[sp].V, me[i].M, mp[sp], mp[sp], me[i].ld, eig[sp].m,
+                            i % 2 ? (const int *)(W + klo[sp]) : nullptr, w[i % 2 * 2], w[i % 2 * 2 + 1]};
+    if (i % 2) continue;
     pl->d_Wi[sp].p = K + wi[sp];
     pl->d_WiT[sp].p = K + wit[sp];
     pl->d_Wo[sp].p = K + wo[sp];
     pl->d_WoT[sp].p = K + wot[sp];
-    FPS_HIP(fps::launch_transpose(Vs[sp], mm, VTs[sp], mm, mm, mm, st));
-    g[cnt++] = product(VTs[sp], mm, D + in[sp].map, mm, K + wi[sp], mm, mm, mm, mm);
-    if (native)
-      FPS_HIP(fps::launch_scale_rows(Vs[sp], (const double *)pl->d_sinv.p, sp, L.m[sp], mm, mm,
-                                     K + wo[sp], st));
-    else
-      g[cnt++] = product(D + in[sp].pmap, mm, Vs[sp], mm, K + wo[sp], mm, mop[sp], mm, mm);
   }
-  FPS_HIP(fps::launch_gemm(g, cnt, st));
-  for (int sp = 0; sp < np; ++sp) {
-    const int64_t mm = mp[sp], lp = pl->mop[sp];
-    const double *D = W + up[sp];
-    FPS_HIP(fps::launch_transpose(K + wi[sp], mm, K + wit[sp], mm, mm, mm, st));
-    FPS_HIP(fps::launch_zero_below(K + wo[sp], (const int *)(D + in[sp].klo),
-                                   native ? L.m[sp] : L.mo[sp], mm, st));
-    FPS_HIP(fps::launch_transpose(K + wo[sp], mm, K + wot[sp], mop[sp], mop[sp], mm, st));
-    if (lift) {
+  FPS_HIP(fps::launch_map_products(mq, cnt, st));
+  if (lift) {  // V^T S^-1 C~(T_k''), m x mop
+    for (int sp = 0; sp < np; ++sp) {
       pl->d_lift[sp].p = K + li[sp];
-      g[sp] = product(VTs[sp], mm, D + in[sp].lmap, lp, K + li[sp], lp, mm, lp, mm);
+      me[sp] = lm[sp].entries(W, W + s0[sp], mp[sp], pl->mop[sp]);
+      mq[sp] = fps::MapProduct{eig[sp].V, me[sp].M, mp[sp], mp[sp], pl->mop[sp], eig[sp].m, nullptr,
+                               K + li[sp], nullptr};
     }
+    FPS_HIP(fps::launch_map_entries(me, np, st));
+    FPS_HIP(fps::launch_map_products(mq, np, st));
   }
-  if (lift) FPS_HIP(fps::launch_gemm(g, np, st));
   std::vector<double> lam((size_t)L.npad);
   FPS_HIP(hipMemcpy(lam.data(), W + lam_at, lam.size() * 8, hipMemcpyDeviceToHost));
   pl->lam.assign((size_t)L.npad, -1.0);
   for (int sp = 0; sp < 2; ++sp)
     std::copy_n(lam.begin() + sp * mp[0], L.m[sp], pl->lam.begin() + sp * mp[0]);
-  std::vector<double> h((size_t)fin.size, 0.0);
+  h.assign((size_t)fin.size, 0.0);
   if (nf > 0) factors_2d(pl, h.data() + mr, h.data() + mc);
   if (lift) {
     // V^T of the scaled C~ coefficients of (1 - t)/2 and (1 + t)/2, which are
     // nonzero at degrees 0 and 1 only: the first row of each V
     const BcLiftConst k = bc_lift_const();
-    for (int sp = 0; sp < 2; ++sp) {
-      if (L.m[sp] == 0) continue;
+    for (int sp = 0; sp < np; ++sp) {
       std::vector<double> v0((size_t)L.m[sp]);
-      FPS_HIP(hipMemcpy(v0.data(), Vs[sp], v0.size() * 8, hipMemcpyDeviceToHost));
+      FPS_HIP(hipMemcpy(v0.data(), eig[sp].V.p, v0.size() * 8, hipMemcpyDeviceToHost));
       for (int64_t i = 0; i < L.m[sp]; ++i) {
         const int64_t r = lina + 2 * (sp * mp[0] + i);
         h[(size_t)r] = k.sinv[sp] * k.am[sp] * v0[(size_t)i];

@@ -1,6 +1,12 @@
 // gfx950 kernels that build the eigenbasis form of the solve at plan time:
 // eigenpairs of the symmetric tridiagonal parity blocks of A~ (App. B
-// decoupling) and the small dense passes around them.
+// decoupling) and the coefficient maps merged with them.
+//
+// The vectors and the merged maps are formed in pairs of doubles (error-free sums and
+// products: T. J. Dekker, Numer. Math. 18 (1971)) and rounded once.  With vectors and
+// maps formed in double the rounding of the solves they enter was up to twice as large
+// (adjoint, native, n = 64: rms 8e-16 of the result, 4e-16 from these, 3e-16 from
+// half-sweeps).
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
@@ -24,7 +30,7 @@ struct EigPair {
 // pivot is left to IEEE: e2 / 0 = inf, the next pivot is -inf and counts.
 __global__ __launch_bounds__(256) void k_tridiag_values(EigPair both, double lo0, double hi0) {
   const TridiagEig &g = both.p[blockIdx.y];
-  const double *__restrict__ d = g.d, *__restrict__ e2 = g.e2;
+  const double *__restrict__ d = g.d.p, *__restrict__ e2 = g.e2;
   double *__restrict__ lam = g.lam;
   const int m = g.m;
   const int lane = threadIdx.x & 63;
@@ -50,101 +56,221 @@ __global__ __launch_bounds__(256) void k_tridiag_values(EigPair both, double lo0
   if (lane == 0) lam[m - 1 - k] = -(lo + 0.5 * (hi - lo));  // most negative first
 }
 
-// Eigenvector of every eigenvalue by the twisted factorization of B - x: the
-// pivots of the top-down and bottom-up eliminations, twisted where their
-// combination is smallest, then one multiplication per entry in each
-// direction.  One lane per vector; pivots and vectors are stored [row][vector],
-// so every access of a wavefront is one 512-byte run.  Dp and Dm are scratch
-// of V's shape (ld columns; V and its padding are zeroed by the caller).
-// (The pointers are parameters for their no-alias promise: without it no entry of d
-// or e is read before the last pivot is stored.)
-__device__ __forceinline__ void tridiag_vector(const double *__restrict__ d,
-                                               const double *__restrict__ e, int m, int a, double x,
-                                               double *__restrict__ Dp, double *__restrict__ Dm,
-                                               double *__restrict__ V, int64_t ld) {
-  constexpr double kEps = 2.220446049250313e-16;
-  auto pivot = [&](double q, double c) { return q == 0.0 ? kEps * c : q; };
-  // both eliminations at once: two independent chains of divisions
-  double qp = 0.0, qm = 0.0;
+// Pairs h + l with |l| <= ulp(h) / 2.  (No contraction: a product folded into a sum is
+// not the rounded product whose error is wanted.)
+struct Pair {
+  double h, l;
+};
+__device__ __forceinline__ Pair quick_sum(double a, double b) {  // |a| >= |b|
+#pragma clang fp contract(off)
+  const double s = a + b;
+  return Pair{s, b - (s - a)};
+}
+__device__ __forceinline__ Pair two_sum(double a, double b) {
+#pragma clang fp contract(off)
+  const double s = a + b, t = s - a;
+  return Pair{s, (a - (s - t)) + (b - t)};
+}
+__device__ __forceinline__ Pair add(Pair a, Pair b) {
+#pragma clang fp contract(off)
+  Pair s = two_sum(a.h, b.h);
+  const Pair t = two_sum(a.l, b.l);
+  s = quick_sum(s.h, s.l + t.h);
+  return quick_sum(s.h, s.l + t.l);
+}
+__device__ __forceinline__ Pair neg(Pair a) { return Pair{-a.h, -a.l}; }
+__device__ __forceinline__ Pair mul(Pair a, Pair b) {
+#pragma clang fp contract(off)
+  const double p = a.h * b.h;
+  return quick_sum(p, __builtin_fma(a.l, b.h, __builtin_fma(a.h, b.l, __builtin_fma(a.h, b.h, -p))));
+}
+__device__ __forceinline__ Pair div(Pair a, Pair b) {
+#pragma clang fp contract(off)
+  const double q = a.h / b.h, r = __builtin_fma(-q, b.h, a.h);  // exact
+  return quick_sum(q, __builtin_fma(-q, b.l, r + a.l) / b.h);
+}
+__device__ __forceinline__ Pair load(const PairArray &a, int64_t i) { return Pair{a.p[i], a.p[a.lo + i]}; }
+__device__ __forceinline__ void store(const PairArray &a, int64_t i, Pair v) {
+  a.p[i] = v.h;
+  a.p[a.lo + i] = v.l;
+}
+
+// Eigenvector of every eigenvalue by the twisted factorization of B - x: the ratios
+// coupling / pivot of the top-down and bottom-up eliminations, twisted where the
+// pivots' combination g is smallest, then one multiplication per entry in each
+// direction.  x comes with the error of a double (1e-12 of the smallest); g / |z|^2 is
+// the Rayleigh quotient's correction, so the first pass squares that error against the gap
+// (neighbours differ by a relative 2 / m) and the second leaves the vector's error at 1e-18
+// or less: the vectors are orthonormal as they are.  One lane per vector; ratios and
+// vectors are stored [row][vector], so every access of a wavefront is one
+// 512-byte run.  Bound by the serial chain of divisions.
+// (The pointers are parameters for their no-alias promise: without it no entry is read
+// before the last one is stored.)
+__device__ __forceinline__ double tridiag_vector(
+    const double *__restrict__ dh, const double *__restrict__ dl, const double *__restrict__ eh,
+    const double *__restrict__ el, int m, int64_t a, double lam, double *__restrict__ cph,
+    double *__restrict__ cpl, double *__restrict__ cmh, double *__restrict__ cml,
+    double *__restrict__ Vh, double *__restrict__ Vl, int64_t ld) {
+  const Pair zero{0.0, 0.0};
+  auto d = [&](int i) { return Pair{dh[i], dl[i]}; };
+  auto e = [&](int i) { return i < 0 ? zero : Pair{eh[i], el[i]}; };
+  auto guard = [](Pair q, double c) {
+    constexpr double kTiny = 4.9303806576313238e-32;  // 2^-104
+    return q.h == 0.0 ? Pair{kTiny * c, 0.0} : q;
+  };
+  Pair x{-lam, 0.0};
+  for (int pass = 0; pass < 2; ++pass) {
+    Pair cp = zero, cm = zero;
+#pragma unroll 2
+    for (int i = 0; i < m; ++i) {
+      const int j = m - 1 - i;
+      const Pair ei = e(i), em = e(j - 1);
+      const Pair qp = add(add(d(i), neg(x)), neg(mul(e(i - 1), cp)));
+      const Pair qm = add(add(d(j), neg(x)), neg(mul(e(j), cm)));
+      cp = div(ei, guard(qp, i + 1 < m ? ei.h : dh[i]));
+      cm = div(em, guard(qm, j > 0 ? em.h : dh[j]));
+      cph[i * ld + a] = cp.h;
+      cpl[i * ld + a] = cp.l;
+      cmh[j * ld + a] = cm.h;
+      cml[j * ld + a] = cm.l;
+    }
+    Pair best = zero;
+    int r = 0;
 #pragma unroll 4
-  for (int i = 0; i < m; ++i) {
-    const int j = m - 1 - i;
-    qp = i == 0 ? d[0] - x : (d[i] - x) - e[i - 1] * e[i - 1] / qp;
-    qm = i == 0 ? d[j] - x : (d[j] - x) - e[j] * e[j] / qm;
-    qp = pivot(qp, i + 1 < m ? e[i] : d[i]);
-    qm = pivot(qm, j > 0 ? e[j - 1] : d[0]);
-    Dp[i * ld + a] = qp;
-    Dm[j * ld + a] = qm;
-  }
-  double best = 0.0;
-  int r = m - 1;
-#pragma unroll 8
-  for (int i = m - 1; i >= 0; --i) {
-    const double t = fabs(Dp[i * ld + a] + Dm[i * ld + a] - (d[i] - x));
-    if (i == m - 1 || t < best) {
-      best = t;
-      r = i;
+    for (int i = 0; i < m; ++i) {
+      const int64_t up = (int64_t)(i > 0 ? i - 1 : 0) * ld + a, dn = (int64_t)(i + 1 < m ? i + 1 : i) * ld + a;
+      Pair t = add(d(i), neg(x));
+      t = add(t, neg(mul(e(i - 1), Pair{cph[up], cpl[up]})));
+      t = add(t, neg(mul(e(i), Pair{cmh[dn], cml[dn]})));  // e(m - 1) = 0
+      if (i == 0 || fabs(t.h) < fabs(best.h)) {
+        best = t;
+        r = i;
+      }
     }
-  }
-  double s = 0.0, zu = 0.0, zd = 0.0;  // towards row 0, towards row m - 1
+    Pair s{1.0, 0.0}, zu{1.0, 0.0}, zd{1.0, 0.0};  // towards row 0, towards row m - 1
 #pragma unroll 4
-  for (int i = 0; i < m; ++i) {
-    const int j = m - 1 - i;
-    if (j < r) zu *= e[j] / Dp[j * ld + a];
-    if (j == r) zu = 1.0;
-    if (j <= r) {
-      V[j * ld + a] = zu;
-      s += zu * zu;
+    for (int i = 0; i < m; ++i) {
+      const int j = m - 1 - i;
+      if (j < r) {
+        zu = mul(zu, Pair{cph[j * ld + a], cpl[j * ld + a]});
+        Vh[j * ld + a] = zu.h;
+        Vl[j * ld + a] = zu.l;
+        s = add(s, mul(zu, zu));
+      }
+      if (i > r) {
+        zd = mul(zd, Pair{cmh[i * ld + a], cml[i * ld + a]});
+        Vh[i * ld + a] = zd.h;
+        Vl[i * ld + a] = zd.l;
+        s = add(s, mul(zd, zd));
+      }
+      if (i == r) {
+        Vh[i * ld + a] = 1.0;
+        Vl[i * ld + a] = 0.0;
+      }
     }
-    if (i > r) {
-      zd *= e[i - 1] / Dm[i * ld + a];
-      V[i * ld + a] = zd;
-      s += zd * zd;
+    x = add(x, div(best, s));
+    if (pass == 0) continue;
+    // 1 / sqrt(s): a Newton step from the double's
+    const double y = 1.0 / sqrt(s.h);
+    const Pair f = add(Pair{1.0, 0.0}, neg(mul(s, mul(Pair{y, 0.0}, Pair{y, 0.0}))));
+    const Pair inv = quick_sum(y, 0.5 * y * f.h);
+#pragma unroll 4
+    for (int i = 0; i < m; ++i) {
+      const Pair v = mul(Pair{Vh[i * ld + a], Vl[i * ld + a]}, inv);
+      Vh[i * ld + a] = v.h;
+      Vl[i * ld + a] = v.l;
     }
-    if (i == r) zd = 1.0;
   }
-  const double inv = 1.0 / sqrt(s);
-#pragma unroll 8
-  for (int i = 0; i < m; ++i) V[i * ld + a] *= inv;
+  return -x.h;
 }
 
 __global__ __launch_bounds__(64) void k_tridiag_vectors(EigPair both) {
   const TridiagEig &g = both.p[blockIdx.y];
   const int a = blockIdx.x * 64 + threadIdx.x;
-  if (a < g.m) tridiag_vector(g.d, g.e, g.m, a, -g.lam[a], g.Dp, g.Dm, g.V, g.ld);
+  if (a < g.m)
+    g.lam[a] = tridiag_vector(g.d.p, g.d.p + g.d.lo, g.e.p, g.e.p + g.e.lo, g.m, a, g.lam[a], g.cp.p,
+                              g.cp.p + g.cp.lo, g.cm.p, g.cm.p + g.cm.lo, g.V.p, g.V.p + g.V.lo, g.ld);
 }
 
-// H = 1.5 I - 0.5 H (n x n): with H = V^T V, V H is the first-order step to
-// the nearest orthonormal basis.
-__global__ void k_polar_factor(double *__restrict__ H, int64_t n) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
-  if (j >= n) return;
-  H[i * n + j] = (i == j ? 1.5 : 0.0) - 0.5 * H[i * n + j];
+struct MapBatch {
+  MapEntries m[4];
+};
+
+__global__ __launch_bounds__(256) void k_map_entries(MapBatch b) {
+  const MapEntries &g = b.m[blockIdx.z];
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x, i = blockIdx.y;
+  if (i >= g.prows || j >= g.ld) return;
+  Pair v{0.0, 0.0};
+  if (i < g.rows && j < g.cols)
+    v = mul(mul(load(g.row, i), load(g.col, j)), mul(load(g.t, j - i + g.rows - 1), load(g.u, i + j)));
+  store(g.M, i * g.ld + j, v);
 }
 
-__global__ void k_zero_below(double *__restrict__ W, const int *__restrict__ klo, int64_t ld) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
-  if (j < ld && j < klo[i / kGemmGroup]) W[i * ld + j] = 0.0;
-}
+struct ProductBatch {
+  MapProduct p[4];
+};
 
-// out[j][i] = in[i][j] through a 64 x 64 LDS tile (both sides in 512-byte
-// runs); rows and cols multiples of 64.
-__global__ __launch_bounds__(256) void k_transpose(const double *__restrict__ in, int64_t ldi,
-                                                   double *__restrict__ out, int64_t ldo) {
-  __shared__ double t[64][65];
-  const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
-  const int x = threadIdx.x & 63, y = threadIdx.x >> 6;
-  for (int k = y; k < 64; k += 4) t[k][x] = in[(r0 + k) * ldi + c0 + x];
-  __syncthreads();
-  for (int k = y; k < 64; k += 4) out[(c0 + k) * ldo + r0 + x] = t[x][k];
-}
-
-// out[i][j] = sinv[2i + s] in[i][j] for i < m (rows beyond are zeroed).
-__global__ void k_scale_rows(const double *__restrict__ in, const double *__restrict__ sinv, int s,
-                             int64_t m, int64_t ld, double *__restrict__ out) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
-  if (j >= ld) return;
-  out[i * ld + j] = i < m ? sinv[2 * i + s] * in[i * ld + j] : 0.0;
+// One 64 x 64 tile of W = V^T M, 16 k at a time through LDS, 4 x 4 entries a thread.  Every
+// product enters its sum with its rounding error and the pairs' cross terms, 12 vector
+// instructions; n = 4096: 0.4 T of them in all four products, a plan's largest pass.
+__global__ __launch_bounds__(256) void k_map_products(ProductBatch b) {
+#pragma clang fp contract(off)
+  constexpr int BK = 16;
+  __shared__ double A[2][BK][64], B[2][BK][64];
+  const MapProduct &g = b.p[blockIdx.z];
+  const int64_t i0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
+  if (i0 >= g.rows || j0 >= g.cols) return;
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  double h[4][4], l[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) h[i][j] = l[i][j] = 0.0;
+  for (int k0 = 0; k0 < g.m; k0 += BK) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int kk = (tid + 256 * q) >> 6, c = tid & 63, k = k0 + kk;
+      // (V beyond its m rows and columns is not written)
+      const Pair v = k < g.m && i0 + c < g.m ? load(g.V, k * g.ldv + i0 + c) : Pair{0.0, 0.0};
+      const Pair w = k < g.m ? load(g.M, k * g.cols + j0 + c) : Pair{0.0, 0.0};
+      A[0][kk][c] = v.h;
+      A[1][kk][c] = v.l;
+      B[0][kk][c] = w.h;
+      B[1][kk][c] = w.l;
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int k = 0; k < BK; ++k) {
+      Pair v[4], w[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v[q] = Pair{A[0][k][ty + 16 * q], A[1][k][ty + 16 * q]};
+        w[q] = Pair{B[0][k][tx + 16 * q], B[1][k][tx + 16 * q]};
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const double p = v[i].h * w[j].h;
+          double e = __builtin_fma(v[i].h, w[j].h, -p);
+          e = __builtin_fma(v[i].l, w[j].h, __builtin_fma(v[i].h, w[j].l, e));
+          const Pair s = two_sum(h[i][j], p);
+          h[i][j] = s.h;
+          l[i][j] += s.l + e;
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t r = i0 + ty + 16 * i, c = j0 + tx + 16 * j;
+      double v = h[i][j] + l[i][j];
+      if (g.zlo != nullptr && r < g.zlo[c / kGemmGroup]) v = 0.0;
+      g.W[r * g.cols + c] = v;
+      if (g.WT != nullptr) g.WT[c * g.rows + r] = v;
+    }
 }
 
 // Error factors of slice z along y and x: Algorithm 2 leaves
@@ -257,30 +383,32 @@ hipError_t launch_tridiag_eig(const TridiagEig *p, double lo, double hi, hipStre
   return hipGetLastError();
 }
 
-hipError_t launch_zero_below(double *W, const int *klo, int64_t rows, int64_t ld, hipStream_t st) {
-  hipLaunchKernelGGL(k_zero_below, dim3((unsigned)((ld + 255) / 256), (unsigned)rows), dim3(256), 0,
-                     st, W, klo, ld);
+hipError_t launch_map_entries(const MapEntries *m, int count, hipStream_t st) {
+  if (count < 1 || count > 4) return hipErrorInvalidValue;
+  MapBatch b{};
+  int64_t rows = 0, ld = 0;
+  for (int i = 0; i < count; ++i) {
+    b.m[i] = m[i];
+    rows = m[i].prows > rows ? m[i].prows : rows;
+    ld = m[i].ld > ld ? m[i].ld : ld;
+  }
+  hipLaunchKernelGGL(k_map_entries, dim3((unsigned)((ld + 255) / 256), (unsigned)rows, (unsigned)count),
+                     dim3(256), 0, st, b);
   return hipGetLastError();
 }
 
-hipError_t launch_polar_factor(double *H, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_polar_factor, dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256), 0,
-                     st, H, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_transpose(const double *in, int64_t ldi, double *out, int64_t ldo, int64_t rows,
-                            int64_t cols, hipStream_t st) {
-  if (rows % 64 || cols % 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_transpose, dim3((unsigned)(cols / 64), (unsigned)(rows / 64)), dim3(256), 0,
-                     st, in, ldi, out, ldo);
-  return hipGetLastError();
-}
-
-hipError_t launch_scale_rows(const double *in, const double *sinv, int s, int64_t m, int64_t rows,
-                             int64_t ld, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_scale_rows, dim3((unsigned)((ld + 255) / 256), (unsigned)rows), dim3(256), 0,
-                     st, in, sinv, s, m, ld, out);
+hipError_t launch_map_products(const MapProduct *p, int count, hipStream_t st) {
+  if (count < 1 || count > 4) return hipErrorInvalidValue;
+  ProductBatch b{};
+  int64_t rows = 0, cols = 0;
+  for (int i = 0; i < count; ++i) {
+    if (p[i].rows % 64 || p[i].cols % 64) return hipErrorInvalidValue;
+    b.p[i] = p[i];
+    rows = p[i].rows > rows ? p[i].rows : rows;
+    cols = p[i].cols > cols ? p[i].cols : cols;
+  }
+  hipLaunchKernelGGL(k_map_products, dim3((unsigned)(cols / 64), (unsigned)(rows / 64), (unsigned)count),
+                     dim3(256), 0, st, b);
   return hipGetLastError();
 }
 
