@@ -273,7 +273,7 @@ int rhs_gemms(const fps_plan *pl, const double *F, char *ws, fps::GemmProb *g1, 
       const int64_t mt = k_round(L.m[t]), rt = t * L.mp[0];
       if (mt == 0) continue;
       g2[cnt++] = fps::GemmProb{T + t * k0, (const double *)pl->d_WiT[t].p, G + rs * npad + rt, ms, mt,
-                                mt, 2 * k0, 1, L.mp[t], 1, npad, 1, 0, 0, nullptr, nullptr,
+                                mt, 2 * k0, 1, L.mp[t], 1, npad, 1, 0, nullptr, nullptr,
                                 mr + 2 * rs, mc + 2 * rt, lr ? lr + 4 * rs : nullptr,
                                 lc ? lc + 4 * rt : nullptr};
     }
@@ -297,10 +297,8 @@ fps::BcLiftConst bc_lift_const() {
 }
 
 // The k-range of a product with Wo (or its transpose) on side `side`.
-void limit_k(fps::GemmProb &g, int side, const std::vector<int> &host, const DeviceView &dev,
-             int high) {
+void limit_k(fps::GemmProb &g, int side, const std::vector<int> &host, const DeviceView &dev) {
   g.kside = side;
-  g.khigh = high;
   g.klim = (const int *)dev.p;
   g.klim_host = host.data();
 }
@@ -326,8 +324,8 @@ int out_gemms(const fps_plan *pl, double *U, char *ws, fps::GemmProb *g1, fps::G
                               Tst, ms, mo[t], mt, npad, 1, mot, 1, mot, 1};
       g2[cnt] = fps::GemmProb{(const double *)pl->d_Wo[s].p, Tst, U + s * N + t, mo[s], mo[t],
                               ms, L.mp[s], 1, mot, 1, 2 * N, 2};
-      limit_k(g1[cnt], 2, pl->klo[t], pl->d_klo[t], 0);
-      limit_k(g2[cnt], 1, pl->klo[s], pl->d_klo[s], 0);
+      limit_k(g1[cnt], 2, pl->mlim[t], pl->d_mlim[t]);
+      limit_k(g2[cnt], 1, pl->mlim[s], pl->d_mlim[s]);
       ++cnt;
     }
   return cnt;
@@ -921,14 +919,14 @@ int adj_in_gemms(const fps_plan *pl, const double *Ubar, char *w, fps::GemmProb 
     if (L.m[s] == 0) continue;
     fps::GemmProb &g = g1[(*cnt1)++];
     g = natural_product((const double *)pl->d_WoT[s].p, mop[s], ms, mo[s], Ubar, out_extent(pl), s, T, k0);
-    limit_k(g, 1, pl->khi[s], pl->d_khi[s], 1);
+    limit_k(g, 1, pl->clim[s], pl->d_clim[s]);
     for (int t = 0; t < 2; ++t) {
       const int64_t mt = k_round(L.m[t]), rt = t * L.mp[0];
       if (L.m[t] == 0) continue;
       g2[cnt] = fps::GemmProb{T + t * k0, (const double *)pl->d_Wo[t].p, G + rs * npad + rt, ms, mt,
-                              k_round(mo[t]), 2 * k0, 1, L.mp[t], 1, npad, 1, 0, 0, nullptr, nullptr,
+                              k_round(mo[t]), 2 * k0, 1, L.mp[t], 1, npad, 1, 0, nullptr, nullptr,
                               mr + 2 * rs, mc + 2 * rt, nullptr, nullptr};
-      limit_k(g2[cnt++], 2, pl->khi[t], pl->d_khi[t], 1);
+      limit_k(g2[cnt++], 2, pl->clim[t], pl->d_clim[t]);
     }
     T += ms * 2 * k0;
   }

@@ -195,8 +195,10 @@ fps_status zeig_shifts(fps_plan *pl, double ea, double eb) {
   pl->zoff[(size_t)pl->cnp] = (int)pl->zp.size();
   pl->n_f32 = 0;
   for (int J : pl->zrJmax) pl->n_f32 += J;
-  // the queries report the slices by decreasing steps, and the longest
-  // slice's shifts as the plan's
+  // the queries report the slices by decreasing steps (of equal ones the lowest mode
+  // first), and the longest slice's shifts as the plan's
+  std::reverse(sl.begin(), sl.begin() + L.m[0]);
+  std::reverse(sl.begin() + L.m[0], sl.end());
   std::stable_sort(sl.begin(), sl.end(), [&](const Slice &u, const Slice &v) {
     return refined ? std::fabs(u.mu) > std::fabs(v.mu) : u.J > v.J;
   });

@@ -24,7 +24,8 @@ namespace {
 // A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator register r of lane l
 // holds C[4r + l / 16][l % 16].
 // Every output entry is accumulated over k in the same order whatever the
-// tile, so launches with different tiles agree bit for bit.
+// tile, so launches with different tiles agree bit for bit; k ascends, so a sum over
+// modes starts with the highest and ends with the lowest, which hold most of it.
 //
 // Requirements (checked by the launcher): K a multiple of 16, sai and sbk
 // even, A and B 16-byte aligned; loads are clamped to M and N, so only K needs
@@ -32,9 +33,8 @@ namespace {
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 
-// order: tile dispatch order (0: natural; 1 / 2: column tile slowest,
-// ascending / descending; 3 / 4: row tile slowest, ascending / descending), so
-// that with a limited k-range the longest tiles start first and the short ones
+// order: tile dispatch order (0: natural; 1: row tile slowest; 2: column tile
+// slowest), so that with a limited k-range the longest tiles start first and the short ones
 // fill the tail.  Workgroups 0 .. nedge-1 take edge units (equal counts per
 // problem), mt x nt tiles per problem follow.
 struct GemmBatch {
@@ -74,24 +74,12 @@ __host__ __device__ inline int edge_units(const GemmProb &g) {
   return edge_column_units(g) + (main_extent(g.M) < g.M ? (int)((g.N + c - 1) / c) : 0);
 }
 
-// k-range [klo, khi) of the tile at (i0, j0): the limits of its first and last
-// 64-row (or column) group, rounded out to the k-tile.
-__host__ __device__ inline void tile_krange(const GemmProb &g, const int *lim, int64_t i0, int64_t j0,
-                                            int T, int64_t *klo_out, int64_t *khi_out) {
-  int64_t klo = 0, khi = g.K;
-  if (g.kside != 0) {
-    const int64_t x0 = g.kside == 1 ? i0 : j0, X = g.kside == 1 ? g.M : g.N;
-    const int64_t last = (x0 + T < X ? x0 + T : X) - 1;
-    if (g.khigh) {
-      const int64_t h = (lim[last / kGroup] + 31) / 32 * 32;
-      khi = h < khi ? h : khi;
-    } else {
-      klo = lim[x0 / kGroup] / 32 * 32;
-      if (klo > khi) klo = khi;
-    }
-  }
-  *klo_out = klo;
-  *khi_out = khi;
+// End of the k-range of the tile at (i0, j0): the limit of its 64-row (or column) group,
+// rounded up to two k-tiles.
+__host__ __device__ inline int64_t tile_kend(const GemmProb &g, const int *lim, int64_t i0, int64_t j0) {
+  if (g.kside == 0) return g.K;
+  const int64_t h = (lim[(g.kside == 1 ? i0 : j0) / kGroup] + 31) / 32 * 32;
+  return h < g.K ? h : g.K;
 }
 
 // The output entry (i, j) from its accumulated product v: the eigenbasis
@@ -131,8 +119,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
   if (i0 >= Mm || j0 >= Nm) return;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int wy = wid >> 1, wx = wid & 1;
-  int64_t klo, khi;
-  tile_krange(g, g.klim, i0, j0, T, &klo, &khi);
 
   // Loaders.  A: thread t reads row t / TA, k-run (t % TA) RA ..; B: thread t
   // reads k-row t / TB, the column pairs bc + 2 TB q, so the threads of a row
@@ -144,15 +130,15 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &g, const int64_t i0, c
   const int ar = tid / TA, ak = (tid % TA) * RA;
   const int bk = tid / TB, bc = (tid % TB) * 2;
   const int64_t arow = i0 + ar < g.M ? i0 + ar : g.M - 1;
-  const double *Ab = g.A + i0 * g.sai + klo, *Bb = g.B + klo * g.sbk;
+  const double *Ab = g.A + i0 * g.sai, *Bb = g.B;
   const uint32_t ao = 8 * ((uint32_t)(arow - i0) * (uint32_t)g.sai + ak);
-  const int nk = (int)((khi - klo + BK - 1) / BK);
+  const int nk = (int)((tile_kend(g, g.klim, i0, j0) + BK - 1) / BK);
   // Columns past N are clamped to the last pair (row strides are even: it exists).
   // Of a natural array the rows past the last are clamped (A is zero there), and the
   // columns past it only in the last k-tile, as before that they lie in the rows that
   // follow; the row may end within a pair, then the pair before holds its first column.
   const int64_t jlast = kKind == kNatural ? g.cols - 2 : (g.N - 1) & ~(int64_t)1;
-  const int lrow = kKind == kNatural ? (int)(g.krows - klo) - (nk - 1) * BK - 1 : 0;
+  const int lrow = kKind == kNatural ? (int)g.krows - (nk - 1) * BK - 1 : 0;
   uint32_t bo[QB], bl[QB];
   bool late[QB];
 #pragma unroll
@@ -413,14 +399,14 @@ __global__ __launch_bounds__(256, 2) void k_gemm(GemmBatch batch) {
     bx = L % nt;
     by = L / nt % mt;
     z = L / (nt * mt);
-  } else if (batch.order <= 2) {
-    const int c = L / (mt * nz), rem = L % (mt * nz);
-    bx = batch.order == 1 ? c : nt - 1 - c;
+  } else if (batch.order == 2) {
+    const int rem = L % (mt * nz);
+    bx = L / (mt * nz);
     z = rem / mt;
     by = rem % mt;
   } else {
-    const int r = L / (nt * nz), rem = L % (nt * nz);
-    by = batch.order == 3 ? r : mt - 1 - r;
+    const int rem = L % (nt * nz);
+    by = L / (nt * nz);
     z = rem / nt;
     bx = rem % nt;
   }
@@ -558,9 +544,7 @@ bool gemm_table(std::vector<GemmDesc> &tab, GemmTable &t, std::vector<int> &map)
     std::vector<Unit> &u = units[k];
     auto add = [&](int64_t i0, int64_t j0, int T) {
       if (i0 >= M || j0 >= N) return;
-      int64_t klo, khi;
-      tile_krange(q, q.klim_host, i0, j0, T, &klo, &khi);
-      u.push_back(Unit{(khi - klo) * T * T, (int)((i0 / 32) << 16 | (j0 / 32) << 1 | (T < t.T ? 1 : 0))});
+      u.push_back(Unit{tile_kend(q, q.klim_host, i0, j0) * T * T, (int)((i0 / 32) << 16 | (j0 / 32) << 1 | (T < t.T ? 1 : 0))});
     };
     for (int64_t i0 = 0; i0 < M; i0 += t.T)
       for (int64_t j0 = 0; j0 < N; j0 += t.T) {
@@ -603,12 +587,10 @@ hipError_t launch_gemm(const GemmProb *probs, int count, hipStream_t st, hipEven
     mt = std::max(mt, (main_extent(q.M) + T - 1) / T);
     nt = std::max(nt, (main_extent(q.N) + T - 1) / T);
     if (kind == kPlain) edge = std::max(edge, (int64_t)edge_units(q));
-    same = same && q.kside == f.kside && q.khigh == f.khigh;
+    same = same && q.kside == f.kside;
   }
-  // longest k-range first: lower limits grow, so the first tiles are the
-  // longest; upper limits grow too, so there the last ones are
-  if (same && f.kside == 2) b.order = f.khigh ? 2 : 1;
-  if (same && f.kside == 1) b.order = f.khigh ? 4 : 3;
+  // longest k-range first: the limits fall
+  if (same) b.order = f.kside;
   b.count = count;
   b.mt = (int)mt;
   b.nt = (int)nt;

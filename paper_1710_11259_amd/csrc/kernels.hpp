@@ -156,10 +156,10 @@ struct GemmProb {
   double *C;
   int64_t M, N, K;
   int64_t sai, sak, sbk, sbj, sci, scj;
-  // Limited k-range: kside 1: A(i,k) = 0, kside 2: B(k,j) = 0 for k below
-  // (khigh 0) or from (khigh 1) klim[x / kGemmGroup], x = i or j; klim
-  // nondecreasing, a device table (klim_host: the same values on the host).
-  int kside, khigh;
+  // Limited k-range: kside 1: A(i,k) = 0, kside 2: B(k,j) = 0 from
+  // k = klim[x / kGemmGroup] on, x = i or j; klim
+  // nonincreasing, a device table (klim_host: the same values on the host).
+  int kside;
   const int *klim, *klim_host;
   // Multiplier of the eigenbasis solve, when mr is non-null: C(i,j) becomes
   //   (acc - sum_q lr[4i+q] lc[4j+q]) (1 - mr[2i+1] mc[2j+1]) / (mr[2i] + mc[2j]),
@@ -184,8 +184,8 @@ struct PairArray {
   int64_t lo;
 };
 // Eigenpairs of two negative definite tridiagonals T (m 0: none) whose negated diagonal is d
-// and coupling e (e[m - 1] = 0; e2 = e^2 in double; device arrays of m): lam[a] ascending
-// from the most negative, V the orthonormal vectors as columns (row length ld, rows and
+// and coupling e (e[m - 1] = 0; e2 = e^2 in double; device arrays of m): lam[a] descending
+// from the one next to zero, V the orthonormal vectors as columns (row length ld, rows and
 // columns from m on unwritten); [lo, hi] encloses sigma(-T); cp, cm scratch of V's shape.
 struct TridiagEig {
   PairArray d, e;
@@ -205,12 +205,12 @@ struct MapEntries {
 hipError_t launch_map_entries(const MapEntries *m, int count, hipStream_t st);
 // W = V^T M (rows x cols, contiguous) and, if WT is not null, its transpose, rounded once
 // from the pairs; V as above, M with row length cols, rows and cols multiples of 64.
-// zlo (or null): W[a][j] = 0 for a < zlo[j / kGemmGroup].  Up to 4 of them.
+// zlim (or null): W[a][j] = 0 from a = zlim[j / kGemmGroup] on.  Up to 4 of them.
 struct MapProduct {
   PairArray V, M;
   int64_t ldv, rows, cols;
   int m;
-  const int *zlo;
+  const int *zlim;
   double *W, *WT;
 };
 hipError_t launch_map_products(const MapProduct *p, int count, hipStream_t st);

@@ -302,7 +302,7 @@ void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam) {
       }
       if (c <= k) lo = x; else hi = x;
     }
-    lam[(size_t)(m - 1 - k)] = -0.5 * (lo + hi);
+    lam[(size_t)k] = -0.5 * (lo + hi);
   }
 }
 

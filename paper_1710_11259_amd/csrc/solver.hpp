@@ -102,9 +102,9 @@ struct fps_plan {
   fps::detail::DeviceView d_Wi[2], d_WiT[2], d_Wo[2], d_WoT[2];
   fps::detail::DeviceView d_mr, d_mc;
   // Where Wo is zero (spectral.cpp): row group g of 64 output coefficients has
-  // no entries below mode klo[g], and mode group h none from row khi[h] on.
-  std::vector<int> klo[2], khi[2];
-  fps::detail::DeviceView d_klo[2], d_khi[2];
+  // no entries from mode mlim[g] on, and mode group h none from row clim[h] on.
+  std::vector<int> mlim[2], clim[2];
+  fps::detail::DeviceView d_mlim[2], d_clim[2];
   std::vector<double> lam;
   // Lift map V^T S^-1 C~(T_k'') by parity (mp x mop) and V^T of the lift's
   // linear factors ([npad][2]), only with FPS_PLAN_DIRICHLET.

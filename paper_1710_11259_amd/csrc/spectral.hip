@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void k_tridiag_values(EigPair both, double lo0
     if (below > 0) lo = xl;
     if (below < 64) hi = xh;
   }
-  if (lane == 0) lam[m - 1 - k] = -(lo + 0.5 * (hi - lo));  // most negative first
+  if (lane == 0) lam[k] = -(lo + 0.5 * (hi - lo));
 }
 
 // Pairs h + l with |l| <= ulp(h) / 2.  (No contraction: a product folded into a sum is
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_map_products(ProductBatch b) {
     for (int j = 0; j < 4; ++j) {
       const int64_t r = i0 + ty + 16 * i, c = j0 + tx + 16 * j;
       double v = h[i][j] + l[i][j];
-      if (g.zlo != nullptr && r < g.zlo[c / kGemmGroup]) v = 0.0;
+      if (g.zlim != nullptr && r >= g.zlim[c / kGemmGroup]) v = 0.0;
       g.W[r * g.cols + c] = v;
       if (g.WT != nullptr) g.WT[c * g.rows + r] = v;
     }

@@ -4,7 +4,8 @@ On data that decay, what the truncation (tol = 1e-17 here) and the data leave is
 rounding of the products themselves.  Bound: the maps are rounded once per entry and
 the partial sums of a product stay near its result, which is at most 1.5 u for each of the
 four products, 6 u = 6.7e-16 in all (relative Frobenius norm, rms over three
-inputs).  Maps whose own formation leaves a few u per entry exceed it."""
+inputs).  Maps whose own formation leaves a few u per entry exceed it, and so do sums
+over modes that start with the largest terms."""
 import numpy as np
 import pytest
 
@@ -51,7 +52,7 @@ def decaying(rng, m):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("n,out", [(64, "cheb"), (64, "native")])
+@pytest.mark.parametrize("n,out", [(n, out) for n in (64, 256, 515) for out in ("cheb", "native")])
 def test_adjoint(n, out):
     p = fps.plan(n, tol=1e-17, tight=True, out=out)
     errs = []
