@@ -132,7 +132,7 @@ fps_status run_overlapping(const fps_batch *bt, int t, const double *in, double 
       if (pl->n == 1) {  // its one block: the input kept in the workspace until the end
         const int64_t n = t ? out_extent(pl) : 1;
         double *keep = (double *)(wb + pl->off_GT);
-        if (stage == 0) FPS_HIP(hipMemcpyAsync(keep, x, n * n * 8, hipMemcpyDeviceToDevice, st));
+        if (stage == 0) FPS_HIP(fps::launch_copy(x, keep, n * n, st));
         if (stage < 3) continue;
         fps::ChainDesc d[4];
         int nb = 0;

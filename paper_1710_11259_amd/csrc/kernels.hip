@@ -46,6 +46,11 @@ __global__ void k_fill(double *__restrict__ dst, int64_t count, double v) {
   if (i < count) dst[i] = v;
 }
 
+__global__ void k_copy(const double *__restrict__ src, double *__restrict__ dst, int64_t count) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < count) dst[i] = src[i];
+}
+
 // --- cube ----------------------------------------------------------------
 
 // natural n^3 -> parity-blocked npad^3 (zero padding)
@@ -86,6 +91,12 @@ hipError_t launch_permute_in(const double *src, double *dst, int64_t n, int64_t 
                              hipStream_t st, const double *sinv) {
   dim3 grid((unsigned)((npad + 255) / 256), (unsigned)npad);
   hipLaunchKernelGGL(k_permute_in, grid, dim3(256), 0, st, src, dst, n, npad, mp0, sinv);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy(const double *src, double *dst, int64_t count, hipStream_t st) {
+  if (count <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_copy, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, src, dst, count);
   return hipGetLastError();
 }
 

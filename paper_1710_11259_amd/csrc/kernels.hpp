@@ -105,6 +105,8 @@ hipError_t launch_permute_in(const double *src, double *dst, int64_t n, int64_t 
 hipError_t launch_permute3_in(const double *src, double *dst, int64_t n, int64_t npad, int64_t mp0,
                               hipStream_t st);
 hipError_t launch_fill(double *dst, int64_t count, double v, hipStream_t st);
+// A kernel, where a copy would put a memcpy node into a captured graph.
+hipError_t launch_copy(const double *src, double *dst, int64_t count, hipStream_t st);
 
 // Nonhomogeneous Dirichlet data (Sec. 6.1), traces bc = [L; R; B; T], each
 // n + 2 Chebyshev coefficients in the mapped variable (L, R in t; B, T in s).
