@@ -598,20 +598,6 @@ fps_status plan2d_build(fps_plan *pl) {
   for (size_t k = 0; k < pl->rsh.size(); ++k)
     if (pl->rf32[k]) pl->n_f32 += pl->rsh[k].J;
   pl->L = fps::make_layout(n);
-  if (prec == FPS_FP64) {
-    // sweep tables of the stage entry point fps_adi_native: one per step (a
-    // rectangle has two)
-    std::vector<double> alpha, beta;
-    for (int j = 0; j < pl->shifts.J; ++j) {
-      alpha.push_back(pl->rect ? pl->sy2 : 1.0);  // rectangle: table 2j: sy2 A~ + p_j,
-      beta.push_back(pl->shifts.p[j]);
-      if (pl->rect) {  // 2j + 1: sx2 A~ - q_j
-        alpha.push_back(pl->sx2);
-        beta.push_back(-pl->shifts.q[j]);
-      }
-    }
-    fps::build_sweep_tables_ab(pl->L, alpha, beta, pl->tab, pl->ctab, nullptr, pl->l1);
-  }
   for (int s = 0; s < 2; ++s) pl->mop[s] = (pl->L.mo[s] + fps::kPad - 1) / fps::kPad * fps::kPad;
 
   const fps::Layout &L = pl->L;
@@ -649,9 +635,7 @@ fps_status plan2d_build(fps_plan *pl) {
 
   if (!(flags & FPS_PLAN_HOST_ONLY)) {
     fps_status s;
-    if ((s = upload(pl->d_tab, pl->tab)) != FPS_OK || (s = upload(pl->d_ctab, pl->ctab)) != FPS_OK ||
-        (s = upload(pl->d_l1, pl->l1)) != FPS_OK ||
-        (s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) != 0)) != FPS_OK)
+    if ((s = spectral_build(pl, (flags & FPS_PLAN_DIRICHLET) != 0)) != FPS_OK)
       return s;
     // chains of more than two chunks: the two row-parity halves of the ADI
     // run on two streams (run_adi)

@@ -162,9 +162,21 @@ long double atilde_off_ld(int64_t i) {
 
 namespace {
 
-// Number of eigenvalues below x of the parity-s block of A~ (m positions):
-// the negative pivots of the LDL^T factorization of the block minus x I.
-int64_t sturm_count(int64_t m, int s, long double x) {
+// The parity-s block of A~ (m positions): diagonal, and coupling of k and k + 1.
+struct Block {
+  std::vector<double> d, e;
+  Block(int64_t m, int s) : d((size_t)m), e((size_t)m) {
+    for (int64_t k = 0; k < m; ++k) {
+      d[(size_t)k] = atilde_diag(2 * k + s);
+      e[(size_t)k] = atilde_off(2 * k + s);
+    }
+  }
+};
+
+// Number of its eigenvalues below x: the negative pivots of the LDL^T
+// factorization of the block minus x I.
+int64_t sturm_count(const Block &B, long double x) {
+  const int64_t m = (int64_t)B.d.size();
   int64_t cnt = 0;
   long double q = 1.0L;
   // a zero pivot counts as negative (x just above an eigenvalue): replaced by
@@ -172,11 +184,11 @@ int64_t sturm_count(int64_t m, int s, long double x) {
   // with e^2 / q still finite in extended precision)
   const long double tiny = std::ldexp(1.0L, -13000);
   for (int64_t k = 0; k < m; ++k) {
-    const long double d = (long double)atilde_diag(2 * k + s) - x;
+    const long double d = (long double)B.d[(size_t)k] - x;
     if (k == 0) {
       q = d;
     } else {
-      const long double e = atilde_off(2 * (k - 1) + s);
+      const long double e = B.e[(size_t)k - 1];
       q = d - e * e / q;
     }
     if (q == 0.0L) q = -tiny;
@@ -264,16 +276,20 @@ void atilde_extremes(int64_t n, long double *lmin, long double *lmax) {
   for (int s = 0; s < 2; ++s) {
     const int64_t m = (n - s + 1) / 2;
     if (m == 0) continue;
+    const Block B(m, s);
+    // (a midpoint that rounds to an end of the bracket changes nothing any more)
     long double lo = -1.0L, hi = 0.0L;  // smallest: count(x) >= 1
     for (int it = 0; it < 200; ++it) {
       const long double mid = 0.5L * (lo + hi);
-      if (sturm_count(m, s, mid) >= 1) hi = mid; else lo = mid;
+      if (mid == lo || mid == hi) break;
+      if (sturm_count(B, mid) >= 1) hi = mid; else lo = mid;
     }
     lo_all = std::min(lo_all, lo);
     lo = -1.0L, hi = 0.0L;  // largest: count(x) == m
     for (int it = 0; it < 200; ++it) {
       const long double mid = 0.5L * (lo + hi);
-      if (sturm_count(m, s, mid) >= m) hi = mid; else lo = mid;
+      if (mid == lo || mid == hi) break;
+      if (sturm_count(B, mid) >= m) hi = mid; else lo = mid;
     }
     hi_all = std::max(hi_all, hi);
   }
@@ -360,6 +376,7 @@ void build_sweep_tables_ab(const Layout &L, const std::vector<double> &alpha,
   l1.assign((size_t)J * 2 * nc * kL1, 0.0);
   std::vector<long double> CF((size_t)(nc + 1) * nc), CBY((size_t)nc * nc), CBX((size_t)nc * nc);
   std::vector<long double> l(ms), ib(ms), u(ms), F2(ms), BF2(ms);
+  const Block blocks[2] = {Block(L.m[0], 0), Block(L.m[1], 1)};
   for (int j = 0; j < J; ++j) {
     for (int s = 0; s < 2; ++s) {
       const int64_t m = L.m[s];
@@ -371,16 +388,17 @@ void build_sweep_tables_ab(const Layout &L, const std::vector<double> &alpha,
       if (m == 0) continue;
       // Thomas factors of (alpha_j A~ + beta_j I) restricted to parity s.
       const long double al = alpha[j], be = beta0[j];
-      long double beta = al * (long double)atilde_diag(s) + be;
+      const std::vector<double> &dg = blocks[s].d, &of = blocks[s].e;
+      long double beta = al * (long double)dg[0] + be;
       ib[0] = 1.0L / beta;
       for (int64_t k = 1; k < m; ++k) {
-        const long double e = al * (long double)atilde_off(2 * (k - 1) + s);
+        const long double e = al * (long double)of[(size_t)k - 1];
         l[k] = e * ib[k - 1];
-        beta = (al * (long double)atilde_diag(2 * k + s) + be) - l[k] * e;
+        beta = (al * (long double)dg[(size_t)k] + be) - l[k] * e;
         ib[k] = 1.0L / beta;
       }
       for (int64_t k = 0; k + 1 < m; ++k)
-        u[k] = al * (long double)atilde_off(2 * k + s) * ib[k];
+        u[k] = al * (long double)of[(size_t)k] * ib[k];
       for (int64_t k = 0; k < ms; ++k) {
         T[T_L * ms + k] = (double)l[k];
         T[T_IB * ms + k] = (double)ib[k];

@@ -88,11 +88,11 @@ struct fps_plan {
   int tab1(int j) const { return rect ? 2 * j : j; }
   int tab2(int j) const { return rect ? 2 * j + 1 : j; }
   fps::Layout L;
-  std::vector<double> tab, ctab, l1;  // host sweep tables
   int64_t mop[2] = {0, 0};          // output parity lengths padded to 64
 
   // device copies
-  fps::detail::DeviceBuf d_tab, d_ctab, d_l1;
+  // Sweep tables of fps_adi_native (FP64 2-D plans), in d_maps.
+  fps::detail::DeviceView d_tab, d_ctab, d_l1;
   // Coefficient maps merged with the eigenvectors V of A~ (spectral.cpp), by
   // parity, zero-padded to multiples of 64, in both orientations: Wi =
   // V^T S^-1 R (mp x mp) and Wo = P S^-1 V (mop x mp; native output S^-1 V,

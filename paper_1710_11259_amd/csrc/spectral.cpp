@@ -87,6 +87,24 @@ void factors_2d(const fps_plan *pl, double *r, double *c) {
   }
 }
 
+// Sweep tables of the stage entry point fps_adi_native: one per step (a rectangle has
+// two).
+struct SweepTables {
+  std::vector<double> pos, chunk, l1;
+  explicit SweepTables(const fps_plan *pl) {
+    std::vector<double> alpha, beta;
+    for (int j = 0; j < pl->shifts.J; ++j) {
+      alpha.push_back(pl->rect ? pl->sy2 : 1.0);  // rectangle: table 2j: sy2 A~ + p_j,
+      beta.push_back(pl->shifts.p[j]);
+      if (pl->rect) {  // 2j + 1: sx2 A~ - q_j
+        alpha.push_back(pl->sx2);
+        beta.push_back(-pl->shifts.q[j]);
+      }
+    }
+    fps::build_sweep_tables_ab(pl->L, alpha, beta, pos, chunk, nullptr, l1);
+  }
+};
+
 // Extended-precision values as pairs in a host image of doubles: h at `at`, l
 // v.size() further on.
 void put_pairs(std::vector<double> &h, int64_t at, const std::vector<long double> &v) {
@@ -133,8 +151,10 @@ struct MapAt {
 // (and shifts) are set; lift: also the Dirichlet lift map, merged the same way.  The maps'
 // closed forms (MapTables) are tables of O(n), so the uploads are short and everything of
 // O(n^2) or more is formed on the device, in pairs of doubles until its one
-// rounding.  One allocation for the plan's tables, one for the temporaries, two uploads
-// and one read-back: at n = 64 the calls take longer than the kernels.
+// rounding.  One allocation for the plan's tables, one for the temporaries, and FP64 2-D
+// plans build their sweep tables on the host while the kernels run (plan creation at n = 64
+// 766 -> 495 us, at 515 5.5 -> 2.6 ms, the bisection for the computed spectrum without its
+// square roots and idle steps included).
 fps_status spectral_build(fps_plan *pl, bool lift) {
   const fps::Layout &L = pl->L;
   const bool native = pl->out_basis == FPS_OUT_NATIVE;
@@ -178,6 +198,11 @@ fps_status spectral_build(fps_plan *pl, bool lift) {
     s0[sp] = tmp.take(2 * mp[sp] * wide);
     s1[sp] = tmp.take(2 * mp[sp] * wide);
   }
+  const bool sweeps = pl->dim == 2 && pl->prec == FPS_FP64;
+  const int64_t steps = sweeps ? (pl->rect ? 2 : 1) * (int64_t)pl->shifts.J : 0;
+  const int64_t tab = keep.take(steps * 2 * fps::kNTab * L.mstride);
+  const int64_t ctab = keep.take(steps * 2 * fps::kNCTab * L.ncmax);
+  const int64_t l1 = keep.take(steps * 2 * L.ncmax * fps::kL1);
   const int64_t nf = pl->dim == 2 ? 2 * L.npad : 0;
   Pieces fin;  // the last upload
   const int64_t mr = fin.take(nf), mc = fin.take(nf), lina = fin.take(lift ? 2 * L.npad : 0);
@@ -241,6 +266,15 @@ fps_status spectral_build(fps_plan *pl, bool lift) {
     }
     FPS_HIP(fps::launch_map_entries(me, np, st));
     FPS_HIP(fps::launch_map_products(mq, np, st));
+  }
+  if (sweeps) {
+    const SweepTables t(pl);
+    pl->d_tab.p = K + tab;
+    pl->d_ctab.p = K + ctab;
+    pl->d_l1.p = K + l1;
+    FPS_HIP(hipMemcpy(K + tab, t.pos.data(), t.pos.size() * 8, hipMemcpyHostToDevice));
+    FPS_HIP(hipMemcpy(K + ctab, t.chunk.data(), t.chunk.size() * 8, hipMemcpyHostToDevice));
+    FPS_HIP(hipMemcpy(K + l1, t.l1.data(), t.l1.size() * 8, hipMemcpyHostToDevice));
   }
   std::vector<double> lam((size_t)L.npad);
   FPS_HIP(hipMemcpy(lam.data(), W + lam_at, lam.size() * 8, hipMemcpyDeviceToHost));

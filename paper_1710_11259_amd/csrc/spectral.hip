@@ -86,8 +86,8 @@ __device__ __forceinline__ Pair mul(Pair a, Pair b) {
 }
 __device__ __forceinline__ Pair div(Pair a, Pair b) {
 #pragma clang fp contract(off)
-  const double q = a.h / b.h, r = __builtin_fma(-q, b.h, a.h);  // exact
-  return quick_sum(q, __builtin_fma(-q, b.l, r + a.l) / b.h);
+  const double inv = 1.0 / b.h, q = a.h * inv, r = __builtin_fma(-q, b.h, a.h);
+  return quick_sum(q, __builtin_fma(-q, b.l, r + a.l) * inv);
 }
 __device__ __forceinline__ Pair load(const PairArray &a, int64_t i) { return Pair{a.p[i], a.p[a.lo + i]}; }
 __device__ __forceinline__ void store(const PairArray &a, int64_t i, Pair v) {
