@@ -270,14 +270,21 @@ __device__ __forceinline__ dbl2 sum_l4(dbl2 v) {
 // X comes from HBM: 8 k-steps (2048 MFMA cycles of the SIMD's wavefronts) ahead, W
 // from the caches: 4.  kExt: ext[c] = the rows S, S + 1 of W^T X in this lane's two
 // columns (all four lanes of a column hold them).
-template <bool kPair, bool kExt>
+// kDown: k from K - 1 down to 0, for sums over degrees, whose first terms are the
+// largest: with those added last the small ones are not rounded against them.  The
+// cylinder's banded solves magnify the rounding of their right-hand sides: three solves
+// that must cancel left 9.9e-15 of the result at n = 64 and 1.5e-14 at 130, both input
+// products downwards 2.1e-15 and 2.3e-15, at the same speed.
+template <bool kPair, bool kExt, bool kDown>
 __device__ __forceinline__ void mul_stream(const double *__restrict__ W, int ldw, int S,
                                            const double *__restrict__ X, const ChainDesc &e, int K,
                                            int r0, int c0, const Lane &l, dbl4 (&acc)[2][2],
                                            dbl2 (&ext)[2]) {
-  const uint32_t wo = 8 * (l.l4 * ldw + 2 * l.l15), xwo = 8 * (l.l4 * ldw);
+  const int l4 = kDown ? 3 - l.l4 : l.l4;  // the lane's row in a k-step
+  const uint32_t wo = 8 * (l4 * ldw + 2 * l.l15), xwo = 8 * (l4 * ldw);
   const Buffer wb(W), xb(X);
   const int rs = (int)e.in_rs, cs = e.in_cs;
+  auto first_row = [&](int k) { return kDown ? K - 4 - k : k; };  // of the k-step at k
   // the last k-step with data, and its rows
   const int last = (e.in_r - 1) & ~3;
   uint32_t xo[2], xl[2];
@@ -286,20 +293,20 @@ __device__ __forceinline__ void mul_stream(const double *__restrict__ W, int ldw
     const int col = c0 + (kPair ? 2 * l.l15 + c : 16 * c + l.l15);
     // (a pair may end one past in_c, in the padding)
     const int cc = (col < e.in_c ? col : kPair ? (e.in_c - 1) & ~1 : e.in_c - 1) * cs;
-    xo[c] = 8 * (l.l4 * rs + cc);
-    xl[c] = 8 * (min(l.l4, e.in_r - 1 - last) * rs + cc);
+    xo[c] = 8 * (l4 * rs + cc);
+    xl[c] = 8 * (min(l4, e.in_r - 1 - last) * rs + cc);
   }
   dbl2 a[4], b[8], x[4];
   ext[0] = ext[1] = dbl2{0.0, 0.0};
   auto load_a = [&](int u, int k) {
-    a[u] = wb.load2(wo, 8 * (r0 + k * ldw));
-    if constexpr (kExt) x[u] = wb.load2(xwo, 8 * (S + k * ldw));
+    a[u] = wb.load2(wo, 8 * (r0 + first_row(k) * ldw));
+    if constexpr (kExt) x[u] = wb.load2(xwo, 8 * (S + first_row(k) * ldw));
   };
-  // kEnd: the k-steps may end or pass the data; those past it read the last row again,
-  // times zeros of W
+  // kEnd: the k-steps may end or pass the data (K - in_r < 32); those past it read the
+  // last row again, times zeros of W
   auto load_b = [&](int u, int k, auto end) {
-    const bool z = decltype(end)::value && k >= last;
-    const uint32_t row = 8 * (z ? last : k) * rs;
+    const bool z = decltype(end)::value && first_row(k) >= last;
+    const uint32_t row = 8 * (z ? last : first_row(k)) * rs;
     const uint32_t o0 = z ? xl[0] : xo[0], o1 = z ? xl[1] : xo[1];
     if constexpr (kPair)
       b[u] = xb.load2(o0, row);
@@ -346,9 +353,10 @@ __device__ __forceinline__ void mul_stream(const double *__restrict__ W, int ldw
   };
   int ks = 0;
 #pragma unroll 1
-  for (; ks + 64 <= e.in_r; ks += 32) chunk(ks, End{}, Inner{});
+  for (; ks + (kDown ? 32 : 64) <= (kDown ? K - 1 : e.in_r); ks += 32) chunk(ks, End{}, Inner{});
+  if constexpr (!kDown)
 #pragma unroll 1
-  for (; ks + 32 < K; ks += 32) chunk(ks, End{}, End{});
+    for (; ks + 32 < K; ks += 32) chunk(ks, End{}, End{});
   chunk(ks, Inner{}, Inner{});
   // columns past in_c took others' data
 #pragma unroll
@@ -375,15 +383,20 @@ struct Kept {
 // their stride per k; w0 the first row (kLeft) or column of W, interleaved if kPair.
 // kExtW: also with W's entries S, S + 1.  kExtT (T W only): also T's extra rows, from
 // te on (P apart).
-template <bool kLeft, bool kPair, bool kExtW, bool kExtT>
+// kDown (T W without extra rows or columns): k from K - 1 down, as above; t[.] are then those
+// of the lane's k within the lowest k-step.
+template <bool kLeft, bool kPair, bool kExtW, bool kExtT, bool kDown>
 __device__ __forceinline__ void mul_kept(const double *T, const int (&t)[2], int ts,
                                          const double *__restrict__ W, int ldw, int S, int K, int w0,
                                          const double *te, int P, const Lane &l, Kept &o) {
-  const uint32_t wo = 8 * (l.l4 * ldw + (kPair ? 2 : 1) * l.l15), xwo = 8 * (l.l4 * ldw);
+  static_assert(!kDown || !(kExtW || kExtT), "downwards without extra rows or columns");
+  const int l4 = kDown ? 3 - l.l4 : l.l4;
+  const uint32_t wo = 8 * (l4 * ldw + (kPair ? 2 : 1) * l.l15), xwo = 8 * (l4 * ldw);
   const Buffer wb(W);
   dbl2 w[4], x[4];
+  auto first_row = [&](int k) { return kDown ? K - 4 - k : k; };
   auto load = [&](int u, int k) {
-    const uint32_t row = 8 * (w0 + k * ldw);
+    const uint32_t row = 8 * (w0 + first_row(k) * ldw);
     if constexpr (kPair)
       w[u] = wb.load2(wo, row);
     else
@@ -408,7 +421,7 @@ __device__ __forceinline__ void mul_kept(const double *T, const int (&t)[2], int
       double tv[2], ev[2];
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
-        tv[r] = T[t[r] + (ks + 4 * u) * ts];
+        tv[r] = T[t[r] + first_row(ks + 4 * u) * ts];
         if constexpr (kExtT) ev[r] = te[r * P + l.l4 + ks + 4 * u];
       }
 #pragma unroll
@@ -474,7 +487,7 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_slab(const Chain
     dbl2 ext[2];
     double *t = T + c0 + (kOut ? 2 : 1) * l.l15;
     if (rows) {
-      mul_stream<kOut, kOut>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
+      mul_stream<kOut, kOut, !kOut>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
       if (l.l4 == 0)
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -482,7 +495,7 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_slab(const Chain
           t[(C::E + 1) * C::P + (kOut ? 1 : 16) * b] = ext[b].y;
         }
     } else {
-      mul_stream<kOut, false>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
+      mul_stream<kOut, false, !kOut>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
     }
     t += (32 * l.wy + 2 * l.l4) * C::P;
 #pragma unroll
@@ -497,10 +510,11 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_slab(const Chain
     __syncthreads();
     return;
   }
-  const int t[2] = {(32 * l.wy + l.l15) * C::P + l.l4, (32 * l.wy + 16 + l.l15) * C::P + l.l4};
+  const int tk = kOut ? l.l4 : 3 - l.l4;
+  const int t[2] = {(32 * l.wy + l.l15) * C::P + tk, (32 * l.wy + 16 + l.l15) * C::P + tk};
   const bool cols = kOut && e.n[0] > C::S && l.wx == 0;
   auto second = [&](auto w, auto t2) {
-    mul_kept<false, !kOut, decltype(w)::value, decltype(t2)::value>(
+    mul_kept<false, !kOut, decltype(w)::value, decltype(t2)::value, !kOut>(
         T, t, 1, e.m[0], e.ld[0], C::S, e.k[0], c0, T + C::E * C::P, C::P, l, o);
   };
   using No = std::false_type;
@@ -581,7 +595,7 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_strip(const Chai
   Kept o;
   if (r0 < e.k[3]) {
     dbl2 ext[2];
-    mul_stream<true, false>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
+    mul_stream<true, false, false>(e.m[1], e.ld[1], C::S, X, e, e.k[1], r0, c0, l, o.acc, ext);
     const int j = c0 + 2 * l.l15;  // columns j, j + 1 (in_c is even)
     const Buffer mb(e.mt);
     const uint32_t mrs = 8 * (uint32_t)e.mt_rs, mlane = 2 * l.l4 * mrs + 8 * j;
@@ -606,9 +620,9 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_strip(const Chai
   const int t[2] = {l.l4 * C::E + c0 + 16 * odd + l.l15, l.l4 * C::E + c0 + 16 * (1 - odd) + l.l15};
   const bool rows = e.n[3] > C::S && l.wy == 0;
   if (rows)
-    mul_kept<true, true, true, false>(T, t, C::E, e.m[3], e.ld[3], C::S, e.k[3], r0, T, 0, l, o);
+    mul_kept<true, true, true, false, false>(T, t, C::E, e.m[3], e.ld[3], C::S, e.k[3], r0, T, 0, l, o);
   else
-    mul_kept<true, true, false, false>(T, t, C::E, e.m[3], e.ld[3], C::S, e.k[3], r0, T, 0, l, o);
+    mul_kept<true, true, false, false, false>(T, t, C::E, e.m[3], e.ld[3], C::S, e.k[3], r0, T, 0, l, o);
   if (r0 + 32 <= e.out_r && c0 + 32 <= e.out_c) {
     const Buffer ob(out);
     const uint32_t rs = 8 * (uint32_t)e.out_rs, lane = 2 * l.l4 * rs + 8 * l.l15;
@@ -671,7 +685,7 @@ bool chain_ok(const ChainDesc &d, int nb, int mode) {
   if (mode == 0 ? d.in_cs != 2 || d.out_cs != 1 || d.out_c % 2 || d.zoff != 0 || d.n[0] > S || d.n[1] > S
                 : mode != 3 || d.in_cs != 1 || d.out_cs != 2 || (d.zcol & ~1) != 0)
     return false;
-  return mat(0, S + 2) && mat(1, S + 2) && d.in_r <= d.k[1] && d.in_c <= d.k[0] && d.r0 >= 0 &&
+  return mat(0, S + 2) && mat(1, S + 2) && d.in_r <= d.k[1] && d.k[1] - d.in_r < 32 && d.in_c <= d.k[0] && d.r0 >= 0 &&
          d.r0 % chain_part(nb) == 0 && d.r0 < d.n[1] && d.r0 < S;
 }
 

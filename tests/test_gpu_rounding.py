@@ -1,4 +1,5 @@
-"""Rounding of the adjoint solve, against a reference in extended precision.
+"""Rounding of the solves themselves: adjoints against a reference in extended precision,
+cylinders by superposition.
 
 On data that decay, what the truncation (tol = 1e-17 here) and the data leave is the
 rounding of the products themselves.  Bound: the maps are rounded once per entry and
@@ -63,3 +64,28 @@ def test_adjoint(n, out):
         errs.append(float(np.linalg.norm((got - want).astype(float)) / np.linalg.norm(want.astype(float))))
     print(f"n={n} {out} rel err {errs}", flush=True)
     assert np.sqrt(np.mean(np.square(errs))) <= 6 * 2.0 ** -53
+
+
+# U(A + B) - U(A) - U(B) for inputs whose sum is exact: what is left is rounding.  The banded
+# solves magnify the rounding of their right-hand sides some 20 times at these sizes: 20 u
+# sqrt(3) for three solves, 3.8e-15; with the right-hand sides' sums started from their
+# largest terms it is 1e-14.
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [64, 130])
+def test_cylinder_superposition(n):
+    nt = 32
+    p = fps.plan_cylinder(n, nt)
+    k = np.abs(np.arange(nt) - nt // 2)
+    i = np.arange(n)
+    w = (1.0 + i) ** -2
+    weight = ((1.0 + k) ** -2)[:, None, None, None] * w[:, None] * w
+    weight = weight * ((i % 2)[None, :] == (k % 2)[:, None])[:, None, :, None]
+    errs = []
+    for seed in range(8):
+        rng = np.random.default_rng(seed)
+        A, B = (torch.from_numpy((rng.standard_normal((nt, 2, n, n)) * weight).astype(np.float32)).cuda().double()
+                for _ in range(2))
+        UA = fps.solve(p, A)
+        errs.append(float((fps.solve(p, A + B) - UA - fps.solve(p, B)).norm() / UA.norm()))
+    print(f"n={n} superposition {errs}", flush=True)
+    assert np.sqrt(np.mean(np.square(errs))) <= 5e-15
