@@ -297,18 +297,66 @@ void atilde_extremes(int64_t n, long double *lmin, long double *lmax) {
   *lmax = hi_all;
 }
 
+namespace {
+
+// Eigenvalue of the symmetric tridiagonal (diagonal d, couplings -e) next to x: one Rayleigh
+// quotient step, x + g / |z|^2 with z the vector of the twisted factorization and g its
+// smallest pivot combination.  c: scratch, 2 m.
+long double rayleigh_step(const std::vector<long double> &d, const std::vector<long double> &e,
+                          long double x, std::vector<long double> &c) {
+  const int64_t m = (int64_t)d.size();
+  long double *up = c.data(), *dn = c.data() + m;  // coupling / pivot, towards row 0 and m - 1
+  const long double tiny = std::numeric_limits<long double>::epsilon();
+  auto ratio = [&](long double num, long double q, long double scale) {
+    return num / (q == 0.0L ? tiny * scale : q);
+  };
+  for (int64_t i = 0; i < m; ++i) {
+    const int64_t j = m - 1 - i;
+    const long double qu = d[i] - x - (i > 0 ? e[i - 1] * up[i - 1] : 0.0L);
+    const long double qd = d[j] - x - (i > 0 ? e[j] * dn[j + 1] : 0.0L);
+    up[i] = ratio(i + 1 < m ? e[i] : 0.0L, qu, d[i]);
+    dn[j] = ratio(j > 0 ? e[j - 1] : 0.0L, qd, d[j]);
+  }
+  int64_t r = 0;
+  long double g = 0.0L;
+  for (int64_t i = 0; i < m; ++i) {
+    const long double t = d[i] - x - (i > 0 ? e[i - 1] * up[i - 1] : 0.0L) -
+                          (i + 1 < m ? e[i] * dn[i + 1] : 0.0L);
+    if (i == 0 || std::fabs(t) < std::fabs(g)) {
+      g = t;
+      r = i;
+    }
+  }
+  long double s = 1.0L, z = 1.0L;
+  for (int64_t i = r - 1; i >= 0; --i) {
+    z *= up[i];
+    s += z * z;
+  }
+  z = 1.0L;
+  for (int64_t i = r + 1; i < m; ++i) {
+    z *= dn[i];
+    s += z * z;
+  }
+  return x + g / s;
+}
+
+}  // namespace
+
 void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam) {
   const int64_t m = (n - s + 1) / 2;
   lam.assign((size_t)m, 0.0);
+  std::vector<long double> dl((size_t)m), el((size_t)m), scratch(2 * (size_t)m);
   std::vector<double> d((size_t)m), e2((size_t)m, 0.0);
   for (int64_t k = 0; k < m; ++k) {
-    d[(size_t)k] = -atilde_diag(2 * k + s);
-    const double e = atilde_off(2 * k + s);
-    e2[(size_t)k] = e * e;
+    dl[(size_t)k] = -atilde_diag_ld(2 * k + s);
+    el[(size_t)k] = atilde_off_ld(2 * k + s);
+    d[(size_t)k] = (double)dl[(size_t)k];
+    e2[(size_t)k] = (double)(el[(size_t)k] * el[(size_t)k]);
   }
   for (int64_t k = 0; k < m; ++k) {  // k-th smallest of -A~, in [1 / (30 n^4), 1]
+    // to 1e-9, far below the distance of its neighbours (a relative 2 / m)
     double lo = 0.5 / (30.0 * (double)n * (double)n * (double)n * (double)n), hi = 1.01;
-    for (int it = 0; it < 75 && hi > lo * (1.0 + 4e-16); ++it) {
+    for (int it = 0; it < 75 && hi > lo * (1.0 + 1e-9); ++it) {
       const double x = hi > 2.0 * lo ? std::sqrt(lo * hi) : 0.5 * (lo + hi);
       int64_t c = 0;
       double q = 1.0;
@@ -318,7 +366,9 @@ void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam) {
       }
       if (c <= k) lo = x; else hi = x;
     }
-    lam[(size_t)k] = -0.5 * (lo + hi);
+    long double x = 0.5L * ((long double)lo + (long double)hi);
+    for (int pass = 0; pass < 2; ++pass) x = rayleigh_step(dl, el, x, scratch);
+    lam[(size_t)k] = (double)-x;
   }
 }
 

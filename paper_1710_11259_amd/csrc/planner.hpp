@@ -85,8 +85,8 @@ bool tridiag_eigen(std::vector<long double> &d, std::vector<long double> e,
 // Sturm-sequence bisection in extended precision; both are negative.
 void atilde_extremes(int64_t n, long double *lmin, long double *lmax);
 
-// Eigenvalues of the parity-s block of A~, descending (the one next to zero first), to
-// relative accuracy ~m eps by Sturm-sequence bisection in double.
+// Eigenvalues of the parity-s block of A~, descending (the one next to zero first), rounded
+// once: Sturm-sequence bisection in double, then Rayleigh quotients in extended precision.
 void atilde_eigenvalues(int64_t n, int s, std::vector<double> &lam);
 
 // Entries of A~ = -S^-1 M S^-1 (symmetric, zero +-1 diagonals):
