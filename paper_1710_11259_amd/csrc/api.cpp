@@ -872,8 +872,8 @@ fps_status fps_adi_native(fps_plan *pl, const double *G, double *Y, void *ws, vo
     return s;
   const int J = pl->shifts.J;
   FPS_HIP(fps::launch_finalize((double *)(w + pl->off_O1), (double *)(w + pl->off_ab),
-                               pl->tab_dev(pl->tab2(J - 1)), Y, nullptr, L.n, L.npad, L.mp[0],
-                               L.mstride, L.ncmax, st));
+                               pl->tab_dev(pl->tab2(J - 1)), Y, L.n, L.npad, L.mp[0], L.mstride,
+                               L.ncmax, st));
   return FPS_OK;
 }
 

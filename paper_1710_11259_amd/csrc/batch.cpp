@@ -7,7 +7,6 @@
 #include <algorithm>
 #include <map>
 #include <new>
-#include <numeric>
 #include <vector>
 
 #include "solver.hpp"
@@ -27,7 +26,6 @@ struct fps_batch {
   std::vector<int64_t> n;            // per problem, caller's order
   std::vector<fps_plan *> sub;       // one plan per distinct n (owned)
   std::vector<int> which;            // problem -> index into sub
-  std::vector<int> order;            // sorted position -> problem (n descending)
   std::vector<int64_t> f_off, u_off, ws_off;  // per problem: F / U entries, workspace bytes
   int64_t in_entries = 0, out_entries = 0, ws_bytes = 0;
   int J_max = 0;                     // steps of the longest ADI (over all rounds)
@@ -219,10 +217,8 @@ fps_status fps_batch_create(fps_batch **out, int dim, int count, const int64_t *
     bt->out_entries += e * e;
     bt->ws_bytes += align256(pl->ws_bytes);
   }
-  bt->order.resize(count);
-  std::iota(bt->order.begin(), bt->order.end(), 0);
-  std::stable_sort(bt->order.begin(), bt->order.end(), [&](int a, int c) { return n[a] > n[c]; });
-  // every problem's 64 x 64 tiles must be countable by one launch
+  // the limit on a batch: 64 x 64 tiles of all problems' padded arrays (the products' units
+  // are at most 4 per tile, but a batch whose memory exists has far fewer)
   int64_t tiles = 0;
   for (int b = 0; b < count; ++b) {
     const fps::Layout &L = bt->plan_of(b)->L;

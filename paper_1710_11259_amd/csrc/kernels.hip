@@ -9,9 +9,8 @@ namespace fps {
 namespace {
 
 __global__ void k_finalize(const double *__restrict__ x, const double *__restrict__ ab,
-                           const double *__restrict__ tab, double *__restrict__ out,
-                           const double *__restrict__ sinv, int64_t n, int64_t npad, int64_t mp0,
-                           int64_t mstride, int64_t ncmax) {
+                           const double *__restrict__ tab, double *__restrict__ out, int64_t n,
+                           int64_t npad, int64_t mp0, int64_t mstride, int64_t ncmax) {
   const int64_t col = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y;
   if (col >= npad) return;
   const int s = r >= mp0 ? 1 : 0;
@@ -24,20 +23,17 @@ __global__ void k_finalize(const double *__restrict__ x, const double *__restric
   const int64_t kc = col - (t ? mp0 : 0);
   const int64_t i = 2 * k + s, j = 2 * kc + t;
   if (i >= n || j >= n) return;
-  out[i * n + j] = sinv ? v * sinv[i] * sinv[j] : v;
+  out[i * n + j] = v;
 }
 
 __global__ void k_permute_in(const double *__restrict__ src, double *__restrict__ dst, int64_t n,
-                             int64_t npad, int64_t mp0, const double *__restrict__ sinv) {
+                             int64_t npad, int64_t mp0) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, r = blockIdx.y;
   if (q >= npad) return;
   const int s = r >= mp0 ? 1 : 0, t = q >= mp0 ? 1 : 0;
   const int64_t i = 2 * (r - (s ? mp0 : 0)) + s, j = 2 * (q - (t ? mp0 : 0)) + t;
   double v = 0.0;
-  if (i < n && j < n) {
-    v = src[i * n + j];
-    if (sinv) v *= sinv[i] * sinv[j];
-  }
+  if (i < n && j < n) v = src[i * n + j];
   dst[r * npad + q] = v;
 }
 
@@ -79,18 +75,17 @@ hipError_t launch_permute3_in(const double *src, double *dst, int64_t n, int64_t
 }
 
 hipError_t launch_finalize(const double *x, const double *ab, const double *tab, double *out,
-                           const double *sinv, int64_t n, int64_t npad, int64_t mp0,
-                           int64_t mstride, int64_t ncmax, hipStream_t st) {
+                           int64_t n, int64_t npad, int64_t mp0, int64_t mstride, int64_t ncmax,
+                           hipStream_t st) {
   dim3 grid((unsigned)((npad + 255) / 256), (unsigned)npad);
-  hipLaunchKernelGGL(k_finalize, grid, dim3(256), 0, st, x, ab, tab, out, sinv, n, npad, mp0, mstride,
-                     ncmax);
+  hipLaunchKernelGGL(k_finalize, grid, dim3(256), 0, st, x, ab, tab, out, n, npad, mp0, mstride, ncmax);
   return hipGetLastError();
 }
 
 hipError_t launch_permute_in(const double *src, double *dst, int64_t n, int64_t npad, int64_t mp0,
-                             hipStream_t st, const double *sinv) {
+                             hipStream_t st) {
   dim3 grid((unsigned)((npad + 255) / 256), (unsigned)npad);
-  hipLaunchKernelGGL(k_permute_in, grid, dim3(256), 0, st, src, dst, n, npad, mp0, sinv);
+  hipLaunchKernelGGL(k_permute_in, grid, dim3(256), 0, st, src, dst, n, npad, mp0);
   return hipGetLastError();
 }
 

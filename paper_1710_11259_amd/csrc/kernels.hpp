@@ -14,13 +14,10 @@ namespace fps {
 // rows of a parity-blocked array (npad rows = chain positions of both parities, row
 // stride ld), one chain per storage column (ncols of them).
 //   input  v = in_scale * in + (carry correction of the producing pass)
-//   rhs    r = v + sg * g (g non-null) or v
+//   rhs    r = v + sg * g
 //   solve  x = T^-1 r along each chain (per parity), T the pass's
 //          tridiagonal (tables)
-//   output out_mode 0: v - sigma x stored transposed (requires
-//          ncols == ld == npad); 1: x in place orientation; 2: v - sigma x in place
-//          orientation; 3: x stored transposed (as mode 0).  Chunk-level
-//          carries are not applied by the
+//   output out_mode 1: x; 2: v - sigma x.  Chunk-level carries are not applied by the
 //          producer: it leaves its chunk boundary values in `lv`;
 //          launch_reduce turns them into carries, which the consumer (the
 //          next sweep, or k_finalize) folds in.
@@ -37,7 +34,7 @@ struct SweepArgs {
   const double *lv_prev;
   const double *ctab_prev;
   double carry_scale;
-  const double *g;         // G term, same layout as `in`, or nullptr
+  const double *g;         // G term, same layout as `in`
   double sg;
   const double *tab;       // this pass's tables [2][kNTab][mstride]
   const double *l1;        // this pass's segment-carry combinations [2][ncmax][kL1]
@@ -61,7 +58,7 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st, hipEvent_t ev0 = nul
 
 // Row-chain half-sweep: the same pass along the storage rows of `in`
 // (chains = rows, positions = columns, ncols = npad chains), stored in the
-// same layout (out_mode 1: x, 2: v - sigma x); no g term.  The producer's carries fold in
+// same layout; no g term (g null, r = v).  The producer's carries fold in
 // as in launch_sweep with the producer's chains along the columns; its
 // chunk boundary values go to lv ([ncmax][2][2][npad], chains = rows).
 // Equals launch_sweep on the transposed arrays bit for bit.
@@ -90,15 +87,14 @@ inline int reduce_lanes(int64_t ncmax) {
 inline int reduce_chains(int64_t ncmax) { return kReduceThreads / reduce_lanes(ncmax); }
 
 // Y = x[r][col] + carries (final pass, non-transposed): the natural-order n x n array
-// `out`, entry (i, j) times sinv_i * sinv_j when `sinv` is non-null.
+// `out`.
 hipError_t launch_finalize(const double *x, const double *ab, const double *tab, double *out,
-                           const double *sinv, int64_t n, int64_t npad, int64_t mp0,
-                           int64_t mstride, int64_t ncmax, hipStream_t st);
+                           int64_t n, int64_t npad, int64_t mp0, int64_t mstride, int64_t ncmax,
+                           hipStream_t st);
 
-// natural n x n (ld n) -> parity-blocked npad x npad (zero padding); with
-// `sinv` non-null, entry (i, j) is multiplied by sinv[i] * sinv[j].
+// natural n x n (ld n) -> parity-blocked npad x npad (zero padding).
 hipError_t launch_permute_in(const double *src, double *dst, int64_t n, int64_t npad, int64_t mp0,
-                             hipStream_t st, const double *sinv = nullptr);
+                             hipStream_t st);
 
 // Cube (npad^3 arrays [z][y][x], every axis parity-blocked):
 // natural n^3 -> parity-blocked npad^3 (zero padding).
@@ -138,8 +134,8 @@ struct CylSolveGroup {
   unsigned pivots;  // bit b: a row exchange in some z column of 64 b .. 64 b + 63
 };
 // Cylinder: the banded r-solves of every (|k| group, z column) with the
-// plan's LU factors (see cylinder.cpp), one thread applying them to all the
-// group's right-hand sides; X0 holds the right-hand sides (rows of parity
+// plan's LU factors (see cylinder.cpp), one thread applying them to half of
+// the group's right-hand sides (one mode's two parts); X0 holds the right-hand sides (rows of parity
 // rp, overwritten), X1 receives yhat (rows of parity wp).
 hipError_t launch_cyl_solve(double *X0, double *X1, const double *fac, const CylSolveGroup *grp,
                             int ngroups, int64_t m, int64_t mp, hipStream_t st);

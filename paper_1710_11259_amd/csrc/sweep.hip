@@ -61,10 +61,9 @@ static_assert(T_L == 0 && T_IB == 1 && T_U == 2 && T_F1 == 3 && T_BK1 == 4, "tab
 // One workgroup unit of a sweep: chain block bx (64 chains) and chunk row
 // by (parity-0 chunks first).
 //   v   = in_scale * in + (chunk carries of the producing pass)
-//   rhs = v + sg * g (kG) or v;
+//   rhs = v + sg * g (column chains) or v (row chains);
 //   x   = T^-1 rhs with T the pass's tridiagonal (tables);
-//   out = x (out_mode 1, 3) or v - sigma x (out_mode 0, 2); modes 0 and 3 store
-//         transposed.
+//   out = x (out_mode 1) or v - sigma x (out_mode 2).
 
 // Geometry of the unit at chunk row `by` for wavefront w.
 struct Unit {
@@ -160,7 +159,6 @@ __device__ __forceinline__ void load_small(const SweepArgs &a, const Unit &u, co
 
 // Streaming loads (rows clamped for the idle segments past the chain end):
 // v <- in, y <- g.
-template <bool kG>
 __device__ __forceinline__ void load_stream(const SweepArgs &a, const Unit &u, const Cols &q,
                                             double *v, double *y) {
   const int64_t npad = a.npad, ld = a.ld;
@@ -170,13 +168,11 @@ __device__ __forceinline__ void load_stream(const SweepArgs &a, const Unit &u, c
     const int64_t r = u.row0 + i < npad ? u.row0 + i : npad - 1;
     v[i] = in[r * ld + q.col];
   }
-  if constexpr (kG) {
-    const double *__restrict__ gp = a.g;
+  const double *__restrict__ gp = a.g;
 #pragma unroll
-    for (int i = 0; i < kSeg; ++i) {
-      const int64_t r = u.row0 + i < npad ? u.row0 + i : npad - 1;
-      y[i] = load_nt(gp + r * ld + q.col);
-    }
+  for (int i = 0; i < kSeg; ++i) {
+    const int64_t r = u.row0 + i < npad ? u.row0 + i : npad - 1;
+    y[i] = load_nt(gp + r * ld + q.col);
   }
 }
 
@@ -192,13 +188,13 @@ __device__ __forceinline__ void load_stream_rows(const SweepArgs &a, const Unit 
 }
 
 // Elimination and store of one unit.
-template <bool kG, bool kTL>
+template <bool kRows>
 __device__ __forceinline__ void compute_store(const SweepArgs &a, const Unit &u, const Cols &q,
                                               const Small &m, double *v, double *y, double *lds,
                                               int tid, int lane, int w) {
   const int64_t ncols = a.ncols, ld = a.ld;
   const bool has_prev = a.tab_prev != nullptr;
-  if constexpr (kTL) {
+  if constexpr (kRows) {
     // Row chains: wave w holds rows (chains) w * kSeg + i with one position
     // per lane; after the turnaround lane holds chain `lane` at the
     // positions of segment w, as in the column-chain pass.
@@ -230,7 +226,7 @@ __device__ __forceinline__ void compute_store(const SweepArgs &a, const Unit &u,
 #pragma unroll
   for (int i = 0; i < kSeg; ++i) {
     v[i] = isc * v[i] + Ab[2 * i] * cA + Ab[2 * i + 1] * cB;
-    y[i] = kG ? v[i] + (act * a.sg) * y[i] : v[i];
+    y[i] = kRows ? v[i] : v[i] + (act * a.sg) * y[i];
   }
 
   // Forward elimination with zero carry-in, then the segment carry.
@@ -257,13 +253,13 @@ __device__ __forceinline__ void compute_store(const SweepArgs &a, const Unit &u,
   // forward values, r_k = y_k + l_k y_{k-1} (y_{-1} = cf1), so v need not
   // live on.
   const double sigma = a.sigma;
-  const bool out_x = a.out_mode == 1 || a.out_mode == 3;
+  const bool out_x = a.out_mode == 1;
   double xnext = 0.0, xfirst = 0.0;
 #pragma unroll
   for (int i = kSeg - 1; i >= 0; --i) {
     const double x = y[i] * Tib[i] - Tu[i] * xnext;
     double rhs;
-    if constexpr (kG)
+    if constexpr (!kRows)
       rhs = v[i];
     else
       rhs = y[i] + Tl[i] * (i > 0 ? y[i - 1] : cf1);
@@ -286,16 +282,16 @@ __device__ __forceinline__ void compute_store(const SweepArgs &a, const Unit &u,
   if (w == 0) a.lv[(((int64_t)u.c * 2 + u.s) * 2 + 1) * ncols + q.col] = xfirst + Tbk1[0] * cb1;
 
   double *__restrict__ out = a.out;
-  if (a.out_mode == 1 || a.out_mode == 2) {
+  if constexpr (!kRows) {
     if (u.active) {
 #pragma unroll
       for (int i = 0; i < kSeg; ++i) out[(u.row0 + i) * ld + q.col] = y[i];
     }
     return;
   }
-  // Transposed store staged through LDS: the workgroup's 64 x 64 tile
-  // (chain positions x chains) is transposed so that output row col0 + j
-  // receives the chunk's 64 positions as one contiguous 512-byte run.
+  // Rows again through LDS: the workgroup's 64 x 64 tile (chain positions x
+  // chains) is turned around so that row col0 + j receives the chunk's 64
+  // positions as one contiguous 512-byte run.
   static_assert(kChunk == kCols && kChunk * (kChunk + 1) <= kSweepLds, "store tile");
   __syncthreads();  // the early region is dead
 #pragma unroll
@@ -319,7 +315,7 @@ __device__ __forceinline__ void compute_store(const SweepArgs &a, const Unit &u,
   }
 }
 
-template <bool kG, bool kTL>
+template <bool kRows>
 __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int bx, const int by,
                                             double *lds) {
   const int tid = threadIdx.x;
@@ -330,18 +326,17 @@ __device__ __forceinline__ void sweep_block(const SweepArgs &a, const int bx, co
   Small m;
   load_small(a, u, q, tid, m);
   double v[kSeg], y[kSeg];
-  if constexpr (kTL)
+  if constexpr (kRows)
     load_stream_rows(a, u, q, lane, w, v);
   else
-    load_stream<kG>(a, u, q, v, y);
-  compute_store<kG, kTL>(a, u, q, m, v, y, lds, tid, lane, w);
+    load_stream(a, u, q, v, y);
+  compute_store<kRows>(a, u, q, m, v, y, lds, tid, lane, w);
 }
 
 // Six wavefronts per SIMD (three workgroups per compute unit) fit.
-template <bool kG>
 __global__ __launch_bounds__(kCols *kWaves, 6) void k_sweep(SweepArgs a) {
   __shared__ double lds[kSweepLds];
-  sweep_block<kG, false>(a, blockIdx.x + a.blk0, blockIdx.y + a.chk0, lds);
+  sweep_block<false>(a, blockIdx.x + a.blk0, blockIdx.y + a.chk0, lds);
 }
 
 // Row-chain sweep (chains along the array's rows, stored in place of the
@@ -350,7 +345,7 @@ __global__ __launch_bounds__(kCols *kWaves, 6) void k_sweep(SweepArgs a) {
 // grid, so the workgroups in flight together cover whole rows.
 __global__ __launch_bounds__(kCols *kWaves, 6) void k_sweep_rows(SweepArgs a) {
   __shared__ double lds[kSweepLds];
-  sweep_block<false, true>(a, blockIdx.y + a.blk0, blockIdx.x + a.chk0, lds);
+  sweep_block<true>(a, blockIdx.y + a.blk0, blockIdx.x + a.chk0, lds);
 }
 
 template <typename K>
@@ -375,7 +370,7 @@ static bool ranges_ok(const SweepArgs &a) {
 
 hipError_t launch_sweep(const SweepArgs &a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   const int nchunks = a.nc0 + a.nc1;
-  if (a.npad % kCols != 0 || a.ncols % kCols != 0 || nchunks <= 0 || a.in == nullptr)
+  if (a.npad % kCols != 0 || a.ncols % kCols != 0 || nchunks <= 0 || a.in == nullptr || a.g == nullptr)
     return hipErrorInvalidValue;
   if (!ranges_ok(a)) return hipErrorInvalidValue;
   if (a.ctab_prev != nullptr) {  // carries formed in the sweep: at most two chunks per chain
@@ -383,31 +378,27 @@ hipError_t launch_sweep(const SweepArgs &a, hipStream_t st, hipEvent_t ev0, hipE
   } else if ((a.ab_prev == nullptr) != (a.tab_prev == nullptr)) {
     return hipErrorInvalidValue;
   }
-  if ((a.out_mode == 0 || a.out_mode == 3) && (a.ncols != a.npad || a.ld != a.npad))
-    return hipErrorInvalidValue;
-  if (a.out_mode < 0 || a.out_mode > 3) return hipErrorInvalidValue;
+  if (a.out_mode != 1 && a.out_mode != 2) return hipErrorInvalidValue;
   if (a.ld < a.ncols) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.blk1 > 0 ? a.blk1 - a.blk0 : a.ncols / kCols),
                   (unsigned)(a.chk1 > 0 ? a.chk1 - a.chk0 : nchunks), 1u);
-  return run(a.g != nullptr ? k_sweep<true> : k_sweep<false>, grid, a, st, ev0, ev1);
+  return run(k_sweep, grid, a, st, ev0, ev1);
 }
 
-hipError_t launch_sweep_rows(const SweepArgs &a0, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  const int nchunks = a0.nc0 + a0.nc1;
-  if (a0.npad % kCols != 0 || a0.ncols % kCols != 0 || nchunks <= 0 || a0.in == nullptr ||
-      a0.out == nullptr)
+hipError_t launch_sweep_rows(const SweepArgs &a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  const int nchunks = a.nc0 + a.nc1;
+  if (a.npad % kCols != 0 || a.ncols % kCols != 0 || nchunks <= 0 || a.in == nullptr ||
+      a.out == nullptr)
     return hipErrorInvalidValue;
-  if (a0.ncols != a0.npad || a0.ld < a0.npad || a0.ld % 4 != 0) return hipErrorInvalidValue;
-  if (a0.out_mode != 1 && a0.out_mode != 2) return hipErrorInvalidValue;
-  if (a0.g != nullptr) return hipErrorInvalidValue;
-  if (a0.ctab_prev != nullptr) {
-    if (a0.tab_prev == nullptr || a0.lv_prev == nullptr || a0.ncmax > 2) return hipErrorInvalidValue;
-  } else if ((a0.ab_prev == nullptr) != (a0.tab_prev == nullptr)) {
+  if (a.ncols != a.npad || a.ld < a.npad || a.ld % 4 != 0) return hipErrorInvalidValue;
+  if (a.out_mode != 1 && a.out_mode != 2) return hipErrorInvalidValue;
+  if (a.g != nullptr) return hipErrorInvalidValue;
+  if (a.ctab_prev != nullptr) {
+    if (a.tab_prev == nullptr || a.lv_prev == nullptr || a.ncmax > 2) return hipErrorInvalidValue;
+  } else if ((a.ab_prev == nullptr) != (a.tab_prev == nullptr)) {
     return hipErrorInvalidValue;
   }
-  if (!ranges_ok(a0)) return hipErrorInvalidValue;
-  SweepArgs a = a0;
-  a.out_mode = a0.out_mode == 1 ? 3 : 0;  // the same outputs, stored along rows
+  if (!ranges_ok(a)) return hipErrorInvalidValue;
   const int nbx = a.blk1 > 0 ? a.blk1 - a.blk0 : (int)(a.ncols / kCols);
   const int nby = a.chk1 > 0 ? a.chk1 - a.chk0 : nchunks;
   const dim3 grid((unsigned)nby, (unsigned)nbx, 1u);
