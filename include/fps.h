@@ -174,8 +174,9 @@ fps_status fps_plan_info(const fps_plan *plan, int *J, int64_t *workspace_bytes,
                          int64_t *out_entries);
 
 /* Refinement structure of a plan: the number of rounds (1 for FPS_FP64) and
- * the number of inner ADI steps of its float rounds, summed (0 for
- * FPS_FP64).  Either pointer may be null. */
+ * the number of inner ADI steps of the rounds that its schedule derives for
+ * float storage, summed (0 for FPS_FP64; the solves store nothing in float).
+ * Either pointer may be null. */
 fps_status fps_plan_refinement(const fps_plan *plan, int *rounds, int *f32_steps);
 
 /* The ADI steps and the inner tolerance of each refinement round (host
@@ -289,9 +290,9 @@ fps_status fps_adi_native(fps_plan *plan, const double *G_dev, double *Y_dev, vo
  * ms_host[0..min(count, cap)-1] (ms_host may be null when cap is 0), sets
  * *launches to their count, and resets the count.  Square and rectangle
  * plans: fps_adi_native's half-steps 1 and 2 of Algorithm 2 alternate,
- * starting with half-step 1; the solves and adjoints time their four product
- * launches; cube
- * plans time their product launches.
+ * starting with half-step 1; the solves and adjoints time their product
+ * launches, one up to n = 128 (adjoints with Chebyshev output 126) and four
+ * beyond.  Cube plans: three launches up to n = 256, more beyond.
  */
 fps_status fps_plan_set_sweep_timing(fps_plan *plan, int capacity);
 fps_status fps_plan_sweep_time(fps_plan *plan, double *ms_host, int64_t cap, int64_t *launches);

@@ -210,8 +210,8 @@ class Plan:
 
     def sweep_time(self, cap: int = 1 << 20):
         """Per-launch milliseconds of the timed launches since the last call
-        (adi_native: half-step 1 and half-step 2 alternate; 2-D solves: their
-        four products)."""
+        (adi_native: half-step 1 and half-step 2 alternate; solves: their
+        products, one launch up to n = 128 and four beyond, cubes three or more)."""
         buf = (ctypes.c_double * cap)()
         cnt = ctypes.c_int64()
         _check(lib().fps_plan_sweep_time(self._h, buf, cap, ctypes.byref(cnt)))
@@ -379,8 +379,8 @@ def _solve_fn_class():
 
     class SolveFn(torch.autograd.Function):
         """Differentiable square solve.  forward: U = solve(F) for F of shape
-        (n, n) or (batch, n, n); backward: the adjoint solve (same ADI sweeps
-        between transposed coefficient maps), nothing stored from the forward
+        (n, n) or (batch, n, n); backward: the adjoint solve (the same
+        products transposed), nothing stored from the forward
         pass because the map is linear in F.  A batch of square FP64 problems
         runs as one fps_batch (each product stage of all problems in one
         launch, forward and backward); its results equal the per-problem

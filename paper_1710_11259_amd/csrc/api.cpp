@@ -516,8 +516,9 @@ fps_status plan_common(fps_plan **out, int dim, int64_t n, int bc, double tol, i
 }
 
 std::vector<RefineRound> refine_schedule(double tol, bool dirichlet) {
-  // Float rounds solve A~ dY + dY A~ = r_k to kRoundTol with every sweep
-  // array stored in float.  On smooth right-hand sides such a round
+  // The schedule is derived for rounds that solve A~ dY + dY A~ = r_k to kRoundTol
+  // with every sweep array stored in float (the closed form stores none).  On
+  // smooth right-hand sides such a round
   // contracts the error by about kContract (emulated at n = 64 .. 4096:
   // 5e-6 to 8e-6 per round, down to the FP64 level near 1e-14); the last
   // round only needs to take the error reached so far to tol, with a
@@ -572,8 +573,6 @@ fps_status plan2d_build(fps_plan *pl) {
   }
   pl->rounds = (int)pl->rtol.size();
   pl->rsh.assign(pl->rtol.size(), fps::ShiftSet{});
-  pl->rbase.assign(pl->rtol.size(), 0);
-  int steps = 0;
   for (size_t k = 0; k < pl->rtol.size(); ++k) {
     fps::ShiftSet &sh = pl->rsh[k];
     if (!fps::zolotarev_shifts(pl->sx2 * ea, pl->sx2 * eb, -pl->sy2 * eb, -pl->sy2 * ea,
@@ -586,12 +585,9 @@ fps_status plan2d_build(fps_plan *pl) {
     // ~ (sx2 + sy2) / |shift| in some modes, and the large-shift steps that
     // follow it damp those modes.  In the opposite order the symmetrized
     // iterate carries ~1e-10 relative error on Dirichlet-lift right-hand
-    // sides (rows 0, 1 spanning every column mode) instead of ~1e-13, and
-    // float storage (refinement rounds) stalls or diverges from n ~ 256 on.
+    // sides (rows 0, 1 spanning every column mode) instead of ~1e-13.
     std::reverse(sh.p.begin(), sh.p.end());
     std::reverse(sh.q.begin(), sh.q.end());
-    pl->rbase[k] = steps;
-    steps += sh.J;
   }
   pl->shifts = pl->rsh[0];
   pl->n_f32 = 0;
@@ -613,14 +609,14 @@ fps_status plan2d_build(fps_plan *pl) {
   const int64_t mobar = pl->mop[0] + pl->mop[1];
   if (L.npad * mobar * 8 > pl->off_lv - pl->off_O0)
     return fail(FPS_E_STATE, "internal: output temporary exceeds workspace");
-  pl->off_X = 4 * sq + lvb + abb;
   // second boundary-value buffer for sweeps that form their own carries
   // (chains of at most two chunks); after everything else
   const bool fused = L.ncmax <= 2;
-  pl->ws_bytes = pl->off_X + align256(mobar * mobar * 8);
-  if (prec == FPS_FP32_REFINED) {
-    pl->ws_bytes += sq;  // kept: workspaces of a plan size stay interchangeable
-  }
+  // The size has room for an output array, and for a second square in refined plans, that
+  // nothing uses: it is what callers have allocated, and the sizes that fps_solve_noalloc
+  // accepts follow from it.
+  pl->ws_bytes = 4 * sq + lvb + abb + align256(mobar * mobar * 8);
+  if (prec == FPS_FP32_REFINED) pl->ws_bytes += sq;
   if (flags & FPS_PLAN_DIRICHLET) {
     pl->off_bc = pl->ws_bytes;
     pl->ws_bytes += align256((4 * L.npad + 8) * 8);

@@ -527,7 +527,7 @@ __global__ __launch_bounds__((Unit<NB, W>::kThreads), 4) void k_slab(const Chain
   const uint32_t rs = 8 * (uint32_t)e.out_rs, lane = l.l4 * rs + 16 * l.l15;
   if (r0 + 32 <= e.out_r && c0 + 32 <= e.out_c) {
     // the zeros of a unit and its partner of the other column parity: each writes
-    // every other row of both (cylinder 256 x 256: 413 -> 346 MB written, 481 -> 475 us)
+    // every other row of both (cylinder 256 x 256: 413 -> 341 MB written, 481 -> 475 us)
     const Buffer zb(out + e.zoff - e.zcol);
 #pragma unroll
     for (int a = 0; a < 2; ++a)

@@ -323,9 +323,8 @@ fps_status cube_plan_build(fps_plan *pl) {
     pl->mqc[sp] = ((native ? L.m[sp] : L.mo[sp]) + 1) / 2 * 2;
   }
   // Workspace: six arrays of (up to) npad^3 (input stages in G / O0 / O1, Y^ in ZR,
-  // output stages in O0..O1 and RX..RX + 1), then what the chunk carries of
-  // npad^2 chains would take (kept, so that workspaces allocated for a plan
-  // size stay interchangeable).
+  // output stages in O0..O1 and RX..RX + 1), then room for the chunk carries of npad^2
+  // chains, which nothing uses: the size is what callers have allocated.
   const int64_t vol = align256(L.npad * L.npad * L.npad * 8);
   const int64_t ch = L.npad * L.npad;
   pl->off_G = 0;

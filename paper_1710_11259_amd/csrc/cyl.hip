@@ -218,9 +218,10 @@ hipError_t launch_cyl_solve(double *X0, double *X1, const double *fac, const Cyl
   const int64_t nzb = (2 * mp + 63) / 64, units = nzb * ngroups;
   // n <= 512, n_theta <= 1024: at most 8 x 513 units
   // Pairs from two units per compute unit on: 496 -> 481 us for the whole solve at
-  // 256 x 256 (516 units), 161 against 161 at 200 x 96 (196 units).  With fewer units
-  // the halves are faster apart, on more compute units: 118 against 123 us at 256 x 64
-  // (132 units), 22.5 against 24.4 at 64 x 64 (33 units).
+  // 256 x 256 (516 units).  With fewer units the halves are as fast or faster apart, on more
+  // compute units (apart / paired): 22.5 / 24.4 us at 64 x 64 (33 units), 118 / 123 at 256 x 64
+  // (132), 190 / 193 at 256 x 96 (196), 306 / 318 at 256 x 160 (324), 420 / 421 at 256 x 224 (452),
+  // 465.6 / 465.1 at 256 x 254 (512); the one size found the other way is 256 x 128 (260), 244 / 234.
   const int paired = units >= 512;
   const unsigned grid = (unsigned)(paired ? units : (units + 7) / 8 * 16);
   hipLaunchKernelGGL(k_cyl_solve, dim3(grid), dim3(paired ? 128 : 64), 0, st, X0, X1, fac, grp,

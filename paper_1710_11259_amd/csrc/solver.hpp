@@ -64,14 +64,13 @@ struct fps_plan {
   unsigned flags = 0;
   bool on_device = false;
 
-  fps::ShiftSet shifts;     // shifts of the ADI the sweeps run (FP32_REFINED: of round 0)
+  fps::ShiftSet shifts;     // shifts of the ADI (FP32_REFINED: of round 0)
   // Refinement rounds (FP32_REFINED; FP64 plans have one round, the plain
-  // ADI): round k runs an ADI to rtol[k] with the shifts rsh[k], whose step j
-  // uses the tables of step rbase[k] + j; with rf32[k] set it stores every
-  // sweep array in float.  n_f32 counts the steps of the float rounds.
+  // ADI): round k is an ADI to rtol[k] with the shifts rsh[k], which enters the
+  // solve through its error factors; rf32[k]: a round of the schedule that is derived for
+  // float storage (nothing is stored in float).  n_f32 counts those rounds' steps.
   int rounds = 1;
   std::vector<fps::ShiftSet> rsh;
-  std::vector<int> rbase;
   std::vector<double> rtol;
   std::vector<char> rf32;
   int n_f32 = 0;
@@ -116,17 +115,13 @@ struct fps_plan {
 
   // workspace layout (byte offsets)
   int64_t off_G = 0, off_GT = 0, off_O0 = 0, off_O1 = 0, off_lv = 0, off_ab = 0;
-  // Second chunk-boundary-value buffer: 2-D plans' second half-steps write
-  // lv2 and first ones lv; z-eigenbasis cube plans whose sweeps form their
-  // carries themselves use it the same way.  2-D plans: the carries of first
-  // half-steps go to ab2, those of second ones (and the final pass's) to ab,
-  // so that the two row-parity halves of the ADI can run on two streams
-  // without sharing a buffer element.
+  // fps_adi_native: second half-steps write their chunk boundary values to lv2
+  // and first ones to lv; the carries of first half-steps go to ab2, those of
+  // second ones (and the final pass's) to ab, so that the two row-parity halves of
+  // the ADI can run on two streams without sharing a buffer element.
   int64_t off_lv2 = 0, off_ab2 = 0;
-  int64_t off_X = 0;  // adjoint: the output cotangent in the parity-blocked layout
-  // Dirichlet lift (2-D plans with FPS_PLAN_DIRICHLET): the traces' scaled
-  // C~ second-derivative coefficients [4][npad] (parity-blocked) and their
-  // values at -1 and +1 [8].
+  // Dirichlet lift (2-D plans with FPS_PLAN_DIRICHLET): the traces' values at -1
+  // and +1 [8].
   int64_t off_bc = 0;
 
   // Cube (dim 3), nested method: `shifts` holds the outer shifts (p in
@@ -191,8 +186,8 @@ fps_status upload(DeviceBuf &b, const std::vector<T> &h) {
   return FPS_OK;
 }
 // The refinement rounds of an FP32_REFINED plan with target tolerance tol:
-// each round's inner ADI tolerance and whether it stores its sweep arrays in
-// float (Dirichlet plans end with an FP64 round).
+// each round's inner ADI tolerance and whether the schedule derives it for float
+// storage (Dirichlet plans end with one for float64).
 struct RefineRound {
   double tol;
   bool f32;
