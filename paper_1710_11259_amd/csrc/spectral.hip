@@ -101,7 +101,8 @@ __device__ __forceinline__ void store(const PairArray &a, int64_t i, Pair v) {
 // direction.  x comes with the error of a double (1e-12 of the smallest); g / |z|^2 is
 // the Rayleigh quotient's correction, so the first pass squares that error against the gap
 // (neighbours differ by a relative 2 / m) and the second leaves the vector's error at 1e-18
-// or less: the vectors are orthonormal as they are.  One lane per vector; ratios and
+// or less, the few highest modes apart (1e-14 at n = 4096: T's entries have 64 bits): the
+// vectors are orthonormal as they are.  One lane per vector; ratios and
 // vectors are stored [row][vector], so every access of a wavefront is one
 // 512-byte run.  Bound by the serial chain of divisions.
 // (The pointers are parameters for their no-alias promise: without it no entry is read
